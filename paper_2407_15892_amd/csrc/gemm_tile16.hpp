@@ -36,10 +36,10 @@ struct Cfg16 {
   }
 };
 
-// source row (within a block of 128 A rows) held by LDS / MFMA row m = 16 t + 4 g + r of the block
-template <bool kPermute> __device__ __forceinline__ int a_row_of_block_row16(int m) {
+// source row (within a block of 16 TILES A rows) held by LDS / MFMA row m = 16 t + 4 g + r of the block
+template <bool kPermute, int TILES = 8> __device__ __forceinline__ int a_row_of_block_row16(int m) {
   if (!kPermute) return m;
-  return 32 * ((m >> 2) & 3) + 4 * (m >> 4) + (m & 3);
+  return 4 * TILES * ((m >> 2) & 3) + 4 * (m >> 4) + (m & 3);
 }
 // K-contiguous panel [EXT rows][BK k]; LDS row = MFMA row order (a permutation, if any, is applied at the source)
 template <class C, int EXT, int TILES, bool kPermute>
@@ -52,7 +52,7 @@ struct PanelKC16 {
   static constexpr int SPW = NSLOT / C::kWaves;
   static_assert(NSLOT % C::kWaves == 0, "slots must divide over waves");
   static_assert(BK == 64, "row swizzle below is the one for 128-byte rows");
-  static_assert(!kPermute || (EXT % 128 == 0 && TILES == 8), "the permutation works on blocks of 128 rows");
+  static_assert(!kPermute || EXT % (16 * TILES) == 0, "the permutation works on the blocks of 16 TILES rows of a wave");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t voff[SPW];
   uint32_t kelem[SPW];
@@ -89,7 +89,10 @@ struct PanelKC16 {
                                        int wave, int lane, int wave_side_index) {
     const int rows = rows_valid < (uint32_t)EXT ? (int)rows_valid : EXT;
     init_map(base, ld_elems, rows, k_elems, wave, lane, wave_side_index,
-             [](int lrow) { return (lrow & ~127) + a_row_of_block_row16<kPermute>(lrow & 127); }, true);
+             [](int lrow) {
+               constexpr int kBlock = 16 * TILES;
+               return (lrow & ~(kBlock - 1)) + a_row_of_block_row16<kPermute, TILES>(lrow & (kBlock - 1));
+             }, true);
   }
   __device__ __forceinline__ void issue_one(int i, uint32_t panel_lds, uint32_t k0) const {
     dma16(rsrc, (k0 + kelem[i]) < k_limit ? voff[i] + k0 * 2 : kOutOfRange, panel_lds + (slot0 + i) * 1024);
@@ -106,7 +109,8 @@ struct PanelKC16 {
 // K-strided panel [BK k][EXT index], read with the transposing LDS read.  A quarter wave (16 lanes) feeds
 // one 8-deep k group of a 16-wide tile: lane j of the quarter hands over the 4 consecutive indices
 // 4 * (j % 4) .. + 3 at k row j / 4 (and, in a second read, 4 rows further).  kPermute (A side only): those
-// 4 MFMA rows 16 t + 4 q + r read indices 32 q + 4 t + r of the 128-wide block, applied in the read addresses.
+// 4 MFMA rows 16 t + 4 q + r read indices 4 TILES q + 4 t + r of the 16 TILES wide block, applied in the read
+// addresses.
 template <class C, int EXT, int TILES, bool kPermute = false>
 struct PanelKS16 {
   static constexpr int BK = C::BK;
@@ -116,7 +120,8 @@ struct PanelKS16 {
   static constexpr int NSLOT = BK / RPS;
   static constexpr int SPW = NSLOT / C::kWaves;
   static_assert(NSLOT % C::kWaves == 0, "slots must divide over waves");
-  static_assert(!kPermute || (EXT % 128 == 0 && TILES == 8), "the permutation works on blocks of 128 indices");
+  static_assert(!kPermute || EXT % (16 * TILES) == 0, "the permutation works on the blocks of 16 TILES indices of a wave");
+  static_assert(EXT == 64 || EXT == 128 || EXT == 256, "the swizzles below are for these row lengths");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t voff[SPW];
   uint32_t ok_mask, ld_bytes, slot0;
@@ -128,7 +133,11 @@ struct PanelKS16 {
   // The two lane quarters that are served in one clock read k rows 8 apart: in memory order bit 3 of the k row
   // moves them to the other 128-byte half of the 256-byte bank window.  (With the permutation both quarters
   // need the same 8-byte half of all 16 chunks of the window, which no 16-byte swizzle can separate.)
+  // EXT = 64: a k row is half the bank window, so the row's bit 0 selects a half already.  Smaller TILES bring the
+  // permuted pieces closer together (4 TILES indices apart): the rows then differ in the chunk bits these leave free.
   __device__ __forceinline__ static uint32_t swz(uint32_t krow) {
+    if (EXT == 64) return kPermute ? 4 * ((krow >> 1) & 1) : (2 * ((krow >> 1) & 1)) ^ (4 * ((krow >> 3) & 1));
+    if (EXT == 128 && kPermute) return (krow & 1) ^ (8 * ((krow >> 1) & 1));
     return kPermute ? (krow & 3) : (2 * (krow & 3)) ^ (8 * ((krow >> 3) & 1));
   }
 
@@ -149,8 +158,7 @@ struct PanelKS16 {
     const int g = lane >> 4, i16 = lane & 15, q = i16 & 3;
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
-      const int col = kPermute ? wave_side_index * 128 + 32 * q + 4 * t
-                               : wave_side_index * (16 * TILES) + 16 * t + 4 * q;
+      const int col = wave_side_index * (16 * TILES) + (kPermute ? 4 * TILES * q + 4 * t : 16 * t + 4 * q);
       const int krow = 8 * g + (i16 >> 2);
       rd[t] = krow * RB + (((col >> 3) ^ swz(krow)) * 16) + (col & 7) * 2;
     }

@@ -6,6 +6,7 @@
 #include "host_util.hpp"
 #include "mst_mlp_kernels.hpp"
 
+#include <cmath>
 #include <mutex>
 
 namespace {
@@ -18,8 +19,6 @@ struct Plan {
   int M;
   int C;            // rows per chunk = ceil(S / M)
   int n_chunks;     // non-empty chunks
-  int n_dt, n_it;   // 256-wide tiles of d and of I
-  int n_it128;      // 128-wide tiles of I (gate/up kernel)
   size_t slot;      // bytes of one chunk-sized bf16 [C, I] buffer
 };
 
@@ -33,9 +32,6 @@ mst_status make_plan(int64_t S, int64_t d, int64_t I, int32_t M, Plan* p) {
   p->S = S; p->d = d; p->I = I; p->M = M;
   p->C = (int)C;
   p->n_chunks = (int)((S + C - 1) / C);
-  p->n_dt = (int)((d + kTile - 1) / kTile);
-  p->n_it = (int)((I + kTile - 1) / kTile);
-  p->n_it128 = (int)((I + kGateUpI - 1) / kGateUpI);
   p->slot = mst_host::align_up((size_t)C * I * 2, 256);
   return MST_OK;
 }
@@ -44,6 +40,21 @@ mst_host::Profiler g_prof;
 struct Scope : mst_host::Scope {
   Scope(hipStream_t s, int k) : mst_host::Scope(g_prof, s, k) {}
 };
+
+// The smaller tiles of gemm_small.hpp: 128 x 128 (80 KB of LDS, two workgroups on a compute unit); 64 x 64 (40 KB, four);
+// 64 x 64 with deeper pipelines (56 KB) for launches of one workgroup per compute unit, where nothing else hides the
+// latency of the loads: down at 200 tokens 74 us against 105 with the shallow one.
+typedef CfgSmall<4, 4, 2, 3, 2> Tile128;
+typedef CfgSmall<2, 2, 2, 3, 2> Tile64;
+typedef CfgSmall<2, 2, 2, 4, 3> Tile64Deep;
+
+template <class C, class Set>
+void set_small_attributes(Set set) {
+  set((const void*)k_mlp_gateup_small<C, false>);
+  set((const void*)k_mlp_gateup_small<C, true>);
+  set((const void*)k_mlp_gemm_nt_small<C>);
+  set((const void*)k_mlp_gemm_nn_small<C>);
+}
 
 mst_host::PerDeviceOnce g_attr_once;
 bool set_kernel_attributes() {   // on the current device
@@ -54,6 +65,9 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_mlp_gateup<false>);
   set((const void*)k_mlp_gateup<true>);
   set((const void*)k_mlp_gemm_nt);
+  set_small_attributes<Tile128>(set);
+  set_small_attributes<Tile64>(set);
+  set_small_attributes<Tile64Deep>(set);
   set((const void*)k_mlp_gemm_nn<Tile16>);
   set((const void*)k_mlp_gemm_nn<Tile16HalfB>);
   set((const void*)k_mlp_dw3<false>);
@@ -81,6 +95,74 @@ int rows_of(const Plan& p, int i) {
 
 constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident per CU
 
+// Which block tile a GEMM of n_a x n_b outputs (A side: weights, B side: tokens) and `ksteps` K steps of 64 runs with.
+// The figures are microseconds fitted to launches of the three kinds (gate/up, down, dA/dX) at 64 to 3000 tokens,
+// d = 256 to 4096, I = 896 to 14336; they only have to rank the tiles, and every tile gives the same bits:
+//   256 x 256      1.25 per K step + 7 (first loads, epilogue), in whole rounds of kNumCu
+//   128 x 128      1.0 per K step + 4 for two workgroups on a compute unit, 0.65 of that for a lone one; further rounds
+//                  overlap.  1024 tokens, d = 4096, I = 14336: down 156 us (256 tiles) against 308 (64 tiles of 256),
+//                  dX 302 against 607; 3000 tokens, d = 768, I = 2304: gate/up 26 against 39
+//   64 x 64        0.45 per K step + 3 for a lone workgroup, 0.85 with four on a compute unit.  512 tokens, d = 2048,
+//                  I = 5632: dA 20.5 (704 tiles) against 43 (44 of 256) and 23 (176 of 128)
+//   64 x 64 deep   0.31 per K step + 2.7 for a lone workgroup.  256 tokens, d = 256, I = 896: down 5.7 against 18;
+//                  200 tokens, d = 4096, I = 14336: down 74 against 250 (16 tiles of 256), dX 144 against 523
+enum TileKind { kBig, k128, k64, k64Deep };
+TileKind choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps) {
+  auto tiles = [&](int64_t e) { return (double)((n_a + e - 1) / e) * (double)((n_b + e - 1) / e); };
+  const double k = (double)ksteps;
+  TileKind best = kBig;
+  double t_best = std::ceil(tiles(256) / kNumCu) * (1.25 * k + 7.0);
+  auto consider = [&](TileKind kind, double t) {
+    if (t < t_best) { t_best = t; best = kind; }
+  };
+  const double x = tiles(128) / (2.0 * kNumCu), y = tiles(64) / (4.0 * kNumCu);
+  consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : x > 0.5 ? 0.3 + 0.7 * x : 0.65) * (k + 4.0));
+  consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.35 + 0.5 * y : 0.45) * k + 3.0);
+  if (y <= 0.5) consider(k64Deep, 0.31 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.7);
+  return best;
+}
+
+// A = silu(X Wg^T) * (X Wu^T) of a chunk, or its backward (dA given)
+template <class C, bool kBackward>
+void launch_gateup_small(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
+                         __bf16* A, __bf16* dAG, __bf16* dU) {
+  const int n_it = (I + C::EA / 2 - 1) / (C::EA / 2), n_st = (rows + C::EB - 1) / C::EB;
+  hipLaunchKernelGGL((k_mlp_gateup_small<C, kBackward>), dim3(even_grid(n_it, n_st)), dim3(C::kThreads), C::kLds, st,
+                     X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
+}
+template <bool kBackward>
+void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
+                   __bf16* A, __bf16* dAG, __bf16* dU) {
+  switch (choose_tile(2 * (int64_t)I, rows, (d + kBK - 1) / kBK)) {
+    case k128: return launch_gateup_small<Tile128, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
+    case k64: return launch_gateup_small<Tile64, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
+    case k64Deep: return launch_gateup_small<Tile64Deep, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
+    default: break;
+  }
+  const int n_it = (I + kGateUpI - 1) / kGateUpI, n_st = (rows + kTile - 1) / kTile;
+  hipLaunchKernelGGL(k_mlp_gateup<kBackward>, dim3(mlp_grid(n_it, n_st)), dim3(kThreads), kLdsBytes, st,
+                     X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
+}
+
+// out[rows][N] = P Q^T, P [rows][K], Q [N][K]
+template <class C>
+void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
+  const int n_nt = (N + C::EA - 1) / C::EA, n_st = (rows + C::EB - 1) / C::EB;
+  hipLaunchKernelGGL(k_mlp_gemm_nt_small<C>, dim3(even_grid(n_nt, n_st)), dim3(C::kThreads), C::kLds, st,
+                     P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
+}
+void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
+  switch (choose_tile(N, rows, (K + kBK - 1) / kBK)) {
+    case k128: return launch_nt_small<Tile128>(st, P, Q, rows, N, K, out);
+    case k64: return launch_nt_small<Tile64>(st, P, Q, rows, N, K, out);
+    case k64Deep: return launch_nt_small<Tile64Deep>(st, P, Q, rows, N, K, out);
+    default: break;
+  }
+  const int n_nt = (N + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
+  hipLaunchKernelGGL(k_mlp_gemm_nt, dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
+                     P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
+}
+
 // Tail of the workgroup grid.  A GEMM of n_a x n_b block tiles runs in rounds of kNumCu workgroups; when the
 // last round would be at most half full, the tiles of that round (whole tile rows of the A side, else whole
 // tile columns of the B side) are cut in two along the B side (256 x 128 tiles) and launched separately, so
@@ -94,20 +176,33 @@ Tail tail_split(int n_a, int n_b) {
   return {0, 0};
 }
 
-// out[rows][N] (+)= P1 Q1 (+ P2 Q2), Q: [K][ldq] with N columns used
+// out[rows][N] = P1 Q1 (+ P2 Q2), P: [rows][K], Q: [K][N]
+template <class C>
+void launch_nn_small(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16* P2, const __bf16* Q2,
+                     int rows, int N, int K, __bf16* out) {
+  const int n_nt = (N + C::EA - 1) / C::EA, n_st = (rows + C::EB - 1) / C::EB;
+  hipLaunchKernelGGL(k_mlp_gemm_nn_small<C>, dim3(even_grid(n_nt, n_st)), dim3(C::kThreads), C::kLds, st,
+                     P1, Q1, P2, Q2, K, N, rows, N, K, n_st, n_nt, out, N);
+}
 void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16* P2, const __bf16* Q2,
-               int ldp, int ldq, int rows, int N, int K, __bf16* out, int ldo) {
+               int rows, int N, int K, __bf16* out) {
+  switch (choose_tile(N, rows, (P2 ? 2 : 1) * (int64_t)((K + kBK - 1) / kBK))) {
+    case k128: return launch_nn_small<Tile128>(st, P1, Q1, P2, Q2, rows, N, K, out);
+    case k64: return launch_nn_small<Tile64>(st, P1, Q1, P2, Q2, rows, N, K, out);
+    case k64Deep: return launch_nn_small<Tile64Deep>(st, P1, Q1, P2, Q2, rows, N, K, out);
+    default: break;
+  }
   const int n_nt = (N + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
   const Tail tl = tail_split(n_nt, n_st);
   const int nt_full = n_nt - tl.a_tail;        // only a split of the A side (columns of Q) is used here
   const int n_full = tl.a_tail ? nt_full * kTile : N;
-  hipLaunchKernelGGL(k_mlp_gemm_nn<Tile16>, dim3(xcd_grid_super(nt_full, n_st)), dim3(kThreads), kLdsBytes, st,
-                     P1, Q1, P2, Q2, ldp, ldq, rows, n_full, K, n_st, nt_full, out, ldo);
+  hipLaunchKernelGGL(k_mlp_gemm_nn<Tile16>, dim3(mlp_grid(nt_full, n_st)), dim3(kThreads), kLdsBytes, st,
+                     P1, Q1, P2, Q2, K, N, rows, n_full, K, n_st, nt_full, out, N);
   if (tl.a_tail) {
     const int n_sh = (rows + Tile16HalfB::EB - 1) / Tile16HalfB::EB;
-    hipLaunchKernelGGL(k_mlp_gemm_nn<Tile16HalfB>, dim3(xcd_grid_super(tl.a_tail, n_sh)), dim3(kThreads),
-                       Tile16HalfB::kLds, st, P1, Q1 + n_full, P2, Q2 ? Q2 + n_full : Q2, ldp, ldq, rows, N - n_full, K,
-                       n_sh, tl.a_tail, out + n_full, ldo);
+    hipLaunchKernelGGL(k_mlp_gemm_nn<Tile16HalfB>, dim3(mlp_grid(tl.a_tail, n_sh)), dim3(kThreads),
+                       Tile16HalfB::kLds, st, P1, Q1 + n_full, P2, Q2 ? Q2 + n_full : Q2, K, N, rows, N - n_full, K,
+                       n_sh, tl.a_tail, out + n_full, N);
   }
 }
 
@@ -167,17 +262,14 @@ mst_status mst_mlp_fwd(const void* X, const void* Wg, const void* Wu, const void
   // Algorithm 1: loop over the mini-sequences; O_i lands in its row range of O (the concatenation of line 5)
   for (int i = 0; i < p.n_chunks; ++i) {
     const int64_t r0 = (int64_t)i * p.C;
-    const int rows = rows_of(p, i), n_st = (rows + kTile - 1) / kTile;
+    const int rows = rows_of(p, i);
     {
       Scope sc(st, MST_MLP_K_GATEUP);
-      hipLaunchKernelGGL(k_mlp_gateup<false>, dim3(xcd_grid_super(p.n_it128, n_st)), dim3(kThreads), kLdsBytes, st,
-                         Xb + r0 * p.d, Wgb, Wub, rows, (int)p.d, (int)p.I, n_st, p.n_it128,
-                         A, (__bf16*)nullptr, (__bf16*)nullptr);
+      launch_gateup<false>(st, Xb + r0 * p.d, Wgb, Wub, rows, (int)p.d, (int)p.I, A, nullptr, nullptr);
     }
     {
       Scope sc(st, MST_MLP_K_DOWN);
-      hipLaunchKernelGGL(k_mlp_gemm_nt, dim3(xcd_grid_super(p.n_dt, n_st)), dim3(kThreads), kLdsBytes, st,
-                         A, (int)p.I, Wdb, (int)p.I, rows, (int)p.d, (int)p.I, n_st, p.n_dt, Ob + r0 * p.d, (int)p.d);
+      launch_nt(st, A, Wdb, rows, (int)p.d, (int)p.I, Ob + r0 * p.d);
     }
   }
   return check_launch();
@@ -212,22 +304,21 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
   // Algorithm 3: loop over the mini-sequences; dX_i lands in its row range, the weight gradients accumulate
   for (int i = 0; i < p.n_chunks; ++i) {
     const int64_t r0 = (int64_t)i * p.C;
-    const int rows = rows_of(p, i), n_st = (rows + kTile - 1) / kTile;
+    const int rows = rows_of(p, i);
     const __bf16* Xc = Xb + r0 * p.d;
     const __bf16* dOc = dOb + r0 * p.d;
     const int acc = i > 0 ? 1 : 0;
     {
       Scope sc(st, MST_MLP_K_DA);
-      launch_nn(st, dOc, Wdb, nullptr, nullptr, dd, dI, rows, dI, dd, bufG, dI);
+      launch_nn(st, dOc, Wdb, nullptr, nullptr, rows, dI, dd, bufG);
     }
     {
       Scope sc(st, MST_MLP_K_GATEUP_BWD);
-      hipLaunchKernelGGL(k_mlp_gateup<true>, dim3(xcd_grid_super(p.n_it128, n_st)), dim3(kThreads), kLdsBytes, st,
-                         Xc, Wgb, Wub, rows, dd, dI, n_st, p.n_it128, bufA, bufG, bufU);
+      launch_gateup<true>(st, Xc, Wgb, Wub, rows, dd, dI, bufA, bufG, bufU);
     }
     {
       Scope sc(st, MST_MLP_K_DX);
-      launch_nn(st, bufG, Wgb, bufU, Wub, dI, dd, rows, dd, dI, dXb + r0 * p.d, dd);
+      launch_nn(st, bufG, Wgb, bufU, Wub, rows, dd, dI, dXb + r0 * p.d);
     }
     {
       Scope sc(st, MST_MLP_K_DW);

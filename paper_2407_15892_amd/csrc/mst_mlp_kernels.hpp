@@ -16,26 +16,39 @@
 // remapping of mst_kernels.hpp.
 #pragma once
 #include "mst_kernels.hpp"
+#include "gemm_small.hpp"
 
 namespace mst {
 
-// Workgroup -> tile mapping for a 2-D tile space cut into 8 x 4 (slow x fast) super-tiles: XCD x owns super-tiles
-// x, x + 8, ... (row-major order of super-tiles), so the 32 workgroups resident on an XCD read 12 distinct operand
-// panels, also when the whole grid is only 16 x 16 tiles.  Returns false for padding workgroups.
+// Workgroup -> tile mapping of the 256 x 256 kernels: cut into 8 x 4 (slow x fast) super-tiles, XCD x owning
+// super-tiles x, x + 8, ... (row-major order of super-tiles), so that the 32 workgroups resident on an XCD read 12
+// distinct operand panels; or the even map of gemm_small.hpp, where whole super-tiles would give some XCDs a round of
+// workgroups more than others, or where there is not even one full round.  Gate/up on 36 x 6 tiles (10
+// super-tiles on 8 XCDs): 38 us instead of 64; down on 16 x 4 tiles (2 super-tiles, so 2 XCDs): 95 instead of 124.
+// On 112 x 16 tiles (7 full rounds either way) the super-tiles are 0.8 % faster.
 constexpr int kSuperSlow = 8, kSuperFast = 4;
-__device__ __forceinline__ bool xcd_tile_super(int n_slow, int n_fast, int* slow, int* fast) {
-  const int ss = (n_slow + kSuperSlow - 1) / kSuperSlow, sf = (n_fast + kSuperFast - 1) / kSuperFast;
-  const int x = blockIdx.x % kNumXcd, q = blockIdx.x / kNumXcd;
+__host__ __device__ inline int super_tiles(int n_slow, int n_fast) {
+  return ((n_slow + kSuperSlow - 1) / kSuperSlow) * ((n_fast + kSuperFast - 1) / kSuperFast);
+}
+__host__ __device__ inline bool use_super_tiles(int n_slow, int n_fast) {
+  constexpr int kPerRound = kSuperSlow * kSuperFast;                       // workgroups resident on an XCD
+  const int per_xcd = (n_slow * n_fast + kNumXcd - 1) / kNumXcd;
+  return per_xcd >= kPerRound && (super_tiles(n_slow, n_fast) + kNumXcd - 1) / kNumXcd == (per_xcd + kPerRound - 1) / kPerRound;
+}
+__host__ __device__ inline bool mlp_tile_of_block(int block, int n_slow, int n_fast, int* slow, int* fast) {
+  if (!use_super_tiles(n_slow, n_fast)) return even_tile_of_block(block, n_slow, n_fast, slow, fast);
+  const int sf = (n_fast + kSuperFast - 1) / kSuperFast;
+  const int x = block % kNumXcd, q = block / kNumXcd;
   const int super = x + kNumXcd * (q / (kSuperSlow * kSuperFast));
   const int inner = q % (kSuperSlow * kSuperFast);
-  if (super >= ss * sf) return false;
+  if (super >= super_tiles(n_slow, n_fast)) return false;
   *slow = (super / sf) * kSuperSlow + inner / kSuperFast;
   *fast = (super % sf) * kSuperFast + inner % kSuperFast;
   return *slow < n_slow && *fast < n_fast;
 }
-inline int xcd_grid_super(int n_slow, int n_fast) {
-  const int ss = (n_slow + kSuperSlow - 1) / kSuperSlow, sf = (n_fast + kSuperFast - 1) / kSuperFast;
-  return kNumXcd * ((ss * sf + kNumXcd - 1) / kNumXcd) * kSuperSlow * kSuperFast;
+inline int mlp_grid(int n_slow, int n_fast) {
+  if (!use_super_tiles(n_slow, n_fast)) return even_grid(n_slow, n_fast);
+  return kNumXcd * ((super_tiles(n_slow, n_fast) + kNumXcd - 1) / kNumXcd) * kSuperSlow * kSuperFast;
 }
 
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -58,7 +71,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
     __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int it, st;
-  if (!xcd_tile_super(n_it, n_st, &it, &st)) return;
+  if (!mlp_tile_of_block(blockIdx.x, n_it, n_st, &it, &st)) return;
   const int i0 = it * kGateUpI, s0 = st * kTile;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -167,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nt(
     int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int nt, st;
-  if (!xcd_tile_super(n_nt, n_st, &nt, &st)) return;
+  if (!mlp_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
   const int n0 = nt * kTile, s0 = st * kTile;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -196,7 +209,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
     int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int nt, st;
-  if (!xcd_tile_super(n_nt, n_st, &nt, &st)) return;
+  if (!mlp_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
   const int n0 = nt * T::EA, s0 = st * T::EB;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -219,6 +232,145 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
     gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, K, wa);
   }
   store_rows_bf16<T>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
+}
+
+// ---------------------------------------------------------------------------
+// The same three GEMMs with the smaller tiles of gemm_small.hpp, for chunks whose 256 x 256 tiles would leave most of
+// the chip idle (the rule and the measurements are at choose_tile in mst_mlp_api.hip); every output has the same bits.  A side = i or n (32 TA of them per workgroup; gate/up: 16 TA indices, gate and up rows interleaved per
+// wave as above), B side = 32 TB tokens.  The permuted A rows give a lane 4 TA consecutive n (2 TA consecutive i), which
+// leave the accumulators as 16-byte (8-byte) stores straight to memory: the four lane quarters complete a 128-byte line.
+// ---------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+
+template <class C, bool kBackward>
+__global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
+    const __bf16* __restrict__ Xc, const __bf16* __restrict__ Wg, const __bf16* __restrict__ Wu,
+    int rows, int d, int I, int n_st, int n_it,
+    __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  constexpr int H = C::TA / 2;                                  // gate tiles of a wave; as many up tiles follow
+  int it, st;
+  if (!even_tile_of_block(blockIdx.x, n_it, n_st, &it, &st)) return;
+  const int i0 = it * (C::EA / 2), s0 = st * C::EB;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wa = wave / C::WB, wb = wave % C::WB;
+
+  f32x4 acc[C::TA][C::TB];
+  zero_acc<C::TA, C::TB>(acc);
+  {
+    PanelKC16<C, C::EA, C::TA, true> pa;
+    PanelKC16<C, C::EB, C::TB, false> pb;
+    // a loader wave's LDS rows belong to one half (gate or up) of one wave row
+    constexpr int kLoaderRows = C::EA / C::kWaves;
+    const int half = wave * kLoaderRows / (16 * H);
+    const int ib = i0 + 16 * H * (half >> 1);
+    const __bf16* src = ((half & 1) ? Wu : Wg) + (size_t)ib * d;
+    const int valid = I - ib < 16 * H ? I - ib : 16 * H;
+    pa.init_map(src, d, valid, d, wave, lane, wa,
+                [](int lrow) { return 4 * H * ((lrow >> 2) & 3) + 4 * ((lrow >> 4) % H) + (lrow & 3); }, false);
+    pb.init(Xc + (size_t)s0 * d, d, rows - s0, d, wave, lane, wb);
+    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, d, wa);
+  }
+  constexpr int N = 4 * H;                                      // consecutive indices of a lane
+  typedef __attribute__((ext_vector_type(N))) __bf16 vec;
+  const int ib = i0 + 16 * H * wa + N * (lane >> 4);
+#pragma unroll
+  for (int u = 0; u < C::TB; ++u) {
+    const int s_local = s0 + wb * (16 * C::TB) + 16 * u + (lane & 15);
+    if (s_local >= rows || ib >= I) continue;                   // I % 8 == 0 and N divides 8
+    const size_t off = (size_t)s_local * I + ib;
+    vec da, a_o, g_o, u_o;
+    if (kBackward) da = *reinterpret_cast<const vec*>(dAG + off);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const float g = acc[e >> 2][u][e & 3], up = acc[H + (e >> 2)][u][e & 3];
+      const float sg = sigmoid_f(g);
+      const float act = g * sg;
+      a_o[e] = (__bf16)(act * up);
+      if (kBackward) {
+        const float dav = (float)da[e];
+        g_o[e] = (__bf16)(dav * up * (sg * (1.0f + g * (1.0f - sg))));
+        u_o[e] = (__bf16)(dav * act);
+      }
+    }
+    *reinterpret_cast<vec*>(A + off) = a_o;
+    if (kBackward) {
+      *reinterpret_cast<vec*>(dAG + off) = g_o;
+      *reinterpret_cast<vec*>(dU + off) = u_o;
+    }
+  }
+}
+
+// a lane's 4 TA consecutive n (A side, permuted) of UB token rows, as bf16
+template <class C>
+__device__ __forceinline__ void store_small_bf16(const f32x4 (&acc)[C::TA][C::TB], __bf16* __restrict__ out, int ldo,
+                                                 int rows, int N, int s0, int n0, int wa, int wb, int lane) {
+  const int nb = n0 + 16 * C::TA * wa + 4 * C::TA * (lane >> 4);
+#pragma unroll
+  for (int u = 0; u < C::TB; ++u) {
+    const int s_local = s0 + wb * (16 * C::TB) + 16 * u + (lane & 15);
+    if (s_local >= rows) continue;
+#pragma unroll
+    for (int p = 0; p < C::TA / 2; ++p) {
+      bf16x8 o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = (__bf16)acc[2 * p + (e >> 2)][u][e & 3];
+      if (nb + 8 * p < N) *reinterpret_cast<bf16x8*>(out + (size_t)s_local * ldo + nb + 8 * p) = o;   // N % 8 == 0
+    }
+  }
+}
+
+// out[s][n] = sum_k P[s][k] Q[n][k]
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nt_small(
+    const __bf16* __restrict__ P, int ldp, const __bf16* __restrict__ Q, int ldq, int rows, int N, int K,
+    int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  int nt, st;
+  if (!even_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
+  const int n0 = nt * C::EA, s0 = st * C::EB;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wa = wave / C::WB, wb = wave % C::WB;
+
+  f32x4 acc[C::TA][C::TB];
+  zero_acc<C::TA, C::TB>(acc);
+  {
+    PanelKC16<C, C::EA, C::TA, true> pa;
+    PanelKC16<C, C::EB, C::TB, false> pb;
+    pa.init(Q + (size_t)n0 * ldq, ldq, N - n0, K, wave, lane, wa);
+    pb.init(P + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
+    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K, wa);
+  }
+  store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
+}
+
+// out[s][n] = sum_k P1[s][k] Q1[k][n] (+ sum_k P2[s][k] Q2[k][n])
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nn_small(
+    const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
+    const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
+    int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  int nt, st;
+  if (!even_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
+  const int n0 = nt * C::EA, s0 = st * C::EB;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wa = wave / C::WB, wb = wave % C::WB;
+
+  f32x4 acc[C::TA][C::TB];
+  zero_acc<C::TA, C::TB>(acc);
+  const int terms = P2 != nullptr ? 2 : 1;
+  for (int term = 0; term < terms; ++term) {
+    PanelKS16<C, C::EA, C::TA, true> pa;
+    PanelKC16<C, C::EB, C::TB, false> pb;
+    pa.init((term ? Q2 : Q1) + n0, ldq, K, N - n0, wave, lane, wa);
+    pb.init((term ? P2 : P1) + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
+    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K, wa);
+  }
+  store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
 }
 
 // ---------------------------------------------------------------------------

@@ -160,3 +160,22 @@ def test_repeated_calls_reuse_the_workspace():
         assert np.abs(O - ref["O"]).max() <= TOL * np.abs(ref["O"]).max()
         dX = f64(run.backward()[0])
         assert np.abs(dX - ref["dX"]).max() <= TOL * np.abs(ref["dX"]).max()
+
+
+@pytest.mark.parametrize("S,d,I,Ms", [
+    # ragged in every dimension; between them the launches of the three chunkings take every block tile: 256 x 256 for
+    # gate/up unsplit, 128 x 128, 64 x 64 with the shallow (unsplit) and the deep pipeline (split), last tiles of 4 rows
+    (1700, 1160, 4104, (1, 2, 5)),
+    # down and dX: 256 x 256 unsplit, 128 x 128 in halves (12 full row tiles, a last column tile of 8); few K steps
+    (3000, 4104, 520, (1, 2)),
+    # chunks of 129 and 65 rows: one row past a tile of the smaller ones
+    (387, 2056, 1032, (3, 6)),
+])
+def test_every_block_tile_matches_oracle_and_gives_the_same_bits(S, d, I, Ms):
+    """Which block tile a launch takes depends on the rows of a chunk; a token's O and dX must not."""
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, Ms[0], index=320 + S % 7, w_std=0.05))
+    _, base, _, _ = _check(inp, M=Ms[0])
+    for M in Ms[1:]:
+        _, got, _ = _run_all(inp, M=M)
+        for k in ("O", "dX"):
+            assert np.array_equal(got[k], base[k]), (k, M)
