@@ -1,31 +1,30 @@
 // Smaller block tiles for launches that would leave most compute units without a 256 x 256 tile.
 //
-// A workgroup owns a (32 TA) x (16 TB WB) output tile.  Panels, fragments and MFMA order are those of gemm_tile16.hpp
-// and every output is summed over K in the same order as in the 256 x 256 kernels, so results do not depend on the
-// tile a launch was given, bit for bit (a split of K between groups of waves would be up to a quarter faster with 128
-// to 256 tiles, but its sums would depend on the rows of a chunk, that is on M).
+// A workgroup of four waves (2 x 2) owns a (32 TA) x (32 TB) output tile.  Panels, fragments and MFMA order are those of
+// gemm_tile16.hpp and every output is summed over K in the same order as in the 256 x 256 kernels, so results do not
+// depend on the tile a launch was given, bit for bit (a split of K between groups of waves would be up to a quarter
+// faster with 128 to 256 tiles, but its sums would depend on the rows of a chunk, that is on M).
 //
-// What bounds it: a 128 x 128 tile moves twice the bytes per flop of a 256 x 256 one from L2 into LDS (64 flop per byte,
-// about what one compute unit's load path and matrix cores balance at), a 64 x 64 tile four times; these tiles pay
-// where the large ones leave compute units idle or spend their time on first loads and epilogues.
+// What bounds it: LDS.  A 128 x 128 tile reads and writes 96 KB of it per K step of 512 MFMA clocks (64 x 64 wave tiles;
+// a 256 x 256 tile: 256 KB per 2048), and moves twice the bytes per flop from L2; a 64 x 64 tile twice as much again.
+// These tiles pay where the large ones leave compute units idle or spend their time on first loads and epilogues.
 #pragma once
 #include "gemm_tile.hpp"
 #include "gemm_tile16.hpp"
 
 namespace mst {
 
-// wave grid 2 x WB, wave tile (16 TA) x (16 TB), NSA and NSB LDS stages of the two panels
-template <int TA_, int TB_, int WB_, int NSA_, int NSB_>
+// wave tile (16 TA) x (16 TB), NSA and NSB LDS stages of the two panels; kPipelined: see the two main loops
+template <int TA_, int TB_, int NSA_, int NSB_, bool kPipelined_>
 struct CfgSmall {
-  static constexpr int WA = 2, WB = WB_, TA = TA_, TB = TB_, BK = 64;
+  static constexpr int WA = 2, WB = 2, TA = TA_, TB = TB_, BK = 64;
   static constexpr int NSA = NSA_, NSB = NSB_;
-  static_assert(NSB >= 2 && (NSA == NSB || NSA == NSB + 1), "the wait in the main loop counts on this");
+  static constexpr bool kPipelined = kPipelined_;
   static constexpr int kWaves = WA * WB, kThreads = 64 * kWaves;
   static constexpr int EA = 16 * TA * WA, EB = 16 * TB * WB;
   static constexpr int kPanelA = EA * BK * 2, kPanelB = EB * BK * 2;
   static constexpr int kLds = NSA * kPanelA + NSB * kPanelB;
   static constexpr int kKK = BK / 32;
-  static constexpr bool kPingPong = kWaves == 8;         // two waves per SIMD, half a step apart (see gemm_mainloop_pp)
   static_assert(kLds <= 163840, "all of a compute unit's LDS at most");
   typedef f32x4 Acc;
   __device__ __forceinline__ static Acc mma(bf16x8 a, bf16x8 b, Acc c) {
@@ -33,33 +32,27 @@ struct CfgSmall {
   }
 };
 
-// One K step: a memory phase (loads of the later stages between the fragment reads of this one), then the MFMAs.  With
-// four waves a barrier per step keeps them together and a second workgroup on the compute unit fills the gaps; with
-// eight the two halves alternate, one barrier per phase.
+// For compute units that hold two or more workgroups.  A K step is a memory phase (loads of the later stages between the
+// fragment reads of this one), then the MFMAs, with one barrier; another workgroup fills the gaps.  In step kt a wave
+// issues its B loads for step kt + 1, then its A loads for step kt + 2, which stay in flight over the next wait.
 template <class C, class PA, class PB>
-__device__ __forceinline__ void gemm_mainloop_small(f32x4 (&acc)[C::TA][C::TB], const PA& pa, const PB& pb, char* smem,
-                                                    int k_begin, int k_end, int group) {
-  // In step kt a wave issues its B loads for step kt + NSB - 1, then its A loads for step kt + NSA - 1; the wait that
-  // opens the next step leaves everything in flight that was issued after that step's own panels.
-  constexpr int kAhead = (C::NSB - 2) * (PA::SPW + PB::SPW) + (C::NSA > C::NSB ? PA::SPW : 0);
+__device__ __forceinline__ void gemm_mainloop_shared(f32x4 (&acc)[C::TA][C::TB], const PA& pa, const PB& pb, char* smem,
+                                                     int k_begin, int k_end) {
+  static_assert(C::NSA == 3 && C::NSB == 2, "three A stages, two B stages");
+  constexpr int kAhead = PA::SPW;
   const uint32_t ldsA = lds_addr_of(smem), ldsB = ldsA + C::NSA * C::kPanelA;
   const char* smemB = smem + C::NSA * C::kPanelA;
   const int nk = (k_end - k_begin + C::BK - 1) / C::BK;
-#pragma unroll
-  for (int j = 0; j < C::NSA - 1; ++j) {
-    const int jb = j - (C::NSA - C::NSB);
-    if (jb >= 0) pb.issue(ldsB + jb * C::kPanelB, k_begin + jb * C::BK);
-    pa.issue(ldsA + j * C::kPanelA, k_begin + j * C::BK);
-  }
+  pa.issue(ldsA, k_begin);
+  pb.issue(ldsB, k_begin);
+  pa.issue(ldsA + C::kPanelA, k_begin + C::BK);
   wait_vmcnt<kAhead>();
   __builtin_amdgcn_s_barrier();
-  if (C::kPingPong && group == 1) __builtin_amdgcn_s_barrier();
   int ca = 0, cb = 0;
-  int ka = k_begin + (C::NSA - 1) * C::BK, kb = k_begin + (C::NSB - 1) * C::BK;
+  int kb = k_begin + C::BK, ka = kb + C::BK;
   for (int kt = 0; kt < nk; ++kt) {
-    // ---- memory phase
     int na = ca + C::NSA - 1; if (na >= C::NSA) na -= C::NSA;
-    int nb = cb + C::NSB - 1; if (nb >= C::NSB) nb -= C::NSB;
+    const int nb = cb ^ 1;
     const char* a_panel = smem + ca * C::kPanelA;
     const char* b_panel = smemB + cb * C::kPanelB;
     bf16x8 a[C::kKK][C::TA], b[C::kKK][C::TB];
@@ -76,13 +69,7 @@ __device__ __forceinline__ void gemm_mainloop_small(f32x4 (&acc)[C::TA][C::TB], 
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (C::kPingPong && group == 1) wait_vmcnt<kAhead>();   // the other half reads the next stages behind the next barrier
     __builtin_amdgcn_sched_barrier(0);
-    if (C::kPingPong) {
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // ---- compute phase
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int kk = 0; kk < C::kKK; ++kk)
@@ -94,18 +81,100 @@ __device__ __forceinline__ void gemm_mainloop_small(f32x4 (&acc)[C::TA][C::TB], 
           acc[t][u] = C::mma(a[kk][t], b[kk][u], acc[t][u]);
         }
     __builtin_amdgcn_s_setprio(0);
-    if (!C::kPingPong || group == 0) wait_vmcnt<kAhead>();
+    wait_vmcnt<kAhead>();
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     ca = ca + 1 == C::NSA ? 0 : ca + 1;
-    cb = cb + 1 == C::NSB ? 0 : cb + 1;
-    ka += C::BK;
+    cb ^= 1;
     kb += C::BK;
+    ka += C::BK;
   }
-  if (C::kPingPong && group == 0) __builtin_amdgcn_s_barrier();
   wait_vmcnt<0>();
   __syncthreads();
+}
+
+// For a workgroup that has its compute unit to itself: one wave per SIMD, so nothing else issues MFMAs while it reads.
+// Each step therefore reads the fragments of the next one into a second set of registers between its own MFMAs (a
+// quarter wave of slack per load: 4 MFMAs after every load and its share of the reads).
+//
+// Stages, of NS per panel: step kt reads stage kt + 1, loads stage kt + NS - 1 into the place of stage kt - 1 (whose
+// fragments every wave has in registers, as its MFMAs of step kt - 1 needed them before the barrier), and stages
+// kt + 2 .. kt + NS - 2 are in flight at its wait.  64 x 64 tiles, NS = 5, 512 tokens, d = 2048, I = 5632: dX 41 us
+// against 57 with the loop above, down 22 against 27; 128 x 128, NS = 4, 1668 tokens, d = 1544, I = 5384: dX 91
+// against 120, down 52 against 58.
+template <class C, class PA, class PB>
+__device__ __forceinline__ void gemm_mainloop_pipelined(f32x4 (&acc)[C::TA][C::TB], const PA& pa, const PB& pb, char* smem,
+                                                        int k_begin, int k_end) {
+  static_assert(C::NSA == C::NSB && C::NSA >= 3, "as many stages of both panels");
+  constexpr int NS = C::NSA;
+  constexpr int kLoads = PB::SPW + PA::SPW, kFrags = C::kKK * (C::TA + C::TB), kMma = C::kKK * C::TA * C::TB;
+  const uint32_t ldsA = lds_addr_of(smem), ldsB = ldsA + NS * C::kPanelA;
+  const char* smemB = smem + NS * C::kPanelA;
+  const int nk = (k_end - k_begin + C::BK - 1) / C::BK;
+#pragma unroll
+  for (int j = 0; j < NS - 1; ++j) {
+    pb.issue(ldsB + j * C::kPanelB, k_begin + j * C::BK);
+    pa.issue(ldsA + j * C::kPanelA, k_begin + j * C::BK);
+  }
+  wait_vmcnt<(NS - 2) * kLoads>();
+  __builtin_amdgcn_s_barrier();
+  typedef bf16x8 FragsA[C::kKK][C::TA];
+  typedef bf16x8 FragsB[C::kKK][C::TB];
+  FragsA a0, a1;
+  FragsB b0, b1;
+#pragma unroll
+  for (int kk = 0; kk < C::kKK; ++kk) {
+#pragma unroll
+    for (int t = 0; t < C::TA; ++t) a0[kk][t] = pa.frag(smem, t, kk);
+#pragma unroll
+    for (int u = 0; u < C::TB; ++u) b0[kk][u] = pb.frag(smemB, u, kk);
+  }
+  int rd = 1, ld = NS - 1, kl = k_begin + (NS - 1) * C::BK;      // stage to read, stage to load, its k
+  auto step = [&](FragsA& a, FragsB& b, FragsA& an, FragsB& bn) {
+    wait_vmcnt<(NS - 3) * kLoads>();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const char* a_panel = smem + rd * C::kPanelA;
+    const char* b_panel = smemB + rd * C::kPanelB;
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      if (j < PB::SPW) pb.issue_one(j, ldsB + ld * C::kPanelB, kl);
+      else pa.issue_one(j - PB::SPW, ldsA + ld * C::kPanelA, kl);
+#pragma unroll
+      for (int f = j * kFrags / kLoads; f < (j + 1) * kFrags / kLoads; ++f) {
+        const int kk = f / (C::TA + C::TB), r = f % (C::TA + C::TB);
+        if (r < C::TA) an[kk][r] = pa.frag(a_panel, r, kk);
+        else bn[kk][r - C::TA] = pb.frag(b_panel, r - C::TA, kk);
+      }
+#pragma unroll
+      for (int m = j * kMma / kLoads; m < (j + 1) * kMma / kLoads; ++m) {
+        const int kk = m / (C::TA * C::TB), t = m / C::TB % C::TA, uu = m % C::TB;
+        const int u = (t & 1) ? C::TB - 1 - uu : uu;
+        acc[t][u] = C::mma(a[kk][t], b[kk][u], acc[t][u]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    rd = rd + 1 == NS ? 0 : rd + 1;
+    ld = ld + 1 == NS ? 0 : ld + 1;
+    kl += C::BK;
+  };
+  int kt = 0;
+  for (; kt + 2 <= nk; kt += 2) {
+    step(a0, b0, a1, b1);
+    step(a1, b1, a0, b0);
+  }
+  if (kt < nk) step(a0, b0, a1, b1);
+  wait_vmcnt<0>();
+  __syncthreads();
+}
+
+template <class C, class PA, class PB>
+__device__ __forceinline__ void gemm_mainloop_small(f32x4 (&acc)[C::TA][C::TB], const PA& pa, const PB& pb, char* smem,
+                                                    int k_begin, int k_end) {
+  if constexpr (C::kPipelined) gemm_mainloop_pipelined<C>(acc, pa, pb, smem, k_begin, k_end);
+  else gemm_mainloop_shared<C>(acc, pa, pb, smem, k_begin, k_end);
 }
 
 // Workgroup -> tile map: every XCD gets an equal, contiguous share of the tiles, ordered in bands of eight fast tiles, so

@@ -41,12 +41,12 @@ struct Scope : mst_host::Scope {
   Scope(hipStream_t s, int k) : mst_host::Scope(g_prof, s, k) {}
 };
 
-// The smaller tiles of gemm_small.hpp: 128 x 128 (80 KB of LDS, two workgroups on a compute unit); 64 x 64 (40 KB, four);
-// 64 x 64 with deeper pipelines (56 KB) for launches of one workgroup per compute unit, where nothing else hides the
-// latency of the loads: down at 200 tokens 74 us against 105 with the shallow one.
-typedef CfgSmall<4, 4, 2, 3, 2> Tile128;
-typedef CfgSmall<2, 2, 2, 3, 2> Tile64;
-typedef CfgSmall<2, 2, 2, 4, 3> Tile64Deep;
+// The smaller tiles of gemm_small.hpp: 128 x 128 and 64 x 64 with several workgroups on a compute unit (80 and 40 KB of
+// LDS: two and four), and both software-pipelined for launches that have a compute unit for every workgroup.
+typedef CfgSmall<4, 4, 3, 2, false> Tile128;
+typedef CfgSmall<4, 4, 4, 4, true> Tile128Lone;
+typedef CfgSmall<2, 2, 3, 2, false> Tile64;
+typedef CfgSmall<2, 2, 5, 5, true> Tile64Lone;
 
 template <class C, class Set>
 void set_small_attributes(Set set) {
@@ -66,8 +66,9 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_mlp_gateup<true>);
   set((const void*)k_mlp_gemm_nt);
   set_small_attributes<Tile128>(set);
+  set_small_attributes<Tile128Lone>(set);
   set_small_attributes<Tile64>(set);
-  set_small_attributes<Tile64Deep>(set);
+  set_small_attributes<Tile64Lone>(set);
   set((const void*)k_mlp_gemm_nn<Tile16>);
   set((const void*)k_mlp_gemm_nn<Tile16HalfB>);
   set((const void*)k_mlp_dw3<false>);
@@ -99,14 +100,15 @@ constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident
 // The figures are microseconds fitted to launches of the three kinds (gate/up, down, dA/dX) at 64 to 3000 tokens,
 // d = 256 to 4096, I = 896 to 14336; they only have to rank the tiles, and every tile gives the same bits:
 //   256 x 256      1.25 per K step + 7 (first loads, epilogue), in whole rounds of kNumCu
-//   128 x 128      1.0 per K step + 4 for two workgroups on a compute unit, 0.65 of that for a lone one; further rounds
-//                  overlap.  1024 tokens, d = 4096, I = 14336: down 156 us (256 tiles) against 308 (64 tiles of 256),
-//                  dX 302 against 607; 3000 tokens, d = 768, I = 2304: gate/up 26 against 39
-//   64 x 64        0.45 per K step + 3 for a lone workgroup, 0.85 with four on a compute unit.  512 tokens, d = 2048,
-//                  I = 5632: dA 20.5 (704 tiles) against 43 (44 of 256) and 23 (176 of 128)
-//   64 x 64 deep   0.31 per K step + 2.7 for a lone workgroup.  256 tokens, d = 256, I = 896: down 5.7 against 18;
-//                  200 tokens, d = 4096, I = 14336: down 74 against 250 (16 tiles of 256), dX 144 against 523
-enum TileKind { kBig, k128, k64, k64Deep };
+//   128 x 128      1.0 per K step + 4 for two workgroups on a compute unit; further rounds overlap.  3000 tokens,
+//                  d = 768, I = 2304: gate/up 26 us against 39
+//   128 x 128 lone 0.55 per K step + 3.2, up to kNumCu tiles.  1024 tokens, d = 4096, I = 14336: down 140 us (256 tiles)
+//                  against 308 (64 tiles of 256), dX 266 against 607
+//   64 x 64        0.45 (few workgroups on a compute unit) to 0.85 (four) per K step + 2.5.  1536 tokens, d = 1536,
+//                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256)
+//   64 x 64 lone   0.24 per K step + 2.5.  256 tokens, d = 256, I = 896: down 5.5 against 18; 200 tokens, d = 4096,
+//                  I = 14336: down 63 against 250 (16 tiles of 256), dX 129 against 523
+enum TileKind { kBig, k128, k128Lone, k64, k64Lone };
 TileKind choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps) {
   auto tiles = [&](int64_t e) { return (double)((n_a + e - 1) / e) * (double)((n_b + e - 1) / e); };
   const double k = (double)ksteps;
@@ -116,9 +118,10 @@ TileKind choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps) {
     if (t < t_best) { t_best = t; best = kind; }
   };
   const double x = tiles(128) / (2.0 * kNumCu), y = tiles(64) / (4.0 * kNumCu);
-  consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : x > 0.5 ? 0.3 + 0.7 * x : 0.65) * (k + 4.0));
-  consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.35 + 0.5 * y : 0.45) * k + 3.0);
-  if (y <= 0.5) consider(k64Deep, 0.31 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.7);
+  if (x <= 0.5) consider(k128Lone, 0.55 * k + 3.2);
+  else consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : 0.3 + 0.7 * x) * (k + 4.0));
+  consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.3 + 0.4 * y : 0.45) * k + 2.5);
+  if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
 }
 
@@ -135,8 +138,9 @@ void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf
                    __bf16* A, __bf16* dAG, __bf16* dU) {
   switch (choose_tile(2 * (int64_t)I, rows, (d + kBK - 1) / kBK)) {
     case k128: return launch_gateup_small<Tile128, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
+    case k128Lone: return launch_gateup_small<Tile128Lone, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
     case k64: return launch_gateup_small<Tile64, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
-    case k64Deep: return launch_gateup_small<Tile64Deep, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
+    case k64Lone: return launch_gateup_small<Tile64Lone, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
     default: break;
   }
   const int n_it = (I + kGateUpI - 1) / kGateUpI, n_st = (rows + kTile - 1) / kTile;
@@ -154,8 +158,9 @@ void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows,
 void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
   switch (choose_tile(N, rows, (K + kBK - 1) / kBK)) {
     case k128: return launch_nt_small<Tile128>(st, P, Q, rows, N, K, out);
+    case k128Lone: return launch_nt_small<Tile128Lone>(st, P, Q, rows, N, K, out);
     case k64: return launch_nt_small<Tile64>(st, P, Q, rows, N, K, out);
-    case k64Deep: return launch_nt_small<Tile64Deep>(st, P, Q, rows, N, K, out);
+    case k64Lone: return launch_nt_small<Tile64Lone>(st, P, Q, rows, N, K, out);
     default: break;
   }
   const int n_nt = (N + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
@@ -188,8 +193,9 @@ void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16*
                int rows, int N, int K, __bf16* out) {
   switch (choose_tile(N, rows, (P2 ? 2 : 1) * (int64_t)((K + kBK - 1) / kBK))) {
     case k128: return launch_nn_small<Tile128>(st, P1, Q1, P2, Q2, rows, N, K, out);
+    case k128Lone: return launch_nn_small<Tile128Lone>(st, P1, Q1, P2, Q2, rows, N, K, out);
     case k64: return launch_nn_small<Tile64>(st, P1, Q1, P2, Q2, rows, N, K, out);
-    case k64Deep: return launch_nn_small<Tile64Deep>(st, P1, Q1, P2, Q2, rows, N, K, out);
+    case k64Lone: return launch_nn_small<Tile64Lone>(st, P1, Q1, P2, Q2, rows, N, K, out);
     default: break;
   }
   const int n_nt = (N + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;

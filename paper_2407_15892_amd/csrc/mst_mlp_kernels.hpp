@@ -270,7 +270,7 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
     pa.init_map(src, d, valid, d, wave, lane, wa,
                 [](int lrow) { return 4 * H * ((lrow >> 2) & 3) + 4 * ((lrow >> 4) % H) + (lrow & 3); }, false);
     pb.init(Xc + (size_t)s0 * d, d, rows - s0, d, wave, lane, wb);
-    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, d, wa);
+    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, d);
   }
   constexpr int N = 4 * H;                                      // consecutive indices of a lane
   typedef __attribute__((ext_vector_type(N))) __bf16 vec;
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nt_small(
     PanelKC16<C, C::EB, C::TB, false> pb;
     pa.init(Q + (size_t)n0 * ldq, ldq, N - n0, K, wave, lane, wa);
     pb.init(P + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
-    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K, wa);
+    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K);
   }
   store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
 }
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nn_small(
     PanelKC16<C, C::EB, C::TB, false> pb;
     pa.init((term ? Q2 : Q1) + n0, ldq, K, N - n0, wave, lane, wa);
     pb.init((term ? P2 : P1) + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
-    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K, wa);
+    gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K);
   }
   store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
 }
