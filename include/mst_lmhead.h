@@ -223,7 +223,9 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
  *                            in one launch: their tile spaces then share one partly filled last round of
  *                            workgroups instead of leaving one each (same arithmetic as BLOCKS, bit for bit).
  *   MST_BWD_SCHEDULE_AUTO    (default) PAIRS or BLOCKS_FUSED, whichever a host-side cost model (rounds of
- *                            workgroups plus fp32 gradient traffic) ranks faster for the shape.
+ *                            workgroups plus fp32 gradient traffic) ranks faster for the shape.  It also looks at block
+ *                            shapes that the forced orders do not take: a single window, and a window's dH contraction
+ *                            in up to 8 splits with running sums of their own, added in fixed order at the end.
  * mst_set_bwd_schedule: host; the override belongs to the CALLING THREAD (thread-local, AUTO in every new
  * thread) and takes effect at that thread's next backward call, so one caller's setting never changes the
  * summation order of another thread's call; MST_ERR_BAD_SHAPE for an unknown value.
@@ -242,7 +244,8 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
  * over an n_slow x n_fast space of 256 x 256 tiles has mst_tile_grid(n_slow, n_fast) workgroups; workgroup b lands
  * on XCD b % 8, which owns a contiguous range of the slow coordinate and walks it in 4 x 8 rectangles of tiles:
  * order 0 (forward, dH, dW kernels) band by band of 4 slow tiles inside super-groups of 32 fast tiles, order 1
- * (dlogits kernel) group by group of 8 fast tiles.  mst_tile_of_workgroup writes the tile of workgroup `workgroup`
+ * (dlogits kernel) group by group of 8 fast tiles.  (Backward launches whose slow coordinate would leave more than an
+ * eighth of that grid as padding deal the tiles out evenly instead.)  mst_tile_of_workgroup writes the tile of workgroup `workgroup`
  * and returns 1, or returns 0 for a padding workgroup (it exits at once), or -1 for bad arguments.  Every tile is
  * the image of exactly one workgroup.
  */

@@ -191,6 +191,6 @@ __host__ __device__ inline bool even_tile_of_block(int block, int n_slow, int n_
   *fast = f0 + r - *slow * fs;
   return true;
 }
-inline int even_grid(int n_slow, int n_fast) { return 8 * ((n_slow * n_fast + 7) / 8); }
+__host__ __device__ inline int even_grid(int n_slow, int n_fast) { return 8 * ((n_slow * n_fast + 7) / 8); }
 
 }  // namespace mst

@@ -8,6 +8,7 @@
 #include "host_util.hpp"
 #include "mst_kernels.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -18,6 +19,7 @@ using namespace mst;
 constexpr int kNumCu = 256;          // MI355X compute units; only steers the schedule choices (splits, blocks)
 constexpr int kMaxDhSplit = 16;
 constexpr int kMaxWindows = 64;      // most vocabulary windows the block schedule considers
+constexpr int kMaxBlockSplit = 8;    // most splits of a window's dH contraction
 
 // Override of the backward order, per calling thread: a caller that forces an order cannot change the
 // summation order of a call another thread is making at the same time.
@@ -53,6 +55,7 @@ struct Plan {
   bool blk_use;
   bool blk_fused;     // dH and dW of a block from one launch
   int blk_rows, blk_n_rb, blk_win_tiles, blk_n_win, blk_ldg;
+  int blk_split;      // splits of a window's dH contraction, each with running sums of its own
   size_t blk_acc;     // byte offset of the dH sums
   double est_pairs_us, est_blocks_us;   // the cost model's figures (for the record; see choose_schedule)
 };
@@ -68,11 +71,137 @@ struct Plan {
 //           R covers S), dH of a row block accumulates over the windows (S*d*4 bytes, far smaller than dW when
 //           V >> d).
 // The estimate counts rounds of kNumCu workgroups per launch at a nominal time per K step, plus the fp32
-// gradient traffic at a nominal bandwidth; it only has to rank the candidates.
+// gradient traffic at a nominal bandwidth; it only has to rank the candidates.  The automatic choice looks at more
+// block shapes afterwards (choose_split_blocks).
 constexpr double kUsPerKStep = 1.5;      // one 256 x 256 x 64 block-tile step with one workgroup per CU
 constexpr double kRmwBytesPerUs = 4.0e6; // fp32 read-modify-write streams next to a running GEMM
 double rounds_us(int64_t tiles, int64_t k) {
   return (double)((tiles + kNumCu - 1) / kNumCu) * (double)((k + kBK - 1) / kBK) * kUsPerKStep;
+}
+
+// Block shapes with splits of dH's contraction, or with a single window.  With few row tiles (1024 rows x 4096: 64 tiles
+// of dH) the unsplit dH tiles of a block are too few and too long to share a launch with its dW tiles, so the printed
+// order with its read-modify-write of dW per pair used to be taken: S = 1024, d = 4096, V = 128256, M = 4: step 4.6 ms,
+// with two splits and four windows 3.4 ms.
+//
+// The model, in microseconds, fitted to launches of the 8B-shaped configurations at S = 200 to 32768.  A 256 x 256 tile
+// takes 1.375 per K step with all compute units busy (the chip is power limited then), 1.25 otherwise, plus what its ends
+// take: dlogits 6; dH sums 8, and 8 more where they are read; dW 12 plus 0.1 per K step up to 20, and 10 more where it
+// is read.  A launch takes whole rounds of kNumCu tiles at the faster rate, all its tiles at the slower one, or its
+// bytes at 4.6 TB/s, whichever is longest, plus 2.  dH + dW: the dH tiles first, the dW tiles as compute units come
+// free; bound by bytes it takes a third longer than the bytes alone (dH's loads wait behind dW's stores: 200 rows,
+// V = 128256: 930 for the 3.3 GB that take 740 in two launches).
+constexpr double kBusyStepUs = 1.375, kStepUs = 1.25, kHbmBytesPerUs = 4.6e6;
+struct TileCost {
+  double ksteps, ends;
+  double busy() const { return kBusyStepUs * ksteps + ends; }
+  double alone() const { return kStepUs * ksteps + ends; }
+};
+TileCost tile_cost(int64_t k, double ends) { return {(double)((k + kBK - 1) / kBK), ends}; }
+TileCost dlogits_cost(int64_t d) { return tile_cost(d, 6.0); }
+TileCost dh_cost(int64_t k, bool add) { return tile_cost(k, add ? 16.0 : 8.0); }
+TileCost dw_cost(int64_t rows, bool add) {
+  TileCost c = tile_cost(rows, 0.0);
+  c.ends = 12.0 + (c.ksteps < 80.0 ? 0.1 * c.ksteps : 8.0) + (add ? 10.0 : 0.0);
+  return c;
+}
+double launch_us(int64_t tiles, TileCost c, double bytes) {
+  const double rounds = (double)((tiles + kNumCu - 1) / kNumCu) * c.alone(), busy = (double)tiles / kNumCu * c.busy();
+  return 2.0 + std::max(std::max(rounds, busy), bytes / kHbmBytesPerUs);
+}
+// n1 tiles of c1, then n2 of c2, handed out in this order
+double launch_us(int64_t n1, TileCost c1, int64_t n2, TileCost c2, double bytes) {
+  const double t1 = c1.alone(), t2 = c2.alone();
+  const int64_t late = n1 % kNumCu;                           // so many units start on the second kind one t1 after the others
+  const double a = (double)(n1 / kNumCu) * t1, b = a + t1;
+  auto done = [&](double t) {
+    return (int64_t)((t - a) / t2 + 1e-9) * (kNumCu - late) + (t > b ? (int64_t)((t - b) / t2 + 1e-9) * late : 0);
+  };
+  double span = b + ((double)(n2 / kNumCu) + 2.0) * t2;       // an upper bound
+  const int64_t lo = n2 / kNumCu, lag = (int64_t)(t1 / t2) + 1;
+  for (int64_t j = lo > lag ? lo - lag : 0; j <= lo + lag + 1; ++j) {
+    if (done(a + (double)j * t2) >= n2 && a + (double)j * t2 < span) span = a + (double)j * t2;
+    if (late && done(b + (double)j * t2) >= n2 && b + (double)j * t2 < span) span = b + (double)j * t2;
+  }
+  if (late && span < b) span = b;
+  const double busy = ((double)n1 * c1.busy() + (double)n2 * c2.busy()) / kNumCu;
+  return 2.0 + std::max(std::max(span, busy), 1.3 * bytes / kHbmBytesPerUs);
+}
+
+double pairs_us(const Plan* p) {
+  const int64_t S = p->S, d = p->d, V = p->V, C = p->C;
+  const double w_all = 2.0 * (double)V * (double)d;                        // bytes of W
+  double t = 0.0;
+  for (int ia = 0; ia < p->n_chunks; ia += 2) {
+    int64_t rows_pair = 0;
+    for (int i = ia; i < ia + 2 && i < p->n_chunks; ++i) {
+      const int64_t rows = (S - (int64_t)i * C) < C ? (S - (int64_t)i * C) : C, n_st = (rows + kTile - 1) / kTile;
+      const double g = 2.0 * (double)rows * (double)V, part = 4.0 * (double)p->dh_split * (double)(rows * d);
+      rows_pair += rows;
+      t += launch_us(n_st * p->n_vt, dlogits_cost(d), w_all + g);
+      t += launch_us(n_st * p->n_jt * p->dh_split, dh_cost((int64_t)p->dh_ksteps * kBK, false), w_all + g + part);
+      if (p->dh_split > 1) t += 4.0 + part / kHbmBytesPerUs;
+    }
+    t += launch_us((int64_t)p->n_vt * p->n_jt, dw_cost(rows_pair, ia > 0), (ia > 0 ? 4.0 : 2.0) * w_all);
+  }
+  return t;
+}
+
+double blocks_us(const Plan* p, int64_t R, int n_rb, int win_tiles, int n_win, int split) {
+  const int64_t S = p->S, d = p->d, V = p->V;
+  const double w_all = 2.0 * (double)V * (double)d;
+  double t = 0.0;
+  for (int rb = 0; rb < n_rb; ++rb) {
+    const int64_t rows = (S - rb * R) < R ? (S - rb * R) : R, n_st = (rows + kTile - 1) / kTile;
+    const double sum_bytes = n_win > 1 || split > 1 ? 4.0 * (double)split * (double)(n_st * p->n_jt) * (kTile * kTile) : 0.0;
+    for (int w = 0; w < n_win; ++w) {
+      const int64_t v0 = (int64_t)w * win_tiles * kTile, cols = V - v0 < (int64_t)win_tiles * kTile ? V - v0 : (int64_t)win_tiles * kTile;
+      const int64_t tiles_w = (cols + kTile - 1) / kTile;
+      const double w_bytes = w_all * (double)cols / (double)V, g_bytes = 2.0 * (double)(rows * cols);
+      t += launch_us(n_st * tiles_w, dlogits_cost(d), w_bytes + g_bytes);
+      t += launch_us(n_st * p->n_jt * split, dh_cost((cols + split - 1) / split, w > 0), tiles_w * p->n_jt, dw_cost(rows, rb > 0),
+                     w_bytes + g_bytes + (rb > 0 ? 4.0 : 2.0) * w_bytes + (w > 0 ? 2.0 : 1.0) * sum_bytes);
+    }
+    if (split > 1) t += 4.0 + sum_bytes / kHbmBytesPerUs;
+  }
+  return t;
+}
+
+// Looks for a block shape with one window, or with dH's contraction split, that beats `p`'s choice so far by more than
+// the model is good for.
+void choose_split_blocks(Plan* p) {
+  const int64_t S = p->S, d = p->d;
+  const double pairs = pairs_us(p);
+  const double so_far = p->blk_use ? blocks_us(p, p->blk_rows, p->blk_n_rb, p->blk_win_tiles, p->blk_n_win, 1) : pairs;
+  double best = 0.95 * std::min(so_far, pairs);
+  bool found = false;
+  for (int n_win = 1; n_win <= kMaxWindows && n_win <= p->n_vt; ++n_win) {
+    const int win_tiles = (p->n_vt + n_win - 1) / n_win;
+    if ((p->n_vt + win_tiles - 1) / win_tiles != n_win) continue;          // same partition as a smaller count
+    const int64_t ldg_w = (int64_t)win_tiles * kTile;
+    for (int split = 1; split <= kMaxBlockSplit && split <= win_tiles; split *= 2) {
+      const int64_t per_row = ldg_w * 2 + (n_win > 1 || split > 1 ? (int64_t)split * p->n_jt * kTile * 4 : 0);
+      if (p->b_total < 256 + (size_t)per_row * kTile) break;
+      int64_t R = (int64_t)((p->b_total - 256) / (size_t)per_row) / kTile * kTile;
+      const int64_t S_up = (S + kTile - 1) / kTile * kTile;
+      if (R > S_up) R = S_up;
+      const int n_rb = (int)((S + R - 1) / R);
+      R = ((S + n_rb - 1) / n_rb + kTile - 1) / kTile * kTile;
+      if (R * ldg_w >= (int64_t(1) << 30) || R * d >= (int64_t(1) << 30)) continue;   // 32-bit offsets inside a block
+      const double t = blocks_us(p, R, n_rb, win_tiles, n_win, split);
+      if (t < best) {
+        best = t;
+        found = true;
+        p->blk_use = true;
+        p->blk_fused = true;
+        p->blk_rows = (int)R; p->blk_n_rb = n_rb; p->blk_win_tiles = win_tiles; p->blk_n_win = n_win;
+        p->blk_ldg = (int)ldg_w;
+        p->blk_split = split;
+        p->blk_acc = align_up((size_t)R * ldg_w * 2, 256);
+      }
+    }
+  }
+  if (found) { p->est_pairs_us = pairs; p->est_blocks_us = best; }
 }
 
 void choose_schedule(Plan* p, int forced) {
@@ -128,11 +257,10 @@ void choose_schedule(Plan* p, int forced) {
         t += rounds_us(n_st * n_jt, cols) + rounds_us(tiles_w * n_jt, rows);               // dH, dW
       }
     }
-    // One launch for the dH and the dW tiles of a block: a partly filled last round of dH workgroups is topped up
-    // with dW tiles, and one launch boundary per block goes away.  Measured: -0.25 to -0.4 % of the step where both
-    // tile counts fill whole rounds anyway (configs 2 and 3: 512 and 1008 tiles), -1.5 to -2 % where they do not
-    // (Gemma shape: 896 dH tiles = 3.5 rounds; config 5: 496).  The automatic choice always takes it; the block
-    // shapes are ranked as separate launches.
+    // One launch for the dH and the dW tiles of a block (BLOCKS_FUSED): a partly filled last round of dH workgroups is
+    // topped up with dW tiles, and one launch boundary per block goes away.  Measured: -0.25 to -0.4 % of the step where
+    // both tile counts fill whole rounds anyway (512 and 1008 tiles), -1.5 to -2 % where they do not (896 dH tiles = 3.5
+    // rounds; 496).  The automatic choice always takes it; the block shapes are ranked as separate launches.
     const bool fuse = forced == MST_BWD_SCHEDULE_BLOCKS_FUSED || forced == MST_BWD_SCHEDULE_AUTO;
     const double t_pick = t;
     if (!p->blk_use || t_pick < best) {
@@ -141,12 +269,16 @@ void choose_schedule(Plan* p, int forced) {
       p->blk_fused = fuse;
       p->blk_rows = (int)R; p->blk_n_rb = n_rb; p->blk_win_tiles = win_tiles; p->blk_n_win = n_win;
       p->blk_ldg = (int)ldg_w;
+      p->blk_split = 1;
       p->blk_acc = align_up((size_t)R * ldg_w * 2, 256);
     }
   }
   p->est_blocks_us = best;
   if (forced == MST_BWD_SCHEDULE_PAIRS) p->blk_use = false;
-  else if (forced == MST_BWD_SCHEDULE_AUTO && p->blk_use && !(best < pairs)) p->blk_use = false;
+  else if (forced == MST_BWD_SCHEDULE_AUTO) {
+    if (!(best < pairs)) p->blk_use = false;
+    choose_split_blocks(p);
+  }
   // MST_BWD_SCHEDULE_BLOCKS and _BLOCKS_FUSED keep the best block shape whenever one fits
 }
 
@@ -238,13 +370,25 @@ bool set_kernel_attributes() {   // on the current device
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess) ok = false;
   };
   set((const void*)k_fwd_gemm_lse);
-  set((const void*)k_bwd_gemm_dlogits);
-  set((const void*)k_bwd_gemm_dh);
-  set((const void*)k_bwd_gemm_dw<false>);
-  set((const void*)k_bwd_gemm_dw<true>);
-  set((const void*)k_bwd_gemm_dh_dw<false>);
-  set((const void*)k_bwd_gemm_dh_dw<true>);
+  set((const void*)k_bwd_gemm_dlogits<false>);
+  set((const void*)k_bwd_gemm_dlogits<true>);
+  set((const void*)k_bwd_gemm_dh<false>);
+  set((const void*)k_bwd_gemm_dh<true>);
+  set((const void*)k_bwd_gemm_dw<false, false>);
+  set((const void*)k_bwd_gemm_dw<true, false>);
+  set((const void*)k_bwd_gemm_dw<false, true>);
+  set((const void*)k_bwd_gemm_dw<true, true>);
+  set((const void*)k_bwd_gemm_dh_dw<false, false>);
+  set((const void*)k_bwd_gemm_dh_dw<true, false>);
+  set((const void*)k_bwd_gemm_dh_dw<false, true>);
+  set((const void*)k_bwd_gemm_dh_dw<true, true>);
   return ok;
+}
+
+auto dlogits_kernel(int n_vt) { return uneven_over_xcds(n_vt) ? k_bwd_gemm_dlogits<true> : k_bwd_gemm_dlogits<false>; }
+auto dw_kernel(bool store_only, int n_vt) {
+  return uneven_over_xcds(n_vt) ? (store_only ? k_bwd_gemm_dw<true, true> : k_bwd_gemm_dw<false, true>)
+                                : (store_only ? k_bwd_gemm_dw<true, false> : k_bwd_gemm_dw<false, false>);
 }
 
 mst_status check_launch() { return hipGetLastError() == hipSuccess ? MST_OK : MST_ERR_LAUNCH; }
@@ -477,7 +621,7 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     const int64_t r0 = (int64_t)i * p.C;
     const int rows = rows_of(i), n_st = (rows + kTile - 1) / kTile;
     Scope sc(st, MST_K_BWD_GEMM_DLOGITS);
-    hipLaunchKernelGGL(k_bwd_gemm_dlogits, dim3(xcd_grid_2d(p.n_vt, n_st)), dim3(kThreads), kLdsBytes, st,
+    hipLaunchKernelGGL(dlogits_kernel(p.n_vt), dim3(launch_grid(p.n_vt, n_st)), dim3(kThreads), kLdsBytes, st,
                        Hb + r0 * p.d, Wb, labels + r0, lse + r0, rows, (int)p.d, (int)p.V, 0, (int)p.V, ignore_index,
                        n_st, p.n_vt, G, p.ldg);
   };
@@ -487,7 +631,7 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     float* partial = static_cast<float*>(partial_space);
     {
       Scope sc(st, MST_K_BWD_GEMM_DH);
-      hipLaunchKernelGGL(k_bwd_gemm_dh, dim3(xcd_grid(n_st * p.n_jt * p.dh_split)), dim3(kThreads), kLdsBytes, st,
+      hipLaunchKernelGGL(k_bwd_gemm_dh<false>, dim3(xcd_grid(n_st * p.n_jt * p.dh_split)), dim3(kThreads), kLdsBytes, st,
                          G, p.ldg, Wb, rows, (int)p.d, (int)p.V, n_st, p.n_jt, p.dh_split, p.dh_ksteps, kDhSplit,
                          nv, grad_loss, partial, p.C, dHb + r0 * p.d);
     }
@@ -501,7 +645,7 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
   auto grad_w = [&](int i_first, int i_last, int rows) {
     const int64_t r0 = (int64_t)i_first * p.C;
     Scope sc(st, MST_K_BWD_GEMM_DW);
-    hipLaunchKernelGGL(i_first > 0 ? k_bwd_gemm_dw<false> : k_bwd_gemm_dw<true>, dim3(xcd_grid_2d(p.n_vt, p.n_jt)),
+    hipLaunchKernelGGL(dw_kernel(i_first == 0, p.n_vt), dim3(launch_grid(p.n_vt, p.n_jt)),
                        dim3(kThreads), kLdsBytes, st,
                        slot[0], p.ldg, Hb + r0 * p.d, rows, (int)p.d, (int)p.V, p.n_vt, p.n_jt,
                        i_last == p.n_chunks - 1 ? 1 : 0, nv, grad_loss, dW);
@@ -514,6 +658,12 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     // accumulate in a fixed order.
     __bf16* G = reinterpret_cast<__bf16*>(ws);
     float* dh_sums = reinterpret_cast<float*>(ws + p.blk_acc);
+    auto launch_dh_reduce_tiles = [&](int n_st, int rows, int64_t r0) {
+      Scope sc(st, MST_K_BWD_DH_REDUCE);
+      const int waves = n_st * p.n_jt * kTA16 * Tile16::kWaves;       // a multiple of the 4 of a workgroup
+      hipLaunchKernelGGL(k_bwd_dh_reduce_tiles, dim3(waves / 4), dim3(256), 0, st, dh_sums, p.blk_split, n_st, p.n_jt, rows,
+                         (int)p.d, nv, grad_loss, dHb + r0 * p.d);
+    };
     for (int rb = 0; rb < p.blk_n_rb; ++rb) {
       const int64_t r0 = (int64_t)rb * p.blk_rows;
       const int rows = (int)((p.S - r0) < p.blk_rows ? (p.S - r0) : p.blk_rows);
@@ -525,30 +675,35 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
         const int Vw = (int)((p.V - v_base) < (int64_t)tiles_w * kTile ? (p.V - v_base) : (int64_t)tiles_w * kTile);
         {
           Scope sc(st, MST_K_BWD_GEMM_DLOGITS);
-          hipLaunchKernelGGL(k_bwd_gemm_dlogits, dim3(xcd_grid_2d(tiles_w, n_st)), dim3(kThreads), kLdsBytes, st,
+          hipLaunchKernelGGL(dlogits_kernel(tiles_w), dim3(launch_grid(tiles_w, n_st)), dim3(kThreads), kLdsBytes, st,
                              Hb + r0 * p.d, Wb + v_base * p.d, labels + r0, lse + r0, rows, (int)p.d, Vw, (int)v_base,
                              (int)p.V, ignore_index, n_st, tiles_w, G, p.blk_ldg);
         }
-        const int mode = w == 0 ? kDhFirst : (w == p.blk_n_win - 1 ? kDhLast : kDhAdd);
+        const bool last_win = w == p.blk_n_win - 1;
+        const int mode = p.blk_split > 1 ? (w == 0 ? kDhFirst : kDhAdd)
+                                         : (w == 0 ? (last_win ? kDhOnly : kDhFirst) : (last_win ? kDhLast : kDhAdd));
         const int dw_last = rb == p.blk_n_rb - 1 ? 1 : 0;
         if (p.blk_fused) {
           Scope sc(st, MST_K_BWD_GEMM_DH_DW);
-          const int dh_grid = xcd_grid_2d(n_st, p.n_jt);
-          hipLaunchKernelGGL(rb > 0 ? k_bwd_gemm_dh_dw<false> : k_bwd_gemm_dh_dw<true>,
-                             dim3(dh_grid + xcd_grid_2d(tiles_w, p.n_jt)), dim3(kThreads), kLdsBytes, st,
+          const int dh_grid = p.blk_split * dh_grid_2d(n_st, p.n_jt);
+          const bool general = p.blk_split > 1 || uneven_over_xcds(n_st) || uneven_over_xcds(tiles_w);
+          hipLaunchKernelGGL(general ? (rb > 0 ? k_bwd_gemm_dh_dw<false, true> : k_bwd_gemm_dh_dw<true, true>)
+                                     : (rb > 0 ? k_bwd_gemm_dh_dw<false, false> : k_bwd_gemm_dh_dw<true, false>),
+                             dim3(dh_grid + launch_grid(tiles_w, p.n_jt)), dim3(kThreads), kLdsBytes, st,
                              G, p.blk_ldg, Wb + v_base * p.d, Hb + r0 * p.d, rows, (int)p.d, Vw, n_st, tiles_w, p.n_jt,
                              dh_grid, mode, dw_last, nv, grad_loss, dh_sums, p.blk_rows, dHb + r0 * p.d,
-                             dW + v_base * p.d);
+                             dW + v_base * p.d, p.blk_split);
+          if (last_win && p.blk_split > 1) launch_dh_reduce_tiles(n_st, rows, r0);
         } else {
           {
             Scope sc(st, MST_K_BWD_GEMM_DH);
-            hipLaunchKernelGGL(k_bwd_gemm_dh, dim3(xcd_grid_2d(n_st, p.n_jt)), dim3(kThreads), kLdsBytes, st,
+            hipLaunchKernelGGL(uneven_over_xcds(n_st) ? k_bwd_gemm_dh<true> : k_bwd_gemm_dh<false>, dim3(dh_grid_2d(n_st, p.n_jt)), dim3(kThreads), kLdsBytes, st,
                                G, p.blk_ldg, Wb + v_base * p.d, rows, (int)p.d, Vw, n_st, p.n_jt, 1, (Vw + kBK - 1) / kBK, mode,
                                nv, grad_loss, dh_sums, p.blk_rows, dHb + r0 * p.d);
           }
           {
             Scope sc(st, MST_K_BWD_GEMM_DW);
-            hipLaunchKernelGGL(rb > 0 ? k_bwd_gemm_dw<false> : k_bwd_gemm_dw<true>, dim3(xcd_grid_2d(tiles_w, p.n_jt)),
+            hipLaunchKernelGGL(dw_kernel(rb == 0, tiles_w), dim3(launch_grid(tiles_w, p.n_jt)),
                                dim3(kThreads), kLdsBytes, st,
                                G, p.blk_ldg, Hb + r0 * p.d, rows, (int)p.d, Vw, tiles_w, p.n_jt,
                                dw_last, nv, grad_loss, dW + v_base * p.d);
@@ -598,7 +753,7 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
   info[2] = p.blk_use ? p.blk_n_rb : (p.n_chunks + 1) / 2;
   info[3] = p.blk_use ? (int64_t)p.blk_win_tiles * kTile : p.V;
   info[4] = p.blk_use ? p.blk_n_win : 1;
-  info[5] = p.blk_use ? 1 : p.dh_split;
+  info[5] = p.blk_use ? p.blk_split : p.dh_split;
   info[6] = (int64_t)p.est_pairs_us;
   info[7] = (int64_t)p.est_blocks_us;
   return MST_OK;

@@ -18,6 +18,7 @@
 #pragma once
 #include "gemm_tile.hpp"
 #include "gemm_tile16.hpp"
+#include "gemm_small.hpp"
 
 namespace mst {
 
@@ -111,15 +112,25 @@ __host__ __device__ inline bool xcd_tile_of_block(int block, int n_slow, int n_f
   return *slow < n_slow;
 }
 constexpr int kXcdRectSlow = 4, kXcdRectFast = 8, kXcdSuper = 32;
-// a kernel that serves several tile spaces passes its own workgroup index as `block`
-__device__ __forceinline__ bool xcd_tile_2d(int n_slow, int n_fast, int* slow, int* fast, int block = -1) {
-  return xcd_tile_of_block<kXcdRectSlow, kXcdRectFast, kXcdSuper>(block < 0 ? (int)blockIdx.x : block, n_slow, n_fast, slow, fast);
-}
-// the same with the fast panels kept from round to round
-__device__ __forceinline__ bool xcd_tile_2d_fast_major(int n_slow, int n_fast, int* slow, int* fast) {
-  return xcd_tile_of_block<kXcdRectSlow, kXcdRectFast, kXcdRectFast>((int)blockIdx.x, n_slow, n_fast, slow, fast);
-}
 __host__ __device__ inline int xcd_grid_2d(int n_slow, int n_fast) { return kNumXcd * ((n_slow + kNumXcd - 1) / kNumXcd) * n_fast; }
+
+// The map of a backward launch (the forward launch balances itself, see TileFeed): the rectangles above, unless the slow coordinate divides so badly over the XCDs that more than an
+// eighth of the grid would be padding (34 vocabulary tiles: 5 per XCD, the last one idle; 12 row tiles: two of eight idle;
+// 4: half of them): then an equal share of the tiles for every XCD (gemm_small.hpp).  kSuper = kXcdRectFast is the
+// order that keeps the fast panels from round to round.
+__host__ __device__ inline bool uneven_over_xcds(int n_slow) {
+  return 8 * (kNumXcd * ((n_slow + kNumXcd - 1) / kNumXcd) - n_slow) > n_slow;
+}
+// A template argument of the kernels, not a branch in them: the few scalar registers that the second map kept alive cost
+// the long launches of the whole-rectangle shapes half a percent.
+template <bool kEven, int kRectSlow = kXcdRectSlow, int kRectFast = kXcdRectFast, int kSuper = kXcdSuper>
+__device__ __forceinline__ bool launch_tile(int block, int n_slow, int n_fast, int* slow, int* fast) {
+  if (kEven && uneven_over_xcds(n_slow)) return even_tile_of_block(block, n_slow, n_fast, slow, fast);
+  return xcd_tile_of_block<kRectSlow, kRectFast, kSuper>(block, n_slow, n_fast, slow, fast);
+}
+__host__ __device__ inline int launch_grid(int n_slow, int n_fast) {
+  return uneven_over_xcds(n_slow) ? even_grid(n_slow, n_fast) : xcd_grid_2d(n_slow, n_fast);
+}
 
 // Persistent workgroups that pull their tiles from per-XCD queues instead of owning one tile each.
 //
@@ -288,7 +299,7 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemm_lse(
   if (queue) feed.init(queue, queue_base, xcd_grid_2d(n_vt, n_st) / kNumXcd, smem);
   for (int block = queue ? feed.next() : (int)blockIdx.x; block >= 0; block = queue ? feed.next() : -1) {
   int vt, st;                                        // an XCD's resident workgroups: 4 vocabulary x 8 row tiles
-  if (!xcd_tile_2d(n_vt, n_st, &vt, &st, block)) {   // padding entry of the map
+  if (!xcd_tile_of_block<kXcdRectSlow, kXcdRectFast, kXcdSuper>(block, n_vt, n_st, &vt, &st)) {   // padding entry of the map
     if (queue) { feed.issue(); feed.resolve(); }
     continue;
   }
@@ -454,13 +465,14 @@ __global__ __launch_bounds__(1024) void k_loss_reduce(const float* __restrict__ 
 // vocabulary entries from there on, G column 0 is the window's first entry; v_base is that entry's absolute
 // index and V_all the whole vocabulary (both only for the labels).  The row-chunk schedule passes the whole
 // vocabulary (v_base = 0, V = V_all).
+template <bool kEven>
 __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dlogits(
     const __bf16* __restrict__ Hc, const __bf16* __restrict__ W, const int* __restrict__ labels_c,
     const float* __restrict__ lse_c, int rows, int d, int V, int v_base, int V_all, int ignore_index, int n_st, int n_vt,
     __bf16* __restrict__ G, int ldg) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int vt, st;                                        // an XCD's resident workgroups: 4 vocabulary x 8 row tiles
-  if (!xcd_tile_2d_fast_major(n_vt, n_st, &vt, &st)) return;
+  if (!launch_tile<kEven, kXcdRectSlow, kXcdRectFast, kXcdRectFast>(blockIdx.x, n_vt, n_st, &vt, &st)) return;
   const int v0 = vt * kTile, s0 = st * kTile;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -555,9 +567,25 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dlogits(
 //             of accumulator (t, u) of wave w, lane l sit at float ((w * 32 + t * 4 + u) * 64 + l) * 4 -- one 16-byte
 //             load or store per accumulator and lane, 1 KB contiguous per wave instruction, whole tiles always
 //             (no masks; the padding of ragged tiles is written and read back like the rest and never leaves).
-constexpr int kDhSplit = 0, kDhFirst = 1, kDhAdd = 2, kDhLast = 3;
+//             With n_split > 1 every split of a window's contraction keeps running sums of its own (split sp behind
+//             the n_st * n_jt tiles of the splits before it), all windows are kDhFirst or kDhAdd, and
+//             k_bwd_dh_reduce_tiles adds the splits at the end.
+//   kDhOnly   one window covers the vocabulary: gamma * result as bf16, nothing to add
+constexpr int kDhSplit = 0, kDhFirst = 1, kDhAdd = 2, kDhLast = 3, kDhOnly = 4;
+// Workgroup -> tile map of the modes that are not kDhSplit.  With row tiles that divide badly over the XCDs the hidden
+// tiles are shared out instead: every XCD then reads its own columns of W (the larger operand) and all of the rows.
+template <bool kEven>
+__device__ __forceinline__ bool dh_tile_of_block(int block, int n_st, int n_jt, int* st, int* jt) {
+  if (kEven && uneven_over_xcds(n_st)) return even_tile_of_block(block, n_jt, n_st, jt, st);
+  return xcd_tile_of_block<kXcdRectSlow, kXcdRectFast, kXcdSuper>(block, n_st, n_jt, st, jt);
+}
+__host__ __device__ inline int dh_grid_2d(int n_st, int n_jt) {
+  return uneven_over_xcds(n_st) ? even_grid(n_jt, n_st) : xcd_grid_2d(n_st, n_jt);
+}
 // The body is a device function (block = index of the workgroup within this kernel's tile space) so that a
 // launch can serve the dH and the dW tiles of a vocabulary window together.
+// kGeneral: dH split, or a map other than whole rectangles.
+template <bool kGeneral>
 __device__ __forceinline__ void dh_tile(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, int rows, int d, int V,
     int n_st, int n_jt, int n_split, int ksteps_per_split, int mode,
@@ -571,8 +599,13 @@ __device__ __forceinline__ void dh_tile(
     st = w % n_st;
     jt = (w / n_st) % n_jt;
     sp = w / (n_st * n_jt);
-  } else if (!xcd_tile_2d(n_st, n_jt, &st, &jt, block)) {   // many row tiles: rectangles of row x hidden tiles per XCD
-    return;
+  } else {
+    if (kGeneral) {
+      const int grid = dh_grid_2d(n_st, n_jt);
+      sp = block / grid;
+      block -= sp * grid;
+    }
+    if (!dh_tile_of_block<kGeneral>(block, n_st, n_jt, &st, &jt)) return;
   }
   const int s0 = st * kTile, j0 = jt * kTile;
   const int lane = threadIdx.x & 63;
@@ -602,7 +635,7 @@ __device__ __forceinline__ void dh_tile(
   zero_acc<kTA16, kTB16>(acc);
   typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
   const __amdgpu_buffer_rsrc_t tile_sums =
-      make_rsrc_uniform(partial + ((size_t)st * n_jt + jt) * (size_t)(kTile * kTile), (uint32_t)(kTile * kTile * 4));
+      make_rsrc_uniform(partial + ((kGeneral ? (size_t)sp * n_st + st : (size_t)st) * n_jt + jt) * (size_t)(kTile * kTile), (uint32_t)(kTile * kTile * 4));
   const uint32_t slot0 = (uint32_t)(wave * (kTA16 * kTB16) * 64 + lane) * 16u;      // this lane's slot of accumulator (0, 0)
   if (mode == kDhAdd || mode == kDhLast) {
     // the running sums of the earlier windows go straight into the accumulators (the loads fly while the first
@@ -628,7 +661,7 @@ __device__ __forceinline__ void dh_tile(
   pb.init(W + j0, d, V, d - j0, wave, lane, wb);
   gemm_mainloop_pp<Tile16>(acc, pa, pb, smem, k_begin, k_end, wa, tie_off);
 
-  const bool to_bf16 = mode == kDhLast || (mode == kDhSplit && n_split == 1);
+  const bool to_bf16 = mode == kDhLast || mode == kDhOnly || (mode == kDhSplit && n_split == 1);
   if (!to_bf16) {
     if (mode == kDhSplit) {        // partials for k_bwd_dh_reduce: row-major
 #pragma unroll
@@ -673,14 +706,39 @@ __device__ __forceinline__ void dh_tile(
   }
 }
 
+template <bool kGeneral>
 __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dh(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, int rows, int d, int V,
     int n_st, int n_jt, int n_split, int ksteps_per_split, int mode,
     const long long* __restrict__ n_valid, float grad_loss,
     float* __restrict__ partial, int rows_stride, __bf16* __restrict__ dHc) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  dh_tile(G, ldg, W, rows, d, V, n_st, n_jt, n_split, ksteps_per_split, mode, n_valid, grad_loss, partial, rows_stride,
+  dh_tile<kGeneral>(G, ldg, W, rows, d, V, n_st, n_jt, n_split, ksteps_per_split, mode, n_valid, grad_loss, partial, rows_stride,
           dHc, blockIdx.x, smem);
+}
+
+// the same for sums in accumulator order (n_split arrays of n_st x n_jt tiles): one wave per row of accumulators (w, t) of
+// a tile.  Bound by reading the sums once (4 splits of 1024 x 4096: 17 us).
+__global__ __launch_bounds__(256) void k_bwd_dh_reduce_tiles(const float* __restrict__ partial, int n_split, int n_st, int n_jt,
+                                                             int rows, int d, const long long* __restrict__ n_valid,
+                                                             float grad_loss, __bf16* __restrict__ dHc) {
+  const int lane = threadIdx.x & 63;
+  const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int t = q % kTA16, wave = q / kTA16 % Tile16::kWaves, tile = q / (kTA16 * Tile16::kWaves);
+  const int st = tile / n_jt, jt = tile % n_jt;
+  const float gamma = gamma_of(n_valid, grad_loss);
+  const size_t split_stride = (size_t)n_st * n_jt * (kTile * kTile);
+#pragma unroll
+  for (int u = 0; u < kTB16; ++u) {
+    const float* src = partial + (size_t)tile * (kTile * kTile) + (((wave * kTA16 + t) * kTB16 + u) * 64 + lane) * 4;
+    f32x4 a = *reinterpret_cast<const f32x4*>(src);
+    for (int sp = 1; sp < n_split; ++sp) a += *reinterpret_cast<const f32x4*>(src + sp * split_stride);
+    const int row = st * kTile + (wave >> 2) * 128 + 16 * t + 4 * (lane >> 4);
+    const int col = jt * kTile + (wave & 3) * 64 + 16 * u + (lane & 15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (row + r < rows && col < d) dHc[(size_t)(row + r) * d + col] = (__bf16)(gamma * a[r]);
+  }
 }
 
 // fixed-order sum over the splits, scale by gamma, round to bf16.  8 outputs per thread.
@@ -860,14 +918,14 @@ __device__ __forceinline__ void dw_tile(
   }
 }
 
-template <bool kStoreOnly>
+template <bool kStoreOnly, bool kEven>
 __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dw(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ Hc, int rows, int d, int V,
     int n_vt, int n_jt, int last, const long long* __restrict__ n_valid, float grad_loss,
     float* __restrict__ dW) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int vt, jt;
-  if (!xcd_tile_2d(n_vt, n_jt, &vt, &jt)) return;
+  if (!launch_tile<kEven>(blockIdx.x, n_vt, n_jt, &vt, &jt)) return;
   const float scale = last ? gamma_of(n_valid, grad_loss) : 1.0f;
   dw_tile(G, ldg, ldg, Hc, d, rows, d, V, vt, jt, kStoreOnly ? 0 : 1, last ? 0 : 1, scale, dW, d, smem);
 }
@@ -876,22 +934,23 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dw(
 // neither depends on the other.  The first dh_grid workgroups take the dH tiles (the longer ones: their
 // contraction runs over the window, dW's over the rows), the rest the dW tiles; with one workgroup per CU the
 // hardware hands out tiles as CUs become free, so the two tile spaces share one partly filled last round
-// instead of leaving one each.  dh_grid = xcd_grid_2d(n_st, n_jt), a multiple of the XCD count, so both tile
-// spaces keep their XCD-aware mapping.
-template <bool kStoreOnly>
+// instead of leaving one each.  dh_grid = dh_split * dh_grid_2d(n_st, n_jt), a multiple of the XCD count, so both
+// tile spaces keep their XCD-aware mapping.
+template <bool kStoreOnly, bool kGeneral>
 __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dh_dw(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, const __bf16* __restrict__ Hc,
     int rows, int d, int V, int n_st, int n_vt, int n_jt, int dh_grid, int dh_mode, int dw_last,
     const long long* __restrict__ n_valid, float grad_loss,
-    float* __restrict__ dh_sums, int rows_stride, __bf16* __restrict__ dHc, float* __restrict__ dW) {
+    float* __restrict__ dh_sums, int rows_stride, __bf16* __restrict__ dHc, float* __restrict__ dW, int dh_split) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   if ((int)blockIdx.x < dh_grid) {
-    dh_tile(G, ldg, W, rows, d, V, n_st, n_jt, 1, (V + kBK - 1) / kBK, dh_mode, n_valid, grad_loss, dh_sums, rows_stride,
-            dHc, blockIdx.x, smem);
+    const int ksteps = (V + kBK - 1) / kBK, n_split = kGeneral ? dh_split : 1;
+    dh_tile<kGeneral>(G, ldg, W, rows, d, V, n_st, n_jt, n_split, kGeneral ? (ksteps + n_split - 1) / n_split : ksteps, dh_mode,
+                      n_valid, grad_loss, dh_sums, rows_stride, dHc, blockIdx.x, smem);
     return;
   }
   int vt, jt;
-  if (!xcd_tile_2d(n_vt, n_jt, &vt, &jt, (int)blockIdx.x - dh_grid)) return;
+  if (!launch_tile<kGeneral>((int)blockIdx.x - dh_grid, n_vt, n_jt, &vt, &jt)) return;
   const float scale = dw_last ? gamma_of(n_valid, grad_loss) : 1.0f;
   dw_tile(G, ldg, ldg, Hc, d, rows, d, V, vt, jt, kStoreOnly ? 0 : 1, dw_last ? 0 : 1, scale, dW, d, smem);
 }

@@ -71,8 +71,10 @@ bool set_kernel_attributes() {   // on the current device
   set_small_attributes<Tile64Lone>(set);
   set((const void*)k_mlp_gemm_nn<Tile16>);
   set((const void*)k_mlp_gemm_nn<Tile16HalfB>);
-  set((const void*)k_mlp_dw3<false>);
-  set((const void*)k_mlp_dw3<true>);
+  set((const void*)k_mlp_dw3<false, false>);
+  set((const void*)k_mlp_dw3<true, false>);
+  set((const void*)k_mlp_dw3<false, true>);
+  set((const void*)k_mlp_dw3<true, true>);
   return ok;
 }
 
@@ -217,7 +219,7 @@ DwProblem dw_problem(const __bf16* G, int ldg, const __bf16* H, int ldh, int d, 
   q.G = G; q.ldg = ldg; q.H = H; q.ldh = ldh; q.d = d; q.V = V;
   q.n_vt = (V + kTile - 1) / kTile;
   q.n_jt = (d + kTile - 1) / kTile;
-  q.grid = xcd_grid_2d(q.n_vt, q.n_jt);
+  q.grid = launch_grid(q.n_vt, q.n_jt);
   q.dW = dW;
   return q;
 }
@@ -332,8 +334,11 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
       ps.p[0] = dw_problem(bufG, dI, Xc, dd, dd, dI, dWg);     // dWg [I][d] (+)= dG^T X
       ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu);     // dWu [I][d] (+)= dU^T X
       ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd);    // dWd [d][I] (+)= dO^T A
-      hipLaunchKernelGGL(acc ? k_mlp_dw3<false> : k_mlp_dw3<true>, dim3(ps.p[0].grid + ps.p[1].grid + ps.p[2].grid),
-                         dim3(kThreads), kLdsBytes, st, ps, rows, i + 1 < p.n_chunks ? 1 : 0);
+      const bool even = uneven_over_xcds(ps.p[0].n_vt) || uneven_over_xcds(ps.p[2].n_vt);
+      const auto kernel = even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
+                               : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
+      hipLaunchKernelGGL(kernel, dim3(ps.p[0].grid + ps.p[1].grid + ps.p[2].grid), dim3(kThreads), kLdsBytes, st,
+                         ps, rows, i + 1 < p.n_chunks ? 1 : 0);
     }
   }
   return check_launch();

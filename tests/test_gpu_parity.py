@@ -407,6 +407,31 @@ def test_block_schedule_matches_oracle(schedule, S, d, V, M, blocks, windows, fu
     _check_full(mi.make_inputs(cfg), grad_loss=0.8, use_lse=False)
 
 
+@pytest.mark.parametrize("S,d,V,M,row_blocks,windows,split", [
+    (1300, 264, 30011, 6, 1, 7, 4),     # splits of a window's contraction, ragged rows, columns (8 of 256) and last window
+    (520, 136, 70001, 3, 1, 3, 8),      # the most splits; two full row tiles and one of 8 rows
+    (2100, 264, 4099, 1, 1, 1, 2),      # one window of the whole vocabulary, last vocabulary tile 3 wide
+    (3000, 264, 2600, 6, 4, 1, 1),      # one window, no split, four row blocks: dH straight to bf16, dW read back
+])
+def test_automatic_block_shapes_with_split_dh_match_oracle(S, d, V, M, row_blocks, windows, split):
+    """The block shapes that only the automatic choice takes (dH's contraction split, every split with running sums of
+    its own; one window), against the oracle, bit-identical across calls and within the declared workspace."""
+    import torch
+    import paper_2407_15892_amd as mst
+    info = mst.mst_bwd_schedule_info(S, d, V, M)
+    assert (info["schedule"], info["row_blocks"], info["windows"], info["dh_split"]) == \
+        (mst.BWD_SCHEDULE_BLOCKS_FUSED, row_blocks, windows, split), info
+    inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=440 + S % 97, w_std=0.3, ignore_frac=0.1, label_dist="zipf"))
+    _check_full(inp, grad_loss=0.8, use_lse=False)
+    run, _, _ = _check_full(inp, grad_loss=0.8)
+    first = (run.dH_t.clone(), run.dW_t.clone())
+    run.pad = 4096
+    run.backward(grad_loss=0.8)
+    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
+    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
+    assert bool((run.last_ws[-4096:] == 0xA5).all()), "wrote past the declared workspace"
+
+
 @pytest.mark.parametrize("which", ["pairs_one_chunk", "blocks"])
 def test_dlogits_block_left_in_the_workspace_matches_oracle(schedule, which):
     """The only direct look at the bf16 dlogits block (Algorithm 4 line 6): after a backward call the start of the
