@@ -6,7 +6,7 @@
 // per-kernel event timing.
 #include "../../include/mst_lmhead.h"
 #include "host_util.hpp"
-#include "mst_kernels.hpp"
+#include "mst_small_kernels.hpp"
 
 #include <algorithm>
 #include <atomic>
@@ -17,7 +17,7 @@ namespace {
 using namespace mst;
 
 constexpr int kNumCu = 256;          // MI355X compute units; only steers the schedule choices (splits, blocks)
-constexpr int kMaxDhSplit = 16;
+constexpr int kMaxDhSplit = 64;
 constexpr int kMaxWindows = 64;      // most vocabulary windows the block schedule considers
 constexpr int kMaxBlockSplit = 8;    // most splits of a window's dH contraction
 
@@ -40,6 +40,9 @@ struct Plan {
   int n_st;         // row tiles of a full chunk
   int dh_split;     // splits of the dH contraction over V
   int dh_ksteps;    // K steps (of kBK) per split
+  // pair order: 64 x 64 tiles instead of 256 x 256 ones, per launch kind (mst_small_kernels.hpp)
+  bool small_dlogits, small_dh, small_dw;
+  int small_dh_split, small_dh_ksteps;
   // forward workspace (byte offsets)
   size_t f_nll, f_tgt, f_part, f_total;
   // backward workspace: two dlogits slots of one chunk each (bf16), contiguous
@@ -109,21 +112,13 @@ double launch_us(int64_t tiles, TileCost c, double bytes) {
   const double rounds = (double)((tiles + kNumCu - 1) / kNumCu) * c.alone(), busy = (double)tiles / kNumCu * c.busy();
   return 2.0 + std::max(std::max(rounds, busy), bytes / kHbmBytesPerUs);
 }
-// n1 tiles of c1, then n2 of c2, handed out in this order
+// n1 tiles of c1, then n2 of c2, handed out in this order: n1 % kNumCu units are late for the second kind by one tile of
+// the first, and the others take tiles of it meanwhile
 double launch_us(int64_t n1, TileCost c1, int64_t n2, TileCost c2, double bytes) {
-  const double t1 = c1.alone(), t2 = c2.alone();
-  const int64_t late = n1 % kNumCu;                           // so many units start on the second kind one t1 after the others
-  const double a = (double)(n1 / kNumCu) * t1, b = a + t1;
-  auto done = [&](double t) {
-    return (int64_t)((t - a) / t2 + 1e-9) * (kNumCu - late) + (t > b ? (int64_t)((t - b) / t2 + 1e-9) * late : 0);
-  };
-  double span = b + ((double)(n2 / kNumCu) + 2.0) * t2;       // an upper bound
-  const int64_t lo = n2 / kNumCu, lag = (int64_t)(t1 / t2) + 1;
-  for (int64_t j = lo > lag ? lo - lag : 0; j <= lo + lag + 1; ++j) {
-    if (done(a + (double)j * t2) >= n2 && a + (double)j * t2 < span) span = a + (double)j * t2;
-    if (late && done(b + (double)j * t2) >= n2 && b + (double)j * t2 < span) span = b + (double)j * t2;
-  }
-  if (late && span < b) span = b;
+  const double t1 = c1.alone(), t2 = c2.alone(), a = (double)(n1 / kNumCu) * t1;
+  const int64_t late = n1 % kNumCu, early = late ? (int64_t)(t1 / t2) * (kNumCu - late) : 0;
+  const double after = late ? a + t1 : a;                     // when all units are through with the first kind
+  const double span = after + (n2 > early ? (double)((n2 - early + kNumCu - 1) / kNumCu) * t2 : 0.0);
   const double busy = ((double)n1 * c1.busy() + (double)n2 * c2.busy()) / kNumCu;
   return 2.0 + std::max(std::max(span, busy), 1.3 * bytes / kHbmBytesPerUs);
 }
@@ -131,61 +126,78 @@ double launch_us(int64_t n1, TileCost c1, int64_t n2, TileCost c2, double bytes)
 double pairs_us(const Plan* p) {
   const int64_t S = p->S, d = p->d, V = p->V, C = p->C;
   const double w_all = 2.0 * (double)V * (double)d;                        // bytes of W
-  double t = 0.0;
-  for (int ia = 0; ia < p->n_chunks; ia += 2) {
-    int64_t rows_pair = 0;
-    for (int i = ia; i < ia + 2 && i < p->n_chunks; ++i) {
-      const int64_t rows = (S - (int64_t)i * C) < C ? (S - (int64_t)i * C) : C, n_st = (rows + kTile - 1) / kTile;
-      const double g = 2.0 * (double)rows * (double)V, part = 4.0 * (double)p->dh_split * (double)(rows * d);
-      rows_pair += rows;
-      t += launch_us(n_st * p->n_vt, dlogits_cost(d), w_all + g);
-      t += launch_us(n_st * p->n_jt * p->dh_split, dh_cost((int64_t)p->dh_ksteps * kBK, false), w_all + g + part);
-      if (p->dh_split > 1) t += 4.0 + part / kHbmBytesPerUs;
-    }
-    t += launch_us((int64_t)p->n_vt * p->n_jt, dw_cost(rows_pair, ia > 0), (ia > 0 ? 4.0 : 2.0) * w_all);
-  }
+  const int split = p->small_dh ? p->small_dh_split : p->dh_split;
+  auto chunk = [&](int64_t rows) {
+    const int64_t n_st = (rows + kTile - 1) / kTile;
+    const double g = 2.0 * (double)rows * (double)V, part = 4.0 * (double)split * (double)(rows * d);
+    double t = p->small_dlogits ? small_launch_us(tiles_of(rows, V, 64), (double)((d + kBK - 1) / kBK))
+                                : launch_us(n_st * p->n_vt, dlogits_cost(d), w_all + g);
+    t += p->small_dh ? small_launch_us(tiles_of(rows, d, 64) * split, (double)p->small_dh_ksteps)
+                     : launch_us(n_st * p->n_jt * split, dh_cost((int64_t)p->dh_ksteps * kBK, false), w_all + g + part);
+    return split > 1 ? t + 4.0 + part / kHbmBytesPerUs : t;
+  };
+  auto dw = [&](int64_t rows, bool add) {
+    return p->small_dw ? small_launch_us(tiles_of(V, d, 64), (double)((rows + kBK - 1) / kBK))
+                       : launch_us((int64_t)p->n_vt * p->n_jt, dw_cost(rows, add), (add ? 4.0 : 2.0) * w_all);
+  };
+  const int64_t last = S - (int64_t)(p->n_chunks - 1) * C;                 // rows of the last chunk
+  const int n_pairs = (p->n_chunks + 1) / 2;
+  const int64_t last_pair = p->n_chunks % 2 ? last : C + last;
+  double t = (double)(p->n_chunks - 1) * chunk(C) + chunk(last);
+  t += n_pairs > 1 ? dw(2 * C, false) + (double)(n_pairs - 2) * dw(2 * C, true) + dw(last_pair, true) : dw(last_pair, false);
   return t;
 }
 
 double blocks_us(const Plan* p, int64_t R, int n_rb, int win_tiles, int n_win, int split) {
-  const int64_t S = p->S, d = p->d, V = p->V;
-  const double w_all = 2.0 * (double)V * (double)d;
-  double t = 0.0;
-  for (int rb = 0; rb < n_rb; ++rb) {
-    const int64_t rows = (S - rb * R) < R ? (S - rb * R) : R, n_st = (rows + kTile - 1) / kTile;
+  const int64_t S = p->S, d = p->d, V = p->V, win = (int64_t)win_tiles * kTile;
+  auto block = [&](int64_t rows, int64_t cols, bool dw_add, bool dh_add) {
+    const int64_t n_st = (rows + kTile - 1) / kTile, tiles_w = (cols + kTile - 1) / kTile;
+    const double w_bytes = 2.0 * (double)(cols * d), g_bytes = 2.0 * (double)(rows * cols);
     const double sum_bytes = n_win > 1 || split > 1 ? 4.0 * (double)split * (double)(n_st * p->n_jt) * (kTile * kTile) : 0.0;
-    for (int w = 0; w < n_win; ++w) {
-      const int64_t v0 = (int64_t)w * win_tiles * kTile, cols = V - v0 < (int64_t)win_tiles * kTile ? V - v0 : (int64_t)win_tiles * kTile;
-      const int64_t tiles_w = (cols + kTile - 1) / kTile;
-      const double w_bytes = w_all * (double)cols / (double)V, g_bytes = 2.0 * (double)(rows * cols);
-      t += launch_us(n_st * tiles_w, dlogits_cost(d), w_bytes + g_bytes);
-      t += launch_us(n_st * p->n_jt * split, dh_cost((cols + split - 1) / split, w > 0), tiles_w * p->n_jt, dw_cost(rows, rb > 0),
-                     w_bytes + g_bytes + (rb > 0 ? 4.0 : 2.0) * w_bytes + (w > 0 ? 2.0 : 1.0) * sum_bytes);
-    }
-    if (split > 1) t += 4.0 + sum_bytes / kHbmBytesPerUs;
-  }
+    return launch_us(n_st * tiles_w, dlogits_cost(d), w_bytes + g_bytes) +
+           launch_us(n_st * p->n_jt * split, dh_cost((cols + split - 1) / split, dh_add), tiles_w * p->n_jt, dw_cost(rows, dw_add),
+                     w_bytes + g_bytes + (dw_add ? 4.0 : 2.0) * w_bytes + (dh_add ? 2.0 : 1.0) * sum_bytes);
+  };
+  auto row_block = [&](int64_t rows, bool dw_add) {           // its first, middle and last window, its reduce
+    const int64_t last = V - (int64_t)(n_win - 1) * win;
+    double t = block(rows, n_win > 1 ? win : last, dw_add, false);
+    if (n_win > 2) t += (double)(n_win - 2) * block(rows, win, dw_add, true);
+    if (n_win > 1) t += block(rows, last, dw_add, true);
+    if (split > 1) t += 4.0 + 4.0 * (double)split * (double)(rows * d) / kHbmBytesPerUs;
+    return t;
+  };
+  double t = row_block(n_rb > 1 ? R : S, false);
+  if (n_rb > 2) t += (double)(n_rb - 2) * row_block(R, true);
+  if (n_rb > 1) t += row_block(S - (int64_t)(n_rb - 1) * R, true);
   return t;
 }
 
 // Looks for a block shape with one window, or with dH's contraction split, that beats `p`'s choice so far by more than
-// the model is good for.
+// the model is good for.  Not where two rounds of dH tiles fill the chip as it is: the shapes of the long configurations
+// are the ones measured.  A few microseconds of host time: more windows than eight past the first count that leaves one
+// row block only make the windows smaller.
 void choose_split_blocks(Plan* p) {
   const int64_t S = p->S, d = p->d;
+  if (p->blk_use && (int64_t)(p->blk_rows / kTile) * p->n_jt >= 2 * kNumCu) return;
   const double pairs = pairs_us(p);
   const double so_far = p->blk_use ? blocks_us(p, p->blk_rows, p->blk_n_rb, p->blk_win_tiles, p->blk_n_win, 1) : pairs;
   double best = 0.95 * std::min(so_far, pairs);
   bool found = false;
-  for (int n_win = 1; n_win <= kMaxWindows && n_win <= p->n_vt; ++n_win) {
-    const int win_tiles = (p->n_vt + n_win - 1) / n_win;
-    if ((p->n_vt + win_tiles - 1) / win_tiles != n_win) continue;          // same partition as a smaller count
-    const int64_t ldg_w = (int64_t)win_tiles * kTile;
-    for (int split = 1; split <= kMaxBlockSplit && split <= win_tiles; split *= 2) {
+  for (int split = 1; split <= kMaxBlockSplit; split *= 2) {
+    int one_row_block_from = 0;
+    for (int n_win = 1; n_win <= kMaxWindows && n_win <= p->n_vt; ++n_win) {
+      if (one_row_block_from && n_win > one_row_block_from + 8) break;
+      const int win_tiles = (p->n_vt + n_win - 1) / n_win;
+      if (split > win_tiles) break;
+      if ((p->n_vt + win_tiles - 1) / win_tiles != n_win) continue;        // same partition as a smaller count
+      const int64_t ldg_w = (int64_t)win_tiles * kTile;
       const int64_t per_row = ldg_w * 2 + (n_win > 1 || split > 1 ? (int64_t)split * p->n_jt * kTile * 4 : 0);
-      if (p->b_total < 256 + (size_t)per_row * kTile) break;
+      if (p->b_total < 256 + (size_t)per_row * kTile) continue;
       int64_t R = (int64_t)((p->b_total - 256) / (size_t)per_row) / kTile * kTile;
       const int64_t S_up = (S + kTile - 1) / kTile * kTile;
       if (R > S_up) R = S_up;
       const int n_rb = (int)((S + R - 1) / R);
+      if (n_rb == 1 && !one_row_block_from) one_row_block_from = n_win;
       R = ((S + n_rb - 1) / n_rb + kTile - 1) / kTile * kTile;
       if (R * ldg_w >= (int64_t(1) << 30) || R * d >= (int64_t(1) << 30)) continue;   // 32-bit offsets inside a block
       const double t = blocks_us(p, R, n_rb, win_tiles, n_win, split);
@@ -285,8 +297,9 @@ void choose_schedule(Plan* p, int forced) {
 // `forced`: one of the MST_BWD_SCHEDULE_* values; only the backward's block shape depends on it.
 // `fwd_cap`: if non-zero, the forward's groups of mini-sequences are shortened until the forward workspace fits
 // into that many bytes (one mini-sequence per group at least; the caller checks f_total against the cap).
+// `schedule`: whether the backward's order and block shape are needed.
 mst_status make_plan(int64_t S, int64_t d, int64_t V, int32_t M, Plan* p, int forced = MST_BWD_SCHEDULE_AUTO,
-                     size_t fwd_cap = 0) {
+                     size_t fwd_cap = 0, bool schedule = true) {
   if (S <= 0 || d <= 0 || V <= 0) return MST_ERR_BAD_SHAPE;
   if (d % 8 != 0) return MST_ERR_BAD_SHAPE;
   if (M < 1 || (int64_t)M > S) return MST_ERR_BAD_M;
@@ -319,6 +332,30 @@ mst_status make_plan(int64_t S, int64_t d, int64_t V, int32_t M, Plan* p, int fo
   p->dh_ksteps = (ksteps + split - 1) / split;
   p->dh_split = (ksteps + p->dh_ksteps - 1) / p->dh_ksteps;
 
+  // Small problems: 64 x 64 tiles where they are estimated faster.  For dH that is ranked with its split count: splits
+  // cost a reduce launch (4 us and the partials).
+  {
+    const double kd = (double)((d + kBK - 1) / kBK);
+    p->small_dlogits = small_launch_us(tiles_of(C, V, 64), kd) < big_launch_us(tiles_of(C, V, 256), kd);
+    const int64_t pair = p->n_chunks > 1 ? 2 * C : C;
+    const double kw = (double)((pair + kBK - 1) / kBK);
+    p->small_dw = small_launch_us(tiles_of(V, d, 64), kw) < big_launch_us(tiles_of(V, d, 256), kw);
+    auto reduce_us = [&](int s) { return s > 1 ? 4.0 + (double)s * (double)(C * d) * 8.0 / 4.6e6 : 0.0; };
+    double t_best = big_launch_us((double)out_tiles * p->dh_split, (double)p->dh_ksteps) + reduce_us(p->dh_split);
+    p->small_dh = false;
+    p->small_dh_split = p->small_dh_ksteps = 0;
+    for (int s = 1; s <= 16 && s <= ksteps && (s == 1 || s <= room); s *= 2) {
+      const int per = (ksteps + s - 1) / s;
+      const double t = small_launch_us(tiles_of(C, d, 64) * s, (double)per) + reduce_us(s);
+      if (t < t_best) {
+        t_best = t;
+        p->small_dh = true;
+        p->small_dh_ksteps = per;
+        p->small_dh_split = (ksteps + per - 1) / per;
+      }
+    }
+  }
+
   // Forward: one GEMM launch per mini-sequence; the (max, sum) pairs per row and vocabulary tile of a group of
   // consecutive mini-sequences are merged by one launch.  A group is as many chunks as fit, with their pairs,
   // into half of one fp32 logits chunk (all of them at the paper-shaped configurations).
@@ -346,7 +383,7 @@ mst_status make_plan(int64_t S, int64_t d, int64_t V, int32_t M, Plan* p, int fo
   p->b_lse = p->b_ctl + sizeof(Control);
   p->b_fwd = p->b_lse + align_up((size_t)S * 4, 256);
   p->b_total_max = p->b_fwd + p->f_total;
-  choose_schedule(p, forced);
+  if (schedule) choose_schedule(p, forced);
   return MST_OK;
 }
 
@@ -370,6 +407,13 @@ bool set_kernel_attributes() {   // on the current device
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess) ok = false;
   };
   set((const void*)k_fwd_gemm_lse);
+  set((const void*)k_fwd_gemm_lse_small<TileFwdSmall>);
+  set((const void*)k_bwd_gemm_dlogits_small<Tile64>);
+  set((const void*)k_bwd_gemm_dlogits_small<Tile64Lone>);
+  set((const void*)k_bwd_gemm_dh_small<Tile64>);
+  set((const void*)k_bwd_gemm_dh_small<Tile64Lone>);
+  set((const void*)k_bwd_gemm_dw_small<Tile64>);
+  set((const void*)k_bwd_gemm_dw_small<Tile64Lone>);
   set((const void*)k_bwd_gemm_dlogits<false>);
   set((const void*)k_bwd_gemm_dlogits<true>);
   set((const void*)k_bwd_gemm_dh<false>);
@@ -423,12 +467,20 @@ mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, c
       // shorter than a 256-row tile costs no idle tile rows, and every row's result is bit-identical for every M.
       const int n_st = (int)((g_rows + kTile - 1) / kTile);
       Scope sc(st, MST_K_FWD_GEMM_LSE);
+      // few tiles: 64 rows each, as long as every workgroup has a compute unit to itself (same bits)
+      const int n_sh = (int)((g_rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB);
+      if ((int64_t)n_sh * p.n_vt <= kNumCu) {
+        hipLaunchKernelGGL(k_fwd_gemm_lse_small<TileFwdSmall>, dim3(even_grid(p.n_vt, n_sh)), dim3(TileFwdSmall::kThreads),
+                           TileFwdSmall::kLds, st, H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_sh, p.n_vt,
+                           part, stride, tgt);
+      } else {
       const int tiles = xcd_grid_2d(p.n_vt, n_st);
       const int grid = queue && tiles > kNumCu ? kNumCu : tiles;
       hipLaunchKernelGGL(k_fwd_gemm_lse, dim3(grid), dim3(kThreads), kLdsBytes, st,
                          H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_st, p.n_vt,
                          part, stride, tgt, queue, queue_base);
       queue_base += tiles / kNumXcd + grid;
+      }
     }
     {
       Scope sc(st, MST_K_LSE_FINALIZE);
@@ -545,7 +597,7 @@ mst_status mst_shift_labels(const int32_t* labels_in, int64_t B, int64_t L, int3
 
 mst_status mst_workspace_bytes(int64_t S, int64_t d, int64_t V, int32_t M, size_t* fwd_bytes, size_t* bwd_bytes) {
   Plan p;
-  mst_status s = make_plan(S, d, V, M, &p);
+  mst_status s = make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false);
   if (s != MST_OK) return s;
   if (fwd_bytes) *fwd_bytes = p.f_total;
   if (bwd_bytes) *bwd_bytes = p.b_total;
@@ -556,7 +608,7 @@ mst_status mst_lmhead_ce_fwd(const void* H, const void* W, const int32_t* labels
                              int32_t ignore_index, int32_t M, void* workspace, size_t workspace_bytes,
                              float* loss, float* lse, int64_t* n_valid, void* stream) {
   Plan p;
-  mst_status s = make_plan(S, d, V, M, &p);
+  mst_status s = make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false);
   if (s != MST_OK) return s;
   if (!H || !W || !labels || !loss) return MST_ERR_NULL_POINTER;
   if (!workspace || workspace_bytes < p.f_total) return MST_ERR_WORKSPACE;
@@ -570,7 +622,7 @@ mst_status mst_lmhead_ce_fwd_static(const void* H, const void* W, const int32_t*
                                     int32_t ignore_index, int32_t M, float* loss, float* lse, int64_t* n_valid,
                                     void* stream) {
   Plan p;
-  mst_status s = make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, (size_t)MST_STATIC_SCRATCH_BYTES);
+  mst_status s = make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, (size_t)MST_STATIC_SCRATCH_BYTES, false);
   if (s != MST_OK) return s;
   if (!H || !W || !labels || !loss) return MST_ERR_NULL_POINTER;
   if (p.f_total > (size_t)MST_STATIC_SCRATCH_BYTES) return MST_ERR_WORKSPACE;   // one mini-sequence alone is too large
@@ -621,6 +673,14 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     const int64_t r0 = (int64_t)i * p.C;
     const int rows = rows_of(i), n_st = (rows + kTile - 1) / kTile;
     Scope sc(st, MST_K_BWD_GEMM_DLOGITS);
+    if (p.small_dlogits) {
+      const int n_vh = (int)((p.V + Tile64::EA - 1) / Tile64::EA), n_sh = (rows + Tile64::EB - 1) / Tile64::EB;
+      const bool lone = lone_small((double)n_vh * n_sh);
+      hipLaunchKernelGGL(lone ? k_bwd_gemm_dlogits_small<Tile64Lone> : k_bwd_gemm_dlogits_small<Tile64>,
+                         dim3(even_grid(n_vh, n_sh)), dim3(Tile64::kThreads), lone ? Tile64Lone::kLds : Tile64::kLds, st,
+                         Hb + r0 * p.d, Wb, labels + r0, lse + r0, rows, (int)p.d, (int)p.V, ignore_index, n_sh, n_vh, G, p.ldg);
+      return;
+    }
     hipLaunchKernelGGL(dlogits_kernel(p.n_vt), dim3(launch_grid(p.n_vt, n_st)), dim3(kThreads), kLdsBytes, st,
                        Hb + r0 * p.d, Wb, labels + r0, lse + r0, rows, (int)p.d, (int)p.V, 0, (int)p.V, ignore_index,
                        n_st, p.n_vt, G, p.ldg);
@@ -629,22 +689,40 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     const int64_t r0 = (int64_t)i * p.C;
     const int rows = rows_of(i), n_st = (rows + kTile - 1) / kTile;
     float* partial = static_cast<float*>(partial_space);
+    const int split = p.small_dh ? p.small_dh_split : p.dh_split;
     {
       Scope sc(st, MST_K_BWD_GEMM_DH);
+      if (p.small_dh) {
+        const int n_jh = (int)((p.d + Tile64::EA - 1) / Tile64::EA), n_sh = (rows + Tile64::EB - 1) / Tile64::EB;
+        const bool lone = lone_small((double)n_jh * n_sh * split);
+        hipLaunchKernelGGL(lone ? k_bwd_gemm_dh_small<Tile64Lone> : k_bwd_gemm_dh_small<Tile64>,
+                           dim3(even_grid(n_jh * split, n_sh)), dim3(Tile64::kThreads), lone ? Tile64Lone::kLds : Tile64::kLds, st,
+                           G, p.ldg, Wb, rows, (int)p.d, (int)p.V, n_sh, n_jh, split, p.small_dh_ksteps, nv, grad_loss,
+                           partial, p.C, dHb + r0 * p.d);
+      } else
       hipLaunchKernelGGL(k_bwd_gemm_dh<false>, dim3(xcd_grid(n_st * p.n_jt * p.dh_split)), dim3(kThreads), kLdsBytes, st,
                          G, p.ldg, Wb, rows, (int)p.d, (int)p.V, n_st, p.n_jt, p.dh_split, p.dh_ksteps, kDhSplit,
                          nv, grad_loss, partial, p.C, dHb + r0 * p.d);
     }
-    if (p.dh_split > 1) {
+    if (split > 1) {
       Scope sc(st, MST_K_BWD_DH_REDUCE);
       const size_t n = (size_t)rows * p.d;
       hipLaunchKernelGGL(k_bwd_dh_reduce, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st,
-                         partial, p.dh_split, (size_t)p.C * p.d, n, nv, grad_loss, dHb + r0 * p.d);
+                         partial, split, (size_t)p.C * p.d, n, nv, grad_loss, dHb + r0 * p.d);
     }
   };
   auto grad_w = [&](int i_first, int i_last, int rows) {
     const int64_t r0 = (int64_t)i_first * p.C;
     Scope sc(st, MST_K_BWD_GEMM_DW);
+    if (p.small_dw) {
+      const int n_vh = (int)((p.V + Tile64::EB - 1) / Tile64::EB), n_jh = (int)((p.d + Tile64::EA - 1) / Tile64::EA);
+      const bool lone = lone_small((double)n_vh * n_jh);
+      hipLaunchKernelGGL(lone ? k_bwd_gemm_dw_small<Tile64Lone> : k_bwd_gemm_dw_small<Tile64>,
+                         dim3(even_grid(n_vh, n_jh)), dim3(Tile64::kThreads), lone ? Tile64Lone::kLds : Tile64::kLds, st,
+                         slot[0], p.ldg, Hb + r0 * p.d, rows, (int)p.d, (int)p.V, n_vh, n_jh, i_first > 0 ? 1 : 0,
+                         i_last == p.n_chunks - 1 ? 1 : 0, nv, grad_loss, dW);
+      return;
+    }
     hipLaunchKernelGGL(dw_kernel(i_first == 0, p.n_vt), dim3(launch_grid(p.n_vt, p.n_jt)),
                        dim3(kThreads), kLdsBytes, st,
                        slot[0], p.ldg, Hb + r0 * p.d, rows, (int)p.d, (int)p.V, p.n_vt, p.n_jt,
@@ -753,7 +831,7 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
   info[2] = p.blk_use ? p.blk_n_rb : (p.n_chunks + 1) / 2;
   info[3] = p.blk_use ? (int64_t)p.blk_win_tiles * kTile : p.V;
   info[4] = p.blk_use ? p.blk_n_win : 1;
-  info[5] = p.blk_use ? p.blk_split : p.dh_split;
+  info[5] = p.blk_use ? p.blk_split : p.small_dh ? p.small_dh_split : p.dh_split;
   info[6] = (int64_t)p.est_pairs_us;
   info[7] = (int64_t)p.est_blocks_us;
   return MST_OK;

@@ -282,6 +282,94 @@ __global__ __launch_bounds__(256) void k_shift_labels(const int* __restrict__ in
   out[i] = (i % L == L - 1) ? ignore_index : in[i + 1];
 }
 
+// (m, l) += (m2, l2) for pairs of a running maximum and the sum of exponentials relative to it.  The multiply-add is
+// spelled out: left to the compiler, which of the two products is fused may differ between the kernels that form the
+// same pairs.
+__device__ __forceinline__ void merge_lse(float& m, float& l, float m2, float l2) {
+  const float mm = fmaxf(m, m2);
+  l = __builtin_fmaf(l, fast_exp2((m - mm) * kLog2e), l2 * fast_exp2((m2 - mm) * kLog2e));
+  m = mm;
+}
+
+// Running log-sum-exp partials and target logits from the accumulators of a 256-entry vocabulary tile (wave grid 2 x WB,
+// TB row tiles per wave).
+template <int TB>
+__device__ __forceinline__ void lse_epilogue(f32x4 (&acc)[kTA16][TB], const int* __restrict__ labels_c, int rows, int V, int vt,
+                                             int s0, float2* __restrict__ part, size_t part_stride, float* __restrict__ tgt,
+                                             int wa, int wb, int lane, char* smem) {
+  const int v0 = vt * kTile;
+  // a lane (quarter g, column c) holds, for each of its TB rows s, the 32 consecutive vocabulary entries
+  // va + 4 t + r (t = 0..7, r = 0..3)
+  const int g = lane >> 4, c = lane & 15;
+  const int va = v0 + wa * 128 + 32 * g;
+  if (v0 + kTile > V) {                              // ragged last vocabulary tile: mask entries >= V
+#pragma unroll
+    for (int t = 0; t < kTA16; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (va + 4 * t + r >= V) {
+#pragma unroll
+          for (int u = 0; u < TB; ++u) acc[t][u][r] = kMasked;
+        }
+  }
+
+  float2* xch = reinterpret_cast<float2*>(smem);     // [wb][u][16] pairs from the wa == 1 waves
+  float m_u[TB], l_u[TB];
+#pragma unroll
+  for (int u = 0; u < TB; ++u) {
+    float m = kMasked;
+#pragma unroll
+    for (int t = 0; t < kTA16; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[t][u][r]);
+    float l = 0.f;
+    // subtract before scaling: with the masking sentinel, a fused (z * log2e - m * log2e)
+    // would leave a huge rounding residue when z == m == sentinel
+#pragma unroll
+    for (int t = 0; t < kTA16; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) l += fast_exp2((acc[t][u][r] - m) * kLog2e);
+    // the four lane quarters hold four 32-entry slices of the same rows
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      const float m2 = __shfl_xor(m, o), l2 = __shfl_xor(l, o);
+      merge_lse(m, l, m2, l2);
+    }
+    m_u[u] = m;
+    l_u[u] = l;
+
+    // target logit straight from the accumulator that holds it
+    const int s_local = s0 + wb * (16 * TB) + 16 * u + c;
+    const int y = s_local < rows ? labels_c[s_local] : -1;
+    const int rel = y - (v0 + wa * 128);
+    if (rel >= 0 && rel < 128 && y < V && (rel >> 5) == g) {
+      const int t_sel = (rel & 31) >> 2, r_sel = rel & 3;
+      float val = 0.f;
+#pragma unroll
+      for (int t = 0; t < kTA16; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (t == t_sel && r == r_sel) val = acc[t][u][r];
+      tgt[s_local] = val;
+    }
+  }
+  // the main loop ended with a barrier, LDS is free
+  if (wa == 1 && lane < 16) {
+#pragma unroll
+    for (int u = 0; u < TB; ++u) xch[(wb * TB + u) * 16 + lane] = make_float2(m_u[u], l_u[u]);
+  }
+  __syncthreads();
+  if (wa == 0 && lane < 16) {
+#pragma unroll
+    for (int u = 0; u < TB; ++u) {
+      const float2 o = xch[(wb * TB + u) * 16 + lane];
+      merge_lse(m_u[u], l_u[u], o.x, o.y);
+      const int s_local = s0 + wb * (16 * TB) + 16 * u + lane;
+      if (s_local < rows) part[(size_t)vt * part_stride + s_local] = make_float2(m_u[u], l_u[u]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // forward: logits tile + running log-sum-exp partials + target logit
 //   A side = vocabulary (W rows), B side = chunk rows (H rows): a lane owns one
@@ -315,79 +403,7 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemm_lse(
   pb.init(Hc + (size_t)s0 * d, d, rows - s0, d, wave, lane, wb);
   gemm_mainloop_pp<Tile16>(acc, pa, pb, smem, 0, d, wa, [&]() { if (queue) feed.resolve(); });
 
-  // a lane (quarter g, column c) holds, for each of its 4 rows s, the 32 consecutive vocabulary entries
-  // va + 4 t + r (t = 0..7, r = 0..3)
-  const int g = lane >> 4, c = lane & 15;
-  const int va = v0 + wa * 128 + 32 * g;
-  if (v0 + kTile > V) {                              // ragged last vocabulary tile: mask entries >= V
-#pragma unroll
-    for (int t = 0; t < kTA16; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (va + 4 * t + r >= V) {
-#pragma unroll
-          for (int u = 0; u < kTB16; ++u) acc[t][u][r] = kMasked;
-        }
-  }
-
-  float2* xch = reinterpret_cast<float2*>(smem);     // [wb][u][16] pairs from the wa == 1 waves
-  float m_u[kTB16], l_u[kTB16];
-#pragma unroll
-  for (int u = 0; u < kTB16; ++u) {
-    float m = kMasked;
-#pragma unroll
-    for (int t = 0; t < kTA16; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[t][u][r]);
-    float l = 0.f;
-    // subtract before scaling: with the masking sentinel, a fused (z * log2e - m * log2e)
-    // would leave a huge rounding residue when z == m == sentinel
-#pragma unroll
-    for (int t = 0; t < kTA16; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) l += fast_exp2((acc[t][u][r] - m) * kLog2e);
-    // the four lane quarters hold four 32-entry slices of the same rows
-#pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-      const float m2 = __shfl_xor(m, o), l2 = __shfl_xor(l, o);
-      const float mm = fmaxf(m, m2);
-      l = l * fast_exp2((m - mm) * kLog2e) + l2 * fast_exp2((m2 - mm) * kLog2e);
-      m = mm;
-    }
-    m_u[u] = m;
-    l_u[u] = l;
-
-    // target logit straight from the accumulator that holds it
-    const int s_local = s0 + wb * 64 + 16 * u + c;
-    const int y = s_local < rows ? labels_c[s_local] : -1;
-    const int rel = y - (v0 + wa * 128);
-    if (rel >= 0 && rel < 128 && y < V && (rel >> 5) == g) {
-      const int t_sel = (rel & 31) >> 2, r_sel = rel & 3;
-      float val = 0.f;
-#pragma unroll
-      for (int t = 0; t < kTA16; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (t == t_sel && r == r_sel) val = acc[t][u][r];
-      tgt[s_local] = val;
-    }
-  }
-  // the main loop ended with a barrier, LDS is free
-  if (wa == 1 && lane < 16) {
-#pragma unroll
-    for (int u = 0; u < kTB16; ++u) xch[(wb * kTB16 + u) * 16 + lane] = make_float2(m_u[u], l_u[u]);
-  }
-  __syncthreads();
-  if (wa == 0 && lane < 16) {
-#pragma unroll
-    for (int u = 0; u < kTB16; ++u) {
-      const float2 o = xch[(wb * kTB16 + u) * 16 + lane];
-      const float mm = fmaxf(m_u[u], o.x);
-      const float l = l_u[u] * fast_exp2((m_u[u] - mm) * kLog2e) + o.y * fast_exp2((o.x - mm) * kLog2e);
-      const int s_local = s0 + wb * 64 + 16 * u + lane;
-      if (s_local < rows) part[(size_t)vt * part_stride + s_local] = make_float2(mm, l);
-    }
-  }
+  lse_epilogue<kTB16>(acc, labels_c, rows, V, vt, s0, part, part_stride, tgt, wa, wb, lane, smem);
   }
 }
 

@@ -44,9 +44,7 @@ struct Scope : mst_host::Scope {
 // The smaller tiles of gemm_small.hpp: 128 x 128 and 64 x 64 with several workgroups on a compute unit (80 and 40 KB of
 // LDS: two and four), and both software-pipelined for launches that have a compute unit for every workgroup.
 typedef CfgSmall<4, 4, 3, 2, false> Tile128;
-typedef CfgSmall<4, 4, 4, 4, true> Tile128Lone;
-typedef CfgSmall<2, 2, 3, 2, false> Tile64;
-typedef CfgSmall<2, 2, 5, 5, true> Tile64Lone;
+typedef CfgSmall<4, 4, 4, 4, true> Tile128Lone;      // Tile64, Tile64Lone: mst_small_kernels.hpp
 
 template <class C, class Set>
 void set_small_attributes(Set set) {
@@ -71,6 +69,8 @@ bool set_kernel_attributes() {   // on the current device
   set_small_attributes<Tile64Lone>(set);
   set((const void*)k_mlp_gemm_nn<Tile16>);
   set((const void*)k_mlp_gemm_nn<Tile16HalfB>);
+  set((const void*)k_mlp_dw3_small<Tile64>);
+  set((const void*)k_mlp_dw3_small<Tile64Lone>);
   set((const void*)k_mlp_dw3<false, false>);
   set((const void*)k_mlp_dw3<true, false>);
   set((const void*)k_mlp_dw3<false, true>);
@@ -214,12 +214,13 @@ void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16*
   }
 }
 
-DwProblem dw_problem(const __bf16* G, int ldg, const __bf16* H, int ldh, int d, int V, float* dW) {
+// tile = 256: the large tiles, in the map of their launch; 64: the small ones, dealt out evenly
+DwProblem dw_problem(const __bf16* G, int ldg, const __bf16* H, int ldh, int d, int V, float* dW, int tile) {
   DwProblem q;
   q.G = G; q.ldg = ldg; q.H = H; q.ldh = ldh; q.d = d; q.V = V;
-  q.n_vt = (V + kTile - 1) / kTile;
-  q.n_jt = (d + kTile - 1) / kTile;
-  q.grid = launch_grid(q.n_vt, q.n_jt);
+  q.n_vt = (V + tile - 1) / tile;
+  q.n_jt = (d + tile - 1) / tile;
+  q.grid = tile == kTile ? launch_grid(q.n_vt, q.n_jt) : even_grid(q.n_vt, q.n_jt);
   q.dW = dW;
   return q;
 }
@@ -308,6 +309,9 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
   __bf16* bufU = reinterpret_cast<__bf16*>(ws + p.slot);      // dU
   __bf16* bufA = reinterpret_cast<__bf16*>(ws + 2 * p.slot);  // A
   const int dI = (int)p.I, dd = (int)p.d;
+  // one tile kind for all chunks: what the large tiles keep between them is not row-major
+  const double dw_tiles64 = 3.0 * tiles_of(p.I, p.d, 64), dw_ksteps = (double)((p.C + kBK - 1) / kBK);
+  const bool small_dw = small_launch_us(dw_tiles64, dw_ksteps) < big_launch_us(3.0 * tiles_of(p.I, p.d, 256), dw_ksteps);
 
   // Algorithm 3: loop over the mini-sequences; dX_i lands in its row range, the weight gradients accumulate
   for (int i = 0; i < p.n_chunks; ++i) {
@@ -330,15 +334,23 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
     }
     {
       Scope sc(st, MST_MLP_K_DW);
+      const int tile = small_dw ? Tile64::EA : kTile;
       DwProblems ps;
-      ps.p[0] = dw_problem(bufG, dI, Xc, dd, dd, dI, dWg);     // dWg [I][d] (+)= dG^T X
-      ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu);     // dWu [I][d] (+)= dU^T X
-      ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd);    // dWd [d][I] (+)= dO^T A
-      const bool even = uneven_over_xcds(ps.p[0].n_vt) || uneven_over_xcds(ps.p[2].n_vt);
-      const auto kernel = even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
-                               : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
-      hipLaunchKernelGGL(kernel, dim3(ps.p[0].grid + ps.p[1].grid + ps.p[2].grid), dim3(kThreads), kLdsBytes, st,
-                         ps, rows, i + 1 < p.n_chunks ? 1 : 0);
+      ps.p[0] = dw_problem(bufG, dI, Xc, dd, dd, dI, dWg, tile);     // dWg [I][d] (+)= dG^T X
+      ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu, tile);     // dWu [I][d] (+)= dU^T X
+      ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd, tile);    // dWd [d][I] (+)= dO^T A
+      const dim3 grid(ps.p[0].grid + ps.p[1].grid + ps.p[2].grid);
+      if (small_dw) {
+        if (lone_small(dw_tiles64))
+          hipLaunchKernelGGL(k_mlp_dw3_small<Tile64Lone>, grid, dim3(Tile64Lone::kThreads), Tile64Lone::kLds, st, ps, rows, acc);
+        else
+          hipLaunchKernelGGL(k_mlp_dw3_small<Tile64>, grid, dim3(Tile64::kThreads), Tile64::kLds, st, ps, rows, acc);
+      } else {
+        const bool even = uneven_over_xcds(ps.p[0].n_vt) || uneven_over_xcds(ps.p[2].n_vt);
+        const auto kernel = even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
+                                 : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), kLdsBytes, st, ps, rows, i + 1 < p.n_chunks ? 1 : 0);
+      }
     }
   }
   return check_launch();

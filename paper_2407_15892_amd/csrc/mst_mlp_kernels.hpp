@@ -15,8 +15,7 @@
 // All kernels use the 256 x 256 block tile main loop of gemm_tile.hpp and the XCD-aware workgroup
 // remapping of mst_kernels.hpp.
 #pragma once
-#include "mst_kernels.hpp"
-#include "gemm_small.hpp"
+#include "mst_small_kernels.hpp"
 
 namespace mst {
 
@@ -396,6 +395,18 @@ __global__ __launch_bounds__(kThreads) void k_mlp_dw3(DwProblems ps, int rows, i
   // 8 x 4 rectangles walked group by group of 4 fast tiles (measured 0.7 % faster here than the LM-head's 4 x 8 bands)
   if (!launch_tile<kEven, 8, 4, 4>(b, q.n_vt, q.n_jt, &vt, &jt)) return;
   dw_tile(q.G, q.ldg, q.ldg, q.H, q.ldh, rows, q.d, q.V, vt, jt, kStoreOnly ? 0 : 1, more, 1.0f, q.dW, q.d, smem);
+}
+
+// the same with 64 x 64 tiles, for problems too small to occupy the chip with large ones (mst_small_kernels.hpp)
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void k_mlp_dw3_small(DwProblems ps, int rows, int accumulate) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  int b = blockIdx.x, which = 0;
+  if (b >= ps.p[0].grid) { b -= ps.p[0].grid; which = 1; if (b >= ps.p[1].grid) { b -= ps.p[1].grid; which = 2; } }
+  const DwProblem& q = ps.p[which];
+  int vt, jt;
+  if (!even_tile_of_block(b, q.n_vt, q.n_jt, &vt, &jt)) return;
+  dw_tile_small<C>(q.G, q.ldg, q.ldg, q.H, q.ldh, rows, q.d, q.V, vt, jt, accumulate != 0, 1.0f, q.dW, q.d, smem);
 }
 
 }  // namespace mst

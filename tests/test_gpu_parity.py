@@ -407,11 +407,33 @@ def test_block_schedule_matches_oracle(schedule, S, d, V, M, blocks, windows, fu
     _check_full(mi.make_inputs(cfg), grad_loss=0.8, use_lse=False)
 
 
+@pytest.mark.parametrize("S,d,V,M", [
+    (1200, 520, 20003, 2),     # 256 x 256 tiles throughout, dH in 19 splits, ragged in every dimension
+    (1300, 520, 7003, 3),      # 64 x 64 tiles in dlogits, dH (4 splits) and dW, whose second pass (one chunk) adds
+    (650, 1032, 12003, 2),     # 64 x 64 in dlogits and dH only; last column tile of 8
+    (200, 1032, 40001, 1),     # 64 x 64 in dH only, 16 splits; a vocabulary of one entry past a tile
+    (257, 2056, 3003, 1),      # one row past a tile: 64-row tiles in the forward too, one workgroup per compute unit
+    (65, 264, 4097, 1),        # the smallest ragged tiles: 1 row, 8 columns, 1 vocabulary entry
+])
+def test_pair_order_with_every_tile_size_matches_oracle(schedule, S, d, V, M):
+    """The printed order picks 64 x 64 or 256 x 256 tiles per launch kind; both against the oracle, element by element,
+    and repeated calls bit for bit."""
+    import torch
+    import paper_2407_15892_amd as mst
+    schedule(mst.BWD_SCHEDULE_PAIRS)
+    inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=450 + S % 97, w_std=0.3, ignore_frac=0.1, label_dist="zipf"))
+    run, _, _ = _check_full(inp, grad_loss=0.8)
+    first = (run.dH_t.clone(), run.dW_t.clone())
+    run.backward(grad_loss=0.8)
+    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
+    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
+
+
 @pytest.mark.parametrize("S,d,V,M,row_blocks,windows,split", [
-    (1300, 264, 30011, 6, 1, 7, 4),     # splits of a window's contraction, ragged rows, columns (8 of 256) and last window
-    (520, 136, 70001, 3, 1, 3, 8),      # the most splits; two full row tiles and one of 8 rows
-    (2100, 264, 4099, 1, 1, 1, 2),      # one window of the whole vocabulary, last vocabulary tile 3 wide
-    (3000, 264, 2600, 6, 4, 1, 1),      # one window, no split, four row blocks: dH straight to bf16, dW read back
+    (495, 112, 63400, 7, 1, 5, 8),      # the most splits, five windows; ragged rows, columns and last window
+    (835, 368, 18219, 1, 1, 1, 8),      # splits of one window: stored, then added by the reduce
+    (2295, 528, 22619, 7, 3, 2, 4),     # three row blocks: dW read back, last column tile of 16
+    (5772, 712, 3700, 3, 2, 1, 1),      # one window, no split: dH straight to bf16
 ])
 def test_automatic_block_shapes_with_split_dh_match_oracle(S, d, V, M, row_blocks, windows, split):
     """The block shapes that only the automatic choice takes (dH's contraction split, every split with running sums of
