@@ -279,10 +279,11 @@ mst_status mst_mfma_probe(int32_t blocks, int32_t iters, float scale, float* sin
  * indexed by the enum below), and clears the record.
  */
 enum {
-  MST_K_LABEL_SCAN = 0,  /* N_valid, label range check                         */
+  MST_K_LABEL_SCAN = 0,  /* backward without n_valid: N_valid, label range check;
+                            forward: clearing the tile queues                   */
   MST_K_FWD_GEMM_LSE,    /* logits tile GEMM + running max / sum-exp epilogue   */
   MST_K_LSE_FINALIZE,    /* combine per-vocab-tile partials into lse, nll       */
-  MST_K_LOSS_REDUCE,     /* fixed-order sum of nll / N_valid                    */
+  MST_K_LOSS_REDUCE,     /* fixed-order sum of nll / N_valid, label range check */
   MST_K_BWD_GEMM_DLOGITS,/* recomputed logits GEMM + softmax-minus-onehot       */
   MST_K_BWD_GEMM_DH,     /* dH_i = dlogits_i W (split over V)                   */
   MST_K_BWD_DH_REDUCE,   /* fixed-order sum of the dH split partials            */

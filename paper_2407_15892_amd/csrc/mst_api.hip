@@ -452,35 +452,44 @@ mst_status prepare_device() {
 }
 
 // forward pass over all chunks: writes lse (if non-null) and nll (if non-null)
-// `queue`: eight zeroed ints for the persistent forward launches (nullptr: one workgroup per tile)
+// `ctl`: its queues serve persistent forward launches (nullptr: one workgroup per tile)
 mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, const int32_t* labels,
-                              int ignore_index, char* ws, float* lse, float* nll, hipStream_t st, int* queue = nullptr) {
-  int queue_base = 0;
+                              int ignore_index, char* ws, float* lse, float* nll, hipStream_t st, Control* ctl = nullptr) {
   float* tgt = reinterpret_cast<float*>(ws + p.f_tgt);
   float2* part = reinterpret_cast<float2*>(ws + p.f_part);
   const size_t stride = (size_t)p.fwd_group_rows;
+  auto rows_of_group = [&](int64_t g0) { return (p.S - g0) < p.fwd_group_rows ? (p.S - g0) : p.fwd_group_rows; };
+  // Few tiles: 64 rows each, as long as every workgroup has a compute unit to itself (same bits); the groups after the
+  // first are not larger.  Otherwise persistent workgroups where there is more than one round of tiles.
+  auto small_tiles = [&](int64_t rows) { return (rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB * p.n_vt; };
+  const bool small = small_tiles(rows_of_group(0)) <= kNumCu;
+  const int64_t tiles_first = (int64_t)xcd_grid_2d(p.n_vt, (int)((rows_of_group(0) + kTile - 1) / kTile));
+  int* queue = ctl && !small && tiles_first > kNumCu ? ctl->queue : nullptr;
+  int queue_base = 0;
+  if (queue) {
+    Scope sc(st, MST_K_LABEL_SCAN);
+    hipLaunchKernelGGL(k_clear_queues, dim3(1), dim3(64), 0, st, ctl);
+  }
   for (int64_t g0 = 0; g0 < p.S; g0 += p.fwd_group_rows) {
-    const int64_t g_rows = (p.S - g0) < p.fwd_group_rows ? (p.S - g0) : p.fwd_group_rows;
-    {
-      // One launch for the group's mini-sequences.  Rows are independent and no logits are stored, so the row tiles
-      // of the launch need not respect the boundaries between the mini-sequences of the group: a mini-sequence
-      // shorter than a 256-row tile costs no idle tile rows, and every row's result is bit-identical for every M.
-      const int n_st = (int)((g_rows + kTile - 1) / kTile);
+    const int64_t g_rows = rows_of_group(g0);
+    // One launch for the group's mini-sequences.  Rows are independent and no logits are stored, so the row tiles
+    // of the launch need not respect the boundaries between the mini-sequences of the group: a mini-sequence
+    // shorter than a 256-row tile costs no idle tile rows, and every row's result is bit-identical for every M.
+    if (small) {
       Scope sc(st, MST_K_FWD_GEMM_LSE);
-      // few tiles: 64 rows each, as long as every workgroup has a compute unit to itself (same bits)
-      const int n_sh = (int)((g_rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB);
-      if ((int64_t)n_sh * p.n_vt <= kNumCu) {
-        hipLaunchKernelGGL(k_fwd_gemm_lse_small<TileFwdSmall>, dim3(even_grid(p.n_vt, n_sh)), dim3(TileFwdSmall::kThreads),
-                           TileFwdSmall::kLds, st, H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_sh, p.n_vt,
-                           part, stride, tgt);
-      } else {
+      const int n_st = (int)((g_rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB);
+      hipLaunchKernelGGL(k_fwd_gemm_lse_small<TileFwdSmall>, dim3(even_grid(p.n_vt, n_st)), dim3(TileFwdSmall::kThreads),
+                         TileFwdSmall::kLds, st, H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_st, p.n_vt,
+                         part, stride, tgt);
+    } else {
+      Scope sc(st, MST_K_FWD_GEMM_LSE);
+      const int n_st = (int)((g_rows + kTile - 1) / kTile);
       const int tiles = xcd_grid_2d(p.n_vt, n_st);
       const int grid = queue && tiles > kNumCu ? kNumCu : tiles;
       hipLaunchKernelGGL(k_fwd_gemm_lse, dim3(grid), dim3(kThreads), kLdsBytes, st,
                          H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_st, p.n_vt,
                          part, stride, tgt, queue, queue_base);
       queue_base += tiles / kNumXcd + grid;
-      }
     }
     {
       Scope sc(st, MST_K_LSE_FINALIZE);
@@ -500,22 +509,17 @@ mst_status check_forward_alignment(const void* H, const void* W, const int32_t* 
   return MST_OK;
 }
 
-// label scan, the chunk loop, the loss: everything the forward call enqueues, on workspace `ws` of p.f_total bytes
+// everything the forward call enqueues, on workspace `ws` of p.f_total bytes
 mst_status enqueue_forward(const Plan& p, const void* H, const void* W, const int32_t* labels, int32_t ignore_index,
                            char* ws, float* loss, float* lse, int64_t* n_valid, void* stream) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  Control* ctl = reinterpret_cast<Control*>(ws);
   float* nll = reinterpret_cast<float*>(ws + p.f_nll);
-  {
-    Scope sc(st, MST_K_LABEL_SCAN);
-    hipLaunchKernelGGL(k_label_scan, dim3(1), dim3(1024), 0, st, labels, (long long)p.S, (int)p.V, ignore_index, ctl);
-  }
-  const mst_status s = run_forward_chunks(p, static_cast<const __bf16*>(H), static_cast<const __bf16*>(W), labels,
-                                          ignore_index, ws, lse, nll, st, ctl->queue);
+  const mst_status s = run_forward_chunks(p, static_cast<const __bf16*>(H), static_cast<const __bf16*>(W), labels, ignore_index,
+                                          ws, lse, nll, st, reinterpret_cast<Control*>(ws));
   if (s != MST_OK) return s;
   {
     Scope sc(st, MST_K_LOSS_REDUCE);
-    hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(1024), 0, st, nll, (long long)p.S, ctl, loss,
+    hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(1024), 0, st, nll, labels, (long long)p.S, (int)p.V, ignore_index, loss,
                        reinterpret_cast<long long*>(n_valid));
   }
   return check_launch();

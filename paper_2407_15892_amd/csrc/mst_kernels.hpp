@@ -41,13 +41,14 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kMasked = -1.0e30f;     // stands for -infinity in max / sum-exp without producing NaN
 constexpr int kNumXcd = 8;
 
-// Control block in the workspace, written by k_label_scan (n_valid is its first member).
+// Control block in the workspace: the forward's tile queues; the label counts where the backward call counts them itself
+// (k_label_scan; n_valid is its first member).
 struct Control {
   long long n_valid;    // rows whose label is neither ignored nor out of range
   int bad_labels;       // rows whose label is outside [0, V) and not the ignore value
   int pad0;
   long long n_valid_checked;   // n_valid, or -1 if bad_labels > 0: what a caller (or the backward pass) is handed
-  int queue[8];         // per-XCD tile queues of the persistent forward launch (see TileFeed); zeroed by the label scan
+  int queue[8];         // per-XCD tile queues of the persistent forward launch (see TileFeed); zeroed by k_clear_queues
   int pad[50];
 };
 static_assert(sizeof(Control) == 256, "control block is one 256-byte line");
@@ -236,6 +237,9 @@ __global__ __launch_bounds__(1024) void k_label_scan(const int* __restrict__ lab
     ctl->bad_labels = tb;
     ctl->n_valid_checked = tb > 0 ? -1 : tv;
   }
+}
+
+__global__ __launch_bounds__(64) void k_clear_queues(Control* ctl) {
   if (threadIdx.x < kNumXcd) ctl->queue[threadIdx.x] = 0;
 }
 
@@ -409,7 +413,10 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemm_lse(
 
 // per row: combine the vocab-tile partials into lse and nll.  A workgroup owns 64 rows; its 16
 // waves each fold every 16th vocabulary tile in ascending order, then the 16 partial results are
-// folded in wave order: the combination order is fixed, so lse is reproducible bit for bit.
+// folded in wave order: the combination order is fixed, so lse is reproducible bit for bit.  The pairs are loaded eight
+// at a time: folded one by one, every load waited for the exponentials before it.
+// (Summing the loss in the workgroup that finishes last was slower than a launch of its own: the device-scope release
+// and acquire around its counter took 6 to 16 us.)
 constexpr int kFinRows = 64;
 constexpr int kFinGroups = 16;
 __global__ __launch_bounds__(kFinRows * kFinGroups) void k_lse_finalize(
@@ -420,23 +427,23 @@ __global__ __launch_bounds__(kFinRows * kFinGroups) void k_lse_finalize(
   const int r = threadIdx.x & (kFinRows - 1), g = threadIdx.x / kFinRows;
   const int s = blockIdx.x * kFinRows + r;
   float m = kMasked, l = 0.f;
+  auto fold = [&](float2 p) { merge_lse(m, l, p.x, p.y); };
   if (s < rows) {
-    for (int vt = g; vt < n_vt; vt += kFinGroups) {
-      const float2 p = part[(size_t)vt * part_stride + s];
-      const float mm = fmaxf(m, p.x);
-      l = l * fast_exp2((m - mm) * kLog2e) + p.y * fast_exp2((p.x - mm) * kLog2e);
-      m = mm;
+    constexpr int kAhead = 8;
+    int vt = g;
+    for (; vt + (kAhead - 1) * kFinGroups < n_vt; vt += kAhead * kFinGroups) {
+      float2 p[kAhead];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) p[i] = part[(size_t)(vt + i * kFinGroups) * part_stride + s];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) fold(p[i]);
     }
+    for (; vt < n_vt; vt += kFinGroups) fold(part[(size_t)vt * part_stride + s]);
   }
   sh[g][r] = make_float2(m, l);
   __syncthreads();
   if (g != 0 || s >= rows) return;
-  for (int q = 1; q < kFinGroups; ++q) {
-    const float2 p = sh[q][r];
-    const float mm = fmaxf(m, p.x);
-    l = l * fast_exp2((m - mm) * kLog2e) + p.y * fast_exp2((p.x - mm) * kLog2e);
-    m = mm;
-  }
+  for (int q = 1; q < kFinGroups; ++q) fold(sh[q][r]);
   const float log_l = __builtin_amdgcn_logf(l) * kLn2;     // v_log_f32 is log2
   const float lse = m + log_l;
   const int y = labels_c[s];
@@ -447,28 +454,50 @@ __global__ __launch_bounds__(kFinRows * kFinGroups) void k_lse_finalize(
   if (nll_c) nll_c[s] = valid ? (m - tgt[s]) + log_l : 0.f;
 }
 
-// loss = sum(nll) / n_valid, fixed summation order, fp64 accumulation.  One workgroup.
-__global__ __launch_bounds__(1024) void k_loss_reduce(const float* __restrict__ nll, long long S,
-                                                      const Control* __restrict__ ctl,
-                                                      float* __restrict__ loss, long long* __restrict__ n_valid_out) {
+// loss = sum(nll) / n_valid, fixed summation order, fp64 accumulation; counts and range-checks the labels on the way (one
+// launch less than with a scan in front of the GEMM).  One workgroup, bound by the latency of its loads: eight rounds of
+// them at a time.
+__global__ __launch_bounds__(1024) void k_loss_reduce(const float* __restrict__ nll, const int* __restrict__ labels, long long S,
+                                                      int V, int ignore_index, float* __restrict__ loss,
+                                                      long long* __restrict__ n_valid_out) {
   __shared__ double sh[1024];
+  __shared__ long long s_valid[16];
+  __shared__ int s_bad[16];
   double a = 0.0;
-  for (long long i = threadIdx.x; i < S; i += 1024) a += (double)nll[i];
+  long long nv = 0;
+  int nb = 0;
+  auto add = [&](float x, int y) {
+    a += (double)x;
+    if (y != ignore_index) {
+      if ((unsigned)y < (unsigned)V) ++nv; else ++nb;
+    }
+  };
+  long long i = threadIdx.x;
+  for (; i + 7 * 1024 < S; i += 8 * 1024) {
+    float x[8];
+    int y[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) { x[k] = nll[i + k * 1024]; y[k] = labels[i + k * 1024]; }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) add(x[k], y[k]);
+  }
+  for (; i < S; i += 1024) add(nll[i], labels[i]);
   sh[threadIdx.x] = a;
+  for (int o = 32; o > 0; o >>= 1) {
+    nv += __shfl_xor(nv, o);
+    nb += __shfl_xor(nb, o);
+  }
+  if ((threadIdx.x & 63) == 0) { s_valid[threadIdx.x >> 6] = nv; s_bad[threadIdx.x >> 6] = nb; }
   __syncthreads();
   for (int o = 512; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const long long nv = ctl->n_valid;
-    if (ctl->bad_labels > 0) {
-      *loss = __builtin_nanf("");
-      if (n_valid_out) *n_valid_out = -1;
-    } else {
-      *loss = nv > 0 ? (float)(sh[0] / (double)nv) : 0.f;
-      if (n_valid_out) *n_valid_out = nv;
-    }
+    long long tv = 0; int tb = 0;
+    for (int k = 0; k < 16; ++k) { tv += s_valid[k]; tb += s_bad[k]; }
+    *loss = tb > 0 ? __builtin_nanf("") : tv > 0 ? (float)(sh[0] / (double)tv) : 0.f;
+    if (n_valid_out) *n_valid_out = tb > 0 ? -1 : tv;
   }
 }
 
