@@ -28,8 +28,6 @@ namespace mst {
 // went away when the fp32 intermediates moved to accumulator order)
 typedef Cfg16<2, 4, 8, 4, 64, 2> Tile16;
 constexpr int kTA16 = Tile16::TA, kTB16 = Tile16::TB;
-// same wave grid, half as wide on the B side: 256 x 128 block tile, wave tile 128 x 32
-typedef Cfg16<2, 4, 8, 2, 64, 2> Tile16HalfB;
 constexpr int kTile = 256;             // Tile16::EA == Tile16::EB
 constexpr int kBK = Tile16::BK;
 constexpr int kThreads = Tile16::kThreads;

@@ -60,15 +60,18 @@ bool set_kernel_attributes() {   // on the current device
   auto set = [&ok](const void* f) {
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess) ok = false;
   };
-  set((const void*)k_mlp_gateup<false>);
-  set((const void*)k_mlp_gateup<true>);
-  set((const void*)k_mlp_gemm_nt);
+  set((const void*)k_mlp_gateup<false, false>);
+  set((const void*)k_mlp_gateup<false, true>);
+  set((const void*)k_mlp_gateup<true, false>);
+  set((const void*)k_mlp_gateup<true, true>);
+  set((const void*)k_mlp_gemm_nt<false>);
+  set((const void*)k_mlp_gemm_nt<true>);
   set_small_attributes<Tile128>(set);
   set_small_attributes<Tile128Lone>(set);
   set_small_attributes<Tile64>(set);
   set_small_attributes<Tile64Lone>(set);
-  set((const void*)k_mlp_gemm_nn<Tile16>);
-  set((const void*)k_mlp_gemm_nn<Tile16HalfB>);
+  set((const void*)k_mlp_gemm_nn<false>);
+  set((const void*)k_mlp_gemm_nn<true>);
   set((const void*)k_mlp_dw3_small<Tile64>);
   set((const void*)k_mlp_dw3_small<Tile64Lone>);
   set((const void*)k_mlp_dw3<false, false>);
@@ -101,7 +104,7 @@ constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident
 // Which block tile a GEMM of n_a x n_b outputs (A side: weights, B side: tokens) and `ksteps` K steps of 64 runs with.
 // The figures are microseconds fitted to launches of the three kinds (gate/up, down, dA/dX) at 64 to 3000 tokens,
 // d = 256 to 4096, I = 896 to 14336; they only have to rank the tiles, and every tile gives the same bits:
-//   256 x 256      1.25 per K step + 7 (first loads, epilogue), in whole rounds of kNumCu
+//   256 x 256      1.25 per K step (1.4 with K-strided weights) + 7 (first loads, epilogue), in whole rounds of kNumCu
 //   128 x 128      1.0 per K step + 4 for two workgroups on a compute unit; further rounds overlap.  3000 tokens,
 //                  d = 768, I = 2304: gate/up 26 us against 39
 //   128 x 128 lone 0.55 per K step + 3.2, up to kNumCu tiles.  1024 tokens, d = 4096, I = 14336: down 140 us (256 tiles)
@@ -110,107 +113,124 @@ constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident
 //                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256)
 //   64 x 64 lone   0.24 per K step + 2.5.  256 tokens, d = 256, I = 896: down 5.5 against 18; 200 tokens, d = 4096,
 //                  I = 14336: down 63 against 250 (16 tiles of 256), dX 129 against 523
+// Where the large tiles end in a partly filled round, whole columns of them may make up the full rounds and a second
+// launch the rest with smaller tiles: gate/up of 1668 tokens, d = 1544, I = 5384 (301 large tiles) as 252 large and 675 of
+// 64 x 64: step of 5003 tokens 1.31 -> 1.23 ms; dA of 4096 tokens, I = 14336 (896 tiles) as 768 large and 512 of
+// 128 x 128: 376 us against 412.  With all compute units busy a K step takes 1.36, with the K-strided weights of dA and
+// dX 1.4 also where some are idle; not split, by this, are the 1376 tiles of gate/up at I = 11008 (2 % slower split).
 enum TileKind { kBig, k128, k128Lone, k64, k64Lone };
-TileKind choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps) {
-  auto tiles = [&](int64_t e) { return (double)((n_a + e - 1) / e) * (double)((n_b + e - 1) / e); };
+struct TileChoice {
+  TileKind kind;      // of the whole, or of what follows the first `head` columns
+  int64_t head;       // A-side extent, a multiple of 256, that large tiles cover in a launch of its own (0: none)
+  double us;
+};
+TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, bool strided) {
   const double k = (double)ksteps;
-  TileKind best = kBig;
-  double t_best = std::ceil(tiles(256) / kNumCu) * (1.25 * k + 7.0);
+  TileChoice best = {kBig, 0, std::ceil(tiles_of(n_a, n_b, 256) / kNumCu) * ((strided ? 1.4 : 1.25) * k + 7.0)};
   auto consider = [&](TileKind kind, double t) {
-    if (t < t_best) { t_best = t; best = kind; }
+    if (t < best.us) best = {kind, 0, t};
   };
-  const double x = tiles(128) / (2.0 * kNumCu), y = tiles(64) / (4.0 * kNumCu);
+  const double x = tiles_of(n_a, n_b, 128) / (2.0 * kNumCu), y = tiles_of(n_a, n_b, 64) / (4.0 * kNumCu);
   if (x <= 0.5) consider(k128Lone, 0.55 * k + 3.2);
   else consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : 0.3 + 0.7 * x) * (k + 4.0));
   consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.3 + 0.4 * y : 0.45) * k + 2.5);
   if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
 }
+TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, bool strided) {
+  const TileChoice whole = choose_whole(n_a, n_b, ksteps, strided);
+  const int64_t t_a = (n_a + kTile - 1) / kTile, t_b = (n_b + kTile - 1) / kTile;
+  const int64_t full = t_a * t_b / kNumCu * kNumCu, cols = full / t_b;       // full rounds; columns of tiles in them
+  if (cols == 0 || cols == t_a) return whole;
+  const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, strided);
+  const double t = (double)(full / kNumCu) * ((strided ? 1.4 : 1.36) * (double)ksteps + 7.0) + rest.us + 2.0;
+  return rest.kind != kBig && t < whole.us ? TileChoice{rest.kind, cols * kTile, t} : whole;
+}
 
 // A = silu(X Wg^T) * (X Wu^T) of a chunk, or its backward (dA given)
 template <class C, bool kBackward>
-void launch_gateup_small(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
+void launch_gateup_small(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int n_i, int ldi,
                          __bf16* A, __bf16* dAG, __bf16* dU) {
-  const int n_it = (I + C::EA / 2 - 1) / (C::EA / 2), n_st = (rows + C::EB - 1) / C::EB;
+  const int n_it = (n_i + C::EA / 2 - 1) / (C::EA / 2), n_st = (rows + C::EB - 1) / C::EB;
   hipLaunchKernelGGL((k_mlp_gateup_small<C, kBackward>), dim3(even_grid(n_it, n_st)), dim3(C::kThreads), C::kLds, st,
-                     X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
+                     X, Wg, Wu, rows, d, n_i, ldi, n_st, n_it, A, dAG, dU);
 }
 template <bool kBackward>
 void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
                    __bf16* A, __bf16* dAG, __bf16* dU) {
-  switch (choose_tile(2 * (int64_t)I, rows, (d + kBK - 1) / kBK)) {
-    case k128: return launch_gateup_small<Tile128, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
-    case k128Lone: return launch_gateup_small<Tile128Lone, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
-    case k64: return launch_gateup_small<Tile64, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
-    case k64Lone: return launch_gateup_small<Tile64Lone, kBackward>(st, X, Wg, Wu, rows, d, I, A, dAG, dU);
-    default: break;
+  const TileChoice c = choose_tile(2 * (int64_t)I, rows, (d + kBK - 1) / kBK, false);
+  const int i0 = (int)(c.head / 2), n_i = I - i0;               // the second launch's indices
+  if (c.kind == kBig || i0) {
+    const int n_it = ((i0 ? i0 : I) + kGateUpI - 1) / kGateUpI, n_st = (rows + kTile - 1) / kTile;
+    const auto kernel = use_super_tiles(n_it, n_st) ? k_mlp_gateup<kBackward, true> : k_mlp_gateup<kBackward, false>;
+    hipLaunchKernelGGL(kernel, dim3(mlp_grid(n_it, n_st)), dim3(kThreads), kLdsBytes, st,
+                       X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
   }
-  const int n_it = (I + kGateUpI - 1) / kGateUpI, n_st = (rows + kTile - 1) / kTile;
-  hipLaunchKernelGGL(k_mlp_gateup<kBackward>, dim3(mlp_grid(n_it, n_st)), dim3(kThreads), kLdsBytes, st,
-                     X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
+  Wg += (size_t)i0 * d;
+  Wu += (size_t)i0 * d;
+  A += i0;
+  if (kBackward) { dAG += i0; dU += i0; }
+  switch (c.kind) {
+    case k128: return launch_gateup_small<Tile128, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
+    case k128Lone: return launch_gateup_small<Tile128Lone, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
+    case k64: return launch_gateup_small<Tile64, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
+    case k64Lone: return launch_gateup_small<Tile64Lone, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
+    default: return;
+  }
 }
 
 // out[rows][N] = P Q^T, P [rows][K], Q [N][K]
 template <class C>
-void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
+void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out, int ldo) {
   const int n_nt = (N + C::EA - 1) / C::EA, n_st = (rows + C::EB - 1) / C::EB;
   hipLaunchKernelGGL(k_mlp_gemm_nt_small<C>, dim3(even_grid(n_nt, n_st)), dim3(C::kThreads), C::kLds, st,
-                     P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
+                     P, K, Q, K, rows, N, K, n_st, n_nt, out, ldo);
 }
 void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
-  switch (choose_tile(N, rows, (K + kBK - 1) / kBK)) {
-    case k128: return launch_nt_small<Tile128>(st, P, Q, rows, N, K, out);
-    case k128Lone: return launch_nt_small<Tile128Lone>(st, P, Q, rows, N, K, out);
-    case k64: return launch_nt_small<Tile64>(st, P, Q, rows, N, K, out);
-    case k64Lone: return launch_nt_small<Tile64Lone>(st, P, Q, rows, N, K, out);
-    default: break;
+  const TileChoice c = choose_tile(N, rows, (K + kBK - 1) / kBK, false);
+  const int n0 = (int)c.head;
+  if (c.kind == kBig || n0) {
+    const int n_nt = ((n0 ? n0 : N) + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
+    hipLaunchKernelGGL(use_super_tiles(n_nt, n_st) ? k_mlp_gemm_nt<true> : k_mlp_gemm_nt<false>, dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
+                       P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
   }
-  const int n_nt = (N + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
-  hipLaunchKernelGGL(k_mlp_gemm_nt, dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
-                     P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
-}
-
-// Tail of the workgroup grid.  A GEMM of n_a x n_b block tiles runs in rounds of kNumCu workgroups; when the
-// last round would be at most half full, the tiles of that round (whole tile rows of the A side, else whole
-// tile columns of the B side) are cut in two along the B side (256 x 128 tiles) and launched separately, so
-// that the last round is full and shorter.
-struct Tail { int a_tail, b_tail; };
-Tail tail_split(int n_a, int n_b) {
-  const int total = n_a * n_b, rem = total % kNumCu;
-  if (total < kNumCu || rem == 0 || 2 * rem > kNumCu) return {0, 0};
-  if (rem % n_b == 0) return {rem / n_b, 0};
-  if (rem % n_a == 0) return {0, rem / n_a};
-  return {0, 0};
+  Q += (size_t)n0 * K;
+  out += n0;
+  switch (c.kind) {
+    case k128: return launch_nt_small<Tile128>(st, P, Q, rows, N - n0, K, out, N);
+    case k128Lone: return launch_nt_small<Tile128Lone>(st, P, Q, rows, N - n0, K, out, N);
+    case k64: return launch_nt_small<Tile64>(st, P, Q, rows, N - n0, K, out, N);
+    case k64Lone: return launch_nt_small<Tile64Lone>(st, P, Q, rows, N - n0, K, out, N);
+    default: return;
+  }
 }
 
 // out[rows][N] = P1 Q1 (+ P2 Q2), P: [rows][K], Q: [K][N]
 template <class C>
 void launch_nn_small(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16* P2, const __bf16* Q2,
-                     int rows, int N, int K, __bf16* out) {
+                     int rows, int N, int K, int ldq, __bf16* out) {
   const int n_nt = (N + C::EA - 1) / C::EA, n_st = (rows + C::EB - 1) / C::EB;
   hipLaunchKernelGGL(k_mlp_gemm_nn_small<C>, dim3(even_grid(n_nt, n_st)), dim3(C::kThreads), C::kLds, st,
-                     P1, Q1, P2, Q2, K, N, rows, N, K, n_st, n_nt, out, N);
+                     P1, Q1, P2, Q2, K, ldq, rows, N, K, n_st, n_nt, out, ldq);
 }
 void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16* P2, const __bf16* Q2,
                int rows, int N, int K, __bf16* out) {
-  switch (choose_tile(N, rows, (P2 ? 2 : 1) * (int64_t)((K + kBK - 1) / kBK))) {
-    case k128: return launch_nn_small<Tile128>(st, P1, Q1, P2, Q2, rows, N, K, out);
-    case k128Lone: return launch_nn_small<Tile128Lone>(st, P1, Q1, P2, Q2, rows, N, K, out);
-    case k64: return launch_nn_small<Tile64>(st, P1, Q1, P2, Q2, rows, N, K, out);
-    case k64Lone: return launch_nn_small<Tile64Lone>(st, P1, Q1, P2, Q2, rows, N, K, out);
-    default: break;
+  const TileChoice c = choose_tile(N, rows, (P2 ? 2 : 1) * (int64_t)((K + kBK - 1) / kBK), true);
+  const int n0 = (int)c.head;
+  if (c.kind == kBig || n0) {
+    const int n = n0 ? n0 : N, n_nt = (n + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
+    hipLaunchKernelGGL(use_super_tiles(n_nt, n_st) ? k_mlp_gemm_nn<true> : k_mlp_gemm_nn<false>, dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
+                       P1, Q1, P2, Q2, K, N, rows, n, K, n_st, n_nt, out, N);
   }
-  const int n_nt = (N + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
-  const Tail tl = tail_split(n_nt, n_st);
-  const int nt_full = n_nt - tl.a_tail;        // only a split of the A side (columns of Q) is used here
-  const int n_full = tl.a_tail ? nt_full * kTile : N;
-  hipLaunchKernelGGL(k_mlp_gemm_nn<Tile16>, dim3(mlp_grid(nt_full, n_st)), dim3(kThreads), kLdsBytes, st,
-                     P1, Q1, P2, Q2, K, N, rows, n_full, K, n_st, nt_full, out, N);
-  if (tl.a_tail) {
-    const int n_sh = (rows + Tile16HalfB::EB - 1) / Tile16HalfB::EB;
-    hipLaunchKernelGGL(k_mlp_gemm_nn<Tile16HalfB>, dim3(mlp_grid(tl.a_tail, n_sh)), dim3(kThreads),
-                       Tile16HalfB::kLds, st, P1, Q1 + n_full, P2, Q2 ? Q2 + n_full : Q2, K, N, rows, N - n_full, K,
-                       n_sh, tl.a_tail, out + n_full, N);
+  Q1 += n0;
+  if (Q2) Q2 += n0;
+  out += n0;
+  switch (c.kind) {
+    case k128: return launch_nn_small<Tile128>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
+    case k128Lone: return launch_nn_small<Tile128Lone>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
+    case k64: return launch_nn_small<Tile64>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
+    case k64Lone: return launch_nn_small<Tile64Lone>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
+    default: return;
   }
 }
 

@@ -25,29 +25,31 @@ namespace mst {
 // workgroups more than others, or where there is not even one full round.  Gate/up on 36 x 6 tiles (10
 // super-tiles on 8 XCDs): 38 us instead of 64; down on 16 x 4 tiles (2 super-tiles, so 2 XCDs): 95 instead of 124.
 // On 112 x 16 tiles (7 full rounds either way) the super-tiles are 0.8 % faster.
+// A template argument of the kernels, so that the long launches carry one map only.
 constexpr int kSuperSlow = 8, kSuperFast = 4;
-__host__ __device__ inline int super_tiles(int n_slow, int n_fast) {
+inline int super_tiles(int n_slow, int n_fast) {
   return ((n_slow + kSuperSlow - 1) / kSuperSlow) * ((n_fast + kSuperFast - 1) / kSuperFast);
 }
-__host__ __device__ inline bool use_super_tiles(int n_slow, int n_fast) {
+inline bool use_super_tiles(int n_slow, int n_fast) {
   constexpr int kPerRound = kSuperSlow * kSuperFast;                       // workgroups resident on an XCD
   const int per_xcd = (n_slow * n_fast + kNumXcd - 1) / kNumXcd;
   return per_xcd >= kPerRound && (super_tiles(n_slow, n_fast) + kNumXcd - 1) / kNumXcd == (per_xcd + kPerRound - 1) / kPerRound;
 }
-__host__ __device__ inline bool mlp_tile_of_block(int block, int n_slow, int n_fast, int* slow, int* fast) {
-  if (!use_super_tiles(n_slow, n_fast)) return even_tile_of_block(block, n_slow, n_fast, slow, fast);
-  const int sf = (n_fast + kSuperFast - 1) / kSuperFast;
-  const int x = block % kNumXcd, q = block / kNumXcd;
-  const int super = x + kNumXcd * (q / (kSuperSlow * kSuperFast));
-  const int inner = q % (kSuperSlow * kSuperFast);
-  if (super >= super_tiles(n_slow, n_fast)) return false;
-  *slow = (super / sf) * kSuperSlow + inner / kSuperFast;
-  *fast = (super % sf) * kSuperFast + inner % kSuperFast;
-  return *slow < n_slow && *fast < n_fast;
-}
 inline int mlp_grid(int n_slow, int n_fast) {
   if (!use_super_tiles(n_slow, n_fast)) return even_grid(n_slow, n_fast);
   return kNumXcd * ((super_tiles(n_slow, n_fast) + kNumXcd - 1) / kNumXcd) * kSuperSlow * kSuperFast;
+}
+template <bool kSuper>
+__device__ __forceinline__ bool mlp_tile(int n_slow, int n_fast, int* slow, int* fast) {
+  if (!kSuper) return even_tile_of_block(blockIdx.x, n_slow, n_fast, slow, fast);
+  const int ss = (n_slow + kSuperSlow - 1) / kSuperSlow, sf = (n_fast + kSuperFast - 1) / kSuperFast;
+  const int x = blockIdx.x % kNumXcd, q = blockIdx.x / kNumXcd;
+  const int super = x + kNumXcd * (q / (kSuperSlow * kSuperFast));
+  const int inner = q % (kSuperSlow * kSuperFast);
+  if (super >= ss * sf) return false;
+  *slow = (super / sf) * kSuperSlow + inner / kSuperFast;
+  *fast = (super % sf) * kSuperFast + inner % kSuperFast;
+  return *slow < n_slow && *fast < n_fast;
 }
 
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -63,14 +65,14 @@ __device__ __forceinline__ float sigmoid_f(float g) { return fast_rcp(1.0f + fas
 //   kBackward: dAG holds dA on entry and receives dG (same element, same lane); dU and A are written.
 // ---------------------------------------------------------------------------
 constexpr int kGateUpI = 128;   // intermediate indices per workgroup
-template <bool kBackward>
+template <bool kBackward, bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
     const __bf16* __restrict__ Xc, const __bf16* __restrict__ Wg, const __bf16* __restrict__ Wu,
     int rows, int d, int I, int n_st, int n_it,
     __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int it, st;
-  if (!mlp_tile_of_block(blockIdx.x, n_it, n_st, &it, &st)) return;
+  if (!mlp_tile<kSuper>(n_it, n_st, &it, &st)) return;
   const int i0 = it * kGateUpI, s0 = st * kTile;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -174,12 +176,13 @@ __device__ __forceinline__ void store_rows_bf16(const f32x4 (&acc)[T::TA][T::TB]
 // out[s][n] = sum_k P[s][k] Q[n][k]      (both operands K-contiguous; used for O_chunk = A Wd^T)
 //   A side = n (rows of Q, permuted so a lane holds 32 consecutive n), B side = s (rows of P)
 // ---------------------------------------------------------------------------
+template <bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nt(
     const __bf16* __restrict__ P, int ldp, const __bf16* __restrict__ Q, int ldq, int rows, int N, int K,
     int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int nt, st;
-  if (!mlp_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
+  if (!mlp_tile<kSuper>(n_nt, n_st, &nt, &st)) return;
   const int n0 = nt * kTile, s0 = st * kTile;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -199,16 +202,17 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nt(
 // out[s][n] = sum_k P1[s][k] Q1[k][n] (+ sum_k P2[s][k] Q2[k][n])   (Q K-strided)
 //   used for dA = dO Wd (one term, K = d) and dX = dG Wg + dU Wu (two terms, K = I each)
 //   A side = n (columns of Q, read transposed with the row permutation, so a lane holds 32 consecutive n
-//   and stores 64 bytes), B side = s (rows of P).  T: Tile16, or Tile16HalfB for a partly filled last round.
+//   and stores 64 bytes), B side = s (rows of P).
 // ---------------------------------------------------------------------------
-template <class T>
+template <bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
     int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
+  typedef Tile16 T;
   int nt, st;
-  if (!mlp_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
+  if (!mlp_tile<kSuper>(n_nt, n_st, &nt, &st)) return;
   const int n0 = nt * T::EA, s0 = st * T::EB;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -244,7 +248,7 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 template <class C, bool kBackward>
 __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
     const __bf16* __restrict__ Xc, const __bf16* __restrict__ Wg, const __bf16* __restrict__ Wu,
-    int rows, int d, int I, int n_st, int n_it,
+    int rows, int d, int I /* indices of this launch */, int ldi, int n_st, int n_it,
     __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int H = C::TA / 2;                                  // gate tiles of a wave; as many up tiles follow
@@ -278,7 +282,7 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
   for (int u = 0; u < C::TB; ++u) {
     const int s_local = s0 + wb * (16 * C::TB) + 16 * u + (lane & 15);
     if (s_local >= rows || ib >= I) continue;                   // I % 8 == 0 and N divides 8
-    const size_t off = (size_t)s_local * I + ib;
+    const size_t off = (size_t)s_local * ldi + ib;
     vec da, a_o, g_o, u_o;
     if (kBackward) da = *reinterpret_cast<const vec*>(dAG + off);
 #pragma unroll

@@ -168,6 +168,10 @@ def test_repeated_calls_reuse_the_workspace():
     (1700, 1160, 4104, (1, 2, 5)),
     # down and dX: 256 x 256 unsplit, 128 x 128 in halves (12 full row tiles, a last column tile of 8); few K steps
     (3000, 4104, 520, (1, 2)),
+    # full rounds of large tiles and a second launch with smaller ones behind them: gate/up and dA unsplit
+    (1700, 1032, 9800, (1, 2)),
+    # the same for down and dX
+    (1700, 9480, 1032, (1, 2)),
     # chunks of 129 and 65 rows: one row past a tile of the smaller ones
     (387, 2056, 1032, (3, 6)),
 ])
