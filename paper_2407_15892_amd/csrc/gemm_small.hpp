@@ -15,9 +15,9 @@
 namespace mst {
 
 // wave tile (16 TA) x (16 TB), NSA and NSB LDS stages of the two panels; kPipelined: see the two main loops
-template <int TA_, int TB_, int NSA_, int NSB_, bool kPipelined_>
+template <int TA_, int TB_, int NSA_, int NSB_, bool kPipelined_, int BK_ = 64>
 struct CfgSmall {
-  static constexpr int WA = 2, WB = 2, TA = TA_, TB = TB_, BK = 64;
+  static constexpr int WA = 2, WB = 2, TA = TA_, TB = TB_, BK = BK_;
   static constexpr int NSA = NSA_, NSB = NSB_;
   static constexpr bool kPipelined = kPipelined_;
   static constexpr int kWaves = WA * WB, kThreads = 64 * kWaves;

@@ -51,7 +51,7 @@ struct PanelKC16 {
   static constexpr int NSLOT = EXT / RPS;
   static constexpr int SPW = NSLOT / C::kWaves;
   static_assert(NSLOT % C::kWaves == 0, "slots must divide over waves");
-  static_assert(BK == 64, "row swizzle below is the one for 128-byte rows");
+  static_assert(BK == 64 || BK == 128, "row swizzles below are the ones for 128- and 256-byte rows");
   static_assert(!kPermute || EXT % (16 * TILES) == 0, "the permutation works on the blocks of 16 TILES rows of a wave");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t voff[SPW];
@@ -61,8 +61,8 @@ struct PanelKC16 {
 
   // XOR swizzle of the 16-byte chunk index.  ds_read_b128 serves 16 lanes (256 bytes, all 64 banks) per clock;
   // the 16 lanes of a quarter wave read 16 consecutive rows at one logical chunk, so the chunk index is XORed
-  // with the row bits that do not already select a bank.
-  __device__ __forceinline__ static int swz(int row) { return (row >> 1) & 7; }
+  // with the row bits that do not already select a bank (none of them does with 256-byte rows).
+  __device__ __forceinline__ static int swz(int row) { return BK == 128 ? row & 15 : (row >> 1) & 7; }
 
   // `row_of(lrow)`: source row, relative to `base`, that LDS row lrow of the panel holds; rows >= rows_valid read zeros
   template <class RowOf>

@@ -45,6 +45,7 @@ struct Scope : mst_host::Scope {
 // LDS: two and four), and both software-pipelined for launches that have a compute unit for every workgroup.
 typedef CfgSmall<4, 4, 3, 2, false> Tile128;
 typedef CfgSmall<4, 4, 4, 4, true> Tile128Lone;      // Tile64, Tile64Lone: mst_small_kernels.hpp
+typedef CfgSmall<2, 2, 5, 5, true, 128> Tile64Long;  // K steps of 128: half as many barriers in a long contraction
 
 template <class C, class Set>
 void set_small_attributes(Set set) {
@@ -70,6 +71,7 @@ bool set_kernel_attributes() {   // on the current device
   set_small_attributes<Tile128Lone>(set);
   set_small_attributes<Tile64>(set);
   set_small_attributes<Tile64Lone>(set);
+  set_small_attributes<Tile64Long>(set);
   set((const void*)k_mlp_gemm_nn<false>);
   set((const void*)k_mlp_gemm_nn<true>);
   set((const void*)k_mlp_dw3_small<Tile64>);
@@ -113,12 +115,14 @@ constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident
 //                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256)
 //   64 x 64 lone   0.24 per K step + 2.5.  256 tokens, d = 256, I = 896: down 5.5 against 18; 200 tokens, d = 4096,
 //                  I = 14336: down 63 against 250 (16 tiles of 256), dX 129 against 523
+//   64 x 64 long   the same with K steps of 128, 0.22 per 64 + 3.5, for one workgroup per compute unit: the down of 200
+//                  tokens 53, of 512 tokens (d = 2048, I = 5632) 21.6 against 22.5; slower at fewer than 64 K steps
 // Where the large tiles end in a partly filled round, whole columns of them may make up the full rounds and a second
 // launch the rest with smaller tiles: gate/up of 1668 tokens, d = 1544, I = 5384 (301 large tiles) as 252 large and 675 of
 // 64 x 64: step of 5003 tokens 1.31 -> 1.23 ms; dA of 4096 tokens, I = 14336 (896 tiles) as 768 large and 512 of
 // 128 x 128: 376 us against 412.  With all compute units busy a K step takes 1.36, with the K-strided weights of dA and
 // dX 1.4 also where some are idle; not split, by this, are the 1376 tiles of gate/up at I = 11008 (2 % slower split).
-enum TileKind { kBig, k128, k128Lone, k64, k64Lone };
+enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long };
 struct TileChoice {
   TileKind kind;      // of the whole, or of what follows the first `head` columns
   int64_t head;       // A-side extent, a multiple of 256, that large tiles cover in a launch of its own (0: none)
@@ -134,6 +138,7 @@ TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, bool strided) 
   if (x <= 0.5) consider(k128Lone, 0.55 * k + 3.2);
   else consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : 0.3 + 0.7 * x) * (k + 4.0));
   consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.3 + 0.4 * y : 0.45) * k + 2.5);
+  if (y <= 0.25 && ksteps >= 64) consider(k64Long, 0.22 * k + 3.5);
   if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
 }
@@ -175,6 +180,7 @@ void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf
     case k128Lone: return launch_gateup_small<Tile128Lone, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
     case k64: return launch_gateup_small<Tile64, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
     case k64Lone: return launch_gateup_small<Tile64Lone, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
+    case k64Long: return launch_gateup_small<Tile64Long, kBackward>(st, X, Wg, Wu, rows, d, n_i, I, A, dAG, dU);
     default: return;
   }
 }
@@ -201,6 +207,7 @@ void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N
     case k128Lone: return launch_nt_small<Tile128Lone>(st, P, Q, rows, N - n0, K, out, N);
     case k64: return launch_nt_small<Tile64>(st, P, Q, rows, N - n0, K, out, N);
     case k64Lone: return launch_nt_small<Tile64Lone>(st, P, Q, rows, N - n0, K, out, N);
+    case k64Long: return launch_nt_small<Tile64Long>(st, P, Q, rows, N - n0, K, out, N);
     default: return;
   }
 }
@@ -230,6 +237,7 @@ void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16*
     case k128Lone: return launch_nn_small<Tile128Lone>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
     case k64: return launch_nn_small<Tile64>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
     case k64Lone: return launch_nn_small<Tile64Lone>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
+    case k64Long: return launch_nn_small<Tile64Long>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
     default: return;
   }
 }

@@ -172,6 +172,8 @@ def test_repeated_calls_reuse_the_workspace():
     (1700, 1032, 9800, (1, 2)),
     # the same for down and dX
     (1700, 9480, 1032, (1, 2)),
+    # long contractions on few tiles (K steps of 128 in down and dX, the last one ragged), one chunk of 65 rows
+    (195, 520, 4360, (1, 3)),
     # chunks of 129 and 65 rows: one row past a tile of the smaller ones
     (387, 2056, 1032, (3, 6)),
 ])
