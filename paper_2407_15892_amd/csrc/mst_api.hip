@@ -113,12 +113,17 @@ double launch_us(int64_t tiles, TileCost c, double bytes) {
   return 2.0 + std::max(std::max(rounds, busy), bytes / kHbmBytesPerUs);
 }
 // n1 tiles of c1, then n2 of c2, handed out in this order: n1 % kNumCu units are late for the second kind by one tile of
-// the first, and the others take tiles of it meanwhile
+// the first, and the others take tiles of it meanwhile.  The end is that of the n2-th tile: a multiple of t2 after the
+// moment `a` when the others are free, or after the late ones are.
 double launch_us(int64_t n1, TileCost c1, int64_t n2, TileCost c2, double bytes) {
   const double t1 = c1.alone(), t2 = c2.alone(), a = (double)(n1 / kNumCu) * t1;
-  const int64_t late = n1 % kNumCu, early = late ? (int64_t)(t1 / t2) * (kNumCu - late) : 0;
-  const double after = late ? a + t1 : a;                     // when all units are through with the first kind
-  const double span = after + (n2 > early ? (double)((n2 - early + kNumCu - 1) / kNumCu) * t2 : 0.0);
+  const int64_t late = n1 % kNumCu, others = kNumCu - late;
+  const int64_t f = late ? (int64_t)(t1 / t2) : 0, c = late ? f + 1 : 0;    // whole tiles before the late ones' first, + 1
+  auto up = [](int64_t n, int64_t by) { return n > 0 ? (n + by - 1) / by : 0; };
+  const int64_t j = up(n2, others);
+  const double with_others = (double)(j <= c ? j : up(n2 + late * c, kNumCu)) * t2;
+  const double with_late = t1 + (double)up(n2 - others * f, kNumCu) * t2;
+  const double span = a + (late ? std::max(t1, std::min(with_others, with_late)) : with_others);
   const double busy = ((double)n1 * c1.busy() + (double)n2 * c2.busy()) / kNumCu;
   return 2.0 + std::max(std::max(span, busy), 1.3 * bytes / kHbmBytesPerUs);
 }
@@ -216,10 +221,31 @@ void choose_split_blocks(Plan* p) {
   if (found) { p->est_pairs_us = pairs; p->est_blocks_us = best; }
 }
 
+int64_t dh_split_room(const Plan* p) { return ((int64_t)p->C * p->ldg * 2) / ((int64_t)p->C * p->d * 4); }
+
+// Splits of the pair order's dH: among the counts that fit (at most `most`, at most one per K step, partials must fit into
+// the dlogits slot that is free at that moment: dh_split_room) the one with the fullest rounds of workgroups, with a small penalty per
+// split for the fp32 partials it adds.
+int best_dh_split(const Plan* p, int ksteps, int most) {
+  const int out_tiles = p->n_st * p->n_jt;
+  const int64_t room = dh_split_room(p);
+  int split = 1;
+  double best = -1.0;
+  for (int s = 1; s <= most && s <= ksteps && (s == 1 || s <= room); ++s) {
+    const int wgs = out_tiles * s;
+    const int rounds = (wgs + kNumCu - 1) / kNumCu;
+    const double score = (double)wgs / ((double)rounds * kNumCu) - 0.002 * s;
+    if (score > best) { best = score; split = s; }
+  }
+  const int per = (ksteps + split - 1) / split;
+  return (ksteps + per - 1) / per;
+}
+
 void choose_schedule(Plan* p, int forced) {
   const int64_t S = p->S, d = p->d, V = p->V, C = p->C;
   const int n_vt = p->n_vt, n_jt = p->n_jt;
-  // pairs
+  // pairs (the estimate is calibrated for at most 16 splits of dH)
+  const int ksteps = (int)((V + kBK - 1) / kBK), split = best_dh_split(p, ksteps, 16);
   double pairs = 0.0;
   for (int ia = 0; ia < p->n_chunks; ia += 2) {
     int64_t rows_pair = 0;
@@ -228,8 +254,8 @@ void choose_schedule(Plan* p, int forced) {
       const int64_t n_st = (rows + kTile - 1) / kTile;
       rows_pair += rows;
       pairs += rounds_us(n_st * n_vt, d);                                                  // dlogits
-      pairs += rounds_us(n_st * n_jt * p->dh_split, (int64_t)p->dh_ksteps * kBK);           // dH
-      if (p->dh_split > 1) pairs += 2.0 * (double)(p->dh_split * rows * d * 4) / kRmwBytesPerUs;
+      pairs += rounds_us(n_st * n_jt * split, (int64_t)((ksteps + split - 1) / split) * kBK);   // dH
+      if (split > 1) pairs += 2.0 * (double)(split * rows * d * 4) / kRmwBytesPerUs;
     }
     pairs += rounds_us((int64_t)n_vt * n_jt, rows_pair);                                   // dW
     pairs += (double)((ia > 0 ? 8 : 4) * V * d) / kRmwBytesPerUs;
@@ -314,21 +340,12 @@ mst_status make_plan(int64_t S, int64_t d, int64_t V, int32_t M, Plan* p, int fo
   p->n_vt = (int)((V + kTile - 1) / kTile);
   p->n_jt = (int)((d + kTile - 1) / kTile);
   p->n_st = (int)((C + kTile - 1) / kTile);
-  // dH: few output tiles, long contraction -> split V so that the workgroups fill whole rounds of kNumCu
-  // (one workgroup is resident per CU).  Among the split counts that fit (at most kMaxDhSplit, at most one per
-  // K step, partials must fit into the dlogits slot that is free at that moment) take the one with the fullest
-  // rounds, with a small penalty per split for the fp32 partials it adds.
+  // dH: few output tiles, long contraction -> split V so that the workgroups fill whole rounds of kNumCu (one workgroup
+  // is resident per CU)
   const int out_tiles = p->n_st * p->n_jt;
   const int ksteps = (int)((V + kBK - 1) / kBK);
-  const int64_t room = (C * ldg * 2) / (C * d * 4);
-  int split = 1;
-  double best = -1.0;
-  for (int s = 1; s <= kMaxDhSplit && s <= ksteps && (s == 1 || s <= room); ++s) {
-    const int wgs = out_tiles * s;
-    const int rounds = (wgs + kNumCu - 1) / kNumCu;
-    const double score = (double)wgs / ((double)rounds * kNumCu) - 0.002 * s;
-    if (score > best) { best = score; split = s; }
-  }
+  const int64_t room = dh_split_room(p);
+  const int split = best_dh_split(p, ksteps, kMaxDhSplit);
   p->dh_ksteps = (ksteps + split - 1) / split;
   p->dh_split = (ksteps + p->dh_ksteps - 1) / p->dh_ksteps;
 
@@ -429,10 +446,10 @@ bool set_kernel_attributes() {   // on the current device
   return ok;
 }
 
-auto dlogits_kernel(int n_vt) { return uneven_over_xcds(n_vt) ? k_bwd_gemm_dlogits<true> : k_bwd_gemm_dlogits<false>; }
-auto dw_kernel(bool store_only, int n_vt) {
-  return uneven_over_xcds(n_vt) ? (store_only ? k_bwd_gemm_dw<true, true> : k_bwd_gemm_dw<false, true>)
-                                : (store_only ? k_bwd_gemm_dw<true, false> : k_bwd_gemm_dw<false, false>);
+auto dlogits_kernel(bool even) { return even ? k_bwd_gemm_dlogits<true> : k_bwd_gemm_dlogits<false>; }
+auto dw_kernel(bool store_only, bool even) {
+  return even ? (store_only ? k_bwd_gemm_dw<true, true> : k_bwd_gemm_dw<false, true>)
+              : (store_only ? k_bwd_gemm_dw<true, false> : k_bwd_gemm_dw<false, false>);
 }
 
 mst_status check_launch() { return hipGetLastError() == hipSuccess ? MST_OK : MST_ERR_LAUNCH; }
@@ -685,7 +702,8 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
                          Hb + r0 * p.d, Wb, labels + r0, lse + r0, rows, (int)p.d, (int)p.V, ignore_index, n_sh, n_vh, G, p.ldg);
       return;
     }
-    hipLaunchKernelGGL(dlogits_kernel(p.n_vt), dim3(launch_grid(p.n_vt, n_st)), dim3(kThreads), kLdsBytes, st,
+    const bool even = use_even_map(p.n_vt, n_st);
+    hipLaunchKernelGGL(dlogits_kernel(even), dim3(launch_grid(even, p.n_vt, n_st)), dim3(kThreads), kLdsBytes, st,
                        Hb + r0 * p.d, Wb, labels + r0, lse + r0, rows, (int)p.d, (int)p.V, 0, (int)p.V, ignore_index,
                        n_st, p.n_vt, G, p.ldg);
   };
@@ -727,7 +745,8 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
                          i_last == p.n_chunks - 1 ? 1 : 0, nv, grad_loss, dW);
       return;
     }
-    hipLaunchKernelGGL(dw_kernel(i_first == 0, p.n_vt), dim3(launch_grid(p.n_vt, p.n_jt)),
+    const bool even = use_even_map(p.n_vt, p.n_jt);
+    hipLaunchKernelGGL(dw_kernel(i_first == 0, even), dim3(launch_grid(even, p.n_vt, p.n_jt)),
                        dim3(kThreads), kLdsBytes, st,
                        slot[0], p.ldg, Hb + r0 * p.d, rows, (int)p.d, (int)p.V, p.n_vt, p.n_jt,
                        i_last == p.n_chunks - 1 ? 1 : 0, nv, grad_loss, dW);
@@ -757,7 +776,8 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
         const int Vw = (int)((p.V - v_base) < (int64_t)tiles_w * kTile ? (p.V - v_base) : (int64_t)tiles_w * kTile);
         {
           Scope sc(st, MST_K_BWD_GEMM_DLOGITS);
-          hipLaunchKernelGGL(dlogits_kernel(tiles_w), dim3(launch_grid(tiles_w, n_st)), dim3(kThreads), kLdsBytes, st,
+          const bool even = use_even_map(tiles_w, n_st);
+          hipLaunchKernelGGL(dlogits_kernel(even), dim3(launch_grid(even, tiles_w, n_st)), dim3(kThreads), kLdsBytes, st,
                              Hb + r0 * p.d, Wb + v_base * p.d, labels + r0, lse + r0, rows, (int)p.d, Vw, (int)v_base,
                              (int)p.V, ignore_index, n_st, tiles_w, G, p.blk_ldg);
         }
@@ -767,25 +787,34 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
         const int dw_last = rb == p.blk_n_rb - 1 ? 1 : 0;
         if (p.blk_fused) {
           Scope sc(st, MST_K_BWD_GEMM_DH_DW);
-          const int dh_grid = p.blk_split * dh_grid_2d(n_st, p.n_jt);
-          const bool general = p.blk_split > 1 || uneven_over_xcds(n_st) || uneven_over_xcds(tiles_w);
+          auto dh_share = [&](bool even) {
+            return even ? xcd_share(p.blk_split * p.n_jt, n_st, true) : p.blk_split * xcd_share(n_st, p.n_jt, false);
+          };
+          auto share = [&](bool even) { return dh_share(even) + xcd_share(tiles_w, p.n_jt, even); };
+          const bool both = saves_a_round(share(false), share(true));
+          const bool dh_even = both || uneven_over_xcds(n_st) || saves_a_round(dh_share(false), dh_share(true));
+          const bool dw_even = both || use_even_map(tiles_w, p.n_jt);
+          const bool general = p.blk_split > 1 || dh_even || dw_even;
+          const int dh_grid = dh_grid_2d(dh_even, p.blk_split, n_st, p.n_jt);
           hipLaunchKernelGGL(general ? (rb > 0 ? k_bwd_gemm_dh_dw<false, true> : k_bwd_gemm_dh_dw<true, true>)
                                      : (rb > 0 ? k_bwd_gemm_dh_dw<false, false> : k_bwd_gemm_dh_dw<true, false>),
-                             dim3(dh_grid + launch_grid(tiles_w, p.n_jt)), dim3(kThreads), kLdsBytes, st,
+                             dim3(dh_grid + launch_grid(dw_even, tiles_w, p.n_jt)), dim3(kThreads), kLdsBytes, st,
                              G, p.blk_ldg, Wb + v_base * p.d, Hb + r0 * p.d, rows, (int)p.d, Vw, n_st, tiles_w, p.n_jt,
                              dh_grid, mode, dw_last, nv, grad_loss, dh_sums, p.blk_rows, dHb + r0 * p.d,
-                             dW + v_base * p.d, p.blk_split);
+                             dW + v_base * p.d, p.blk_split, dh_even ? 1 : 0, dw_even ? 1 : 0);
           if (last_win && p.blk_split > 1) launch_dh_reduce_tiles(n_st, rows, r0);
         } else {
           {
             Scope sc(st, MST_K_BWD_GEMM_DH);
-            hipLaunchKernelGGL(uneven_over_xcds(n_st) ? k_bwd_gemm_dh<true> : k_bwd_gemm_dh<false>, dim3(dh_grid_2d(n_st, p.n_jt)), dim3(kThreads), kLdsBytes, st,
+            const bool even = use_even_map(n_st, p.n_jt);
+            hipLaunchKernelGGL(even ? k_bwd_gemm_dh<true> : k_bwd_gemm_dh<false>, dim3(dh_grid_2d(even, 1, n_st, p.n_jt)), dim3(kThreads), kLdsBytes, st,
                                G, p.blk_ldg, Wb + v_base * p.d, rows, (int)p.d, Vw, n_st, p.n_jt, 1, (Vw + kBK - 1) / kBK, mode,
                                nv, grad_loss, dh_sums, p.blk_rows, dHb + r0 * p.d);
           }
           {
             Scope sc(st, MST_K_BWD_GEMM_DW);
-            hipLaunchKernelGGL(dw_kernel(rb == 0, tiles_w), dim3(launch_grid(tiles_w, p.n_jt)),
+            const bool even = use_even_map(tiles_w, p.n_jt);
+            hipLaunchKernelGGL(dw_kernel(rb == 0, even), dim3(launch_grid(even, tiles_w, p.n_jt)),
                                dim3(kThreads), kLdsBytes, st,
                                G, p.blk_ldg, Hb + r0 * p.d, rows, (int)p.d, Vw, tiles_w, p.n_jt,
                                dw_last, nv, grad_loss, dW + v_base * p.d);

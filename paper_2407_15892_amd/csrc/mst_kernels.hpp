@@ -113,23 +113,32 @@ __host__ __device__ inline bool xcd_tile_of_block(int block, int n_slow, int n_f
 constexpr int kXcdRectSlow = 4, kXcdRectFast = 8, kXcdSuper = 32;
 __host__ __device__ inline int xcd_grid_2d(int n_slow, int n_fast) { return kNumXcd * ((n_slow + kNumXcd - 1) / kNumXcd) * n_fast; }
 
-// The map of a backward launch (the forward launch balances itself, see TileFeed): the rectangles above, unless the slow coordinate divides so badly over the XCDs that more than an
-// eighth of the grid would be padding (34 vocabulary tiles: 5 per XCD, the last one idle; 12 row tiles: two of eight idle;
-// 4: half of them): then an equal share of the tiles for every XCD (gemm_small.hpp).  kSuper = kXcdRectFast is the
-// order that keeps the fast panels from round to round.
-__host__ __device__ inline bool uneven_over_xcds(int n_slow) {
+// The map of a backward launch (the forward launch balances itself, see TileFeed): the rectangles above, or an equal share
+// of the tiles for every XCD (gemm_small.hpp).  The latter where the slow coordinate divides so badly over the XCDs that
+// more than an eighth of the grid would be padding (34 vocabulary tiles: 5 per XCD, the last one idle; 12 row tiles: two
+// XCDs idle), and in launches of a few rounds where it saves one (36 x 7 tiles of dlogits: 35 on seven XCDs of 32 compute
+// units, 51 us against 31.6; the step of 4731 tokens, d = 896, V = 62794 that has them 2.83 -> 2.16 ms, its dH and dW
+// tiles, whose shares add up to 36 against 32, included).  Which one is a template argument of the kernels, not a branch in them: the scalar registers that
+// the second map kept alive cost the long launches of the whole-rectangle shapes half a percent.
+inline int xcd_share(int n_slow, int n_fast, bool even) {       // tiles of the XCD that has most
+  return even ? (n_slow * n_fast + kNumXcd - 1) / kNumXcd : (n_slow + kNumXcd - 1) / kNumXcd * n_fast;
+}
+inline bool saves_a_round(int share, int even_share) {
+  constexpr int kCu = 32, kFewRounds = 4;                       // compute units of an XCD
+  return even_share <= kFewRounds * kCu && (share + kCu - 1) / kCu > (even_share + kCu - 1) / kCu;
+}
+inline bool uneven_over_xcds(int n_slow) {
   return 8 * (kNumXcd * ((n_slow + kNumXcd - 1) / kNumXcd) - n_slow) > n_slow;
 }
-// A template argument of the kernels, not a branch in them: the few scalar registers that the second map kept alive cost
-// the long launches of the whole-rectangle shapes half a percent.
-template <bool kEven, int kRectSlow = kXcdRectSlow, int kRectFast = kXcdRectFast, int kSuper = kXcdSuper>
-__device__ __forceinline__ bool launch_tile(int block, int n_slow, int n_fast, int* slow, int* fast) {
-  if (kEven && uneven_over_xcds(n_slow)) return even_tile_of_block(block, n_slow, n_fast, slow, fast);
+inline bool use_even_map(int n_slow, int n_fast) {
+  return uneven_over_xcds(n_slow) || saves_a_round(xcd_share(n_slow, n_fast, false), xcd_share(n_slow, n_fast, true));
+}
+template <int kRectSlow = kXcdRectSlow, int kRectFast = kXcdRectFast, int kSuper = kXcdSuper>
+__device__ __forceinline__ bool launch_tile(bool even, int block, int n_slow, int n_fast, int* slow, int* fast) {
+  if (even) return even_tile_of_block(block, n_slow, n_fast, slow, fast);
   return xcd_tile_of_block<kRectSlow, kRectFast, kSuper>(block, n_slow, n_fast, slow, fast);
 }
-__host__ __device__ inline int launch_grid(int n_slow, int n_fast) {
-  return uneven_over_xcds(n_slow) ? even_grid(n_slow, n_fast) : xcd_grid_2d(n_slow, n_fast);
-}
+inline int launch_grid(bool even, int n_slow, int n_fast) { return even ? even_grid(n_slow, n_fast) : xcd_grid_2d(n_slow, n_fast); }
 
 // Persistent workgroups that pull their tiles from per-XCD queues instead of owning one tile each.
 //
@@ -515,7 +524,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dlogits(
     __bf16* __restrict__ G, int ldg) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int vt, st;                                        // an XCD's resident workgroups: 4 vocabulary x 8 row tiles
-  if (!launch_tile<kEven, kXcdRectSlow, kXcdRectFast, kXcdRectFast>(blockIdx.x, n_vt, n_st, &vt, &st)) return;
+  if (!launch_tile<kXcdRectSlow, kXcdRectFast, kXcdRectFast>(kEven, blockIdx.x, n_vt, n_st, &vt, &st)) return;
   const int v0 = vt * kTile, s0 = st * kTile;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -615,26 +624,37 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dlogits(
 //             k_bwd_dh_reduce_tiles adds the splits at the end.
 //   kDhOnly   one window covers the vocabulary: gamma * result as bf16, nothing to add
 constexpr int kDhSplit = 0, kDhFirst = 1, kDhAdd = 2, kDhLast = 3, kDhOnly = 4;
-// Workgroup -> tile map of the modes that are not kDhSplit.  With row tiles that divide badly over the XCDs the hidden
-// tiles are shared out instead: every XCD then reads its own columns of W (the larger operand) and all of the rows.
-template <bool kEven>
-__device__ __forceinline__ bool dh_tile_of_block(int block, int n_st, int n_jt, int* st, int* jt) {
-  if (kEven && uneven_over_xcds(n_st)) return even_tile_of_block(block, n_jt, n_st, jt, st);
+// Workgroup -> tile map of the modes that are not kDhSplit.  Dealt out evenly, the hidden tiles of all splits are the slow
+// coordinate: every XCD then reads its own part of W (the larger operand) and all of the rows.
+__device__ __forceinline__ bool dh_tile_of_block(bool even, int block, int n_split, int n_st, int n_jt, int* sp, int* st, int* jt) {
+  if (even) {
+    int slow;
+    if (!even_tile_of_block(block, n_split * n_jt, n_st, &slow, st)) return false;
+    *sp = slow / n_jt;
+    *jt = slow - *sp * n_jt;
+    return true;
+  }
+  *sp = 0;
+  if (n_split > 1) {
+    const int grid = xcd_grid_2d(n_st, n_jt);
+    *sp = block / grid;
+    block -= *sp * grid;
+  }
   return xcd_tile_of_block<kXcdRectSlow, kXcdRectFast, kXcdSuper>(block, n_st, n_jt, st, jt);
 }
-__host__ __device__ inline int dh_grid_2d(int n_st, int n_jt) {
-  return uneven_over_xcds(n_st) ? even_grid(n_jt, n_st) : xcd_grid_2d(n_st, n_jt);
+inline int dh_grid_2d(bool even, int n_split, int n_st, int n_jt) {
+  return even ? even_grid(n_split * n_jt, n_st) : n_split * xcd_grid_2d(n_st, n_jt);
 }
 // The body is a device function (block = index of the workgroup within this kernel's tile space) so that a
 // launch can serve the dH and the dW tiles of a vocabulary window together.
-// kGeneral: dH split, or a map other than whole rectangles.
+// kGeneral: dH split, or (`even`) tiles dealt out evenly.
 template <bool kGeneral>
 __device__ __forceinline__ void dh_tile(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, int rows, int d, int V,
     int n_st, int n_jt, int n_split, int ksteps_per_split, int mode,
     const long long* __restrict__ n_valid, float grad_loss,
     float* __restrict__ partial /* [n_split][rows_stride][d] */, int rows_stride,
-    __bf16* __restrict__ dHc /* written by kDhSplit with n_split == 1 and by kDhLast */, int block, char* smem) {
+    __bf16* __restrict__ dHc /* written by kDhSplit with n_split == 1, kDhOnly and kDhLast */, int block, bool even, char* smem) {
   int st, jt, sp = 0;
   if (mode == kDhSplit) {
     const int w = xcd_work_item(n_st * n_jt * n_split);   // not combined with other tile spaces: uses blockIdx.x
@@ -643,12 +663,7 @@ __device__ __forceinline__ void dh_tile(
     jt = (w / n_st) % n_jt;
     sp = w / (n_st * n_jt);
   } else {
-    if (kGeneral) {
-      const int grid = dh_grid_2d(n_st, n_jt);
-      sp = block / grid;
-      block -= sp * grid;
-    }
-    if (!dh_tile_of_block<kGeneral>(block, n_st, n_jt, &st, &jt)) return;
+    if (!dh_tile_of_block(kGeneral && even, block, kGeneral ? n_split : 1, n_st, n_jt, &sp, &st, &jt)) return;
   }
   const int s0 = st * kTile, j0 = jt * kTile;
   const int lane = threadIdx.x & 63;
@@ -757,7 +772,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dh(
     float* __restrict__ partial, int rows_stride, __bf16* __restrict__ dHc) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   dh_tile<kGeneral>(G, ldg, W, rows, d, V, n_st, n_jt, n_split, ksteps_per_split, mode, n_valid, grad_loss, partial, rows_stride,
-          dHc, blockIdx.x, smem);
+          dHc, blockIdx.x, kGeneral, smem);
 }
 
 // the same for sums in accumulator order (n_split arrays of n_st x n_jt tiles): one wave per row of accumulators (w, t) of
@@ -968,7 +983,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dw(
     float* __restrict__ dW) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int vt, jt;
-  if (!launch_tile<kEven>(blockIdx.x, n_vt, n_jt, &vt, &jt)) return;
+  if (!launch_tile(kEven, blockIdx.x, n_vt, n_jt, &vt, &jt)) return;
   const float scale = last ? gamma_of(n_valid, grad_loss) : 1.0f;
   dw_tile(G, ldg, ldg, Hc, d, rows, d, V, vt, jt, kStoreOnly ? 0 : 1, last ? 0 : 1, scale, dW, d, smem);
 }
@@ -977,23 +992,23 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dw(
 // neither depends on the other.  The first dh_grid workgroups take the dH tiles (the longer ones: their
 // contraction runs over the window, dW's over the rows), the rest the dW tiles; with one workgroup per CU the
 // hardware hands out tiles as CUs become free, so the two tile spaces share one partly filled last round
-// instead of leaving one each.  dh_grid = dh_split * dh_grid_2d(n_st, n_jt), a multiple of the XCD count, so both
+// instead of leaving one each.  dh_grid = dh_grid_2d(dh_even, dh_split, n_st, n_jt), a multiple of the XCD count, so both
 // tile spaces keep their XCD-aware mapping.
 template <bool kStoreOnly, bool kGeneral>
 __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dh_dw(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, const __bf16* __restrict__ Hc,
     int rows, int d, int V, int n_st, int n_vt, int n_jt, int dh_grid, int dh_mode, int dw_last,
     const long long* __restrict__ n_valid, float grad_loss,
-    float* __restrict__ dh_sums, int rows_stride, __bf16* __restrict__ dHc, float* __restrict__ dW, int dh_split) {
+    float* __restrict__ dh_sums, int rows_stride, __bf16* __restrict__ dHc, float* __restrict__ dW, int dh_split, int dh_even, int dw_even) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   if ((int)blockIdx.x < dh_grid) {
     const int ksteps = (V + kBK - 1) / kBK, n_split = kGeneral ? dh_split : 1;
     dh_tile<kGeneral>(G, ldg, W, rows, d, V, n_st, n_jt, n_split, kGeneral ? (ksteps + n_split - 1) / n_split : ksteps, dh_mode,
-                      n_valid, grad_loss, dh_sums, rows_stride, dHc, blockIdx.x, smem);
+                      n_valid, grad_loss, dh_sums, rows_stride, dHc, blockIdx.x, dh_even != 0, smem);
     return;
   }
   int vt, jt;
-  if (!launch_tile<kGeneral>((int)blockIdx.x - dh_grid, n_vt, n_jt, &vt, &jt)) return;
+  if (!launch_tile(kGeneral && dw_even, (int)blockIdx.x - dh_grid, n_vt, n_jt, &vt, &jt)) return;
   const float scale = dw_last ? gamma_of(n_valid, grad_loss) : 1.0f;
   dw_tile(G, ldg, ldg, Hc, d, rows, d, V, vt, jt, kStoreOnly ? 0 : 1, dw_last ? 0 : 1, scale, dW, d, smem);
 }

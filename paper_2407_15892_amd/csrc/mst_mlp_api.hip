@@ -242,13 +242,13 @@ void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16*
   }
 }
 
-// tile = 256: the large tiles, in the map of their launch; 64: the small ones, dealt out evenly
-DwProblem dw_problem(const __bf16* G, int ldg, const __bf16* H, int ldh, int d, int V, float* dW, int tile) {
+// tile: 256 or 64; even: dealt out evenly over the XCDs (always so with the small ones)
+DwProblem dw_problem(const __bf16* G, int ldg, const __bf16* H, int ldh, int d, int V, float* dW, int tile, bool even) {
   DwProblem q;
   q.G = G; q.ldg = ldg; q.H = H; q.ldh = ldh; q.d = d; q.V = V;
   q.n_vt = (V + tile - 1) / tile;
   q.n_jt = (d + tile - 1) / tile;
-  q.grid = tile == kTile ? launch_grid(q.n_vt, q.n_jt) : even_grid(q.n_vt, q.n_jt);
+  q.grid = launch_grid(even, q.n_vt, q.n_jt);
   q.dW = dW;
   return q;
 }
@@ -339,7 +339,10 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
   const int dI = (int)p.I, dd = (int)p.d;
   // one tile kind for all chunks: what the large tiles keep between them is not row-major
   const double dw_tiles64 = 3.0 * tiles_of(p.I, p.d, 64), dw_ksteps = (double)((p.C + kBK - 1) / kBK);
+  const int n_it = (int)((p.I + kTile - 1) / kTile), n_dt = (int)((p.d + kTile - 1) / kTile);
+  auto share = [&](bool even) { return 2 * xcd_share(n_it, n_dt, even) + xcd_share(n_dt, n_it, even); };
   const bool small_dw = small_launch_us(dw_tiles64, dw_ksteps) < big_launch_us(3.0 * tiles_of(p.I, p.d, 256), dw_ksteps);
+  const bool even = small_dw || uneven_over_xcds(n_it) || uneven_over_xcds(n_dt) || saves_a_round(share(false), share(true));
 
   // Algorithm 3: loop over the mini-sequences; dX_i lands in its row range, the weight gradients accumulate
   for (int i = 0; i < p.n_chunks; ++i) {
@@ -364,9 +367,9 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
       Scope sc(st, MST_MLP_K_DW);
       const int tile = small_dw ? Tile64::EA : kTile;
       DwProblems ps;
-      ps.p[0] = dw_problem(bufG, dI, Xc, dd, dd, dI, dWg, tile);     // dWg [I][d] (+)= dG^T X
-      ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu, tile);     // dWu [I][d] (+)= dU^T X
-      ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd, tile);    // dWd [d][I] (+)= dO^T A
+      ps.p[0] = dw_problem(bufG, dI, Xc, dd, dd, dI, dWg, tile, even);     // dWg [I][d] (+)= dG^T X
+      ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu, tile, even);     // dWu [I][d] (+)= dU^T X
+      ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd, tile, even);    // dWd [d][I] (+)= dO^T A
       const dim3 grid(ps.p[0].grid + ps.p[1].grid + ps.p[2].grid);
       if (small_dw) {
         if (lone_small(dw_tiles64))
@@ -374,7 +377,6 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
         else
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64>, grid, dim3(Tile64::kThreads), Tile64::kLds, st, ps, rows, acc);
       } else {
-        const bool even = uneven_over_xcds(ps.p[0].n_vt) || uneven_over_xcds(ps.p[2].n_vt);
         const auto kernel = even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
                                  : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
         hipLaunchKernelGGL(kernel, grid, dim3(kThreads), kLdsBytes, st, ps, rows, i + 1 < p.n_chunks ? 1 : 0);

@@ -434,6 +434,8 @@ def test_pair_order_with_every_tile_size_matches_oracle(schedule, S, d, V, M):
     (835, 368, 18219, 1, 1, 1, 8),      # splits of one window: stored, then added by the reduce
     (2295, 528, 22619, 7, 3, 2, 4),     # three row blocks: dW read back, last column tile of 16
     (5772, 712, 3700, 3, 2, 1, 1),      # one window, no split: dH straight to bf16
+    (1165, 296, 12987, 1, 1, 1, 8),     # 51 x 5 dlogits tiles, dealt out evenly to save a round
+    (764, 384, 16575, 1, 1, 1, 8),      # 8 x 3 x 2 dH and 65 x 2 dW tiles, dealt out evenly for their sum
 ])
 def test_automatic_block_shapes_with_split_dh_match_oracle(S, d, V, M, row_blocks, windows, split):
     """The block shapes that only the automatic choice takes (dH's contraction split, every split with running sums of
