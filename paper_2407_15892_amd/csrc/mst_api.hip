@@ -178,15 +178,22 @@ double blocks_us(const Plan* p, int64_t R, int n_rb, int win_tiles, int n_win, i
 }
 
 // Looks for a block shape with one window, or with dH's contraction split, that beats `p`'s choice so far by more than
-// the model is good for.  Not where two rounds of dH tiles fill the chip as it is: the shapes of the long configurations
-// are the ones measured.  A few microseconds of host time: more windows than eight past the first count that leaves one
-// row block only make the windows smaller.
+// the model is good for, and for a block shape chosen so far that the pair order beats.  Not where two rounds of dH tiles
+// fill the chip as it is: the shapes of the long configurations are the ones measured.  A few microseconds of host time:
+// more windows than eight past the first count that leaves one row block only make the windows smaller.
+//
+// The choice so far does not know the 64 x 64 tiles of the pair order, so it has to be able to go back: 712 rows,
+// d = 1920, V = 6637, M = 2: backward 289 us in blocks, 119 in pairs.  kPairsBelow: of 68 shapes timed in both orders,
+// pairs below 0.8 of the blocks' estimate took 0.31 to 0.91 of the time (35 shapes); from 0.8 to 1 it was 0.88 to 1.11
+// (33), either way round.
+constexpr double kPairsBelow = 0.8;
 void choose_split_blocks(Plan* p) {
   const int64_t S = p->S, d = p->d;
   if (p->blk_use && (int64_t)(p->blk_rows / kTile) * p->n_jt >= 2 * kNumCu) return;
   const double pairs = pairs_us(p);
   const double so_far = p->blk_use ? blocks_us(p, p->blk_rows, p->blk_n_rb, p->blk_win_tiles, p->blk_n_win, 1) : pairs;
   double best = 0.95 * std::min(so_far, pairs);
+  double cheapest = p->blk_use ? so_far : 0.0;                             // of all block shapes (0: none fits)
   bool found = false;
   for (int split = 1; split <= kMaxBlockSplit; split *= 2) {
     int one_row_block_from = 0;
@@ -206,6 +213,7 @@ void choose_split_blocks(Plan* p) {
       R = ((S + n_rb - 1) / n_rb + kTile - 1) / kTile * kTile;
       if (R * ldg_w >= (int64_t(1) << 30) || R * d >= (int64_t(1) << 30)) continue;   // 32-bit offsets inside a block
       const double t = blocks_us(p, R, n_rb, win_tiles, n_win, split);
+      if (cheapest == 0.0 || t < cheapest) cheapest = t;
       if (t < best) {
         best = t;
         found = true;
@@ -218,7 +226,9 @@ void choose_split_blocks(Plan* p) {
       }
     }
   }
-  if (found) { p->est_pairs_us = pairs; p->est_blocks_us = best; }
+  if (!found && p->blk_use && pairs < kPairsBelow * so_far) p->blk_use = false;
+  p->est_pairs_us = pairs;
+  p->est_blocks_us = found ? best : p->blk_use ? so_far : cheapest;
 }
 
 int64_t dh_split_room(const Plan* p) { return ((int64_t)p->C * p->ldg * 2) / ((int64_t)p->C * p->d * 4); }

@@ -168,6 +168,30 @@ def test_backward_schedule_choice_and_block_shapes(mst):
         mst.mst_set_bwd_schedule(mst.BWD_SCHEDULE_AUTO)
 
 
+def test_automatic_order_is_not_the_dearer_one_by_the_estimates_it_reports(mst):
+    """Host-only: small heads whose 64 x 64 tiles make the pair order cheaper take it (timed: 0.31 to 0.91 of the block
+    order's time), and over random shapes the order taken is never dearer than the other by more than the margins that
+    the choice states (pairs from 0.8 of the blocks' estimate down; blocks from 0.95 of the pairs' estimate down)."""
+    import random
+    for shape in [(512, 1712, 5504, 2), (712, 1920, 6637, 2), (1472, 1280, 6557, 5), (1021, 1792, 10368, 3), (3837, 248, 919, 35)]:
+        assert mst.mst_bwd_schedule_info(*shape)["schedule"] == mst.BWD_SCHEDULE_PAIRS, shape
+    rng = random.Random(20240716)
+    seen = {mst.BWD_SCHEDULE_PAIRS: 0, mst.BWD_SCHEDULE_BLOCKS_FUSED: 0}
+    for _ in range(3000):
+        S, d, V = round(2 ** rng.uniform(5, 14)), 8 * round(2 ** rng.uniform(4, 9)), round(2 ** rng.uniform(9, 17))
+        M = max(1, min(round(V / d * rng.uniform(0.4, 1.5)), S))
+        if mst.binding.mst_workspace_bytes_status(S, d, V, M) != 0:
+            continue
+        info = mst.mst_bwd_schedule_info(S, d, V, M)
+        pairs, blocks = info["est_pairs_us"], info["est_blocks_us"]
+        seen[info["schedule"]] += 1
+        if info["schedule"] == mst.BWD_SCHEDULE_PAIRS:
+            assert blocks == 0 or 0.95 * pairs <= blocks + 1, (S, d, V, M, info)
+        else:
+            assert 0.8 * blocks <= pairs + 1, (S, d, V, M, info)
+    assert min(seen.values()) > 500, seen
+
+
 def test_block_shapes_fit_and_cover_for_random_shapes(mst):
     """Host-only property test of the block schedule's shapes: whenever one is offered it covers S x V with whole
     tiles, fits the reported workspace bytes together with the fp32 dH sums, and keeps 32-bit offsets in range."""
