@@ -240,18 +240,35 @@ mst_status mst_bwd_schedule_info(int64_t S, int64_t d, int64_t V, int32_t M, int
 mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M, int32_t schedule, int64_t* info);
 
 /*
- * Workgroup -> tile map of the GEMM kernels (host-only test aid; the kernels call the same function).  A launch
- * over an n_slow x n_fast space of 256 x 256 tiles has mst_tile_grid(n_slow, n_fast) workgroups; workgroup b lands
- * on XCD b % 8, which owns a contiguous range of the slow coordinate and walks it in 4 x 8 rectangles of tiles:
- * order 0 (forward, dH, dW kernels) band by band of 4 slow tiles inside super-groups of 32 fast tiles, order 1
- * (dlogits kernel) group by group of 8 fast tiles.  (Backward launches whose slow coordinate would leave more than an
- * eighth of that grid as padding deal the tiles out evenly instead.)  mst_tile_of_workgroup writes the tile of workgroup `workgroup`
- * and returns 1, or returns 0 for a padding workgroup (it exits at once), or -1 for bad arguments.  Every tile is
- * the image of exactly one workgroup.
+ * Workgroup -> tile maps of the GEMM kernels (host-only test aids; the kernels call the same functions).
+ *
+ * mst_tile_of_workgroup: the map of the 256 x 256 tiles whose slow coordinate divides well over the XCDs.  A launch
+ * over an n_slow x n_fast space has mst_tile_grid(n_slow, n_fast) workgroups; workgroup b lands on XCD b % 8, which
+ * owns a contiguous range of the slow coordinate and walks it in 4 x 8 rectangles of tiles: order 0 (forward, dH, dW
+ * kernels) band by band of 4 slow tiles inside super-groups of 32 fast tiles, order 1 (dlogits kernel) group by group
+ * of 8 fast tiles.
+ *
+ * mst_dh_tile_of_workgroup: the map of a block order's dH launch of n_split splits.  even = 0: the rectangles above,
+ * with row tiles as the slow coordinate, split after split.  even = 1: an equal, contiguous share of all tiles for
+ * every XCD, with the column tiles of all splits as the slow coordinate and bands of eight row tiles.  With n_split = 1
+ * the latter is the even map of any launch (slow = n_col_tiles, fast = n_row_tiles): every launch with smaller tiles than
+ * 256 x 256 has it, and backward launches of 256 x 256 tiles whose slow coordinate would leave more than an eighth of
+ * the grid above as padding, or, up to four rounds of workgroups, whose busiest XCD would need a round more with the
+ * rectangles.
+ *
+ * Both write the tile of workgroup `workgroup` and return 1, or return 0 for a padding workgroup (it exits at once), or
+ * -1 for bad arguments.  Every tile is the image of exactly one workgroup.
+ *
+ * mst_tile_info (host, pure): info[0] = rows of the forward's tiles (256 vocabulary entries by 64 or 256 rows),
+ * info[1..3] = edge of the dlogits, dH and dW tiles in the pair order (64 or 256).
  */
 int32_t mst_tile_grid(int32_t n_slow, int32_t n_fast);
 int32_t mst_tile_of_workgroup(int32_t n_slow, int32_t n_fast, int32_t order, int32_t workgroup,
                               int32_t* slow, int32_t* fast);
+int32_t mst_dh_tile_grid(int32_t even, int32_t n_split, int32_t n_row_tiles, int32_t n_col_tiles);
+int32_t mst_dh_tile_of_workgroup(int32_t even, int32_t n_split, int32_t n_row_tiles, int32_t n_col_tiles,
+                                 int32_t workgroup, int32_t* split, int32_t* row_tile, int32_t* col_tile);
+mst_status mst_tile_info(int64_t S, int64_t d, int64_t V, int32_t M, int64_t* info);
 
 /*
  * Matrix-core probe (measurement aid, not part of the path).  Enqueues a kernel in

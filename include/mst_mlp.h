@@ -106,12 +106,39 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
                        void* dX, float* dWg, float* dWu, float* dWd, void* stream);
 
 /*
+ * Which block tiles the launches of a chunk of `rows` rows take (host, pure; a test aid).  All give the same O and dX
+ * bit for bit.  info[0..2] = gate/up (forward and backward), info[3..5] = down, info[6..8] = dA, info[9..11] = dX, each as
+ * {MST_MLP_TILE_* of the launch, or of its end; leading columns (of I, d, I, d) that a launch of 256 x 256 tiles of its
+ * own takes before it, 0 for none; 1 where 256 x 256 tiles are laid out in super-tiles}; info[12..13] = the weight
+ * gradients of a call whose chunks have `rows` rows: {MST_MLP_TILE_256, _64 or _64_LONE; 1 where the tiles are dealt out
+ * evenly over the XCDs}.
+ */
+enum {
+  MST_MLP_TILE_256 = 0,   /* 256 x 256, one workgroup per compute unit                  */
+  MST_MLP_TILE_128,       /* 128 x 128, two                                             */
+  MST_MLP_TILE_128_LONE,  /* 128 x 128, one, software-pipelined                         */
+  MST_MLP_TILE_64,        /* 64 x 64, four                                              */
+  MST_MLP_TILE_64_LONE,   /* 64 x 64, one, software-pipelined                           */
+  MST_MLP_TILE_64_LONG    /* the same with K steps of 128                               */
+};
+mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info);
+
+/*
+ * Workgroup -> tile map of the 256 x 256 launches (host-only test aid; the kernels call the same functions), as
+ * mst_tile_of_workgroup in mst_lmhead.h: whole super-tiles of 8 x 4 tiles per XCD where they divide as well over the
+ * XCDs as single tiles do, an equal share of the tiles for every XCD elsewhere and for all smaller tiles.
+ */
+int32_t mst_mlp_tile_grid(int32_t n_slow, int32_t n_fast);
+int32_t mst_mlp_tile_of_workgroup(int32_t n_slow, int32_t n_fast, int32_t workgroup, int32_t* slow, int32_t* fast);
+
+/*
  * Per-kernel timing (host), as in mst_lmhead.h: mst_mlp_profile_enable(every)
  * brackets every `every`-th launch of each kernel kind of the two calls above
  * with HIP events on the caller's stream (0 = off); collect adds, per kind, the
  * elapsed milliseconds, the number of launches they cover and (if the pointer
  * is not NULL) the number of all launches while timing was on (arrays of
- * length MST_MLP_PROFILE_KINDS) and clears the record.
+ * length MST_MLP_PROFILE_KINDS) and clears the record.  A product that ends in
+ * a second launch of smaller tiles is timed, and counted, as one.
  */
 enum {
   MST_MLP_K_GATEUP = 0,   /* A_i = silu(X_i Wg^T) * (X_i Wu^T)                       */

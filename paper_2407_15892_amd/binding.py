@@ -75,6 +75,17 @@ def load_library() -> ctypes.CDLL:
     lib.mst_bwd_schedule_info_for.restype = c.c_int
     lib.mst_bwd_schedule_info_for.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.c_int32,
                                               c.POINTER(c.c_int64)]
+    i32p = c.POINTER(c.c_int32)
+    lib.mst_tile_grid.restype = c.c_int32
+    lib.mst_tile_grid.argtypes = [c.c_int32, c.c_int32]
+    lib.mst_tile_of_workgroup.restype = c.c_int32
+    lib.mst_tile_of_workgroup.argtypes = [c.c_int32] * 4 + [i32p] * 2
+    lib.mst_dh_tile_grid.restype = c.c_int32
+    lib.mst_dh_tile_grid.argtypes = [c.c_int32] * 4
+    lib.mst_dh_tile_of_workgroup.restype = c.c_int32
+    lib.mst_dh_tile_of_workgroup.argtypes = [c.c_int32] * 5 + [i32p] * 3
+    lib.mst_tile_info.restype = c.c_int
+    lib.mst_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.POINTER(c.c_int64)]
     lib.mst_profile_enable.restype = c.c_int
     lib.mst_profile_enable.argtypes = [c.c_int]
     lib.mst_profile_collect.restype = c.c_int
@@ -194,6 +205,13 @@ def mst_bwd_schedule_info(S: int, d: int, V: int, M: int, schedule: Optional[int
     keys = ("schedule", "rows_per_block", "row_blocks", "vocab_per_window", "windows", "dh_split",
             "est_pairs_us", "est_blocks_us")
     return dict(zip(keys, (int(x) for x in info)))
+
+
+def mst_tile_info(S: int, d: int, V: int, M: int) -> dict:
+    """Rows of the forward's tiles, edges of the pair order's dlogits, dH and dW tiles."""
+    info = (ctypes.c_int64 * 4)()
+    _check(load_library().mst_tile_info(S, d, V, M, info))
+    return dict(zip(("fwd", "dlogits", "dh", "dw"), (int(x) for x in info)))
 
 
 def mst_profile_enable(every) -> None:

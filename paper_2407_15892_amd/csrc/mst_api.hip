@@ -478,6 +478,13 @@ mst_status prepare_device() {
   return MST_OK;
 }
 
+// Few tiles: 64 rows each, as long as every workgroup has a compute unit to itself (same bits).  The groups after the first
+// are not larger.
+bool small_forward(const Plan& p) {
+  const int64_t rows = p.S < p.fwd_group_rows ? p.S : p.fwd_group_rows;
+  return (rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB * p.n_vt <= kNumCu;
+}
+
 // forward pass over all chunks: writes lse (if non-null) and nll (if non-null)
 // `ctl`: its queues serve persistent forward launches (nullptr: one workgroup per tile)
 mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, const int32_t* labels,
@@ -486,10 +493,7 @@ mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, c
   float2* part = reinterpret_cast<float2*>(ws + p.f_part);
   const size_t stride = (size_t)p.fwd_group_rows;
   auto rows_of_group = [&](int64_t g0) { return (p.S - g0) < p.fwd_group_rows ? (p.S - g0) : p.fwd_group_rows; };
-  // Few tiles: 64 rows each, as long as every workgroup has a compute unit to itself (same bits); the groups after the
-  // first are not larger.  Otherwise persistent workgroups where there is more than one round of tiles.
-  auto small_tiles = [&](int64_t rows) { return (rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB * p.n_vt; };
-  const bool small = small_tiles(rows_of_group(0)) <= kNumCu;
+  const bool small = small_forward(p);      // otherwise persistent workgroups where there is more than one round of tiles
   const int64_t tiles_first = (int64_t)xcd_grid_2d(p.n_vt, (int)((rows_of_group(0) + kTile - 1) / kTile));
   int* queue = ctl && !small && tiles_first > kNumCu ? ctl->queue : nullptr;
   int queue_base = 0;
@@ -896,6 +900,36 @@ int32_t mst_tile_of_workgroup(int32_t n_slow, int32_t n_fast, int32_t order, int
 int32_t mst_tile_grid(int32_t n_slow, int32_t n_fast) {
   if (n_slow < 1 || n_fast < 1 || (int64_t)xcd_grid_2d(n_slow, 1) * n_fast > 0x7fffffff) return -1;
   return xcd_grid_2d(n_slow, n_fast);
+}
+
+int32_t mst_dh_tile_grid(int32_t even, int32_t n_split, int32_t n_row_tiles, int32_t n_col_tiles) {
+  if (n_split < 1 || n_row_tiles < 1 || n_col_tiles < 1) return -1;
+  if ((int64_t)n_split * n_col_tiles * (kNumXcd * (((int64_t)n_row_tiles + kNumXcd - 1) / kNumXcd)) > 0x7ffffff0) return -1;
+  return dh_grid_2d(even != 0, n_split, n_row_tiles, n_col_tiles);
+}
+
+int32_t mst_dh_tile_of_workgroup(int32_t even, int32_t n_split, int32_t n_row_tiles, int32_t n_col_tiles, int32_t workgroup,
+                                 int32_t* split, int32_t* row_tile, int32_t* col_tile) {
+  const int32_t grid = mst_dh_tile_grid(even, n_split, n_row_tiles, n_col_tiles);
+  if (grid < 0 || workgroup < 0 || workgroup >= grid || !split || !row_tile || !col_tile) return -1;
+  int sp = 0, st = 0, jt = 0;
+  const bool ok = dh_tile_of_block(even != 0, workgroup, n_split, n_row_tiles, n_col_tiles, &sp, &st, &jt);
+  *split = sp;
+  *row_tile = st;
+  *col_tile = jt;
+  return ok ? 1 : 0;
+}
+
+mst_status mst_tile_info(int64_t S, int64_t d, int64_t V, int32_t M, int64_t* info) {
+  if (!info) return MST_ERR_NULL_POINTER;
+  Plan p;
+  const mst_status s = make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false);
+  if (s != MST_OK) return s;
+  info[0] = small_forward(p) ? TileFwdSmall::EB : kTile;
+  info[1] = p.small_dlogits ? Tile64::EA : kTile;
+  info[2] = p.small_dh ? Tile64::EA : kTile;
+  info[3] = p.small_dw ? Tile64::EA : kTile;
+  return MST_OK;
 }
 
 mst_status mst_profile_enable(int every) {

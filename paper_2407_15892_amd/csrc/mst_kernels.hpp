@@ -626,7 +626,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dlogits(
 constexpr int kDhSplit = 0, kDhFirst = 1, kDhAdd = 2, kDhLast = 3, kDhOnly = 4;
 // Workgroup -> tile map of the modes that are not kDhSplit.  Dealt out evenly, the hidden tiles of all splits are the slow
 // coordinate: every XCD then reads its own part of W (the larger operand) and all of the rows.
-__device__ __forceinline__ bool dh_tile_of_block(bool even, int block, int n_split, int n_st, int n_jt, int* sp, int* st, int* jt) {
+__host__ __device__ inline bool dh_tile_of_block(bool even, int block, int n_split, int n_st, int n_jt, int* sp, int* st, int* jt) {
   if (even) {
     int slow;
     if (!even_tile_of_block(block, n_split * n_jt, n_st, &slow, st)) return false;

@@ -122,7 +122,7 @@ constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident
 // 64 x 64: step of 5003 tokens 1.31 -> 1.23 ms; dA of 4096 tokens, I = 14336 (896 tiles) as 768 large and 512 of
 // 128 x 128: 376 us against 412.  With all compute units busy a K step takes 1.36, with the K-strided weights of dA and
 // dX 1.4 also where some are idle; not split, by this, are the 1376 tiles of gate/up at I = 11008 (2 % slower split).
-enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long };
+enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long };   // MST_MLP_TILE_* of the header, in this order
 struct TileChoice {
   TileKind kind;      // of the whole, or of what follows the first `head` columns
   int64_t head;       // A-side extent, a multiple of 256, that large tiles cover in a launch of its own (0: none)
@@ -152,6 +152,25 @@ TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, bool strided) {
   return rest.kind != kBig && t < whole.us ? TileChoice{rest.kind, cols * kTile, t} : whole;
 }
 
+// the choices of the four products of a chunk of `rows` rows
+int64_t ksteps_of(int64_t k) { return (k + kBK - 1) / kBK; }
+TileChoice gateup_tile(int64_t rows, int64_t d, int64_t I) { return choose_tile(2 * I, rows, ksteps_of(d), false); }
+TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) { return choose_tile(N, rows, ksteps_of(K), false); }
+TileChoice nn_tile(int64_t rows, int64_t N, int64_t K, int terms) { return choose_tile(N, rows, terms * ksteps_of(K), true); }
+
+// The weight gradients have one tile kind for all chunks: what the large tiles keep between them is not row-major.
+struct DwChoice { bool small, lone, even; };
+DwChoice dw_choice(int64_t C, int64_t d, int64_t I) {
+  const double tiles64 = 3.0 * tiles_of(I, d, 64), ksteps = (double)ksteps_of(C);
+  const int n_it = (int)((I + kTile - 1) / kTile), n_dt = (int)((d + kTile - 1) / kTile);
+  auto share = [&](bool even) { return 2 * xcd_share(n_it, n_dt, even) + xcd_share(n_dt, n_it, even); };
+  DwChoice c;
+  c.small = small_launch_us(tiles64, ksteps) < big_launch_us(3.0 * tiles_of(I, d, 256), ksteps);
+  c.lone = lone_small(tiles64);
+  c.even = c.small || uneven_over_xcds(n_it) || uneven_over_xcds(n_dt) || saves_a_round(share(false), share(true));
+  return c;
+}
+
 // A = silu(X Wg^T) * (X Wu^T) of a chunk, or its backward (dA given)
 template <class C, bool kBackward>
 void launch_gateup_small(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int n_i, int ldi,
@@ -163,7 +182,7 @@ void launch_gateup_small(hipStream_t st, const __bf16* X, const __bf16* Wg, cons
 template <bool kBackward>
 void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
                    __bf16* A, __bf16* dAG, __bf16* dU) {
-  const TileChoice c = choose_tile(2 * (int64_t)I, rows, (d + kBK - 1) / kBK, false);
+  const TileChoice c = gateup_tile(rows, d, I);
   const int i0 = (int)(c.head / 2), n_i = I - i0;               // the second launch's indices
   if (c.kind == kBig || i0) {
     const int n_it = ((i0 ? i0 : I) + kGateUpI - 1) / kGateUpI, n_st = (rows + kTile - 1) / kTile;
@@ -193,7 +212,7 @@ void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows,
                      P, K, Q, K, rows, N, K, n_st, n_nt, out, ldo);
 }
 void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
-  const TileChoice c = choose_tile(N, rows, (K + kBK - 1) / kBK, false);
+  const TileChoice c = nt_tile(rows, N, K);
   const int n0 = (int)c.head;
   if (c.kind == kBig || n0) {
     const int n_nt = ((n0 ? n0 : N) + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
@@ -222,7 +241,7 @@ void launch_nn_small(hipStream_t st, const __bf16* P1, const __bf16* Q1, const _
 }
 void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16* P2, const __bf16* Q2,
                int rows, int N, int K, __bf16* out) {
-  const TileChoice c = choose_tile(N, rows, (P2 ? 2 : 1) * (int64_t)((K + kBK - 1) / kBK), true);
+  const TileChoice c = nn_tile(rows, N, K, P2 ? 2 : 1);
   const int n0 = (int)c.head;
   if (c.kind == kBig || n0) {
     const int n = n0 ? n0 : N, n_nt = (n + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
@@ -337,12 +356,7 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
   __bf16* bufU = reinterpret_cast<__bf16*>(ws + p.slot);      // dU
   __bf16* bufA = reinterpret_cast<__bf16*>(ws + 2 * p.slot);  // A
   const int dI = (int)p.I, dd = (int)p.d;
-  // one tile kind for all chunks: what the large tiles keep between them is not row-major
-  const double dw_tiles64 = 3.0 * tiles_of(p.I, p.d, 64), dw_ksteps = (double)((p.C + kBK - 1) / kBK);
-  const int n_it = (int)((p.I + kTile - 1) / kTile), n_dt = (int)((p.d + kTile - 1) / kTile);
-  auto share = [&](bool even) { return 2 * xcd_share(n_it, n_dt, even) + xcd_share(n_dt, n_it, even); };
-  const bool small_dw = small_launch_us(dw_tiles64, dw_ksteps) < big_launch_us(3.0 * tiles_of(p.I, p.d, 256), dw_ksteps);
-  const bool even = small_dw || uneven_over_xcds(n_it) || uneven_over_xcds(n_dt) || saves_a_round(share(false), share(true));
+  const DwChoice dw = dw_choice(p.C, p.d, p.I);
 
   // Algorithm 3: loop over the mini-sequences; dX_i lands in its row range, the weight gradients accumulate
   for (int i = 0; i < p.n_chunks; ++i) {
@@ -365,25 +379,62 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
     }
     {
       Scope sc(st, MST_MLP_K_DW);
-      const int tile = small_dw ? Tile64::EA : kTile;
+      const int tile = dw.small ? Tile64::EA : kTile;
       DwProblems ps;
-      ps.p[0] = dw_problem(bufG, dI, Xc, dd, dd, dI, dWg, tile, even);     // dWg [I][d] (+)= dG^T X
-      ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu, tile, even);     // dWu [I][d] (+)= dU^T X
-      ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd, tile, even);    // dWd [d][I] (+)= dO^T A
+      ps.p[0] = dw_problem(bufG, dI, Xc, dd, dd, dI, dWg, tile, dw.even);     // dWg [I][d] (+)= dG^T X
+      ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu, tile, dw.even);     // dWu [I][d] (+)= dU^T X
+      ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd, tile, dw.even);    // dWd [d][I] (+)= dO^T A
       const dim3 grid(ps.p[0].grid + ps.p[1].grid + ps.p[2].grid);
-      if (small_dw) {
-        if (lone_small(dw_tiles64))
+      if (dw.small) {
+        if (dw.lone)
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64Lone>, grid, dim3(Tile64Lone::kThreads), Tile64Lone::kLds, st, ps, rows, acc);
         else
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64>, grid, dim3(Tile64::kThreads), Tile64::kLds, st, ps, rows, acc);
       } else {
-        const auto kernel = even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
+        const auto kernel = dw.even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
                                  : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
         hipLaunchKernelGGL(kernel, grid, dim3(kThreads), kLdsBytes, st, ps, rows, i + 1 < p.n_chunks ? 1 : 0);
       }
     }
   }
   return check_launch();
+}
+
+mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info) {
+  Plan p;
+  const mst_status s = make_plan(rows, d, I, 1, &p);
+  if (s != MST_OK) return s;
+  if (!info) return MST_ERR_NULL_POINTER;
+  auto put = [&](int at, TileChoice c, int64_t n_a, int per_tile) {   // per_tile: indices of a column of large tiles
+    const int64_t head = c.head / kTile * per_tile, n = head ? head : n_a;
+    info[at] = c.kind;
+    info[at + 1] = head;
+    info[at + 2] = (c.kind == kBig || head) && use_super_tiles((int)((n + per_tile - 1) / per_tile), (int)((rows + kTile - 1) / kTile));
+  };
+  put(0, gateup_tile(rows, d, I), I, kGateUpI);
+  put(3, nt_tile(rows, d, I), d, kTile);
+  put(6, nn_tile(rows, I, d, 1), I, kTile);
+  put(9, nn_tile(rows, d, I, 2), d, kTile);
+  const DwChoice dw = dw_choice(rows, d, I);
+  info[12] = dw.small ? (dw.lone ? k64Lone : k64) : kBig;
+  info[13] = dw.even;
+  return MST_OK;
+}
+
+int32_t mst_mlp_tile_grid(int32_t n_slow, int32_t n_fast) {
+  if (n_slow < 1 || n_fast < 1 || (int64_t)n_slow * n_fast > (1 << 28)) return -1;
+  return mlp_grid(n_slow, n_fast);
+}
+
+int32_t mst_mlp_tile_of_workgroup(int32_t n_slow, int32_t n_fast, int32_t workgroup, int32_t* slow, int32_t* fast) {
+  const int32_t grid = mst_mlp_tile_grid(n_slow, n_fast);
+  if (grid < 0 || workgroup < 0 || workgroup >= grid || !slow || !fast) return -1;
+  int s = 0, f = 0;
+  const bool ok = use_super_tiles(n_slow, n_fast) ? super_tile_of_block(workgroup, n_slow, n_fast, &s, &f)
+                                                  : even_tile_of_block(workgroup, n_slow, n_fast, &s, &f);
+  *slow = s;
+  *fast = f;
+  return ok ? 1 : 0;
 }
 
 mst_status mst_mlp_profile_enable(int every) {

@@ -39,17 +39,20 @@ inline int mlp_grid(int n_slow, int n_fast) {
   if (!use_super_tiles(n_slow, n_fast)) return even_grid(n_slow, n_fast);
   return kNumXcd * ((super_tiles(n_slow, n_fast) + kNumXcd - 1) / kNumXcd) * kSuperSlow * kSuperFast;
 }
-template <bool kSuper>
-__device__ __forceinline__ bool mlp_tile(int n_slow, int n_fast, int* slow, int* fast) {
-  if (!kSuper) return even_tile_of_block(blockIdx.x, n_slow, n_fast, slow, fast);
+__host__ __device__ inline bool super_tile_of_block(unsigned block, int n_slow, int n_fast, int* slow, int* fast) {
   const int ss = (n_slow + kSuperSlow - 1) / kSuperSlow, sf = (n_fast + kSuperFast - 1) / kSuperFast;
-  const int x = blockIdx.x % kNumXcd, q = blockIdx.x / kNumXcd;
+  const int x = block % kNumXcd, q = block / kNumXcd;
   const int super = x + kNumXcd * (q / (kSuperSlow * kSuperFast));
   const int inner = q % (kSuperSlow * kSuperFast);
   if (super >= ss * sf) return false;
   *slow = (super / sf) * kSuperSlow + inner / kSuperFast;
   *fast = (super % sf) * kSuperFast + inner % kSuperFast;
   return *slow < n_slow && *fast < n_fast;
+}
+template <bool kSuper>
+__device__ __forceinline__ bool mlp_tile(int n_slow, int n_fast, int* slow, int* fast) {
+  if (!kSuper) return even_tile_of_block(blockIdx.x, n_slow, n_fast, slow, fast);
+  return super_tile_of_block(blockIdx.x, n_slow, n_fast, slow, fast);
 }
 
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }

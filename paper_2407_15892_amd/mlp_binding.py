@@ -46,6 +46,12 @@ def load_mlp_library() -> ctypes.CDLL:
     lib.mst_mlp_bwd.restype = c.c_int
     lib.mst_mlp_bwd.argtypes = [c.c_void_p] * 5 + [c.c_int64, c.c_int64, c.c_int64, c.c_int32,
                                                    c.c_void_p, c.c_size_t] + [c.c_void_p] * 5
+    lib.mst_mlp_tile_info.restype = c.c_int
+    lib.mst_mlp_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.POINTER(c.c_int64)]
+    lib.mst_mlp_tile_grid.restype = c.c_int32
+    lib.mst_mlp_tile_grid.argtypes = [c.c_int32, c.c_int32]
+    lib.mst_mlp_tile_of_workgroup.restype = c.c_int32
+    lib.mst_mlp_tile_of_workgroup.argtypes = [c.c_int32] * 3 + [c.POINTER(c.c_int32)] * 2
     lib.mst_mlp_profile_enable.restype = c.c_int
     lib.mst_mlp_profile_enable.argtypes = [c.c_int]
     lib.mst_mlp_profile_collect.restype = c.c_int
@@ -99,6 +105,20 @@ def mst_mlp_bwd(X, Wg, Wu, Wd, dO, M: int, workspace, dX, dWg, dWu, dWd, stream=
         _ptr(X), _ptr(Wg), _ptr(Wu), _ptr(Wd), _ptr(dO), S, d, I, M,
         _ptr(workspace), workspace.numel() * workspace.element_size(),
         _ptr(dX), _ptr(dWg), _ptr(dWu), _ptr(dWd), _stream_handle(stream)))
+
+
+MLP_TILES = ("256", "128", "128_lone", "64", "64_lone", "64_long")     # MST_MLP_TILE_*
+
+
+def mst_mlp_tile_info(rows: int, d: int, I: int) -> dict:
+    """What a chunk of `rows` rows runs with: per product (tile, leading columns that large tiles take in a launch of their
+    own, large tiles in super-tiles), and for the weight gradients (tile, dealt out evenly)."""
+    a = (ctypes.c_int64 * 14)()
+    _check(load_mlp_library().mst_mlp_tile_info(rows, d, I, a))
+    out = {name: (MLP_TILES[a[3 * i]], int(a[3 * i + 1]), bool(a[3 * i + 2]))
+           for i, name in enumerate(("gateup", "down", "da", "dx"))}
+    out["dw"] = (MLP_TILES[a[12]], bool(a[13]))
+    return out
 
 
 def mst_mlp_profile_enable(every) -> None:

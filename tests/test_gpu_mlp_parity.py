@@ -162,8 +162,10 @@ def test_repeated_calls_reuse_the_workspace():
         assert np.abs(dX - ref["dX"]).max() <= TOL * np.abs(ref["dX"]).max()
 
 
-@pytest.mark.parametrize("S,d,I,Ms", [
-    # ragged in every dimension; between them the launches of the three chunkings take every block tile: 256 x 256 for
+# (S, d, I, chunkings).  Between them every product takes every tile it can (test_mlp_library_abi.py asks the library which
+# ones these are), alone and behind full rounds of large tiles, at ragged edges.
+TILE_SHAPES = [
+    # ragged in every dimension; between them the launches of the three chunkings take most block tiles: 256 x 256 for
     # gate/up unsplit, 128 x 128, 64 x 64 with the shallow (unsplit) and the deep pipeline (split), last tiles of 4 rows
     (1700, 1160, 4104, (1, 2, 5)),
     # down and dX: 256 x 256 unsplit, 128 x 128 in halves (12 full row tiles, a last column tile of 8); few K steps
@@ -176,12 +178,37 @@ def test_repeated_calls_reuse_the_workspace():
     (195, 520, 4360, (1, 3)),
     # chunks of 129 and 65 rows: one row past a tile of the smaller ones
     (387, 2056, 1032, (3, 6)),
-])
+    # down and dX: lone 128 x 128 unsplit; weight gradients of lone 64 x 64 tiles over three chunks
+    (7709, 488, 328, (1, 3)),
+    # gate/up with K steps of 128, the last one ragged, one and two row tiles
+    (61, 4080, 2040, (1, 2)),
+    (65, 4104, 1032, (1, 2)),
+    # super-tiles of large tiles in down and dX; weight gradients of 64 x 64 tiles in two chunks
+    (7995, 1904, 136, (1, 2)),
+    # gate/up: super-tiles alone; full rounds, then 128 x 128, 64 x 64, lone 128 x 128
+    (3017, 200, 7896, (1, 2)),
+    (1982, 272, 10056, (1, 2)),
+    (4050, 328, 2512, (1, 2)),
+    # the same for dA
+    (7954, 152, 1832, (1, 2, 4)),
+    (6153, 392, 3200, (1, 2, 4)),
+    # the same for down and dX
+    (4555, 4352, 264, (1, 2)),
+    (7993, 4816, 136, (1, 2)),
+    (2612, 7616, 264, (1, 3)),
+    (2971, 6616, 360, (1, 2)),
+]
+
+
+@pytest.mark.parametrize("S,d,I,Ms", TILE_SHAPES)
 def test_every_block_tile_matches_oracle_and_gives_the_same_bits(S, d, I, Ms):
-    """Which block tile a launch takes depends on the rows of a chunk; a token's O and dX must not."""
+    """Which block tile a launch takes depends on the rows of a chunk; a token's O and dX must not.  The weight gradients
+    of every chunking (their sums are formed chunk by chunk) against the oracle."""
     inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, Ms[0], index=320 + S % 7, w_std=0.05))
-    _, base, _, _ = _check(inp, M=Ms[0])
+    _, base, ref, _ = _check(inp, M=Ms[0])
     for M in Ms[1:]:
         _, got, _ = _run_all(inp, M=M)
         for k in ("O", "dX"):
             assert np.array_equal(got[k], base[k]), (k, M)
+        for k in ("dWg", "dWu", "dWd"):
+            assert np.abs(got[k] - ref[k]).max() <= TOL * np.abs(ref[k]).max(), (k, M)

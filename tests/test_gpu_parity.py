@@ -172,6 +172,22 @@ def test_forward_is_bit_identical_for_every_number_of_mini_sequences():
             assert bits[0] == ref[0] and np.array_equal(bits[1], ref[1]) and bits[2] == ref[2], f"M = {M}"
 
 
+def test_forward_tiles_of_either_size_give_the_same_bits():
+    """M decides how many rows a forward launch has, and so whether it takes 256- or 64-row tiles (2048 rows here: 256 for
+    M = 1, 64 for shorter groups; test_library_abi.py asks the library): lse and loss keep their bits."""
+    DeviceRun, _ = _harness()
+    inp = mi.make_inputs(mi.custom_config(2048, 264, 4093, 1, index=441, w_std=0.3, ignore_frac=0.07, label_dist="zipf"))
+    ref_o = orc.lmhead_ce_forward(inp.H_f64(), inp.W_f64(), inp.labels, inp.ignore_index)
+    ref = None
+    for M in (1, 128, 2048):
+        loss, lse, nv = DeviceRun(inp, M=M).forward()
+        bits = (np.float32(loss).view(np.uint32), lse.astype(np.float32).view(np.uint32))
+        if ref is None:
+            ref = bits
+            assert nv == ref_o[3] and abs(loss - ref_o[0]) <= LOSS_RTOL * abs(ref_o[0])
+        assert nv == ref_o[3] and bits[0] == ref[0] and np.array_equal(bits[1], ref[1]), f"M = {M}"
+
+
 def test_dW_and_dH_bit_identical_across_runs():
     DeviceRun, _ = _harness()
     import torch
@@ -454,6 +470,28 @@ def test_automatic_block_shapes_with_split_dh_match_oracle(S, d, V, M, row_block
     assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
     assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
     assert bool((run.last_ws[-4096:] == 0xA5).all()), "wrote past the declared workspace"
+
+
+@pytest.mark.parametrize("S,d,V,M", [
+    (975, 1176, 4099, 3),      # 64 x 64 tiles in dlogits, dH and dW, whose second pass (one chunk) adds
+    (712, 1920, 6637, 2),      # in dlogits and dH only
+])
+def test_automatic_order_that_goes_back_to_pairs_matches_oracle(S, d, V, M):
+    """Shapes for which the automatic choice drops a block shape for the pair order: its gradients against the oracle, and
+    the same bits as the pair order asked for."""
+    import torch
+    import paper_2407_15892_amd as mst
+    assert mst.mst_bwd_schedule_info(S, d, V, M)["schedule"] == mst.BWD_SCHEDULE_PAIRS
+    inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=460 + S % 97, w_std=0.3, ignore_frac=0.1, label_dist="zipf"))
+    run, _, _ = _check_full(inp, grad_loss=0.8)
+    first = (run.dH_t.clone(), run.dW_t.clone())
+    try:
+        mst.mst_set_bwd_schedule(mst.BWD_SCHEDULE_PAIRS)
+        run.backward(grad_loss=0.8)
+    finally:
+        mst.mst_set_bwd_schedule(mst.BWD_SCHEDULE_AUTO)
+    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
+    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
 
 
 @pytest.mark.parametrize("which", ["pairs_one_chunk", "blocks"])

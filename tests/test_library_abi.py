@@ -321,3 +321,59 @@ def test_workgroup_to_tile_map_is_a_bijection(mst):
     assert lib.mst_tile_of_workgroup(4, 4, 0, 10 ** 6, ctypes.byref(s), ctypes.byref(f)) == -1
     assert lib.mst_tile_of_workgroup(4, 4, 2, 0, ctypes.byref(s), ctypes.byref(f)) == -1
     assert lib.mst_tile_grid(0, 4) == -1
+
+
+def test_dh_and_even_tile_maps_are_bijections(mst):
+    """The even map (of every small tile, and of large ones that divide badly over the XCDs) and both maps of a dH launch
+    with splits, called on the host: every tile of every split is the image of exactly one workgroup, and the even map
+    gives every XCD (workgroup id mod 8) the same number of workgroups and a contiguous share."""
+    lib = mst.load_library()
+    sp, st, jt = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+    shapes = [(1, 1, 1), (1, 7, 13), (2, 4, 16), (3, 12, 7), (8, 3, 2), (5, 9, 5), (1, 36, 7), (4, 17, 3), (16, 1, 1), (1, 3, 700)]
+    for n_split, n_st, n_jt in shapes:
+        for even in (0, 1):
+            grid = lib.mst_dh_tile_grid(even, n_split, n_st, n_jt)
+            total = n_split * n_st * n_jt
+            assert grid == (8 * -(-total // 8) if even else n_split * 8 * -(-n_st // 8) * n_jt)
+            seen = {}
+            for b in range(grid):
+                rc = lib.mst_dh_tile_of_workgroup(even, n_split, n_st, n_jt, b, ctypes.byref(sp), ctypes.byref(st), ctypes.byref(jt))
+                assert rc in (0, 1)
+                if rc:
+                    t = (sp.value, st.value, jt.value)
+                    assert 0 <= t[0] < n_split and 0 <= t[1] < n_st and 0 <= t[2] < n_jt and t not in seen, (even, b, t)
+                    seen[t] = b
+            assert len(seen) == total
+            if even:
+                share = -(-total // 8)
+                per_xcd = [sum(b % 8 == x for b in seen.values()) for x in range(8)]
+                assert per_xcd == [max(0, min(share, total - x * share)) for x in range(8)]
+                # an XCD's tiles are a range of the order: all of a band of eight row tiles, column by column
+                order = sorted(seen, key=lambda t: (t[1] // 8, t[0], t[2], t[1]))
+                assert [seen[t] for t in order] == [i % share * 8 + i // share for i in range(total)]
+    assert lib.mst_dh_tile_of_workgroup(1, 1, 4, 4, 16, ctypes.byref(sp), ctypes.byref(st), ctypes.byref(jt)) == -1
+    assert lib.mst_dh_tile_of_workgroup(0, 2, 4, 4, -1, ctypes.byref(sp), ctypes.byref(st), ctypes.byref(jt)) == -1
+    assert lib.mst_dh_tile_of_workgroup(0, 2, 4, 4, 0, None, ctypes.byref(st), ctypes.byref(jt)) == -1
+    assert lib.mst_dh_tile_grid(0, 0, 4, 4) == -1 and lib.mst_dh_tile_grid(1, 1 << 20, 1 << 10, 4) == -1
+
+
+def test_tiles_of_the_gpu_tests_are_the_ones_they_name(mst):
+    """test_gpu_parity.py runs shapes for the sake of the tiles that they take: the library's own answer."""
+    want = {                       # forward, dlogits, dH, dW in the pair order, splits of dH
+        (1200, 520, 20003, 2): (256, 256, 256, 256, 19),
+        (1300, 520, 7003, 3): (256, 64, 64, 64, 4),
+        (650, 1032, 12003, 2): (256, 64, 64, 256, None),
+        (200, 1032, 40001, 1): (256, 256, 64, 256, 16),
+        (257, 2056, 3003, 1): (64, 64, 64, 64, None),
+        (65, 264, 4097, 1): (64, 64, 64, 64, None),
+    }
+    for shape, (fwd, dlogits, dh, dw, split) in want.items():
+        info = mst.mst_tile_info(*shape)
+        assert info == {"fwd": fwd, "dlogits": dlogits, "dh": dh, "dw": dw}, (shape, info)
+        if split:
+            assert mst.mst_bwd_schedule_info(*shape, schedule=mst.BWD_SCHEDULE_PAIRS)["dh_split"] == split
+    # the forward's tile changes with M
+    assert [mst.mst_tile_info(2048, 264, 4093, M)["fwd"] for M in (1, 128, 2048)] == [256, 64, 64]
+    with pytest.raises(mst.MstError):
+        mst.mst_tile_info(0, 264, 4093, 1)
+    assert mst.load_library().mst_tile_info(2048, 264, 4093, 1, None) == -1

@@ -89,3 +89,51 @@ def test_null_workspace_and_alignment_errors_come_before_any_launch(mst):
     assert lib.mst_mlp_bwd(fake, fake, fake, fake, fake, S, d, I, M, fake, b - 1, fake, fake, fake, fake, None) == -4
     assert lib.mst_mlp_bwd(fake, fake, fake, fake, fake, S, d, I, M, fake, b, fake, fake + 2, fake, fake, None) == -5
     assert lib.mst_mlp_bwd(fake, fake, fake, fake, fake, S, d, I, 0, fake, b, fake, fake, fake, fake, None) == -3
+
+
+def test_tile_shapes_of_the_gpu_test_take_every_tile(mst):
+    """The library's own answer to which block tiles the shapes of the GPU test run with: every tile of every product alone,
+    large tiles in both maps, every smaller tile (the rare one with K steps of 128 aside) behind full rounds of large
+    ones, and every tile of the weight gradients in a first and in a later chunk."""
+    from tests.test_gpu_mlp_parity import TILE_SHAPES
+    seen = set()
+    for S, d, I, Ms in TILE_SHAPES:
+        for M in Ms:
+            C = -(-S // M)
+            n = -(-S // C)
+            for rows in {C, S - (n - 1) * C}:
+                info = mst.mst_mlp_tile_info(rows, d, I)
+                for product in ("gateup", "down", "da", "dx"):
+                    tile, head, super_tiles = info[product]
+                    assert 0 <= head < (I if product in ("gateup", "da") else d) and (head == 0 or tile != "256")
+                    seen.add((product, tile, super_tiles if tile == "256" else head > 0))
+            tile, even = mst.mst_mlp_tile_info(C, d, I)["dw"]
+            seen |= {("dw", tile, even, 0), ("dw", tile, even, min(n - 1, 1))}
+    want = {("dw", t, e, c) for t, e in (("256", False), ("256", True), ("64", True), ("64_lone", True)) for c in (0, 1)}
+    for product in ("gateup", "down", "da", "dx"):
+        want |= {(product, "256", False), (product, "256", True), (product, "64_long", False)}
+        want |= {(product, t, tail) for t in ("128", "128_lone", "64", "64_lone") for tail in (False, True)}
+    assert want <= seen, sorted(want - seen)
+
+
+def test_workgroup_to_tile_map_is_a_bijection(mst):
+    """Both maps of the 256 x 256 launches, on the host: every tile is the image of exactly one workgroup."""
+    import ctypes
+    lib = mst.load_mlp_library()
+    s, f = ctypes.c_int32(), ctypes.c_int32()
+    maps = set()
+    for n_slow, n_fast in [(1, 1), (3, 5), (8, 4), (16, 4), (36, 6), (112, 16), (43, 7), (56, 16), (9, 33), (64, 8), (7, 100), (130, 2)]:
+        grid = lib.mst_mlp_tile_grid(n_slow, n_fast)
+        maps.add(grid == 8 * -(-n_slow * n_fast // 8))
+        seen = set()
+        for b in range(grid):
+            rc = lib.mst_mlp_tile_of_workgroup(n_slow, n_fast, b, ctypes.byref(s), ctypes.byref(f))
+            assert rc in (0, 1)
+            if rc:
+                assert 0 <= s.value < n_slow and 0 <= f.value < n_fast and (s.value, f.value) not in seen
+                seen.add((s.value, f.value))
+        assert len(seen) == n_slow * n_fast
+    assert maps == {True, False}                     # padded super-tiles are among them
+    assert lib.mst_mlp_tile_of_workgroup(4, 4, 10 ** 6, ctypes.byref(s), ctypes.byref(f)) == -1
+    assert lib.mst_mlp_tile_of_workgroup(4, 4, 0, None, ctypes.byref(f)) == -1
+    assert lib.mst_mlp_tile_grid(0, 4) == -1
