@@ -370,7 +370,9 @@ def main() -> int:
         marks[i + 1].record(stream)
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
-    kern = mst.mst_profile_collect() if timing else {}      # kind -> (ms of the timed launches, timed launches, all launches)
+    # kind -> (ms of the timed launches, timed launches, all launches); "label_scan" is the clearing of the forward's tile
+    # queues here: the labels are counted by the loss launch
+    kern = mst.mst_profile_collect() if timing else {}
     mst.mst_profile_enable(0)
     per_step = sorted(marks[i].elapsed_time(marks[i + 1]) for i in range(args.steps))
 

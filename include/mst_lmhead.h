@@ -223,16 +223,19 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
  *                            in one launch: their tile spaces then share one partly filled last round of
  *                            workgroups instead of leaving one each (same arithmetic as BLOCKS, bit for bit).
  *   MST_BWD_SCHEDULE_AUTO    (default) PAIRS or BLOCKS_FUSED, whichever a host-side cost model (rounds of
- *                            workgroups plus fp32 gradient traffic) ranks faster for the shape.  It also looks at block
- *                            shapes that the forced orders do not take: a single window, and a window's dH contraction
- *                            in up to 8 splits with running sums of their own, added in fixed order at the end.
+ *                            workgroups plus fp32 gradient traffic) ranks faster for the shape.  Shapes with few
+ *                            dH tiles are then ranked again with a finer model, which changes the order where another
+ *                            one is clearly below it (blocks by 5 %, pairs by 20 %) and also looks at block shapes that
+ *                            the forced orders do not take: a single window, and a window's dH contraction in up to 8
+ *                            splits with running sums of their own, added in fixed order at the end.
  * mst_set_bwd_schedule: host; the override belongs to the CALLING THREAD (thread-local, AUTO in every new
  * thread) and takes effect at that thread's next backward call, so one caller's setting never changes the
  * summation order of another thread's call; MST_ERR_BAD_SHAPE for an unknown value.
  * mst_bwd_schedule_info_for: host, pure (no hidden state); fills info[0..7] = {schedule that would run
  * under the override `schedule`, rows per block, row blocks, vocabulary entries per window, windows, dH
  * split count, cost estimate of PAIRS in us, of the block order that would be chosen in us (0 if no block
- * shape fits)}.  mst_bwd_schedule_info: the same with the calling thread's current override.
+ * shape fits), both from the model that decided}.  mst_bwd_schedule_info: the same with the calling thread's
+ * current override.
  */
 enum { MST_BWD_SCHEDULE_AUTO = 0, MST_BWD_SCHEDULE_PAIRS = 1, MST_BWD_SCHEDULE_BLOCKS = 2, MST_BWD_SCHEDULE_BLOCKS_FUSED = 3 };
 mst_status mst_set_bwd_schedule(int32_t schedule);

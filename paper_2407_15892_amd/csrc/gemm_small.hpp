@@ -3,7 +3,9 @@
 // A workgroup of four waves (2 x 2) owns a (32 TA) x (32 TB) output tile.  Panels, fragments and MFMA order are those of
 // gemm_tile16.hpp and every output is summed over K in the same order as in the 256 x 256 kernels, so results do not
 // depend on the tile a launch was given, bit for bit (a split of K between groups of waves would be up to a quarter
-// faster with 128 to 256 tiles, but its sums would depend on the rows of a chunk, that is on M).
+// faster with 128 to 256 tiles, but its sums would depend on the rows of a chunk, that is on M).  The one exception is
+// the LM-head's dH, whose contraction is split between launches' workgroups in any case: the number of splits is chosen
+// with the tile, and with it the order of the fp32 sums.
 //
 // What bounds it: LDS.  A 128 x 128 tile reads and writes 96 KB of it per K step of 512 MFMA clocks (64 x 64 wave tiles;
 // a 256 x 256 tile: 256 KB per 2048), and moves twice the bytes per flop from L2; a 64 x 64 tile twice as much again.

@@ -179,8 +179,8 @@ double blocks_us(const Plan* p, int64_t R, int n_rb, int win_tiles, int n_win, i
 
 // Looks for a block shape with one window, or with dH's contraction split, that beats `p`'s choice so far by more than
 // the model is good for, and for a block shape chosen so far that the pair order beats.  Not where two rounds of dH tiles
-// fill the chip as it is: the shapes of the long configurations are the ones measured.  A few microseconds of host time:
-// more windows than eight past the first count that leaves one row block only make the windows smaller.
+// fill the chip as it is: the shapes of the long configurations are the ones measured.  1 to 12 us of host time for steps
+// of 80 us to 6 ms: more windows than eight past the first count that leaves one row block only make the windows smaller.
 //
 // The choice so far does not know the 64 x 64 tiles of the pair order, so it has to be able to go back: 712 rows,
 // d = 1920, V = 6637, M = 2: backward 289 us in blocks, 119 in pairs.  kPairsBelow: of 68 shapes timed in both orders,
@@ -234,8 +234,8 @@ void choose_split_blocks(Plan* p) {
 int64_t dh_split_room(const Plan* p) { return ((int64_t)p->C * p->ldg * 2) / ((int64_t)p->C * p->d * 4); }
 
 // Splits of the pair order's dH: among the counts that fit (at most `most`, at most one per K step, partials must fit into
-// the dlogits slot that is free at that moment: dh_split_room) the one with the fullest rounds of workgroups, with a small penalty per
-// split for the fp32 partials it adds.
+// the dlogits slot that is free at that moment: dh_split_room) the one with the fullest rounds
+// of workgroups, with a small penalty per split for the fp32 partials it adds.
 int best_dh_split(const Plan* p, int ksteps, int most) {
   const int out_tiles = p->n_st * p->n_jt;
   const int64_t room = dh_split_room(p);
@@ -588,7 +588,7 @@ const char* mst_strerror(mst_status s) {
     case MST_ERR_BAD_SHAPE: return "bad shape: S, d, V must be positive, d % 8 == 0, d < 2^22, V*d < 2^31, ceil(S/M)*V < 2^30";
     case MST_ERR_BAD_M: return "M must satisfy 1 <= M <= S";
     case MST_ERR_WORKSPACE: return "workspace is NULL or too small (see mst_workspace_bytes)";
-    case MST_ERR_ALIGNMENT: return "pointer alignment: H, W, dH 16 bytes; workspace 256 bytes; lse, dW 4 bytes";
+    case MST_ERR_ALIGNMENT: return "pointer alignment: H, W, dH, dW 16 bytes; workspace 256 bytes; n_valid 8 bytes; labels, lse, loss 4 bytes";
     case MST_ERR_LAUNCH: return "the HIP runtime refused a kernel launch or attribute";
     case MST_ERR_NO_DEVICE: return "no current HIP device, or it is not a whole 256-CU gfx950 chip";
     default: return "unknown status";
@@ -735,10 +735,11 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
                            dim3(even_grid(n_jh * split, n_sh)), dim3(Tile64::kThreads), lone ? Tile64Lone::kLds : Tile64::kLds, st,
                            G, p.ldg, Wb, rows, (int)p.d, (int)p.V, n_sh, n_jh, split, p.small_dh_ksteps, nv, grad_loss,
                            partial, p.C, dHb + r0 * p.d);
-      } else
-      hipLaunchKernelGGL(k_bwd_gemm_dh<false>, dim3(xcd_grid(n_st * p.n_jt * p.dh_split)), dim3(kThreads), kLdsBytes, st,
-                         G, p.ldg, Wb, rows, (int)p.d, (int)p.V, n_st, p.n_jt, p.dh_split, p.dh_ksteps, kDhSplit,
-                         nv, grad_loss, partial, p.C, dHb + r0 * p.d);
+      } else {
+        hipLaunchKernelGGL(k_bwd_gemm_dh<false>, dim3(xcd_grid(n_st * p.n_jt * p.dh_split)), dim3(kThreads), kLdsBytes, st,
+                           G, p.ldg, Wb, rows, (int)p.d, (int)p.V, n_st, p.n_jt, p.dh_split, p.dh_ksteps, kDhSplit,
+                           nv, grad_loss, partial, p.C, dHb + r0 * p.d);
+      }
     }
     if (split > 1) {
       Scope sc(st, MST_K_BWD_DH_REDUCE);

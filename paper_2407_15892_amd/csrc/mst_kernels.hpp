@@ -11,10 +11,10 @@
 //             k_bwd_gemm_dh      dH_chunk = dlogits W       (contraction over V, split, fixed-order reduce)
 //             k_bwd_gemm_dw      dW (+)= dlogits^T H_chunk  (contraction over the chunk's rows)
 //
-// All kernels use the 256 x 256 block tile main loop of gemm_tile.hpp.  The
-// linear workgroup id is remapped so that each of the 8 XCDs (which receive
-// workgroups round-robin and own a private L2) works on a contiguous range of
-// the tile space: workgroups that share an operand panel then share an L2.
+// The kernels of this file use the 256 x 256 block tile main loop of gemm_tile.hpp; small problems take the smaller
+// tiles of mst_small_kernels.hpp.  The linear workgroup id is remapped so that each of the 8 XCDs (which receive
+// workgroups round-robin and own a private L2) works on a contiguous range of the tile space: workgroups that share an
+// operand panel then share an L2.
 #pragma once
 #include "gemm_tile.hpp"
 #include "gemm_tile16.hpp"
@@ -118,8 +118,9 @@ __host__ __device__ inline int xcd_grid_2d(int n_slow, int n_fast) { return kNum
 // more than an eighth of the grid would be padding (34 vocabulary tiles: 5 per XCD, the last one idle; 12 row tiles: two
 // XCDs idle), and in launches of a few rounds where it saves one (36 x 7 tiles of dlogits: 35 on seven XCDs of 32 compute
 // units, 51 us against 31.6; the step of 4731 tokens, d = 896, V = 62794 that has them 2.83 -> 2.16 ms, its dH and dW
-// tiles, whose shares add up to 36 against 32, included).  Which one is a template argument of the kernels, not a branch in them: the scalar registers that
-// the second map kept alive cost the long launches of the whole-rectangle shapes half a percent.
+// tiles, whose shares add up to 36 against 32, included).  Which one is a template argument of the kernels, not a branch
+// in them: the scalar registers that the second map kept alive cost the long launches of the whole-rectangle shapes half
+// a percent.
 inline int xcd_share(int n_slow, int n_fast, bool even) {       // tiles of the XCD that has most
   return even ? (n_slow * n_fast + kNumXcd - 1) / kNumXcd : (n_slow + kNumXcd - 1) / kNumXcd * n_fast;
 }

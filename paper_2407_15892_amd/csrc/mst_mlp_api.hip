@@ -108,7 +108,7 @@ constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident
 // d = 256 to 4096, I = 896 to 14336; they only have to rank the tiles, and every tile gives the same bits:
 //   256 x 256      1.25 per K step (1.4 with K-strided weights) + 7 (first loads, epilogue), in whole rounds of kNumCu
 //   128 x 128      1.0 per K step + 4 for two workgroups on a compute unit; further rounds overlap.  3000 tokens,
-//                  d = 768, I = 2304: gate/up 26 us against 39
+//                  d = 768, I = 2304: dA 17 us (432 tiles) against 26 (108 of 256)
 //   128 x 128 lone 0.55 per K step + 3.2, up to kNumCu tiles.  1024 tokens, d = 4096, I = 14336: down 140 us (256 tiles)
 //                  against 308 (64 tiles of 256), dX 266 against 607
 //   64 x 64        0.45 (few workgroups on a compute unit) to 0.85 (four) per K step + 2.5.  1536 tokens, d = 1536,

@@ -10,10 +10,10 @@
 //   backward  k_mlp_gemm_nn        dA = dO_chunk Wd
 //             k_mlp_gateup<true>   gate and up tiles again; dG = dA U silu'(G), dU = dA silu(G), A
 //             k_mlp_gemm_nn        dX_chunk = dG Wg + dU Wu   (two contractions into one accumulator)
-//             k_bwd_gemm_dw        dWg += dG^T X, dWu += dU^T X, dWd += dO^T A   (the LM-head's kernel)
+//             k_mlp_dw3            dWg += dG^T X, dWu += dU^T X, dWd += dO^T A   (the LM-head's dW tile body)
 //
-// All kernels use the 256 x 256 block tile main loop of gemm_tile.hpp and the XCD-aware workgroup
-// remapping of mst_kernels.hpp.
+// These use the 256 x 256 block tile main loop of gemm_tile.hpp; their namesakes ending in _small do the same with the
+// smaller tiles of gemm_small.hpp.  Workgroups are mapped to tiles XCD by XCD.
 #pragma once
 #include "mst_small_kernels.hpp"
 
@@ -242,8 +242,9 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
 
 // ---------------------------------------------------------------------------
 // The same three GEMMs with the smaller tiles of gemm_small.hpp, for chunks whose 256 x 256 tiles would leave most of
-// the chip idle (the rule and the measurements are at choose_tile in mst_mlp_api.hip); every output has the same bits.  A side = i or n (32 TA of them per workgroup; gate/up: 16 TA indices, gate and up rows interleaved per
-// wave as above), B side = 32 TB tokens.  The permuted A rows give a lane 4 TA consecutive n (2 TA consecutive i), which
+// the chip idle (the rule and the measurements are at choose_tile in mst_mlp_api.hip); every output has the same bits.
+// A side = i or n (32 TA of them per workgroup; gate/up: 16 TA indices, gate and up rows interleaved per wave as above),
+// B side = 32 TB tokens.  The permuted A rows give a lane 4 TA consecutive n (2 TA consecutive i), which
 // leave the accumulators as 16-byte (8-byte) stores straight to memory: the four lane quarters complete a 128-byte line.
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;

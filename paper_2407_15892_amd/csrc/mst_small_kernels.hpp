@@ -2,10 +2,10 @@
 // problems whose 256 x 256 tiles would occupy a fraction of the chip: small hidden sizes or vocabularies, short
 // mini-sequences.  What bounds the launches they replace is the time of a single tile -- the latency of its first loads,
 // a few K steps, an epilogue of thousands of instructions per wave -- while most compute units have none.
-// Measured per launch, us, 256 x 256 tiles -> these: 512 rows, d = 256, V = 4096: forward 11.9 -> 6.8; 128 of the rows:
-// dlogits 11.7 -> 4.5, dH with its reduce 15.9 -> 8.7, dW of 256 rows 11.9 -> 4.5.  300 rows, d = 512, V = 8000: forward
-// 15.9 -> 9.4, dlogits 16.1 -> 8.1, dH 23.3 -> 13.2, dW 13.2 -> 9.5.  256 rows, d = 1024, V = 50257 (197 tiles of 256 in
-// dlogits): 33.6 -> 47, so not there.
+// Measured per launch under a kernel trace, us, 256 x 256 tiles -> these: 512 rows, d = 256, V = 4096: forward 16.9 -> 8.0;
+// 128 of the rows: dlogits 12.8 -> 5.3, dH with its reduce 18.4 -> 10.0, dW of 256 rows 10.3 (14.5 where it adds) -> 5.3.
+// 300 rows, d = 512, V = 8000: forward 22.4 -> 12.1, dlogits 18.2 -> 11.4, dH 29.3 -> 15.0, dW 14.7 -> 10.7.  256 rows,
+// d = 1024, V = 50257 (197 tiles of 256 in dlogits): 33.6 -> 47 in a loop of launches, so not there.
 #pragma once
 #include "mst_kernels.hpp"
 
