@@ -216,14 +216,17 @@ def main_mlp(args) -> int:
     tflops = f_exec / (ms_per_step * 1e-3) / 1e12
     roofline, kernels = None, {}
     if kern:
+        units = dict(MLP_FLOP_UNITS)
+        if not kern["dx"][2]:          # served by the launch of the weight gradients
+            units["dw"] += units.pop("dx")
         for k, (ms, n, issued) in kern.items():
             if n:
-                fl = MLP_FLOP_UNITS[k] * S * d * I / (issued / args.steps)
+                fl = units[k] * S * d * I / (issued / args.steps)
                 kernels[k] = {"launches": issued, "timed_launches": n, "avg_ms": ms / n,
                               "total_ms_per_step": ms / n * issued / args.steps, "tflops": fl / (ms / n * 1e-3) / 1e12}
         dom = max(MLP_KINDS, key=lambda k: kernels.get(k, {}).get("total_ms_per_step", 0.0))
         ms, n, issued = kern[dom]
-        fl = MLP_FLOP_UNITS[dom] * S * d * I / (issued / args.steps)
+        fl = units[dom] * S * d * I / (issued / args.steps)
         achieved = fl / (ms / n * 1e-3) / 1e12
         roofline = {"bound": "mfma", "kernel": dom, "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
                     "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,

@@ -63,12 +63,15 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void* p) {
 // memory phase (global->LDS loads of later stages + all fragment reads of the current stage) and a compute
 // phase (all MFMAs of the stage), one workgroup barrier per phase, group 1 running one phase behind group 0.
 //
-// LDS holds NSA = 3 stages of the A panel and NSB = 2 of the B panel (3 * 32 KB + 2 * 32 KB = all 160 KB
+// For the 256 x 256 tile LDS holds NSA = 3 stages of the A panel and NSB = 2 of the B panel (3 * 32 KB + 2 * 32 KB = all 160 KB
 // of a CU for the 256 x 256 tile).  In the memory phase of step kt a wave issues its B loads for step kt + 1
 // and then its A loads for step kt + 2; the wait that opens step kt + 1 (vmcnt(SPW of A)) lets the A loads
 // of step kt + 2 stay in flight.  So the A operand, which is the one every kernel streams from HBM or the
 // memory-side cache, has two K steps to arrive and the B operand one; with two stages each (one K step for
 // both) the matrix pipe was busy 75 % of the clocks, with loads that are never waited for 98 %.
+// A tile that leaves room for a third B stage (128 x 256: 3 * 16 KB + 3 * 32 KB) loads both operands two steps ahead: its
+// phases are half as long, and with the B loads of one step waited for in the next a K step took 1.1 us (they need 1150 to
+// 1500 clocks to land), with three stages 0.8.
 // Loads are always issued, also past the end of K: there they are out of range and write zeros into a stage
 // nobody reads.
 struct NoHook { __device__ __forceinline__ void operator()() const {} };
@@ -79,13 +82,14 @@ template <class C, class PA, class PB, class Hook = NoHook>
 __device__ __forceinline__ void gemm_mainloop_pp(typename C::Acc (&acc)[C::TA][C::TB], const PA& pa, const PB& pb,
                                                  char* smem, int k_begin, int k_end, int group,
                                                  Hook after_issue = Hook()) {
-  static_assert(C::NSA == 3 && C::NSB == 2, "three A stages, two B stages");
-  constexpr int kAhead = PA::SPW;              // loads of one A stage per wave: allowed in flight at a wait
+  static_assert(C::NSA == 3 && (C::NSB == 2 || C::NSB == 3), "three A stages, two or three B stages");
+  constexpr int kAhead = PA::SPW + (C::NSB == 3 ? PB::SPW : 0);   // loads allowed in flight at a wait
   const uint32_t ldsA = lds_addr_of(smem), ldsB = ldsA + C::NSA * C::kPanelA;
   const char* smemB = smem + C::NSA * C::kPanelA;
   const int nk = (k_end - k_begin + C::BK - 1) / C::BK;
   pa.issue(ldsA, k_begin);
   pb.issue(ldsB, k_begin);
+  if constexpr (C::NSB == 3) pb.issue(ldsB + C::kPanelB, k_begin + C::BK);
   pa.issue(ldsA + C::kPanelA, k_begin + C::BK);
   after_issue();
   wait_vmcnt<kAhead>();
@@ -95,7 +99,7 @@ __device__ __forceinline__ void gemm_mainloop_pp(typename C::Acc (&acc)[C::TA][C
   for (int kt = 0; kt < nk; ++kt) {
     // ---- memory phase
     int na = ca + C::NSA - 1; if (na >= C::NSA) na -= C::NSA;
-    const int nb = cb ^ 1;
+    const int nb = C::NSB == 2 ? cb ^ 1 : na;
     const char* a_panel = smem + ca * C::kPanelA;
     const char* b_panel = smemB + cb * C::kPanelB;
     bf16x8 a[C::kKK][C::TA], b[C::kKK][C::TB];
@@ -108,7 +112,7 @@ __device__ __forceinline__ void gemm_mainloop_pp(typename C::Acc (&acc)[C::TA][C
       constexpr int kLoads = PB::SPW + PA::SPW, kFrags = C::kKK * (C::TA + C::TB);
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) {
-        if (j < PB::SPW) pb.issue_one(j, ldsB + nb * C::kPanelB, k_begin + (kt + 1) * C::BK);
+        if (j < PB::SPW) pb.issue_one(j, ldsB + nb * C::kPanelB, k_begin + (kt + C::NSB - 1) * C::BK);
         else pa.issue_one(j - PB::SPW, ldsA + na * C::kPanelA, k_begin + (kt + 2) * C::BK);
 #pragma unroll
         for (int f = j * kFrags / kLoads; f < (j + 1) * kFrags / kLoads; ++f) {
@@ -143,7 +147,7 @@ __device__ __forceinline__ void gemm_mainloop_pp(typename C::Acc (&acc)[C::TA][C
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     ca = ca + 1 == C::NSA ? 0 : ca + 1;
-    cb ^= 1;
+    cb = C::NSB == 2 ? cb ^ 1 : ca;
   }
   if (group == 0) __builtin_amdgcn_s_barrier();
   wait_vmcnt<0>();

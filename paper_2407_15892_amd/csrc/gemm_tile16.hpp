@@ -21,13 +21,14 @@ namespace mst {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-template <int WA_, int WB_, int TA_, int TB_, int BK_, int NS_>
+// NSA and NSB LDS stages of the two panels
+template <int WA_, int WB_, int TA_, int TB_, int BK_, int NSA_, int NSB_>
 struct Cfg16 {
-  static constexpr int WA = WA_, WB = WB_, TA = TA_, TB = TB_, BK = BK_, NS = NS_;
+  static constexpr int WA = WA_, WB = WB_, TA = TA_, TB = TB_, BK = BK_;
   static constexpr int kWaves = WA * WB, kThreads = 64 * kWaves;
   static constexpr int EA = 16 * TA * WA, EB = 16 * TB * WB;
   static constexpr int kPanelA = EA * BK * 2, kPanelB = EB * BK * 2;
-  static constexpr int NSA = NS + 1, NSB = NS;
+  static constexpr int NSA = NSA_, NSB = NSB_;
   static constexpr int kLds = NSA * kPanelA + NSB * kPanelB;
   static constexpr int kKK = BK / 32;            // MFMA k sub-steps per stage
   typedef f32x4 Acc;                             // accumulator of one 16 x 16 MFMA tile

@@ -6,6 +6,7 @@
 // per-kernel event timing.
 #include "../../include/mst_lmhead.h"
 #include "host_util.hpp"
+#include "launch_model.hpp"
 #include "mst_small_kernels.hpp"
 
 #include <algorithm>
@@ -16,7 +17,6 @@ namespace {
 
 using namespace mst;
 
-constexpr int kNumCu = 256;          // MI355X compute units; only steers the schedule choices (splits, blocks)
 constexpr int kMaxDhSplit = 64;
 constexpr int kMaxWindows = 64;      // most vocabulary windows the block schedule considers
 constexpr int kMaxBlockSplit = 8;    // most splits of a window's dH contraction
@@ -87,46 +87,10 @@ double rounds_us(int64_t tiles, int64_t k) {
 // order with its read-modify-write of dW per pair used to be taken: S = 1024, d = 4096, V = 128256, M = 4: step 4.6 ms,
 // with two splits and four windows 3.4 ms.
 //
-// The model, in microseconds, fitted to launches of the 8B-shaped configurations at S = 200 to 32768.  A 256 x 256 tile
-// takes 1.375 per K step with all compute units busy (the chip is power limited then), 1.25 otherwise, plus what its ends
-// take: dlogits 6; dH sums 8, and 8 more where they are read; dW 12 plus 0.1 per K step up to 20, and 10 more where it
-// is read.  A launch takes whole rounds of kNumCu tiles at the faster rate, all its tiles at the slower one, or its
-// bytes at 4.6 TB/s, whichever is longest, plus 2.  dH + dW: the dH tiles first, the dW tiles as compute units come
-// free; bound by bytes it takes a third longer than the bytes alone (dH's loads wait behind dW's stores: 200 rows,
-// V = 128256: 930 for the 3.3 GB that take 740 in two launches).
-constexpr double kBusyStepUs = 1.375, kStepUs = 1.25, kHbmBytesPerUs = 4.6e6;
-struct TileCost {
-  double ksteps, ends;
-  double busy() const { return kBusyStepUs * ksteps + ends; }
-  double alone() const { return kStepUs * ksteps + ends; }
-};
-TileCost tile_cost(int64_t k, double ends) { return {(double)((k + kBK - 1) / kBK), ends}; }
+// The model is that of launch_model.hpp, with a tile's ends, in microseconds: dlogits 6; dH sums 8, and 8 more where they
+// are read; dW as there.
 TileCost dlogits_cost(int64_t d) { return tile_cost(d, 6.0); }
 TileCost dh_cost(int64_t k, bool add) { return tile_cost(k, add ? 16.0 : 8.0); }
-TileCost dw_cost(int64_t rows, bool add) {
-  TileCost c = tile_cost(rows, 0.0);
-  c.ends = 12.0 + (c.ksteps < 80.0 ? 0.1 * c.ksteps : 8.0) + (add ? 10.0 : 0.0);
-  return c;
-}
-double launch_us(int64_t tiles, TileCost c, double bytes) {
-  const double rounds = (double)((tiles + kNumCu - 1) / kNumCu) * c.alone(), busy = (double)tiles / kNumCu * c.busy();
-  return 2.0 + std::max(std::max(rounds, busy), bytes / kHbmBytesPerUs);
-}
-// n1 tiles of c1, then n2 of c2, handed out in this order: n1 % kNumCu units are late for the second kind by one tile of
-// the first, and the others take tiles of it meanwhile.  The end is that of the n2-th tile: a multiple of t2 after the
-// moment `a` when the others are free, or after the late ones are.
-double launch_us(int64_t n1, TileCost c1, int64_t n2, TileCost c2, double bytes) {
-  const double t1 = c1.alone(), t2 = c2.alone(), a = (double)(n1 / kNumCu) * t1;
-  const int64_t late = n1 % kNumCu, others = kNumCu - late;
-  const int64_t f = late ? (int64_t)(t1 / t2) : 0, c = late ? f + 1 : 0;    // whole tiles before the late ones' first, + 1
-  auto up = [](int64_t n, int64_t by) { return n > 0 ? (n + by - 1) / by : 0; };
-  const int64_t j = up(n2, others);
-  const double with_others = (double)(j <= c ? j : up(n2 + late * c, kNumCu)) * t2;
-  const double with_late = t1 + (double)up(n2 - others * f, kNumCu) * t2;
-  const double span = a + (late ? std::max(t1, std::min(with_others, with_late)) : with_others);
-  const double busy = ((double)n1 * c1.busy() + (double)n2 * c2.busy()) / kNumCu;
-  return 2.0 + std::max(std::max(span, busy), 1.3 * bytes / kHbmBytesPerUs);
-}
 
 double pairs_us(const Plan* p) {
   const int64_t S = p->S, d = p->d, V = p->V, C = p->C;

@@ -26,7 +26,9 @@ namespace mst {
 // v_mfma_f32_16x16x32_bf16 per wave (on random operands this power-limited chip sustains more flop/s with it than
 // with v_mfma_f32_32x32x16_bf16, whose only advantage -- 128-byte instead of 64-byte row pieces in fp32 epilogues --
 // went away when the fp32 intermediates moved to accumulator order)
-typedef Cfg16<2, 4, 8, 4, 64, 2> Tile16;
+typedef Cfg16<2, 4, 8, 4, 64, 3, 2> Tile16;
+// half of it on the A side, with three stages of both panels: tiles that share a launch with others and would be its end
+typedef Cfg16<2, 4, 4, 4, 64, 3, 3> Tile16Half;
 constexpr int kTA16 = Tile16::TA, kTB16 = Tile16::TB;
 constexpr int kTile = 256;             // Tile16::EA == Tile16::EB
 constexpr int kBK = Tile16::BK;

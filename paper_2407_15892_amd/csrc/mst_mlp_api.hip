@@ -4,6 +4,7 @@
 // carving, launches, and the optional per-kernel event timing.
 #include "../../include/mst_mlp.h"
 #include "host_util.hpp"
+#include "launch_model.hpp"
 #include "mst_mlp_kernels.hpp"
 
 #include <cmath>
@@ -55,6 +56,14 @@ void set_small_attributes(Set set) {
   set((const void*)k_mlp_gemm_nn_small<C>);
 }
 
+template <class T, class Set>
+void set_dx_dw3_attributes(Set set) {
+  set((const void*)k_mlp_dx_dw3<false, false, T>);
+  set((const void*)k_mlp_dx_dw3<true, false, T>);
+  set((const void*)k_mlp_dx_dw3<false, true, T>);
+  set((const void*)k_mlp_dx_dw3<true, true, T>);
+}
+
 mst_host::PerDeviceOnce g_attr_once;
 bool set_kernel_attributes() {   // on the current device
   bool ok = true;
@@ -80,6 +89,8 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_mlp_dw3<true, false>);
   set((const void*)k_mlp_dw3<false, true>);
   set((const void*)k_mlp_dw3<true, true>);
+  set_dx_dw3_attributes<Tile16>(set);
+  set_dx_dw3_attributes<Tile16Half>(set);
   return ok;
 }
 
@@ -100,8 +111,6 @@ int rows_of(const Plan& p, int i) {
   return (int)((p.S - r0) < p.C ? (p.S - r0) : p.C);
 }
 
-
-constexpr int kNumCu = 256;   // MI355X compute units; one workgroup is resident per CU
 
 // Which block tile a GEMM of n_a x n_b outputs (A side: weights, B side: tokens) and `ksteps` K steps of 64 runs with.
 // The figures are microseconds fitted to launches of the three kinds (gate/up, down, dA/dX) at 64 to 3000 tokens,
@@ -169,6 +178,36 @@ DwChoice dw_choice(int64_t C, int64_t d, int64_t I) {
   c.lone = lone_small(tiles64);
   c.even = c.small || uneven_over_xcds(n_it) || uneven_over_xcds(n_dt) || saves_a_round(share(false), share(true));
   return c;
+}
+
+// Whether dX shares the launch of the chunk's weight gradients (large tiles only), and with which tile (MST_MLP_DX_* of the
+// header).  A K step of a half tile takes 0.8 us, 0.9 with all compute units busy; K-strided weights as at choose_whole.
+// Over twenty shapes of 200 to 4096 rows, d = 1024 to 4096, one and two chunks, both ways timed: the backward call took
+// 0.87 to 1.01 of its time with two launches, 0.96 in the mean, and nowhere was the other tile more than 1.5 % faster.
+// kShared: a shared launch must be this much cheaper (what is left alone, 4096 rows, d = 4096: both take the same).
+constexpr double kShared = 0.98;
+enum DxKind { kDxOwn, kDxWhole, kDxHalf };
+DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwChoice& dw) {
+  if (dw.small) return kDxOwn;
+  auto tiles = [&](int64_t a, int64_t b, int64_t e) { return (a + e - 1) / e * ((b + kTile - 1) / kTile); };
+  const int64_t n_dw = 2 * tiles(I, d, kTile) + tiles(d, I, kTile);
+  const TileCost c = dw_cost(rows, accumulate);
+  const double bytes = (accumulate ? 24.0 : 12.0) * (double)(I * d), ksteps = 2.0 * (double)ksteps_of(I);
+  const double own = kShared * (nn_tile(rows, d, I, 2).us + 2.0 + launch_us(n_dw, c, bytes));
+  const double whole = launch_us(tiles(d, rows, kTile), TileCost{ksteps, 7.0, 1.4, 1.5}, n_dw, c, bytes);
+  const double half = launch_us(tiles(d, rows, Tile16Half::EA), TileCost{ksteps, 7.0, 0.8, 0.9}, n_dw, c, bytes);
+  if (whole > own && half > own) return kDxOwn;
+  return half < whole ? kDxHalf : kDxWhole;
+}
+template <class T>
+void launch_dx_dw3(hipStream_t st, DxProblem x, const DwProblems& ps, int rows, bool even, bool accumulate, int more) {
+  x.n_jt = (x.d + T::EA - 1) / T::EA;
+  x.n_st = (rows + T::EB - 1) / T::EB;
+  x.grid = even_grid(x.n_jt, x.n_st);
+  const auto kernel = even ? (accumulate ? k_mlp_dx_dw3<false, true, T> : k_mlp_dx_dw3<true, true, T>)
+                           : (accumulate ? k_mlp_dx_dw3<false, false, T> : k_mlp_dx_dw3<true, false, T>);
+  hipLaunchKernelGGL(kernel, dim3(x.grid + ps.p[0].grid + ps.p[1].grid + ps.p[2].grid), dim3(kThreads), kLdsBytes, st,
+                     x, ps, rows, more);
 }
 
 // A = silu(X Wg^T) * (X Wu^T) of a chunk, or its backward (dA given)
@@ -373,7 +412,8 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
       Scope sc(st, MST_MLP_K_GATEUP_BWD);
       launch_gateup<true>(st, Xc, Wgb, Wub, rows, dd, dI, bufA, bufG, bufU);
     }
-    {
+    const DxKind dx = choose_dx(rows, p.d, p.I, acc != 0, dw);
+    if (dx == kDxOwn) {
       Scope sc(st, MST_MLP_K_DX);
       launch_nn(st, bufG, Wgb, bufU, Wub, rows, dd, dI, dXb + r0 * p.d);
     }
@@ -390,6 +430,12 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64Lone>, grid, dim3(Tile64Lone::kThreads), Tile64Lone::kLds, st, ps, rows, acc);
         else
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64>, grid, dim3(Tile64::kThreads), Tile64::kLds, st, ps, rows, acc);
+      } else if (dx != kDxOwn) {
+        DxProblem x = {};
+        x.dG = bufG; x.Wg = Wgb; x.dU = bufU; x.Wu = Wub;
+        x.d = dd; x.I = dI; x.dX = dXb + r0 * p.d;
+        const auto launch = dx == kDxHalf ? launch_dx_dw3<Tile16Half> : launch_dx_dw3<Tile16>;
+        launch(st, x, ps, rows, dw.even, acc != 0, i + 1 < p.n_chunks ? 1 : 0);
       } else {
         const auto kernel = dw.even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
                                  : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
@@ -419,6 +465,12 @@ mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info) 
   info[12] = dw.small ? (dw.lone ? k64Lone : k64) : kBig;
   info[13] = dw.even;
   return MST_OK;
+}
+
+int32_t mst_mlp_dx_tile(int64_t rows, int64_t d, int64_t I, int32_t first) {
+  Plan p;
+  if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
+  return choose_dx(rows, d, I, !first, dw_choice(rows, d, I));
 }
 
 int32_t mst_mlp_tile_grid(int32_t n_slow, int32_t n_fast) {

@@ -11,6 +11,7 @@
 //             k_mlp_gateup<true>   gate and up tiles again; dG = dA U silu'(G), dU = dA silu(G), A
 //             k_mlp_gemm_nn        dX_chunk = dG Wg + dU Wu   (two contractions into one accumulator)
 //             k_mlp_dw3            dWg += dG^T X, dWu += dU^T X, dWd += dO^T A   (the LM-head's dW tile body)
+//             k_mlp_dx_dw3         the last two from one launch
 //
 // These use the 256 x 256 block tile main loop of gemm_tile.hpp; their namesakes ending in _small do the same with the
 // smaller tiles of gemm_small.hpp.  Workgroups are mapped to tiles XCD by XCD.
@@ -148,14 +149,13 @@ template <class T>
 __device__ __forceinline__ void store_rows_bf16(const f32x4 (&acc)[T::TA][T::TB], __bf16* __restrict__ out, int ldo,
                                                 int rows, int N, int s0, int n0, int wa, int wb, int wave, int lane,
                                                 char* smem) {
-  static_assert(T::TA == 8 && T::EA == 256, "one 128-wide permuted block per wave row, two wave rows");
   constexpr int kStageRow = T::EA * 2 + 16;
 #pragma unroll
   for (int u = 0; u < T::TB; ++u) {
     const int row = wb * (16 * T::TB) + 16 * u + (lane & 15);
-    char* srow = smem + row * kStageRow + (wa * 128 + 32 * (lane >> 4)) * 2;
+    char* srow = smem + row * kStageRow + (wa * (16 * T::TA) + 4 * T::TA * (lane >> 4)) * 2;
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {                    // tiles 2p and 2p + 1: n = nb + 8p .. + 7
+    for (int p = 0; p < T::TA / 2; ++p) {            // tiles 2p and 2p + 1: n = nb + 8p .. + 7
       bf16x8 o;
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] = (__bf16)acc[2 * p + (e >> 2)][u][e & 3];
@@ -163,12 +163,13 @@ __device__ __forceinline__ void store_rows_bf16(const f32x4 (&acc)[T::TA][T::TB]
     }
   }
   __syncthreads();
-  const int col = (lane & 31) * 8;                   // 8 entries = 16 bytes per lane, 32 lanes per row
+  constexpr int kLanesPerRow = T::EA / 8, kRowsPerStore = 64 / kLanesPerRow;
+  const int col = (lane % kLanesPerRow) * 8;         // 8 entries = 16 bytes per lane
   const bool col_ok = n0 + col < N;                  // N % 8 == 0
   constexpr int kRowsPerWave = T::EB / T::kWaves;
 #pragma unroll
-  for (int i = 0; i < kRowsPerWave / 2; ++i) {
-    const int row = kRowsPerWave * wave + 2 * i + (lane >> 5);
+  for (int i = 0; i < kRowsPerWave / kRowsPerStore; ++i) {
+    const int row = kRowsPerWave * wave + kRowsPerStore * i + lane / kLanesPerRow;
     if (s0 + row < rows && col_ok)
       *reinterpret_cast<bf16x8*>(out + (size_t)(s0 + row) * ldo + n0 + col) =
           *reinterpret_cast<const bf16x8*>(smem + row * kStageRow + col * 2);
@@ -207,15 +208,11 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nt(
 //   A side = n (columns of Q, read transposed with the row permutation, so a lane holds 32 consecutive n
 //   and stores 64 bytes), B side = s (rows of P).
 // ---------------------------------------------------------------------------
-template <bool kSuper>
-__global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
+template <class T>
+__device__ __forceinline__ void nn_tile(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
-    int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  typedef Tile16 T;
-  int nt, st;
-  if (!mlp_tile<kSuper>(n_nt, n_st, &nt, &st)) return;
+    int ldp, int ldq, int rows, int N, int K, int nt, int st, __bf16* __restrict__ out, int ldo, char* smem) {
   const int n0 = nt * T::EA, s0 = st * T::EB;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -238,6 +235,16 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
     gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, K, wa);
   }
   store_rows_bf16<T>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
+}
+template <bool kSuper>
+__global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
+    const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
+    const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
+    int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  int nt, st;
+  if (!mlp_tile<kSuper>(n_nt, n_st, &nt, &st)) return;
+  nn_tile<Tile16>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, nt, st, out, ldo, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -393,16 +400,45 @@ struct DwProblem {
   float* dW;                     // [V][d]
 };
 struct DwProblems { DwProblem p[3]; };
-template <bool kStoreOnly, bool kEven>   // the first chunk only stores; later chunks add to the stored sums; `more`: another chunk follows
-__global__ __launch_bounds__(kThreads) void k_mlp_dw3(DwProblems ps, int rows, int more) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  int b = blockIdx.x, which = 0;
+// kStoreOnly: the first chunk only stores; later chunks add to the stored sums; `more`: another chunk follows
+template <bool kStoreOnly, bool kEven>
+__device__ __forceinline__ void dw3_tile(int b, const DwProblems& ps, int rows, int more, char* smem) {
+  int which = 0;
   if (b >= ps.p[0].grid) { b -= ps.p[0].grid; which = 1; if (b >= ps.p[1].grid) { b -= ps.p[1].grid; which = 2; } }
   const DwProblem& q = ps.p[which];
   int vt, jt;
   // 8 x 4 rectangles walked group by group of 4 fast tiles (measured 0.7 % faster here than the LM-head's 4 x 8 bands)
   if (!launch_tile<8, 4, 4>(kEven, b, q.n_vt, q.n_jt, &vt, &jt)) return;
   dw_tile(q.G, q.ldg, q.ldg, q.H, q.ldh, rows, q.d, q.V, vt, jt, kStoreOnly ? 0 : 1, more, 1.0f, q.dW, q.d, smem);
+}
+template <bool kStoreOnly, bool kEven>
+__global__ __launch_bounds__(kThreads) void k_mlp_dw3(DwProblems ps, int rows, int more) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  dw3_tile<kStoreOnly, kEven>(blockIdx.x, ps, rows, more, smem);
+}
+
+// dX = dG Wg + dU Wu and the weight gradients of a chunk from one launch: neither needs the other.  On its own dX is a
+// single, partly filled round of long tiles (its contraction is 2 I), or of smaller, slower ones that fill the chip; here
+// its large tiles occupy some compute units while the others work through the short tiles of the weight gradients, whose
+// stores then also overlap with MFMAs.  First dx.grid workgroups: dX, the longer ones, dealt out evenly over the XCDs.
+// T: 256 x 256, or half of that on the A side (hidden index) where whole tiles would be the end of the launch.
+// Both launches -> one, us: 1024 rows, d = 4096, I = 14336: 638 -> 570 (half tiles); 2048 rows of it 1050 -> 940 (whole);
+// 1668 rows, d = 1544, I = 5384: 206 -> 170 (half).
+struct DxProblem {
+  const __bf16 *dG, *Wg, *dU, *Wu;   // [rows][I], [I][d]
+  int d, I, n_st, n_jt, grid;        // grid: workgroups of this problem, a multiple of the XCD count
+  __bf16* dX;                        // [rows][d]
+};
+template <bool kStoreOnly, bool kEven, class T>
+__global__ __launch_bounds__(kThreads) void k_mlp_dx_dw3(DxProblem x, DwProblems ps, int rows, int more) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if ((int)blockIdx.x < x.grid) {
+    int jt, st;
+    if (!even_tile_of_block(blockIdx.x, x.n_jt, x.n_st, &jt, &st)) return;
+    nn_tile<T>(x.dG, x.Wg, x.dU, x.Wu, x.I, x.d, rows, x.d, x.I, jt, st, x.dX, x.d, smem);
+    return;
+  }
+  dw3_tile<kStoreOnly, kEven>((int)blockIdx.x - x.grid, ps, rows, more, smem);
 }
 
 // the same with 64 x 64 tiles, for problems too small to occupy the chip with large ones (mst_small_kernels.hpp)

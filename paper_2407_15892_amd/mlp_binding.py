@@ -48,6 +48,8 @@ def load_mlp_library() -> ctypes.CDLL:
                                                    c.c_void_p, c.c_size_t] + [c.c_void_p] * 5
     lib.mst_mlp_tile_info.restype = c.c_int
     lib.mst_mlp_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.POINTER(c.c_int64)]
+    lib.mst_mlp_dx_tile.restype = c.c_int32
+    lib.mst_mlp_dx_tile.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_mlp_tile_grid.restype = c.c_int32
     lib.mst_mlp_tile_grid.argtypes = [c.c_int32, c.c_int32]
     lib.mst_mlp_tile_of_workgroup.restype = c.c_int32
@@ -119,6 +121,14 @@ def mst_mlp_tile_info(rows: int, d: int, I: int) -> dict:
            for i, name in enumerate(("gateup", "down", "da", "dx"))}
     out["dw"] = (MLP_TILES[a[12]], bool(a[13]))
     return out
+
+
+MLP_DX_TILES = ("own", "256", "128")     # MST_MLP_DX_*
+
+
+def mst_mlp_dx_tile(rows: int, d: int, I: int, first: bool) -> str:
+    """How dX of a chunk is computed: in a launch of its own, or by that of the weight gradients with this tile."""
+    return MLP_DX_TILES[load_mlp_library().mst_mlp_dx_tile(rows, d, I, int(first))]
 
 
 def mst_mlp_profile_enable(every) -> None:

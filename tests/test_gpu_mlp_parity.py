@@ -212,3 +212,29 @@ def test_every_block_tile_matches_oracle_and_gives_the_same_bits(S, d, I, Ms):
             assert np.array_equal(got[k], base[k]), (k, M)
         for k in ("dWg", "dWu", "dWd"):
             assert np.abs(got[k] - ref[k]).max() <= TOL * np.abs(ref[k]).max(), (k, M)
+
+
+# (S, d, I, {M: how dX of each chunk is computed}): in a launch of its own, or by that of the weight gradients with 256 x 256
+# or 128 x 256 tiles; these over tiles dealt out evenly (the first, third and last shape) and in rectangles
+DX_SHAPES = [
+    (797, 2080, 1008, {1: ["128"], 2: ["128", "128"], 3: ["own"] * 3}),
+    (1661, 1864, 1848, {1: ["own"], 2: ["128", "128"]}),
+    (2713, 2264, 808, {1: ["256"], 2: ["128", "256"], 3: ["own"] * 3}),
+    (4061, 2000, 1896, {2: ["256", "256"], 3: ["own"] * 3}),
+    (2697, 6360, 224, {1: ["own"]}),
+]
+
+
+@pytest.mark.parametrize("S,d,I,kinds", DX_SHAPES)
+def test_dx_beside_the_weight_gradients_matches_oracle_and_keeps_its_bits(S, d, I, kinds):
+    MlpDeviceRun, _ = _harness()
+    import paper_2407_15892_amd as mst
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=330 + S % 7, w_std=0.05))
+    base = None
+    for M, want in kinds.items():
+        C = -(-S // M)
+        rows = [min(C, S - i * C) for i in range(M)]
+        assert [mst.mst_mlp_dx_tile(r, d, I, i == 0) for i, r in enumerate(rows)] == want
+        _, got, _, _ = _check(inp, M=M)
+        base = got["dX"] if base is None else base
+        assert np.array_equal(got["dX"], base), M      # a token's dX does not depend on who computed it
