@@ -263,8 +263,21 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
  * -1 for bad arguments.  Every tile is the image of exactly one workgroup.
  *
  * mst_tile_info (host, pure): info[0] = rows of the forward's tiles (256 vocabulary entries by 64 or 256 rows),
- * info[1..3] = edge of the dlogits, dH and dW tiles in the pair order (64 or 256).
+ * info[1..3] = edge of the dlogits, dH and dW tiles in the pair order where each has launches of its own (64 or 256).
+ *
+ * mst_pair_launches (host, pure): how the pair order launches the three products, -1 for bad arguments.  The joint forms
+ * are for problems whose tiles are all 64 x 64: the dlogits of a pair of mini-sequences from one launch, its dH and dW from
+ * another, dH in tiles whose contraction is split between the four waves of a workgroup; or, for a single mini-sequence,
+ * in the 64 x 64 tiles and the splits that it has in a launch of its own.
  */
+enum {
+  MST_PAIR_SEPARATE = 0,
+  MST_PAIR_KSPLIT_32X16,      /* dH tiles of 32 hidden indices by 16 rows */
+  MST_PAIR_KSPLIT_64X16,
+  MST_PAIR_KSPLIT_64X32,
+  MST_PAIR_SPLIT              /* one mini-sequence: split partials        */
+};
+int32_t mst_pair_launches(int64_t S, int64_t d, int64_t V, int32_t M);
 int32_t mst_tile_grid(int32_t n_slow, int32_t n_fast);
 int32_t mst_tile_of_workgroup(int32_t n_slow, int32_t n_fast, int32_t order, int32_t workgroup,
                               int32_t* slow, int32_t* fast);

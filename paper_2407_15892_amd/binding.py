@@ -86,6 +86,8 @@ def load_library() -> ctypes.CDLL:
     lib.mst_dh_tile_of_workgroup.argtypes = [c.c_int32] * 5 + [i32p] * 3
     lib.mst_tile_info.restype = c.c_int
     lib.mst_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.POINTER(c.c_int64)]
+    lib.mst_pair_launches.restype = c.c_int32
+    lib.mst_pair_launches.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_profile_enable.restype = c.c_int
     lib.mst_profile_enable.argtypes = [c.c_int]
     lib.mst_profile_collect.restype = c.c_int
@@ -212,6 +214,14 @@ def mst_tile_info(S: int, d: int, V: int, M: int) -> dict:
     info = (ctypes.c_int64 * 4)()
     _check(load_library().mst_tile_info(S, d, V, M, info))
     return dict(zip(("fwd", "dlogits", "dh", "dw"), (int(x) for x in info)))
+
+
+PAIR_LAUNCHES = ("separate", "32x16", "64x16", "64x32", "split")     # MST_PAIR_*
+
+
+def mst_pair_launches(S: int, d: int, V: int, M: int) -> str:
+    """How the pair order launches dH and dW: separately, or jointly with dH tiles of that kind."""
+    return PAIR_LAUNCHES[load_library().mst_pair_launches(S, d, V, M)]
 
 
 def mst_profile_enable(every) -> None:

@@ -179,6 +179,74 @@ __device__ __forceinline__ void gemm_mainloop_small(f32x4 (&acc)[C::TA][C::TB], 
   else gemm_mainloop_shared<C>(acc, pa, pb, smem, k_begin, k_end);
 }
 
+// One wave's share of a contraction, for tiles whose K is split between the four waves of a workgroup: wave w takes the
+// K steps (of 32) w, w + 4, w + 8, ...  Every wave has LDS stages of its own and waits for nobody.
+//
+// In step s the fragments of step s are in registers; the stage they came from is loaded anew with step s + NS, those of
+// step s + 1 are read between the MFMAs, and the steps s + 2 .. s + NS are in flight.
+template <int TA_, int TB_, int NS_>
+struct CfgKSplit {
+  static constexpr int TA = TA_, TB = TB_, BK = 32, NS = NS_;
+  static constexpr int kWaves = 1, kSplit = 4, kThreads = 64 * kSplit;      // kWaves: of a panel's loaders
+  static constexpr int EA = 16 * TA, EB = 16 * TB;
+  static constexpr int kPanelA = EA * BK * 2, kPanelB = EB * BK * 2;
+  static constexpr int kLds = kSplit * NS * (kPanelA + kPanelB);
+  static constexpr int kKK = 1;
+  typedef f32x4 Acc;
+};
+template <class C, class PA, class PB>
+__device__ __forceinline__ void gemm_mainloop_ksplit(f32x4 (&acc)[C::TA][C::TB], const PA& pa, const PB& pb, char* smem,
+                                                     int wave, int k) {
+  constexpr int NS = C::NS, kLoads = PA::SPW + PB::SPW, kStride = C::kSplit * C::BK;
+  const int n_step = (k + kStride - 1) / kStride;
+  char* const mine = smem + wave * NS * (C::kPanelA + C::kPanelB);
+  const uint32_t lds = lds_addr_of(mine);
+  auto issue = [&](int slot, int s) {
+    const uint32_t at = lds + slot * (C::kPanelA + C::kPanelB);
+    const int k0 = s * kStride + wave * C::BK;
+    pb.issue(at + C::kPanelA, k0);
+    pa.issue(at, k0);
+  };
+  bf16x8 a0[C::TA], b0[C::TB], a1[C::TA], b1[C::TB];
+  auto read = [&](int slot, bf16x8 (&a)[C::TA], bf16x8 (&b)[C::TB]) {
+    const char* at = mine + slot * (C::kPanelA + C::kPanelB);
+#pragma unroll
+    for (int u = 0; u < C::TB; ++u) b[u] = pb.frag(at + C::kPanelA, u, 0);
+#pragma unroll
+    for (int t = 0; t < C::TA; ++t) a[t] = pa.frag(at, t, 0);
+  };
+#pragma unroll
+  for (int j = 0; j < NS; ++j) issue(j, j);
+  wait_vmcnt<(NS - 1) * kLoads>();
+  read(0, a0, b0);
+  int slot = 0;
+  auto step = [&](int s, bf16x8 (&a)[C::TA], bf16x8 (&b)[C::TB], bf16x8 (&an)[C::TA], bf16x8 (&bn)[C::TB]) {
+    const int next = slot + 1 == NS ? 0 : slot + 1;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // this step's fragments are out of their stage
+    issue(slot, s + NS);
+    wait_vmcnt<(NS - 1) * kLoads>();
+    read(next, an, bn);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < C::TA; ++t)
+#pragma unroll
+      for (int uu = 0; uu < C::TB; ++uu) {
+        const int u = (t & 1) ? C::TB - 1 - uu : uu;
+        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[u], acc[t][u], 0, 0, 0);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    slot = next;
+  };
+  int s = 0;
+  for (; s + 2 <= n_step; s += 2) {
+    step(s, a0, b0, a1, b1);
+    step(s + 1, a1, b1, a0, b0);
+  }
+  if (s < n_step) step(s, a0, b0, a1, b1);
+  wait_vmcnt<0>();
+  __syncthreads();
+}
+
 // Workgroup -> tile map: every XCD gets an equal, contiguous share of the tiles, ordered in bands of eight fast tiles, so
 // that the 32 workgroups resident on an XCD form a 4 x 8 rectangle (or, with fewer fast tiles, a taller one).
 __host__ __device__ inline bool even_tile_of_block(int block, int n_slow, int n_fast, int* slow, int* fast) {

@@ -52,7 +52,7 @@ struct PanelKC16 {
   static constexpr int NSLOT = EXT / RPS;
   static constexpr int SPW = NSLOT / C::kWaves;
   static_assert(NSLOT % C::kWaves == 0, "slots must divide over waves");
-  static_assert(BK == 64 || BK == 128, "row swizzles below are the ones for 128- and 256-byte rows");
+  static_assert(BK == 32 || BK == 64 || BK == 128, "row swizzles below are the ones for 64-, 128- and 256-byte rows");
   static_assert(!kPermute || EXT % (16 * TILES) == 0, "the permutation works on the blocks of 16 TILES rows of a wave");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t voff[SPW];
@@ -63,7 +63,9 @@ struct PanelKC16 {
   // XOR swizzle of the 16-byte chunk index.  ds_read_b128 serves 16 lanes (256 bytes, all 64 banks) per clock;
   // the 16 lanes of a quarter wave read 16 consecutive rows at one logical chunk, so the chunk index is XORed
   // with the row bits that do not already select a bank (none of them does with 256-byte rows).
-  __device__ __forceinline__ static int swz(int row) { return BK == 128 ? row & 15 : (row >> 1) & 7; }
+  __device__ __forceinline__ static int swz(int row) {
+    return BK == 128 ? row & 15 : BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3;
+  }
 
   // `row_of(lrow)`: source row, relative to `base`, that LDS row lrow of the panel holds; rows >= rows_valid read zeros
   template <class RowOf>
@@ -122,7 +124,8 @@ struct PanelKS16 {
   static constexpr int SPW = NSLOT / C::kWaves;
   static_assert(NSLOT % C::kWaves == 0, "slots must divide over waves");
   static_assert(!kPermute || EXT % (16 * TILES) == 0, "the permutation works on the blocks of 16 TILES indices of a wave");
-  static_assert(EXT == 64 || EXT == 128 || EXT == 256, "the swizzles below are for these row lengths");
+  static_assert(EXT == 16 || EXT == 32 || EXT == 64 || EXT == 128 || EXT == 256, "the swizzles below are for these row lengths");
+  static_assert(EXT > 32 || !kPermute, "rows of 64 bytes are read in memory order");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t voff[SPW];
   uint32_t ok_mask, ld_bytes, slot0;
@@ -134,9 +137,12 @@ struct PanelKS16 {
   // The two lane quarters that are served in one clock read k rows 8 apart: in memory order bit 3 of the k row
   // moves them to the other 128-byte half of the 256-byte bank window.  (With the permutation both quarters
   // need the same 8-byte half of all 16 chunks of the window, which no 16-byte swizzle can separate.)
+  // EXT = 32: four k rows fill the bank window, of which a quarter wave reads one half of each.
   // EXT = 64: a k row is half the bank window, so the row's bit 0 selects a half already.  Smaller TILES bring the
   // permuted pieces closer together (4 TILES indices apart): the rows then differ in the chunk bits these leave free.
   __device__ __forceinline__ static uint32_t swz(uint32_t krow) {
+    if (EXT == 16) return 0;
+    if (EXT == 32) return 2 * ((krow >> 3) & 1);
     if (EXT == 64) return kPermute ? 4 * ((krow >> 1) & 1) : (2 * ((krow >> 1) & 1)) ^ (4 * ((krow >> 3) & 1));
     if (EXT == 128 && kPermute) return (krow & 1) ^ (8 * ((krow >> 1) & 1));
     return kPermute ? (krow & 3) : (2 * (krow & 3)) ^ (8 * ((krow >> 3) & 1));

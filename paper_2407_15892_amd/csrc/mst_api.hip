@@ -43,6 +43,8 @@ struct Plan {
   // pair order: 64 x 64 tiles instead of 256 x 256 ones, per launch kind (mst_small_kernels.hpp)
   bool small_dlogits, small_dh, small_dw;
   int small_dh_split, small_dh_ksteps;
+  int joint;        // pair order: dH and dW from one launch, dlogits of a pair from another (MST_PAIR_* of the header)
+  double joint_us;
   // forward workspace (byte offsets)
   size_t f_nll, f_tgt, f_part, f_total;
   // backward workspace: two dlogits slots of one chunk each (bf16), contiguous
@@ -117,6 +119,44 @@ double pairs_us(const Plan* p) {
   return t;
 }
 
+// Joint launches of the pair order, for problems whose launches all take 64 x 64 tiles.  Microseconds, fitted to launches of
+// 64 to 2400 rows, d = 256 to 2112, V = 2012 to 23326: dlogits of the pair as one launch; dH + dW the longer of one dH
+// workgroup by itself (5, and a time per 128 vocabulary entries by its tile) and the dH loads (16 TB/s; 64-byte pieces cost
+// half as much again) on top of the time of dW.  A call of one chunk can keep the split partials of dH instead: its separate
+// launches less 2.
+// kJoint: of 104 shapes timed in every form none takes longer than with separate launches (0.82 of that in the mean), and
+// the form taken is 0.5 % behind the fastest one in the mean, 8 % at most.
+constexpr double kJoint = 0.95;
+struct JointTile { int j, rows, piece; double step; };
+constexpr JointTile kJointTiles[] = {{TileKSplit32x16::EA, TileKSplit32x16::EB, 48, 0.22},
+                                     {TileKSplit64x16::EA, TileKSplit64x16::EB, 64, 0.27},
+                                     {TileKSplit64x32::EA, TileKSplit64x32::EB, 64, 0.40}};
+double ksplit_us(const Plan* p, const JointTile& t, int64_t rows) {
+  const int64_t n = (rows + t.rows - 1) / t.rows * ((p->d + t.j - 1) / t.j);
+  const double loads = (double)n * (t.piece + t.rows) * 2.0 * (double)p->V / 16.0e6;
+  const double dw = small_launch_us(std::max(257.0, tiles_of(p->V, p->d, 64)), (double)((rows + kBK - 1) / kBK));
+  return 1.0 + small_launch_us(tiles_of(rows, p->V, 64), (double)((p->d + kBK - 1) / kBK)) +
+         std::max(5.0 + t.step * (double)((p->V + 127) / 128), loads + dw);
+}
+void choose_joint(Plan* p) {
+  p->joint = 0;
+  if (!p->small_dlogits || !p->small_dh || !p->small_dw) return;
+  p->joint_us = pairs_us(p);
+  if (p->n_chunks == 1) {
+    p->joint = MST_PAIR_SPLIT;
+    p->joint_us -= 2.0;
+  }
+  double best = kJoint * p->joint_us;
+  for (int k = 0; k < 3; ++k) {
+    double t = 0.0;
+    for (int64_t r0 = 0; r0 < p->S; r0 += 2 * (int64_t)p->C)
+      t += ksplit_us(p, kJointTiles[k], std::min(2 * (int64_t)p->C, p->S - r0));
+    if (t >= best) continue;
+    p->joint = MST_PAIR_KSPLIT_32X16 + k;
+    p->joint_us = best = t;
+  }
+}
+
 double blocks_us(const Plan* p, int64_t R, int n_rb, int win_tiles, int n_win, int split) {
   const int64_t S = p->S, d = p->d, V = p->V, win = (int64_t)win_tiles * kTile;
   auto block = [&](int64_t rows, int64_t cols, bool dw_add, bool dh_add) {
@@ -154,7 +194,7 @@ constexpr double kPairsBelow = 0.8;
 void choose_split_blocks(Plan* p) {
   const int64_t S = p->S, d = p->d;
   if (p->blk_use && (int64_t)(p->blk_rows / kTile) * p->n_jt >= 2 * kNumCu) return;
-  const double pairs = pairs_us(p);
+  const double pairs = p->joint ? p->joint_us : pairs_us(p);
   const double so_far = p->blk_use ? blocks_us(p, p->blk_rows, p->blk_n_rb, p->blk_win_tiles, p->blk_n_win, 1) : pairs;
   double best = 0.95 * std::min(so_far, pairs);
   double cheapest = p->blk_use ? so_far : 0.0;                             // of all block shapes (0: none fits)
@@ -216,6 +256,7 @@ int best_dh_split(const Plan* p, int ksteps, int most) {
 }
 
 void choose_schedule(Plan* p, int forced) {
+  choose_joint(p);
   const int64_t S = p->S, d = p->d, V = p->V, C = p->C;
   const int n_vt = p->n_vt, n_jt = p->n_jt;
   // pairs (the estimate is calibrated for at most 16 splits of dH)
@@ -405,6 +446,10 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_bwd_gemm_dh_small<Tile64Lone>);
   set((const void*)k_bwd_gemm_dw_small<Tile64>);
   set((const void*)k_bwd_gemm_dw_small<Tile64Lone>);
+  set((const void*)k_bwd_gemm_dh_dw_small<TileKSplit32x16, Tile64>);
+  set((const void*)k_bwd_gemm_dh_dw_small<TileKSplit64x16, Tile64>);
+  set((const void*)k_bwd_gemm_dh_dw_small<TileKSplit64x32, Tile64>);
+  set((const void*)k_bwd_gemm_dh_split_dw_small<Tile64>);
   set((const void*)k_bwd_gemm_dlogits<false>);
   set((const void*)k_bwd_gemm_dlogits<true>);
   set((const void*)k_bwd_gemm_dh<false>);
@@ -494,6 +539,17 @@ mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, c
     }
   }
   return check_launch();
+}
+
+// dH and dW of the rows whose dlogits are at G, one launch of small tiles
+template <class CH>
+void launch_ksplit(hipStream_t st, const Plan& p, const __bf16* G, const __bf16* W, const __bf16* H, int rows, int accumulate,
+                   int last, const long long* n_valid, float grad_loss, __bf16* dH, float* dW) {
+  const int n_sh = (rows + CH::EB - 1) / CH::EB, n_jh = (int)((p.d + CH::EA - 1) / CH::EA), dh_grid = even_grid(n_jh, n_sh);
+  const int n_vh = (int)((p.V + Tile64::EB - 1) / Tile64::EB), n_jw = (int)((p.d + Tile64::EA - 1) / Tile64::EA);
+  hipLaunchKernelGGL((k_bwd_gemm_dh_dw_small<CH, Tile64>), dim3(dh_grid + even_grid(n_vh, n_jw)), dim3(Tile64::kThreads),
+                     CH::kLds > Tile64::kLds ? CH::kLds : Tile64::kLds, st, G, p.ldg, W, H, rows, (int)p.d, (int)p.V,
+                     n_sh, n_jh, dh_grid, n_vh, n_jw, accumulate, last, n_valid, grad_loss, dH, dW);
 }
 
 mst_status check_forward_alignment(const void* H, const void* W, const int32_t* labels, const float* loss,
@@ -668,9 +724,9 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
   __bf16* dHb = static_cast<__bf16*>(dH);
 
   auto rows_of = [&](int i) { const int64_t r0 = (int64_t)i * p.C; return (int)((p.S - r0) < p.C ? (p.S - r0) : p.C); };
-  auto dlogits = [&](int i, __bf16* G) {
+  auto dlogits = [&](int i, int rows, __bf16* G) {        // of `rows` rows from chunk i on
     const int64_t r0 = (int64_t)i * p.C;
-    const int rows = rows_of(i), n_st = (rows + kTile - 1) / kTile;
+    const int n_st = (rows + kTile - 1) / kTile;
     Scope sc(st, MST_K_BWD_GEMM_DLOGITS);
     if (p.small_dlogits) {
       const int n_vh = (int)((p.V + Tile64::EA - 1) / Tile64::EA), n_sh = (rows + Tile64::EB - 1) / Tile64::EB;
@@ -684,6 +740,12 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     hipLaunchKernelGGL(dlogits_kernel(even), dim3(launch_grid(even, p.n_vt, n_st)), dim3(kThreads), kLdsBytes, st,
                        Hb + r0 * p.d, Wb, labels + r0, lse + r0, rows, (int)p.d, (int)p.V, 0, (int)p.V, ignore_index,
                        n_st, p.n_vt, G, p.ldg);
+  };
+  auto dh_reduce = [&](int i, int rows, const void* partial, int split) {
+    Scope sc(st, MST_K_BWD_DH_REDUCE);
+    const size_t n = (size_t)rows * p.d;
+    hipLaunchKernelGGL(k_bwd_dh_reduce, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st,
+                       static_cast<const float*>(partial), split, (size_t)p.C * p.d, n, nv, grad_loss, dHb + (int64_t)i * p.C * p.d);
   };
   auto grad_h = [&](int i, const __bf16* G, void* partial_space) {
     const int64_t r0 = (int64_t)i * p.C;
@@ -705,12 +767,7 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
                            nv, grad_loss, partial, p.C, dHb + r0 * p.d);
       }
     }
-    if (split > 1) {
-      Scope sc(st, MST_K_BWD_DH_REDUCE);
-      const size_t n = (size_t)rows * p.d;
-      hipLaunchKernelGGL(k_bwd_dh_reduce, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st,
-                         partial, split, (size_t)p.C * p.d, n, nv, grad_loss, dHb + r0 * p.d);
-    }
+    if (split > 1) dh_reduce(i, rows, partial, split);
   };
   auto grad_w = [&](int i_first, int i_last, int rows) {
     const int64_t r0 = (int64_t)i_first * p.C;
@@ -807,12 +864,39 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
   // Algorithm 4's loop over mini-sequences, two at a time: the chunk pair (A, B) shares one dW pass.
   //   dlogits(A) -> slot 0 | dH(A), partials in slot 1 | dlogits(B) -> slot 1 | dW += [G_A; G_B]^T [H_A; H_B]
   //   | dH(B), partials in slot 0
+  if (p.joint == MST_PAIR_SPLIT) {
+    const int rows = (int)p.S, split = p.small_dh_split;
+    const int n_vh = (int)((p.V + Tile64::EB - 1) / Tile64::EB), n_jh = (int)((p.d + Tile64::EA - 1) / Tile64::EA);
+    const int n_sh = (rows + Tile64::EB - 1) / Tile64::EB, dh_grid = even_grid(n_jh * split, n_sh);
+    dlogits(0, rows, slot[0]);
+    {
+      Scope sc(st, MST_K_BWD_GEMM_DH_DW);
+      hipLaunchKernelGGL(k_bwd_gemm_dh_split_dw_small<Tile64>, dim3(dh_grid + even_grid(n_vh, n_jh)), dim3(Tile64::kThreads),
+                         Tile64::kLds, st, slot[0], p.ldg, Wb, Hb, rows, (int)p.d, (int)p.V, n_sh, n_jh, split, p.small_dh_ksteps,
+                         dh_grid, n_vh, nv, grad_loss, reinterpret_cast<float*>(slot[1]), dHb, dW);
+    }
+    if (split > 1) dh_reduce(0, rows, slot[1], split);
+    return check_launch();
+  }
+  if (p.joint) {
+    // the two slots are contiguous: the pair's dlogits are one matrix
+    for (int ia = 0; ia < p.n_chunks; ia += 2) {
+      const int64_t r0 = (int64_t)ia * p.C;
+      const int rows = (int)std::min(2 * (int64_t)p.C, p.S - r0);
+      dlogits(ia, rows, slot[0]);
+      Scope sc(st, MST_K_BWD_GEMM_DH_DW);
+      const auto launch = p.joint == MST_PAIR_KSPLIT_32X16 ? launch_ksplit<TileKSplit32x16>
+                        : p.joint == MST_PAIR_KSPLIT_64X16 ? launch_ksplit<TileKSplit64x16> : launch_ksplit<TileKSplit64x32>;
+      launch(st, p, slot[0], Wb, Hb + r0 * p.d, rows, ia > 0 ? 1 : 0, ia + 2 >= p.n_chunks ? 1 : 0, nv, grad_loss, dHb + r0 * p.d, dW);
+    }
+    return check_launch();
+  }
   for (int ia = 0; ia < p.n_chunks; ia += 2) {
     const int ib = ia + 1;
-    dlogits(ia, slot[0]);
+    dlogits(ia, rows_of(ia), slot[0]);
     grad_h(ia, slot[0], slot[1]);
     if (ib < p.n_chunks) {
-      dlogits(ib, slot[1]);
+      dlogits(ib, rows_of(ib), slot[1]);
       grad_w(ia, ib, p.C + rows_of(ib));
       grad_h(ib, slot[1], slot[0]);
     } else {
@@ -843,7 +927,7 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
   info[2] = p.blk_use ? p.blk_n_rb : (p.n_chunks + 1) / 2;
   info[3] = p.blk_use ? (int64_t)p.blk_win_tiles * kTile : p.V;
   info[4] = p.blk_use ? p.blk_n_win : 1;
-  info[5] = p.blk_use ? p.blk_split : p.small_dh ? p.small_dh_split : p.dh_split;
+  info[5] = p.blk_use ? p.blk_split : p.joint && p.joint != MST_PAIR_SPLIT ? TileKSplit64x16::kSplit : p.small_dh ? p.small_dh_split : p.dh_split;
   info[6] = (int64_t)p.est_pairs_us;
   info[7] = (int64_t)p.est_blocks_us;
   return MST_OK;
@@ -883,6 +967,12 @@ int32_t mst_dh_tile_of_workgroup(int32_t even, int32_t n_split, int32_t n_row_ti
   *row_tile = st;
   *col_tile = jt;
   return ok ? 1 : 0;
+}
+
+int32_t mst_pair_launches(int64_t S, int64_t d, int64_t V, int32_t M) {
+  Plan p;
+  if (make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_PAIRS) != MST_OK) return -1;
+  return p.joint;
 }
 
 mst_status mst_tile_info(int64_t S, int64_t d, int64_t V, int32_t M, int64_t* info) {

@@ -134,11 +134,10 @@ __global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dlogits_small(
 //   A side = hidden index j (W, K-strided, permuted: a lane holds 4 TA consecutive j), B side = chunk rows (G)
 // ---------------------------------------------------------------------------
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dh_small(
+__device__ __forceinline__ void dh_tile_small(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, int rows, int d, int V,
     int n_st, int n_jt, int n_split, int ksteps_per_split, const long long* __restrict__ n_valid, float grad_loss,
-    float* __restrict__ partial /* [n_split][rows_stride][d] */, int rows_stride, __bf16* __restrict__ dHc) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+    float* __restrict__ partial /* [n_split][rows_stride][d] */, int rows_stride, __bf16* __restrict__ dHc, char* smem) {
   // splits are the slow coordinate: an XCD's workgroups share a range of W and of the columns of G
   int w, st;
   if (!even_tile_of_block(blockIdx.x, n_jt * n_split, n_st, &w, &st)) return;
@@ -181,6 +180,14 @@ __global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dh_small(
       }
     }
   }
+}
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dh_small(
+    const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, int rows, int d, int V,
+    int n_st, int n_jt, int n_split, int ksteps_per_split, const long long* __restrict__ n_valid, float grad_loss,
+    float* __restrict__ partial, int rows_stride, __bf16* __restrict__ dHc) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  dh_tile_small<C>(G, ldg, W, rows, d, V, n_st, n_jt, n_split, ksteps_per_split, n_valid, grad_loss, partial, rows_stride, dHc, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -238,6 +245,98 @@ __global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dw_small(
   if (!even_tile_of_block(blockIdx.x, n_vt, n_jt, &vt, &jt)) return;
   const float scale = last ? gamma_of(n_valid, grad_loss) : 1.0f;
   dw_tile_small<C>(G, ldg, ldg, Hc, d, rows, d, V, vt, jt, accumulate != 0, scale, dW, d, smem);
+}
+
+// ---------------------------------------------------------------------------
+// backward 2 and 3 from one launch: neither needs the other.  In the smallest problems a launch takes 4 to 6 us whatever
+// it does, and the pair order has seven of them per pair of chunks; these two kernels make two of them.
+//
+// A pair of chunks leaves no room for fp32 partials of dH, so the contraction over V is split between the four waves of
+// a workgroup instead and added up in LDS.  A wave's loads are bound by their latency (72 KB in flight on a compute unit,
+// 1.4 us), and 64-byte row pieces cost as much as 128-byte ones, so the tile is 64 hidden indices wide, or 32 where that
+// makes enough more workgroups.  512 rows, d = 256, V = 4096, M = 4: backward 65 us (14 launches) -> 31 (4).
+// ---------------------------------------------------------------------------
+// dH = gamma G W.   A side = hidden index j (W, K-strided), B side = rows (G)
+template <class C>
+__device__ __forceinline__ void dh_tile_ksplit(const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, int rows, int d,
+                                               int V, int st, int jt, const long long* __restrict__ n_valid, float grad_loss,
+                                               __bf16* __restrict__ dHc, char* smem) {
+  const int j0 = jt * C::EA, s0 = st * C::EB;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  f32x4 acc[C::TA][C::TB];
+  zero_acc<C::TA, C::TB>(acc);
+  {
+    PanelKS16<C, C::EA, C::TA> pa;
+    PanelKC16<C, C::EB, C::TB, false> pb;
+    pa.init(W + j0, d, V, d - j0, 0, lane, 0);
+    pb.init(G + (size_t)s0 * ldg, ldg, rows - s0, ldg, 0, lane, 0);
+    gemm_mainloop_ksplit<C>(acc, pa, pb, smem, wave, V);
+  }
+  // every wave's sums side by side in LDS ([row][j], rows padded by 16 bytes), added in the order of the waves
+  constexpr int kRow = C::EA + 4;
+  float* const sums = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int u = 0; u < C::TB; ++u)
+#pragma unroll
+    for (int t = 0; t < C::TA; ++t)
+      *reinterpret_cast<f32x4*>(sums + (wave * C::EB + 16 * u + (lane & 15)) * kRow + 16 * t + 4 * (lane >> 4)) = acc[t][u];
+  __syncthreads();
+  const float gamma = gamma_of(n_valid, grad_loss);
+  constexpr int kPer = 8, kLanesPerRow = C::EA / kPer;
+  for (int i = threadIdx.x; i < C::EB * kLanesPerRow; i += C::kThreads) {
+    const int row = i / kLanesPerRow, col = i % kLanesPerRow * kPer;
+    if (s0 + row >= rows || j0 + col >= d) continue;                  // d % 8 == 0
+    f32x4 v[2] = {};
+#pragma unroll
+    for (int w = 0; w < C::kSplit; ++w)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) v[h] += *reinterpret_cast<const f32x4*>(sums + (w * C::EB + row) * kRow + col + 4 * h);
+    bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) o[e] = (__bf16)(gamma * v[e >> 2][e & 3]);
+    *reinterpret_cast<bf16x8*>(dHc + (size_t)(s0 + row) * d + j0 + col) = o;
+  }
+}
+
+typedef CfgKSplit<2, 1, 3> TileKSplit32x16;      // hidden indices x rows; with their stages they fit into Tile64's LDS, or nearly
+typedef CfgKSplit<4, 1, 2> TileKSplit64x16;
+typedef CfgKSplit<4, 2, 2> TileKSplit64x32;
+
+// the first dh_grid workgroups (a multiple of the XCD count): dH, the longer ones
+template <class CH, class CW>
+__global__ __launch_bounds__(CW::kThreads) void k_bwd_gemm_dh_dw_small(
+    const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, const __bf16* __restrict__ Hc, int rows, int d, int V,
+    int n_sh, int n_jh, int dh_grid, int n_vt, int n_jt, int accumulate, int last, const long long* __restrict__ n_valid,
+    float grad_loss, __bf16* __restrict__ dHc, float* __restrict__ dW) {
+  static_assert(CH::kThreads == CW::kThreads, "one launch");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if ((int)blockIdx.x < dh_grid) {
+    int jt, st;
+    if (!even_tile_of_block(blockIdx.x, n_jh, n_sh, &jt, &st)) return;
+    dh_tile_ksplit<CH>(G, ldg, W, rows, d, V, st, jt, n_valid, grad_loss, dHc, smem);
+    return;
+  }
+  int vt, jt;
+  if (!even_tile_of_block((int)blockIdx.x - dh_grid, n_vt, n_jt, &vt, &jt)) return;
+  const float scale = last ? gamma_of(n_valid, grad_loss) : 1.0f;
+  dw_tile_small<CW>(G, ldg, ldg, Hc, d, rows, d, V, vt, jt, accumulate != 0, scale, dW, d, smem);
+}
+
+// The same for a call of one chunk, where the free dlogits slot holds fp32 partials of dH (for k_bwd_dh_reduce).
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dh_split_dw_small(
+    const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, const __bf16* __restrict__ Hc, int rows, int d, int V,
+    int n_sh, int n_jh, int n_split, int ksteps_per_split, int dh_grid, int n_vt, const long long* __restrict__ n_valid,
+    float grad_loss, float* __restrict__ partial, __bf16* __restrict__ dHc, float* __restrict__ dW) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if ((int)blockIdx.x < dh_grid) {
+    dh_tile_small<C>(G, ldg, W, rows, d, V, n_sh, n_jh, n_split, ksteps_per_split, n_valid, grad_loss, partial, rows, dHc, smem);
+    return;
+  }
+  int vt, jt;
+  if (!even_tile_of_block((int)blockIdx.x - dh_grid, n_vt, n_jh, &vt, &jt)) return;
+  dw_tile_small<C>(G, ldg, ldg, Hc, d, rows, d, V, vt, jt, false, gamma_of(n_valid, grad_loss), dW, d, smem);
 }
 
 }  // namespace mst

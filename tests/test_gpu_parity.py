@@ -472,6 +472,37 @@ def test_automatic_block_shapes_with_split_dh_match_oracle(S, d, V, M, row_block
     assert bool((run.last_ws[-4096:] == 0xA5).all()), "wrote past the declared workspace"
 
 
+@pytest.mark.parametrize("S,d,V,M,launches", [
+    (705, 264, 1025, 5, "32x16"),      # three passes over dW, the last one of a single chunk; last tiles of 1 row, 8 columns
+    (129, 40, 33, 3, "32x16"),         # fewer K steps than waves, one of a single entry
+    (65, 264, 4097, 1, "32x16"),
+    (1203, 264, 2051, 5, "64x16"),
+    (65, 2056, 1003, 2, "64x16"),
+    (700, 648, 1031, 3, "64x32"),
+    (2000, 72, 130, 7, "64x32"),
+    (17, 264, 4097, 1, "split"),       # four splits, one dH tile row
+    (257, 2056, 3003, 1, "split"),     # no split: dH straight to bf16
+    (1, 8, 2, 1, "split"),
+    (1025, 264, 9001, 3, "separate"),  # 64 x 64 tiles throughout, dH in 8 splits
+])
+def test_joint_launches_of_the_pair_order_match_oracle(schedule, S, d, V, M, launches):
+    """dH and dW of small problems from one launch, in every form, with and without sums of an earlier pair in dW: against
+    the oracle, the same bits call after call, within the declared workspace."""
+    import torch
+    import paper_2407_15892_amd as mst
+    schedule(mst.BWD_SCHEDULE_PAIRS)
+    assert mst.mst_pair_launches(S, d, V, M) == launches
+    assert mst.mst_tile_info(S, d, V, M)["dw"] == 64
+    inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=470 + S % 97, w_std=0.3, ignore_frac=0.1, label_dist="zipf"))
+    run, _, _ = _check_full(inp, grad_loss=0.8)
+    first = (run.dH_t.clone(), run.dW_t.clone())
+    run.pad = 4096
+    run.backward(grad_loss=0.8)
+    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
+    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
+    assert bool((run.last_ws[-4096:] == 0xA5).all()), "wrote past the declared workspace"
+
+
 @pytest.mark.parametrize("S,d,V,M", [
     (975, 1176, 4099, 3),      # 64 x 64 tiles in dlogits, dH and dW, whose second pass (one chunk) adds
     (712, 1920, 6637, 2),      # in dlogits and dH only
