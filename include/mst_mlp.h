@@ -107,8 +107,8 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
 
 /*
  * Which block tiles the launches of a chunk of `rows` rows take (host, pure; a test aid).  All give the same O and dX
- * bit for bit.  info[0..2] = gate/up (forward and backward), info[3..5] = down, info[6..8] = dA, info[9..11] = dX where it has a
- * launch of its own (mst_mlp_dx_tile), each as
+ * bit for bit.  info[0..2] = gate/up (forward and backward), info[3..5] = down, info[6..8] = dA and info[9..11] = dX
+ * where they have launches of their own (mst_mlp_da_in_gateup, mst_mlp_dx_tile), each as
  * {MST_MLP_TILE_* of the launch, or of its end; leading columns (of I, d, I, d) that a launch of 256 x 256 tiles of its
  * own takes before it, 0 for none; 1 where 256 x 256 tiles are laid out in super-tiles}; info[12..13] = the weight
  * gradients of a call whose chunks have `rows` rows: {MST_MLP_TILE_256, _64 or _64_LONE; 1 where the tiles are dealt out
@@ -120,7 +120,8 @@ enum {
   MST_MLP_TILE_128_LONE,  /* 128 x 128, one, software-pipelined                         */
   MST_MLP_TILE_64,        /* 64 x 64, four                                              */
   MST_MLP_TILE_64_LONE,   /* 64 x 64, one, software-pipelined                           */
-  MST_MLP_TILE_64_LONG    /* the same with K steps of 128                               */
+  MST_MLP_TILE_64_LONG,   /* the same with K steps of 128                               */
+  MST_MLP_TILE_32         /* 32 x 32, K steps of 128 (not gate/up)                      */
 };
 mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info);
 
@@ -131,9 +132,17 @@ mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info);
 enum {
   MST_MLP_DX_OWN = 0,     /* in a launch of its own, with the tiles that mst_mlp_tile_info names   */
   MST_MLP_DX_SHARED_256,  /* by the launch of the weight gradients, 256 x 256 tiles                */
-  MST_MLP_DX_SHARED_128   /* the same, 128 (hidden index) x 256 (rows)                             */
+  MST_MLP_DX_SHARED_128,  /* the same, 128 (hidden index) x 256 (rows)                             */
+  MST_MLP_DX_SHARED_64,   /* the same, 64 x 64 tiles, as those of the weight gradients             */
+  MST_MLP_DX_SHARED_32    /* the same, 32 x 32                                                     */
 };
 int32_t mst_mlp_dx_tile(int64_t rows, int64_t d, int64_t I, int32_t first);
+
+/*
+ * 1 where dA of a chunk of `rows` rows is computed by the launch of gate/up's backward, 0 where it has a launch of its own
+ * (with the tiles that mst_mlp_tile_info names), -1 on bad shapes (host, pure; a test aid).
+ */
+int32_t mst_mlp_da_in_gateup(int64_t rows, int64_t d, int64_t I);
 
 /*
  * Workgroup -> tile map of the 256 x 256 launches (host-only test aid; the kernels call the same functions), as
@@ -156,7 +165,8 @@ enum {
   MST_MLP_K_GATEUP = 0,   /* A_i = silu(X_i Wg^T) * (X_i Wu^T)                       */
   MST_MLP_K_DOWN,         /* O_i = A_i Wd^T                                          */
   MST_MLP_K_DA,           /* dA_i = dO_i Wd                                          */
-  MST_MLP_K_GATEUP_BWD,   /* recomputed gate/up GEMM + dG_i, dU_i, A_i epilogue      */
+  MST_MLP_K_GATEUP_BWD,   /* recomputed gate/up GEMM + dG_i, dU_i, A_i epilogue; with
+                             dA_i in it where one launch serves both                 */
   MST_MLP_K_DX,           /* dX_i = dG_i Wg + dU_i Wu                                */
   MST_MLP_K_DW,           /* dWg += dG_i^T X_i, dWu += dU_i^T X_i, dWd += dO_i^T A_i; with
                              dX_i in it where one launch serves both                 */

@@ -47,6 +47,7 @@ struct Scope : mst_host::Scope {
 typedef CfgSmall<4, 4, 3, 2, false> Tile128;
 typedef CfgSmall<4, 4, 4, 4, true> Tile128Lone;      // Tile64, Tile64Lone: mst_small_kernels.hpp
 typedef CfgSmall<2, 2, 5, 5, true, 128> Tile64Long;  // K steps of 128: half as many barriers in a long contraction
+typedef CfgSmall<1, 1, 5, 5, true, 128> Tile32;      // 32 x 32, for products of a few 64 x 64 tiles
 
 template <class C, class Set>
 void set_small_attributes(Set set) {
@@ -81,6 +82,11 @@ bool set_kernel_attributes() {   // on the current device
   set_small_attributes<Tile64>(set);
   set_small_attributes<Tile64Lone>(set);
   set_small_attributes<Tile64Long>(set);
+  set((const void*)k_mlp_gemm_nt_small<Tile32>);
+  set((const void*)k_mlp_gemm_nn_small<Tile32>);
+  set((const void*)k_mlp_gateup_small<Tile64Lone, true, true>);
+  set((const void*)k_mlp_dx_dw3_small<Tile64Lone, Tile64Lone>);
+  set((const void*)k_mlp_dx_dw3_small<Tile32, Tile64Lone>);
   set((const void*)k_mlp_gemm_nn<false>);
   set((const void*)k_mlp_gemm_nn<true>);
   set((const void*)k_mlp_dw3_small<Tile64>);
@@ -126,18 +132,24 @@ int rows_of(const Plan& p, int i) {
 //                  I = 14336: down 63 against 250 (16 tiles of 256), dX 129 against 523
 //   64 x 64 long   the same with K steps of 128, 0.22 per 64 + 3.5, for one workgroup per compute unit: the down of 200
 //                  tokens 53, of 512 tokens (d = 2048, I = 5632) 21.6 against 22.5; slower at fewer than 64 K steps
+//   32 x 32        0.11 per 64 (0.17 with K-strided weights) + 3 where there are few 64 x 64 tiles (more than 128, or 64
+//                  K-strided, move too much through L2 for this): a quarter of the LDS traffic per K step, and four times
+//                  the compute units.  Forward of 64 tokens, d = 2048, I = 6000: 33 us -> 22, of 500, d = 640, I = 1800:
+//                  18.9 -> 15; backward of 178 tokens, d = 520, I = 1456: 35 -> 30.  Not for gate/up (pairs of row tiles)
 // Where the large tiles end in a partly filled round, whole columns of them may make up the full rounds and a second
 // launch the rest with smaller tiles: gate/up of 1668 tokens, d = 1544, I = 5384 (301 large tiles) as 252 large and 675 of
 // 64 x 64: step of 5003 tokens 1.31 -> 1.23 ms; dA of 4096 tokens, I = 14336 (896 tiles) as 768 large and 512 of
 // 128 x 128: 376 us against 412.  With all compute units busy a K step takes 1.36, with the K-strided weights of dA and
 // dX 1.4 also where some are idle; not split, by this, are the 1376 tiles of gate/up at I = 11008 (2 % slower split).
-enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long };   // MST_MLP_TILE_* of the header, in this order
+enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long, k32 };   // MST_MLP_TILE_* of the header, in this order
 struct TileChoice {
   TileKind kind;      // of the whole, or of what follows the first `head` columns
   int64_t head;       // A-side extent, a multiple of 256, that large tiles cover in a launch of its own (0: none)
   double us;
 };
-TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, bool strided) {
+enum Weights { kGateUp, kContiguous, kStrided };                 // gate/up, down, dA and dX
+TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
+  const bool strided = w == kStrided;
   const double k = (double)ksteps;
   TileChoice best = {kBig, 0, std::ceil(tiles_of(n_a, n_b, 256) / kNumCu) * ((strided ? 1.4 : 1.25) * k + 7.0)};
   auto consider = [&](TileKind kind, double t) {
@@ -148,24 +160,25 @@ TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, bool strided) 
   else consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : 0.3 + 0.7 * x) * (k + 4.0));
   consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.3 + 0.4 * y : 0.45) * k + 2.5);
   if (y <= 0.25 && ksteps >= 64) consider(k64Long, 0.22 * k + 3.5);
+  if (w != kGateUp && tiles_of(n_a, n_b, 64) <= (strided ? 64.0 : 128.0)) consider(k32, (strided ? 0.17 : 0.11) * k + 3.0);
   if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
 }
-TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, bool strided) {
-  const TileChoice whole = choose_whole(n_a, n_b, ksteps, strided);
+TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
+  const TileChoice whole = choose_whole(n_a, n_b, ksteps, w);
   const int64_t t_a = (n_a + kTile - 1) / kTile, t_b = (n_b + kTile - 1) / kTile;
   const int64_t full = t_a * t_b / kNumCu * kNumCu, cols = full / t_b;       // full rounds; columns of tiles in them
   if (cols == 0 || cols == t_a) return whole;
-  const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, strided);
-  const double t = (double)(full / kNumCu) * ((strided ? 1.4 : 1.36) * (double)ksteps + 7.0) + rest.us + 2.0;
+  const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, w);
+  const double t = (double)(full / kNumCu) * ((w == kStrided ? 1.4 : 1.36) * (double)ksteps + 7.0) + rest.us + 2.0;
   return rest.kind != kBig && t < whole.us ? TileChoice{rest.kind, cols * kTile, t} : whole;
 }
 
 // the choices of the four products of a chunk of `rows` rows
 int64_t ksteps_of(int64_t k) { return (k + kBK - 1) / kBK; }
-TileChoice gateup_tile(int64_t rows, int64_t d, int64_t I) { return choose_tile(2 * I, rows, ksteps_of(d), false); }
-TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) { return choose_tile(N, rows, ksteps_of(K), false); }
-TileChoice nn_tile(int64_t rows, int64_t N, int64_t K, int terms) { return choose_tile(N, rows, terms * ksteps_of(K), true); }
+TileChoice gateup_tile(int64_t rows, int64_t d, int64_t I) { return choose_tile(2 * I, rows, ksteps_of(d), kGateUp); }
+TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) { return choose_tile(N, rows, ksteps_of(K), kContiguous); }
+TileChoice nn_tile(int64_t rows, int64_t N, int64_t K, int terms) { return choose_tile(N, rows, terms * ksteps_of(K), kStrided); }
 
 // The weight gradients have one tile kind for all chunks: what the large tiles keep between them is not row-major.
 struct DwChoice { bool small, lone, even; };
@@ -180,15 +193,32 @@ DwChoice dw_choice(int64_t C, int64_t d, int64_t I) {
   return c;
 }
 
-// Whether dX shares the launch of the chunk's weight gradients (large tiles only), and with which tile (MST_MLP_DX_* of the
-// header).  A K step of a half tile takes 0.8 us, 0.9 with all compute units busy; K-strided weights as at choose_whole.
+// dA computed by gate/up's backward launch: where both are one short tile deep, a launch less is worth more than the
+// second contraction in it.  Up to 16 K steps: backward of 256 tokens, d = 256, I = 896: 22.4 -> 19.6 us; of 256, d = 1024,
+// I = 2816: 46.7 -> 45.2; from 24 on nothing (100 tokens, d = 1536) to 3 % slower (64, d = 4096).
+bool fuse_da(int64_t rows, int64_t d, int64_t I) {
+  const TileChoice c = gateup_tile(rows, d, I);
+  return c.kind == k64Lone && c.head == 0 && ksteps_of(d) <= 16;
+}
+
+// Whether dX shares the launch of the chunk's weight gradients, and with which tile (MST_MLP_DX_* of the header).
+//
+// Small tiles: both in one launch of lone 64 x 64 tiles, dX in 32 x 32 ones where few (72 in a shared launch; 78 take as
+// long either way).  Over 47 shapes of 64 to 8000 rows, d = 152 to 768, the backward call took 0.67 to 1.00 of its time with
+// two launches (256 rows, d = 256, I = 896: 22.4 -> 16.2 us; 300, d = 656, I = 2000: 46 -> 37).
+//
+// Large tiles: a K step of a half tile takes 0.8 us, 0.9 with all compute units busy; K-strided weights as at choose_whole.
 // Over twenty shapes of 200 to 4096 rows, d = 1024 to 4096, one and two chunks, both ways timed: the backward call took
 // 0.87 to 1.01 of its time with two launches, 0.96 in the mean, and nowhere was the other tile more than 1.5 % faster.
 // kShared: a shared launch must be this much cheaper (what is left alone, 4096 rows, d = 4096: both take the same).
 constexpr double kShared = 0.98;
-enum DxKind { kDxOwn, kDxWhole, kDxHalf };
+enum DxKind { kDxOwn, kDxWhole, kDxHalf, kDx64, kDx32 };
 DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwChoice& dw) {
-  if (dw.small) return kDxOwn;
+  if (dw.small) {
+    const TileChoice own = nn_tile(rows, d, I, 2);
+    if (own.kind < k64 || own.head) return kDxOwn;
+    return tiles_of(d, rows, 64) <= 72.0 ? kDx32 : kDx64;
+  }
   auto tiles = [&](int64_t a, int64_t b, int64_t e) { return (a + e - 1) / e * ((b + kTile - 1) / kTile); };
   const int64_t n_dw = 2 * tiles(I, d, kTile) + tiles(d, I, kTile);
   const TileCost c = dw_cost(rows, accumulate);
@@ -210,13 +240,23 @@ void launch_dx_dw3(hipStream_t st, DxProblem x, const DwProblems& ps, int rows, 
                      x, ps, rows, more);
 }
 
+template <class CX>
+void launch_dx_dw3_small(hipStream_t st, DxProblem x, const DwProblems& ps, int rows, int accumulate) {
+  typedef Tile64Lone CW;
+  x.n_jt = (x.d + CX::EA - 1) / CX::EA;
+  x.n_st = (rows + CX::EB - 1) / CX::EB;
+  x.grid = even_grid(x.n_jt, x.n_st);
+  hipLaunchKernelGGL((k_mlp_dx_dw3_small<CX, CW>), dim3(x.grid + ps.p[0].grid + ps.p[1].grid + ps.p[2].grid), dim3(CW::kThreads),
+                     CX::kLds > CW::kLds ? CX::kLds : CW::kLds, st, x, ps, rows, accumulate);
+}
+
 // A = silu(X Wg^T) * (X Wu^T) of a chunk, or its backward (dA given)
-template <class C, bool kBackward>
+template <class C, bool kBackward, bool kDa = false>
 void launch_gateup_small(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int n_i, int ldi,
-                         __bf16* A, __bf16* dAG, __bf16* dU) {
+                         __bf16* A, __bf16* dAG, __bf16* dU, DaProblem da = DaProblem{}) {
   const int n_it = (n_i + C::EA / 2 - 1) / (C::EA / 2), n_st = (rows + C::EB - 1) / C::EB;
-  hipLaunchKernelGGL((k_mlp_gateup_small<C, kBackward>), dim3(even_grid(n_it, n_st)), dim3(C::kThreads), C::kLds, st,
-                     X, Wg, Wu, rows, d, n_i, ldi, n_st, n_it, A, dAG, dU);
+  hipLaunchKernelGGL((k_mlp_gateup_small<C, kBackward, kDa>), dim3(even_grid(n_it, n_st)), dim3(C::kThreads), C::kLds, st,
+                     X, Wg, Wu, rows, d, n_i, ldi, n_st, n_it, A, dAG, dU, da);
 }
 template <bool kBackward>
 void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
@@ -266,6 +306,7 @@ void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N
     case k64: return launch_nt_small<Tile64>(st, P, Q, rows, N - n0, K, out, N);
     case k64Lone: return launch_nt_small<Tile64Lone>(st, P, Q, rows, N - n0, K, out, N);
     case k64Long: return launch_nt_small<Tile64Long>(st, P, Q, rows, N - n0, K, out, N);
+    case k32: return launch_nt_small<Tile32>(st, P, Q, rows, N - n0, K, out, N);
     default: return;
   }
 }
@@ -296,6 +337,7 @@ void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16*
     case k64: return launch_nn_small<Tile64>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
     case k64Lone: return launch_nn_small<Tile64Lone>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
     case k64Long: return launch_nn_small<Tile64Long>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
+    case k32: return launch_nn_small<Tile32>(st, P1, Q1, P2, Q2, rows, N - n0, K, N, out);
     default: return;
   }
 }
@@ -404,13 +446,17 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
     const __bf16* Xc = Xb + r0 * p.d;
     const __bf16* dOc = dOb + r0 * p.d;
     const int acc = i > 0 ? 1 : 0;
-    {
+    const bool da_in_gateup = fuse_da(rows, p.d, p.I);
+    if (!da_in_gateup) {
       Scope sc(st, MST_MLP_K_DA);
       launch_nn(st, dOc, Wdb, nullptr, nullptr, rows, dI, dd, bufG);
     }
     {
       Scope sc(st, MST_MLP_K_GATEUP_BWD);
-      launch_gateup<true>(st, Xc, Wgb, Wub, rows, dd, dI, bufA, bufG, bufU);
+      if (da_in_gateup)
+        launch_gateup_small<Tile64Lone, true, true>(st, Xc, Wgb, Wub, rows, dd, dI, dI, bufA, bufG, bufU, DaProblem{dOc, Wdb});
+      else
+        launch_gateup<true>(st, Xc, Wgb, Wub, rows, dd, dI, bufA, bufG, bufU);
     }
     const DxKind dx = choose_dx(rows, p.d, p.I, acc != 0, dw);
     if (dx == kDxOwn) {
@@ -425,17 +471,18 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
       ps.p[1] = dw_problem(bufU, dI, Xc, dd, dd, dI, dWu, tile, dw.even);     // dWu [I][d] (+)= dU^T X
       ps.p[2] = dw_problem(dOc, dd, bufA, dI, dI, dd, dWd, tile, dw.even);    // dWd [d][I] (+)= dO^T A
       const dim3 grid(ps.p[0].grid + ps.p[1].grid + ps.p[2].grid);
-      if (dw.small) {
+      DxProblem x = {};
+      x.dG = bufG; x.Wg = Wgb; x.dU = bufU; x.Wu = Wub;
+      x.d = dd; x.I = dI; x.dX = dXb + r0 * p.d;
+      if (dx == kDx64 || dx == kDx32) {
+        (dx == kDx32 ? launch_dx_dw3_small<Tile32> : launch_dx_dw3_small<Tile64Lone>)(st, x, ps, rows, acc);
+      } else if (dx != kDxOwn) {
+        (dx == kDxHalf ? launch_dx_dw3<Tile16Half> : launch_dx_dw3<Tile16>)(st, x, ps, rows, dw.even, acc != 0, i + 1 < p.n_chunks ? 1 : 0);
+      } else if (dw.small) {
         if (dw.lone)
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64Lone>, grid, dim3(Tile64Lone::kThreads), Tile64Lone::kLds, st, ps, rows, acc);
         else
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64>, grid, dim3(Tile64::kThreads), Tile64::kLds, st, ps, rows, acc);
-      } else if (dx != kDxOwn) {
-        DxProblem x = {};
-        x.dG = bufG; x.Wg = Wgb; x.dU = bufU; x.Wu = Wub;
-        x.d = dd; x.I = dI; x.dX = dXb + r0 * p.d;
-        const auto launch = dx == kDxHalf ? launch_dx_dw3<Tile16Half> : launch_dx_dw3<Tile16>;
-        launch(st, x, ps, rows, dw.even, acc != 0, i + 1 < p.n_chunks ? 1 : 0);
       } else {
         const auto kernel = dw.even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
                                  : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
@@ -471,6 +518,12 @@ int32_t mst_mlp_dx_tile(int64_t rows, int64_t d, int64_t I, int32_t first) {
   Plan p;
   if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
   return choose_dx(rows, d, I, !first, dw_choice(rows, d, I));
+}
+
+int32_t mst_mlp_da_in_gateup(int64_t rows, int64_t d, int64_t I) {
+  Plan p;
+  if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
+  return fuse_da(rows, d, I) ? 1 : 0;
 }
 
 int32_t mst_mlp_tile_grid(int32_t n_slow, int32_t n_fast) {

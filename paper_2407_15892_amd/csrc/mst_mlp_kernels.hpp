@@ -256,11 +256,14 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 
-template <class C, bool kBackward>
+// kDa: dA is computed here too, not read: dA = dO Wd over the same indices and tokens (Wd K-strided), rounded to bf16 as in
+// memory.  One launch less, for launches that are one short tile deep (see fuse_da in mst_mlp_api.hip).
+struct DaProblem { const __bf16 *dO, *Wd; };      // [rows][d] of the chunk, [d][ldi]
+template <class C, bool kBackward, bool kDa = false>
 __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
     const __bf16* __restrict__ Xc, const __bf16* __restrict__ Wg, const __bf16* __restrict__ Wu,
     int rows, int d, int I /* indices of this launch */, int ldi, int n_st, int n_it,
-    __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU) {
+    __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU, DaProblem da_in) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int H = C::TA / 2;                                  // gate tiles of a wave; as many up tiles follow
   int it, st;
@@ -269,6 +272,26 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wa = wave / C::WB, wb = wave % C::WB;
+
+  constexpr int N = 4 * H;                                      // consecutive indices of a lane
+  typedef __attribute__((ext_vector_type(N))) __bf16 vec;
+  vec da_own[C::TB];
+  if constexpr (kDa) {
+    static_assert(H == 1 && C::NSA == C::NSB, "the indices of a lane are those of an unpermuted 16-row tile");
+    typedef CfgSmall<H, C::TB, C::NSA, C::NSB, true, C::BK> CD;
+    static_assert(CD::kLds <= C::kLds, "the same launch");
+    f32x4 acc[CD::TA][CD::TB];
+    zero_acc<CD::TA, CD::TB>(acc);
+    PanelKS16<CD, CD::EA, CD::TA> pa;
+    PanelKC16<CD, CD::EB, CD::TB, false> pb;
+    pa.init(da_in.Wd + i0, ldi, d, I - i0, wave, lane, wa);
+    pb.init(da_in.dO + (size_t)s0 * d, d, rows - s0, d, wave, lane, wb);
+    gemm_mainloop_small<CD>(acc, pa, pb, smem, 0, d);
+#pragma unroll
+    for (int u = 0; u < C::TB; ++u)
+#pragma unroll
+      for (int e = 0; e < N; ++e) da_own[u][e] = (__bf16)acc[0][u][e];
+  }
 
   f32x4 acc[C::TA][C::TB];
   zero_acc<C::TA, C::TB>(acc);
@@ -286,8 +309,6 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
     pb.init(Xc + (size_t)s0 * d, d, rows - s0, d, wave, lane, wb);
     gemm_mainloop_small<C>(acc, pa, pb, smem, 0, d);
   }
-  constexpr int N = 4 * H;                                      // consecutive indices of a lane
-  typedef __attribute__((ext_vector_type(N))) __bf16 vec;
   const int ib = i0 + 16 * H * wa + N * (lane >> 4);
 #pragma unroll
   for (int u = 0; u < C::TB; ++u) {
@@ -295,7 +316,8 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
     if (s_local >= rows || ib >= I) continue;                   // I % 8 == 0 and N divides 8
     const size_t off = (size_t)s_local * ldi + ib;
     vec da, a_o, g_o, u_o;
-    if (kBackward) da = *reinterpret_cast<const vec*>(dAG + off);
+    if (kDa) da = da_own[u];
+    else if (kBackward) da = *reinterpret_cast<const vec*>(dAG + off);
 #pragma unroll
     for (int e = 0; e < N; ++e) {
       const float g = acc[e >> 2][u][e & 3], up = acc[H + (e >> 2)][u][e & 3];
@@ -320,17 +342,19 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
 template <class C>
 __device__ __forceinline__ void store_small_bf16(const f32x4 (&acc)[C::TA][C::TB], __bf16* __restrict__ out, int ldo,
                                                  int rows, int N, int s0, int n0, int wa, int wb, int lane) {
+  constexpr int kPer = C::TA == 1 ? 4 : 8;                        // N % 8 == 0: a store is inside or outside
+  typedef __attribute__((ext_vector_type(kPer))) __bf16 vec;
   const int nb = n0 + 16 * C::TA * wa + 4 * C::TA * (lane >> 4);
 #pragma unroll
   for (int u = 0; u < C::TB; ++u) {
     const int s_local = s0 + wb * (16 * C::TB) + 16 * u + (lane & 15);
     if (s_local >= rows) continue;
 #pragma unroll
-    for (int p = 0; p < C::TA / 2; ++p) {
-      bf16x8 o;
+    for (int p = 0; p < 4 * C::TA / kPer; ++p) {
+      vec o;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = (__bf16)acc[2 * p + (e >> 2)][u][e & 3];
-      if (nb + 8 * p < N) *reinterpret_cast<bf16x8*>(out + (size_t)s_local * ldo + nb + 8 * p) = o;   // N % 8 == 0
+      for (int e = 0; e < kPer; ++e) o[e] = (__bf16)acc[(kPer * p + e) >> 2][u][e & 3];
+      if (nb + kPer * p < N) *reinterpret_cast<vec*>(out + (size_t)s_local * ldo + nb + kPer * p) = o;
     }
   }
 }
@@ -362,11 +386,10 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nt_small(
 
 // out[s][n] = sum_k P1[s][k] Q1[k][n] (+ sum_k P2[s][k] Q2[k][n])
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nn_small(
+__device__ __forceinline__ void nn_tile_small(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
-    int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+    int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo, char* smem) {
   int nt, st;
   if (!even_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
   const int n0 = nt * C::EA, s0 = st * C::EB;
@@ -378,13 +401,21 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nn_small(
   zero_acc<C::TA, C::TB>(acc);
   const int terms = P2 != nullptr ? 2 : 1;
   for (int term = 0; term < terms; ++term) {
-    PanelKS16<C, C::EA, C::TA, true> pa;
+    PanelKS16<C, C::EA, C::TA, (C::TA > 1)> pa;                   // one 16-row tile: the permutation is the identity
     PanelKC16<C, C::EB, C::TB, false> pb;
     pa.init((term ? Q2 : Q1) + n0, ldq, K, N - n0, wave, lane, wa);
     pb.init((term ? P2 : P1) + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
     gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K);
   }
   store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
+}
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nn_small(
+    const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
+    const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
+    int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  nn_tile_small<C>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, n_st, n_nt, out, ldo, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -443,14 +474,29 @@ __global__ __launch_bounds__(kThreads) void k_mlp_dx_dw3(DxProblem x, DwProblems
 
 // the same with 64 x 64 tiles, for problems too small to occupy the chip with large ones (mst_small_kernels.hpp)
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_mlp_dw3_small(DwProblems ps, int rows, int accumulate) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  int b = blockIdx.x, which = 0;
+__device__ __forceinline__ void dw3_tile_small(int b, const DwProblems& ps, int rows, int accumulate, char* smem) {
+  int which = 0;
   if (b >= ps.p[0].grid) { b -= ps.p[0].grid; which = 1; if (b >= ps.p[1].grid) { b -= ps.p[1].grid; which = 2; } }
   const DwProblem& q = ps.p[which];
   int vt, jt;
   if (!even_tile_of_block(b, q.n_vt, q.n_jt, &vt, &jt)) return;
   dw_tile_small<C>(q.G, q.ldg, q.ldg, q.H, q.ldh, rows, q.d, q.V, vt, jt, accumulate != 0, 1.0f, q.dW, q.d, smem);
+}
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void k_mlp_dw3_small(DwProblems ps, int rows, int accumulate) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  dw3_tile_small<C>(blockIdx.x, ps, rows, accumulate, smem);
+}
+// and with dX beside them (CX: its tile)
+template <class CX, class CW>
+__global__ __launch_bounds__(CW::kThreads) void k_mlp_dx_dw3_small(DxProblem x, DwProblems ps, int rows, int accumulate) {
+  static_assert(CX::kThreads == CW::kThreads, "one launch");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if ((int)blockIdx.x < x.grid) {
+    nn_tile_small<CX>(x.dG, x.Wg, x.dU, x.Wu, x.I, x.d, rows, x.d, x.I, x.n_st, x.n_jt, x.dX, x.d, smem);
+    return;
+  }
+  dw3_tile_small<CW>((int)blockIdx.x - x.grid, ps, rows, accumulate, smem);
 }
 
 }  // namespace mst

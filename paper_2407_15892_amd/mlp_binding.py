@@ -50,6 +50,8 @@ def load_mlp_library() -> ctypes.CDLL:
     lib.mst_mlp_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.POINTER(c.c_int64)]
     lib.mst_mlp_dx_tile.restype = c.c_int32
     lib.mst_mlp_dx_tile.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
+    lib.mst_mlp_da_in_gateup.restype = c.c_int32
+    lib.mst_mlp_da_in_gateup.argtypes = [c.c_int64, c.c_int64, c.c_int64]
     lib.mst_mlp_tile_grid.restype = c.c_int32
     lib.mst_mlp_tile_grid.argtypes = [c.c_int32, c.c_int32]
     lib.mst_mlp_tile_of_workgroup.restype = c.c_int32
@@ -109,7 +111,7 @@ def mst_mlp_bwd(X, Wg, Wu, Wd, dO, M: int, workspace, dX, dWg, dWu, dWd, stream=
         _ptr(dX), _ptr(dWg), _ptr(dWu), _ptr(dWd), _stream_handle(stream)))
 
 
-MLP_TILES = ("256", "128", "128_lone", "64", "64_lone", "64_long")     # MST_MLP_TILE_*
+MLP_TILES = ("256", "128", "128_lone", "64", "64_lone", "64_long", "32")     # MST_MLP_TILE_*
 
 
 def mst_mlp_tile_info(rows: int, d: int, I: int) -> dict:
@@ -123,12 +125,17 @@ def mst_mlp_tile_info(rows: int, d: int, I: int) -> dict:
     return out
 
 
-MLP_DX_TILES = ("own", "256", "128")     # MST_MLP_DX_*
+MLP_DX_TILES = ("own", "256", "128", "64", "32")     # MST_MLP_DX_*
 
 
 def mst_mlp_dx_tile(rows: int, d: int, I: int, first: bool) -> str:
     """How dX of a chunk is computed: in a launch of its own, or by that of the weight gradients with this tile."""
     return MLP_DX_TILES[load_mlp_library().mst_mlp_dx_tile(rows, d, I, int(first))]
+
+
+def mst_mlp_da_in_gateup(rows: int, d: int, I: int) -> bool:
+    """Whether dA of a chunk is computed by the launch of gate/up's backward."""
+    return load_mlp_library().mst_mlp_da_in_gateup(rows, d, I) == 1
 
 
 def mst_mlp_profile_enable(every) -> None:

@@ -215,13 +215,15 @@ def test_every_block_tile_matches_oracle_and_gives_the_same_bits(S, d, I, Ms):
 
 
 # (S, d, I, {M: how dX of each chunk is computed}): in a launch of its own, or by that of the weight gradients with 256 x 256
-# or 128 x 256 tiles; these over tiles dealt out evenly (the first, third and last shape) and in rectangles
+# or 128 x 256 tiles (its own dealt out evenly or in rectangles)
 DX_SHAPES = [
-    (797, 2080, 1008, {1: ["128"], 2: ["128", "128"], 3: ["own"] * 3}),
+    (797, 2080, 1008, {1: ["128"], 2: ["128", "128"], 3: ["64"] * 3}),
     (1661, 1864, 1848, {1: ["own"], 2: ["128", "128"]}),
-    (2713, 2264, 808, {1: ["256"], 2: ["128", "256"], 3: ["own"] * 3}),
+    (2713, 2264, 808, {1: ["256"], 2: ["128", "256"], 3: ["64"] * 3}),
     (4061, 2000, 1896, {2: ["256", "256"], 3: ["own"] * 3}),
-    (2697, 6360, 224, {1: ["own"]}),
+    (673, 5496, 584, {1: ["own"], 2: ["own", "256"]}),        # the tiles of its own launch: 64 x 64 in chunks,
+    (2697, 6360, 224, {1: ["own"]}),                         # lone 64 x 64
+    (3711, 4392, 312, {1: ["own"]}),                         # and 32 x 32 behind full rounds of large ones
 ]
 
 
@@ -238,3 +240,45 @@ def test_dx_beside_the_weight_gradients_matches_oracle_and_keeps_its_bits(S, d, 
         _, got, _, _ = _check(inp, M=M)
         base = got["dX"] if base is None else base
         assert np.array_equal(got["dX"], base), M      # a token's dX does not depend on who computed it
+
+
+# (S, d, I, {M: (how dX of every chunk is computed, dA in the launch of gate/up's backward)}): the launches of small problems,
+# and 32 x 32 tiles in every product that takes them
+SMALL_SHAPES = [
+    (65, 264, 904, {1: ("32", True), 2: ("32", True)}),       # last tiles of one row, of 8 columns
+    (513, 264, 776, {1: ("32", True), 5: ("32", True)}),
+    (1, 8, 8, {1: ("32", True)}),                             # fewer K than one step
+    (97, 72, 40, {3: ("32", True)}),
+    (33, 1032, 2056, {1: ("32", False), 2: ("32", False)}),   # dA in 32 x 32 tiles
+    (450, 776, 1992, {1: ("64", True), 7: ("32", True)}),
+    (2001, 264, 1032, {1: ("64", False), 2: ("64", False)}),
+    (41, 2056, 4104, {1: ("own", False)}),                    # dX in 32 x 32 tiles, its last K step of 128 ragged
+    (300, 520, 16, {1: ("32", True)}),
+]
+
+
+@pytest.mark.parametrize("S,d,I,kinds", SMALL_SHAPES)
+def test_launches_of_small_problems_match_oracle_and_keep_their_bits(S, d, I, kinds):
+    MlpDeviceRun, _ = _harness()
+    import paper_2407_15892_amd as mst
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=340 + S % 7, w_std=0.05))
+    base = None
+    for M, (dx, da) in kinds.items():
+        C = -(-S // M)
+        rows = [min(C, S - i * C) for i in range(M)]
+        assert {mst.mst_mlp_dx_tile(r, d, I, i == 0) for i, r in enumerate(rows)} == {dx}
+        assert {mst.mst_mlp_da_in_gateup(r, d, I) for r in rows} == {da}
+        _, got, _, _ = _check(inp, M=M)
+        base = got if base is None else base
+        for k in ("O", "dX"):
+            assert np.array_equal(got[k], base[k]), (k, M)
+    # the same tokens behind rows that give the chunk large tiles
+    C = 1024
+    wide = mi.make_mlp_inputs(mi.custom_mlp_config(S + C, d, I, 1, index=341, w_std=0.05))
+    for name in ("Wg", "Wu", "Wd"):
+        getattr(wide, name + "_bits")[:] = getattr(inp, name + "_bits")
+    for name in ("X", "dO"):
+        getattr(wide, name + "_bits")[C:] = getattr(inp, name + "_bits")
+    _, got, _ = _run_all(wide, M=1)
+    for k in ("O", "dX"):
+        assert np.array_equal(got[k][C:], base[k]), k
