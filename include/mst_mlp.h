@@ -121,7 +121,8 @@ enum {
   MST_MLP_TILE_64,        /* 64 x 64, four                                              */
   MST_MLP_TILE_64_LONE,   /* 64 x 64, one, software-pipelined                           */
   MST_MLP_TILE_64_LONG,   /* the same with K steps of 128                               */
-  MST_MLP_TILE_32         /* 32 x 32, K steps of 128 (not gate/up)                      */
+  MST_MLP_TILE_32,        /* 32 x 32, K steps of 128 (not gate/up)                      */
+  MST_MLP_TILE_128X256    /* 128 (weights) x 256 (rows), one (gate/up and down)         */
 };
 mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info);
 

@@ -71,12 +71,15 @@ bool set_kernel_attributes() {   // on the current device
   auto set = [&ok](const void* f) {
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess) ok = false;
   };
-  set((const void*)k_mlp_gateup<false, false>);
-  set((const void*)k_mlp_gateup<false, true>);
-  set((const void*)k_mlp_gateup<true, false>);
-  set((const void*)k_mlp_gateup<true, true>);
-  set((const void*)k_mlp_gemm_nt<false>);
-  set((const void*)k_mlp_gemm_nt<true>);
+  set((const void*)k_mlp_gateup<Tile16, false, false>);
+  set((const void*)k_mlp_gateup<Tile16, false, true>);
+  set((const void*)k_mlp_gateup<Tile16, true, false>);
+  set((const void*)k_mlp_gateup<Tile16, true, true>);
+  set((const void*)k_mlp_gateup<Tile16Half, false, false>);
+  set((const void*)k_mlp_gateup<Tile16Half, true, false>);
+  set((const void*)k_mlp_gemm_nt<Tile16, false>);
+  set((const void*)k_mlp_gemm_nt<Tile16, true>);
+  set((const void*)k_mlp_gemm_nt<Tile16Half, false>);
   set_small_attributes<Tile128>(set);
   set_small_attributes<Tile128Lone>(set);
   set_small_attributes<Tile64>(set);
@@ -87,8 +90,8 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_mlp_gateup_small<Tile64Lone, true, true>);
   set((const void*)k_mlp_dx_dw3_small<Tile64Lone, Tile64Lone>);
   set((const void*)k_mlp_dx_dw3_small<Tile32, Tile64Lone>);
-  set((const void*)k_mlp_gemm_nn<false>);
-  set((const void*)k_mlp_gemm_nn<true>);
+  set((const void*)k_mlp_gemm_nn<Tile16, false>);
+  set((const void*)k_mlp_gemm_nn<Tile16, true>);
   set((const void*)k_mlp_dw3_small<Tile64>);
   set((const void*)k_mlp_dw3_small<Tile64Lone>);
   set((const void*)k_mlp_dw3<false, false>);
@@ -126,6 +129,10 @@ int rows_of(const Plan& p, int i) {
 //                  d = 768, I = 2304: dA 17 us (432 tiles) against 26 (108 of 256)
 //   128 x 128 lone 0.55 per K step + 3.2, up to kNumCu tiles.  1024 tokens, d = 4096, I = 14336: down 140 us (256 tiles)
 //                  against 308 (64 tiles of 256), dX 266 against 607
+//   128 x 256      0.68 per K step + 5, one round: between the 128 x 128 tiles that need two on a compute unit and the large
+//                  ones that leave half of them idle.  Gate/up of 200 tokens, d = 4096, I = 14336: 74 us (448 tiles of
+//                  128 x 128) -> 60 (224), down of 1300 tokens of it 182 -> 137; with two rounds slower than large tiles,
+//                  with K-strided weights as fast as 128 x 128
 //   64 x 64        0.45 (few workgroups on a compute unit) to 0.85 (four) per K step + 2.5.  1536 tokens, d = 1536,
 //                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256)
 //   64 x 64 lone   0.24 per K step + 2.5.  256 tokens, d = 256, I = 896: down 5.5 against 18; 200 tokens, d = 4096,
@@ -141,14 +148,14 @@ int rows_of(const Plan& p, int i) {
 // 64 x 64: step of 5003 tokens 1.31 -> 1.23 ms; dA of 4096 tokens, I = 14336 (896 tiles) as 768 large and 512 of
 // 128 x 128: 376 us against 412.  With all compute units busy a K step takes 1.36, with the K-strided weights of dA and
 // dX 1.4 also where some are idle; not split, by this, are the 1376 tiles of gate/up at I = 11008 (2 % slower split).
-enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long, k32 };   // MST_MLP_TILE_* of the header, in this order
+enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long, k32, kHalf };   // MST_MLP_TILE_* of the header, in this order
 struct TileChoice {
   TileKind kind;      // of the whole, or of what follows the first `head` columns
   int64_t head;       // A-side extent, a multiple of 256, that large tiles cover in a launch of its own (0: none)
   double us;
 };
 enum Weights { kGateUp, kContiguous, kStrided };                 // gate/up, down, dA and dX
-TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
+TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w, bool rest = false) {
   const bool strided = w == kStrided;
   const double k = (double)ksteps;
   TileChoice best = {kBig, 0, std::ceil(tiles_of(n_a, n_b, 256) / kNumCu) * ((strided ? 1.4 : 1.25) * k + 7.0)};
@@ -160,6 +167,7 @@ TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
   else consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : 0.3 + 0.7 * x) * (k + 4.0));
   consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.3 + 0.4 * y : 0.45) * k + 2.5);
   if (y <= 0.25 && ksteps >= 64) consider(k64Long, 0.22 * k + 3.5);
+  if (!strided && !rest && std::ceil((double)n_a / 128.0) * std::ceil((double)n_b / 256.0) <= kNumCu) consider(kHalf, 0.68 * k + 5.0);
   if (w != kGateUp && tiles_of(n_a, n_b, 64) <= (strided ? 64.0 : 128.0)) consider(k32, (strided ? 0.17 : 0.11) * k + 3.0);
   if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
@@ -169,7 +177,7 @@ TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
   const int64_t t_a = (n_a + kTile - 1) / kTile, t_b = (n_b + kTile - 1) / kTile;
   const int64_t full = t_a * t_b / kNumCu * kNumCu, cols = full / t_b;       // full rounds; columns of tiles in them
   if (cols == 0 || cols == t_a) return whole;
-  const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, w);
+  const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, w, true);
   const double t = (double)(full / kNumCu) * ((w == kStrided ? 1.4 : 1.36) * (double)ksteps + 7.0) + rest.us + 2.0;
   return rest.kind != kBig && t < whole.us ? TileChoice{rest.kind, cols * kTile, t} : whole;
 }
@@ -262,10 +270,16 @@ template <bool kBackward>
 void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
                    __bf16* A, __bf16* dAG, __bf16* dU) {
   const TileChoice c = gateup_tile(rows, d, I);
+  if (c.kind == kHalf) {
+    const int n_it = (I + Tile16Half::EA / 2 - 1) / (Tile16Half::EA / 2), n_st = (rows + Tile16Half::EB - 1) / Tile16Half::EB;
+    hipLaunchKernelGGL((k_mlp_gateup<Tile16Half, kBackward, false>), dim3(even_grid(n_it, n_st)), dim3(kThreads), kLdsBytes, st,
+                       X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
+    return;
+  }
   const int i0 = (int)(c.head / 2), n_i = I - i0;               // the second launch's indices
   if (c.kind == kBig || i0) {
     const int n_it = ((i0 ? i0 : I) + kGateUpI - 1) / kGateUpI, n_st = (rows + kTile - 1) / kTile;
-    const auto kernel = use_super_tiles(n_it, n_st) ? k_mlp_gateup<kBackward, true> : k_mlp_gateup<kBackward, false>;
+    const auto kernel = use_super_tiles(n_it, n_st) ? k_mlp_gateup<Tile16, kBackward, true> : k_mlp_gateup<Tile16, kBackward, false>;
     hipLaunchKernelGGL(kernel, dim3(mlp_grid(n_it, n_st)), dim3(kThreads), kLdsBytes, st,
                        X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
   }
@@ -292,10 +306,16 @@ void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows,
 }
 void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
   const TileChoice c = nt_tile(rows, N, K);
+  if (c.kind == kHalf) {
+    const int n_nt = (N + Tile16Half::EA - 1) / Tile16Half::EA, n_st = (rows + Tile16Half::EB - 1) / Tile16Half::EB;
+    hipLaunchKernelGGL((k_mlp_gemm_nt<Tile16Half, false>), dim3(even_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
+                       P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
+    return;
+  }
   const int n0 = (int)c.head;
   if (c.kind == kBig || n0) {
     const int n_nt = ((n0 ? n0 : N) + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
-    hipLaunchKernelGGL(use_super_tiles(n_nt, n_st) ? k_mlp_gemm_nt<true> : k_mlp_gemm_nt<false>, dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
+    hipLaunchKernelGGL((use_super_tiles(n_nt, n_st) ? k_mlp_gemm_nt<Tile16, true> : k_mlp_gemm_nt<Tile16, false>), dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
                        P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
   }
   Q += (size_t)n0 * K;
@@ -325,7 +345,7 @@ void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16*
   const int n0 = (int)c.head;
   if (c.kind == kBig || n0) {
     const int n = n0 ? n0 : N, n_nt = (n + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
-    hipLaunchKernelGGL(use_super_tiles(n_nt, n_st) ? k_mlp_gemm_nn<true> : k_mlp_gemm_nn<false>, dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
+    hipLaunchKernelGGL((use_super_tiles(n_nt, n_st) ? k_mlp_gemm_nn<Tile16, true> : k_mlp_gemm_nn<Tile16, false>), dim3(mlp_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
                        P1, Q1, P2, Q2, K, N, rows, n, K, n_st, n_nt, out, N);
   }
   Q1 += n0;

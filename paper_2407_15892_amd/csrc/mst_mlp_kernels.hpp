@@ -67,57 +67,58 @@ __device__ __forceinline__ float sigmoid_f(float g) { return fast_rcp(1.0f + fas
 //   up values of one (token, i) sit in the same lane and register of accumulators t and t + 4.
 //   B side = chunk rows (tokens).  A lane owns 4 tokens and 16 consecutive i for each: 32-byte stores.
 //   kBackward: dAG holds dA on entry and receives dG (same element, same lane); dU and A are written.
+//   T: the 256 x 256 tile, or half of it on the A side (64 indices).
 // ---------------------------------------------------------------------------
-constexpr int kGateUpI = 128;   // intermediate indices per workgroup
-template <bool kBackward, bool kSuper>
+constexpr int kGateUpI = 128;   // intermediate indices per workgroup of large tiles
+template <class T, bool kBackward, bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
     const __bf16* __restrict__ Xc, const __bf16* __restrict__ Wg, const __bf16* __restrict__ Wu,
     int rows, int d, int I, int n_st, int n_it,
     __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
+  constexpr int H = T::TA / 2, N = 4 * H;                       // gate tiles of a wave; consecutive indices of a lane
   int it, st;
   if (!mlp_tile<kSuper>(n_it, n_st, &it, &st)) return;
-  const int i0 = it * kGateUpI, s0 = st * kTile;
+  const int i0 = it * (T::EA / 2), s0 = st * T::EB;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wa = wave >> 2, wb = wave & 3;
 
-  f32x4 acc[kTA16][kTB16];
-  zero_acc<kTA16, kTB16>(acc);
-  PanelKC16<Tile16, kTile, kTA16, true> pa;
-  PanelKC16<Tile16, kTile, kTB16, false> pb;
+  f32x4 acc[T::TA][T::TB];
+  zero_acc<T::TA, T::TB>(acc);
+  PanelKC16<T, T::EA, T::TA, true> pa;
+  PanelKC16<T, T::EB, T::TB, false> pb;
   {
-    // A panel, per wave row of 128 LDS rows: MFMA tiles 0..3 are gate rows, tiles 4..7 the up rows of the same 64
-    // intermediate indices; LDS row 16 t + 4 g + r holds index 16 g + 4 (t % 4) + r, so that a lane's gate value
-    // acc[t][u][r] and up value acc[t + 4][u][r] belong to the same index and its 16 indices are consecutive.
-    // As a loader, wave w fills LDS rows 32 w .. 32 w + 31 (tiles 2 (w % 4), 2 (w % 4) + 1 of wave row w / 4).
-    const int q = wave & 3;
-    const int ib = i0 + 64 * (wave >> 2);                       // first index of the loader's wave row
-    const __bf16* src = (q < 2 ? Wg : Wu) + (size_t)ib * d;
+    // A panel, per wave row of 16 TA LDS rows: MFMA tiles 0..H-1 are gate rows, tiles H..2H-1 the up rows of the same 16 H
+    // intermediate indices; LDS row 16 t + 4 g + r holds index N g + 4 (t % H) + r, so that a lane's gate value
+    // acc[t][u][r] and up value acc[t + H][u][r] belong to the same index and its N indices are consecutive.
+    // As a loader, a wave fills an eighth of the LDS rows: they belong to one half (gate or up) of one wave row.
+    const int half = wave * (T::EA / 8) / (16 * H);
+    const int ib = i0 + 16 * H * (half >> 1);                   // first index of the loader's wave row
+    const __bf16* src = ((half & 1) ? Wu : Wg) + (size_t)ib * d;
     int valid = I - ib;
-    if (valid > 64) valid = 64;
+    if (valid > 16 * H) valid = 16 * H;
     pa.init_map(src, d, valid, d, wave, lane, wa,
-                [](int lrow) { const int m = lrow & 127; return 16 * ((m >> 2) & 3) + 4 * ((m >> 4) & 3) + (m & 3); }, false);
+                [](int lrow) { return N * ((lrow >> 2) & 3) + 4 * ((lrow >> 4) % H) + (lrow & 3); }, false);
   }
   pb.init(Xc + (size_t)s0 * d, d, rows - s0, d, wave, lane, wb);
-  gemm_mainloop_pp<Tile16>(acc, pa, pb, smem, 0, d, wa);
+  gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, d, wa);
 
-  const int ib = i0 + 64 * wa + 16 * (lane >> 4);              // this lane's 16 consecutive intermediate indices
+  const int ib = i0 + 16 * H * wa + N * (lane >> 4);           // this lane's N consecutive intermediate indices
 #pragma unroll
-  for (int u = 0; u < kTB16; ++u) {
-    const int s_local = s0 + wb * 64 + 16 * u + (lane & 15);
+  for (int u = 0; u < T::TB; ++u) {
+    const int s_local = s0 + wb * (16 * T::TB) + 16 * u + (lane & 15);
     if (s_local >= rows || ib >= I) continue;                  // I % 8 == 0: a group of 8 is inside or outside
     const size_t off = (size_t)s_local * I + ib;
-    const bool hi_ok = ib + 8 < I;
-    bf16x8 da[2];
+    bf16x8 da[N / 8], a_o[N / 8], g_o[N / 8], u_o[N / 8];
     if (kBackward) {
-      da[0] = *reinterpret_cast<const bf16x8*>(dAG + off);
-      if (hi_ok) da[1] = *reinterpret_cast<const bf16x8*>(dAG + off + 8);
-    }
-    bf16x8 a_o[2], g_o[2], u_o[2];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {                             // index ib + e: tile e / 4, register e % 4
-      const float g = acc[e >> 2][u][e & 3], up = acc[4 + (e >> 2)][u][e & 3];
+      for (int h = 0; h < N / 8; ++h)
+        if (ib + 8 * h < I) da[h] = *reinterpret_cast<const bf16x8*>(dAG + off + 8 * h);
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) {                              // index ib + e: tile e / 4, register e % 4
+      const float g = acc[e >> 2][u][e & 3], up = acc[H + (e >> 2)][u][e & 3];
       const float sg = sigmoid_f(g);
       const float act = g * sg;                                // silu(g)
       a_o[e >> 3][e & 7] = (__bf16)(act * up);
@@ -127,16 +128,15 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
         u_o[e >> 3][e & 7] = (__bf16)(dav * act);                                    // dA * silu(G)
       }
     }
-    *reinterpret_cast<bf16x8*>(A + off) = a_o[0];
-    if (hi_ok) *reinterpret_cast<bf16x8*>(A + off + 8) = a_o[1];
-    if (kBackward) {
-      *reinterpret_cast<bf16x8*>(dAG + off) = g_o[0];
-      *reinterpret_cast<bf16x8*>(dU + off) = u_o[0];
-      if (hi_ok) {
-        *reinterpret_cast<bf16x8*>(dAG + off + 8) = g_o[1];
-        *reinterpret_cast<bf16x8*>(dU + off + 8) = u_o[1];
+#pragma unroll
+    for (int h = 0; h < N / 8; ++h)
+      if (ib + 8 * h < I) {
+        *reinterpret_cast<bf16x8*>(A + off + 8 * h) = a_o[h];
+        if (kBackward) {
+          *reinterpret_cast<bf16x8*>(dAG + off + 8 * h) = g_o[h];
+          *reinterpret_cast<bf16x8*>(dU + off + 8 * h) = u_o[h];
+        }
       }
-    }
   }
 }
 
@@ -180,26 +180,26 @@ __device__ __forceinline__ void store_rows_bf16(const f32x4 (&acc)[T::TA][T::TB]
 // out[s][n] = sum_k P[s][k] Q[n][k]      (both operands K-contiguous; used for O_chunk = A Wd^T)
 //   A side = n (rows of Q, permuted so a lane holds 32 consecutive n), B side = s (rows of P)
 // ---------------------------------------------------------------------------
-template <bool kSuper>
+template <class T, bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nt(
     const __bf16* __restrict__ P, int ldp, const __bf16* __restrict__ Q, int ldq, int rows, int N, int K,
     int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int nt, st;
   if (!mlp_tile<kSuper>(n_nt, n_st, &nt, &st)) return;
-  const int n0 = nt * kTile, s0 = st * kTile;
+  const int n0 = nt * T::EA, s0 = st * T::EB;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wa = wave >> 2, wb = wave & 3;
 
-  f32x4 acc[kTA16][kTB16];
-  zero_acc<kTA16, kTB16>(acc);
-  PanelKC16<Tile16, kTile, kTA16, true> pa;
-  PanelKC16<Tile16, kTile, kTB16, false> pb;
+  f32x4 acc[T::TA][T::TB];
+  zero_acc<T::TA, T::TB>(acc);
+  PanelKC16<T, T::EA, T::TA, true> pa;
+  PanelKC16<T, T::EB, T::TB, false> pb;
   pa.init(Q + (size_t)n0 * ldq, ldq, N - n0, K, wave, lane, wa);
   pb.init(P + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
-  gemm_mainloop_pp<Tile16>(acc, pa, pb, smem, 0, K, wa);
-  store_rows_bf16<Tile16>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
+  gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, K, wa);
+  store_rows_bf16<T>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -236,7 +236,7 @@ __device__ __forceinline__ void nn_tile(
   }
   store_rows_bf16<T>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
 }
-template <bool kSuper>
+template <class T, bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int nt, st;
   if (!mlp_tile<kSuper>(n_nt, n_st, &nt, &st)) return;
-  nn_tile<Tile16>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, nt, st, out, ldo, smem);
+  nn_tile<T>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, nt, st, out, ldo, smem);
 }
 
 // ---------------------------------------------------------------------------

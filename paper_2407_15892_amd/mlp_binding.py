@@ -111,7 +111,7 @@ def mst_mlp_bwd(X, Wg, Wu, Wd, dO, M: int, workspace, dX, dWg, dWu, dWd, stream=
         _ptr(dX), _ptr(dWg), _ptr(dWu), _ptr(dWd), _stream_handle(stream)))
 
 
-MLP_TILES = ("256", "128", "128_lone", "64", "64_lone", "64_long", "32")     # MST_MLP_TILE_*
+MLP_TILES = ("256", "128", "128_lone", "64", "64_lone", "64_long", "32", "128x256")     # MST_MLP_TILE_*
 
 
 def mst_mlp_tile_info(rows: int, d: int, I: int) -> dict:

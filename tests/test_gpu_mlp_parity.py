@@ -282,3 +282,18 @@ def test_launches_of_small_problems_match_oracle_and_keep_their_bits(S, d, I, ki
     _, got, _ = _run_all(wide, M=1)
     for k in ("O", "dX"):
         assert np.array_equal(got[k][C:], base[k]), k
+
+
+@pytest.mark.parametrize("S,d,I,products,M", [
+    (1281, 4104, 2056, ("gateup", "down"), 3),    # last tiles of one row, of 8 indices and columns
+    (700, 1032, 4104, ("gateup",), 2),
+])
+def test_tiles_of_128_by_256_match_oracle_and_keep_their_bits(S, d, I, products, M):
+    import paper_2407_15892_amd as mst
+    whole, split = mst.mst_mlp_tile_info(S, d, I), mst.mst_mlp_tile_info(-(-S // M), d, I)
+    assert all(whole[p][0] == "128x256" != split[p][0] for p in products)
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=350 + S % 7, w_std=0.05))
+    _, base, _, _ = _check(inp, M=1)
+    _, got, _ = _run_all(inp, M=M)
+    for k in ("O", "dX"):
+        assert np.array_equal(got[k], base[k]), k
