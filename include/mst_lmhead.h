@@ -262,7 +262,8 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
  * Both write the tile of workgroup `workgroup` and return 1, or return 0 for a padding workgroup (it exits at once), or
  * -1 for bad arguments.  Every tile is the image of exactly one workgroup.
  *
- * mst_tile_info (host, pure): info[0] = rows of the forward's tiles (256 vocabulary entries by 64 or 256 rows),
+ * mst_tile_info (host, pure): info[0] = the forward's tiles, 64 (256 vocabulary entries by 64 or 32 rows) or 256 (by 256 or
+ * 128; mst_forward_tile_rows, host, pure, names the rows, -1 for bad arguments),
  * info[1..3] = edge of the dlogits, dH and dW tiles in the pair order where each has launches of its own (64 or 256).
  *
  * mst_pair_launches (host, pure): how the pair order launches the three products, -1 for bad arguments.  The joint forms
@@ -277,6 +278,7 @@ enum {
   MST_PAIR_KSPLIT_64X32,
   MST_PAIR_SPLIT              /* one mini-sequence: split partials        */
 };
+int32_t mst_forward_tile_rows(int64_t S, int64_t d, int64_t V, int32_t M);
 int32_t mst_pair_launches(int64_t S, int64_t d, int64_t V, int32_t M);
 int32_t mst_tile_grid(int32_t n_slow, int32_t n_fast);
 int32_t mst_tile_of_workgroup(int32_t n_slow, int32_t n_fast, int32_t order, int32_t workgroup,

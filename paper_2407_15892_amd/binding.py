@@ -86,6 +86,8 @@ def load_library() -> ctypes.CDLL:
     lib.mst_dh_tile_of_workgroup.argtypes = [c.c_int32] * 5 + [i32p] * 3
     lib.mst_tile_info.restype = c.c_int
     lib.mst_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.POINTER(c.c_int64)]
+    lib.mst_forward_tile_rows.restype = c.c_int32
+    lib.mst_forward_tile_rows.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_pair_launches.restype = c.c_int32
     lib.mst_pair_launches.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_profile_enable.restype = c.c_int
@@ -210,10 +212,15 @@ def mst_bwd_schedule_info(S: int, d: int, V: int, M: int, schedule: Optional[int
 
 
 def mst_tile_info(S: int, d: int, V: int, M: int) -> dict:
-    """Rows of the forward's tiles, edges of the pair order's dlogits, dH and dW tiles."""
+    """Class of the forward's tiles, edges of the pair order's dlogits, dH and dW tiles."""
     info = (ctypes.c_int64 * 4)()
     _check(load_library().mst_tile_info(S, d, V, M, info))
     return dict(zip(("fwd", "dlogits", "dh", "dw"), (int(x) for x in info)))
+
+
+def mst_forward_tile_rows(S: int, d: int, V: int, M: int) -> int:
+    """Rows of the forward's tiles (256 vocabulary entries wide)."""
+    return int(load_library().mst_forward_tile_rows(S, d, V, M))
 
 
 PAIR_LAUNCHES = ("separate", "32x16", "64x16", "64x32", "split")     # MST_PAIR_*

@@ -439,7 +439,9 @@ bool set_kernel_attributes() {   // on the current device
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess) ok = false;
   };
   set((const void*)k_fwd_gemm_lse);
-  set((const void*)k_fwd_gemm_lse_small<TileFwdSmall>);
+  set((const void*)k_fwd_gemm_lse_small<TileFwd64>);
+  set((const void*)k_fwd_gemm_lse_small<TileFwd32>);
+  set((const void*)k_fwd_gemm_lse_rows128);
   set((const void*)k_bwd_gemm_dlogits_small<Tile64>);
   set((const void*)k_bwd_gemm_dlogits_small<Tile64Lone>);
   set((const void*)k_bwd_gemm_dh_small<Tile64>);
@@ -487,24 +489,41 @@ mst_status prepare_device() {
   return MST_OK;
 }
 
-// Few tiles: 64 rows each, as long as every workgroup has a compute unit to itself (same bits).  The groups after the first
-// are not larger.
-bool small_forward(const Plan& p) {
+// Rows of the forward's tiles (256 vocabulary entries wide; the same bits): the fewest of 32, 64 and 128 with which every
+// workgroup has a compute unit to itself, else 256.  The groups after the first are not larger.  256 -> 128 rows: 200 rows,
+// d = 4096, V = 32000: 83 us -> 64; 1000 rows, d = 512, V = 8000: 23 -> 19.  64 -> 32: 250 rows, d = 1024, V = 4000: 17.4 -> 13.3.
+int forward_tile_rows(const Plan& p) {
   const int64_t rows = p.S < p.fwd_group_rows ? p.S : p.fwd_group_rows;
-  return (rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB * p.n_vt <= kNumCu;
+  for (const int e : {32, 64, 128})
+    if ((rows + e - 1) / e * p.n_vt <= kNumCu) return e;
+  return kTile;
+}
+// The forward's large launch is persistent (TileFeed) where it takes long: balancing the XCDs is worth 2 % of it, the queues'
+// launch, the first fetch and the synchronisation per tile cost 10 to 20 us.  Rounds of tiles times K steps, persistent or not:
+// 1984 (4096 rows, d = 4096, V = 128256) 2860 us against 2878, 647: 1096 against 1117, 592: the same, 499: 773 against 755,
+// 128 (200 rows, d = 4096, V = 128256): 252 against 234.
+constexpr int64_t kPersistentSteps = 600;
+bool persistent_forward(const Plan& p, int64_t grid) {
+  return (grid + kNumCu - 1) / kNumCu * ((p.d + kBK - 1) / kBK) >= kPersistentSteps;
+}
+
+// One workgroup finishes the forward call: a row per thread, its pairs in registers.  At 8192 pairs (512 rows, V = 4096) the
+// call takes 12.5 us instead of 15.0, at 9600 15.2 instead of 17.1, at 32000 1 us more.
+bool finalize_in_one(const Plan& p) {
+  return p.S <= 1024 && p.S <= p.fwd_group_rows && p.n_vt <= kFinOneTiles && p.S * p.n_vt <= 12288;
 }
 
 // forward pass over all chunks: writes lse (if non-null) and nll (if non-null)
 // `ctl`: its queues serve persistent forward launches (nullptr: one workgroup per tile)
 mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, const int32_t* labels,
-                              int ignore_index, char* ws, float* lse, float* nll, hipStream_t st, Control* ctl = nullptr) {
+                              int ignore_index, char* ws, float* lse, float* nll, hipStream_t st, Control* ctl = nullptr, bool finalize = true) {
   float* tgt = reinterpret_cast<float*>(ws + p.f_tgt);
   float2* part = reinterpret_cast<float2*>(ws + p.f_part);
   const size_t stride = (size_t)p.fwd_group_rows;
   auto rows_of_group = [&](int64_t g0) { return (p.S - g0) < p.fwd_group_rows ? (p.S - g0) : p.fwd_group_rows; };
-  const bool small = small_forward(p);      // otherwise persistent workgroups where there is more than one round of tiles
-  const int64_t tiles_first = (int64_t)xcd_grid_2d(p.n_vt, (int)((rows_of_group(0) + kTile - 1) / kTile));
-  int* queue = ctl && !small && tiles_first > kNumCu ? ctl->queue : nullptr;
+  const int tile_rows = forward_tile_rows(p);
+  const int64_t grid_first = (int64_t)xcd_grid_2d(p.n_vt, (int)((rows_of_group(0) + kTile - 1) / kTile));
+  int* queue = ctl && tile_rows == kTile && persistent_forward(p, grid_first) ? ctl->queue : nullptr;
   int queue_base = 0;
   if (queue) {
     Scope sc(st, MST_K_LABEL_SCAN);
@@ -515,23 +534,25 @@ mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, c
     // One launch for the group's mini-sequences.  Rows are independent and no logits are stored, so the row tiles
     // of the launch need not respect the boundaries between the mini-sequences of the group: a mini-sequence
     // shorter than a 256-row tile costs no idle tile rows, and every row's result is bit-identical for every M.
-    if (small) {
+    const int n_st = (int)((g_rows + tile_rows - 1) / tile_rows);
+    if (tile_rows == kTile) {
       Scope sc(st, MST_K_FWD_GEMM_LSE);
-      const int n_st = (int)((g_rows + TileFwdSmall::EB - 1) / TileFwdSmall::EB);
-      hipLaunchKernelGGL(k_fwd_gemm_lse_small<TileFwdSmall>, dim3(even_grid(p.n_vt, n_st)), dim3(TileFwdSmall::kThreads),
-                         TileFwdSmall::kLds, st, H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_st, p.n_vt,
-                         part, stride, tgt);
-    } else {
-      Scope sc(st, MST_K_FWD_GEMM_LSE);
-      const int n_st = (int)((g_rows + kTile - 1) / kTile);
       const int tiles = xcd_grid_2d(p.n_vt, n_st);
       const int grid = queue && tiles > kNumCu ? kNumCu : tiles;
       hipLaunchKernelGGL(k_fwd_gemm_lse, dim3(grid), dim3(kThreads), kLdsBytes, st,
                          H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_st, p.n_vt,
                          part, stride, tgt, queue, queue_base);
       queue_base += tiles / kNumXcd + grid;
+    } else {
+      Scope sc(st, MST_K_FWD_GEMM_LSE);
+      const auto kernel = tile_rows == 128 ? k_fwd_gemm_lse_rows128
+                        : tile_rows == 64 ? k_fwd_gemm_lse_small<TileFwd64> : k_fwd_gemm_lse_small<TileFwd32>;
+      const int threads = tile_rows == 128 ? kThreads : TileFwd64::kThreads;
+      const int lds = tile_rows == 128 ? Tile16Rows128::kLds : tile_rows == 64 ? TileFwd64::kLds : TileFwd32::kLds;
+      hipLaunchKernelGGL(kernel, dim3(even_grid(p.n_vt, n_st)), dim3(threads), lds, st,
+                         H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_st, p.n_vt, part, stride, tgt);
     }
-    {
+    if (finalize) {
       Scope sc(st, MST_K_LSE_FINALIZE);
       hipLaunchKernelGGL(k_lse_finalize, dim3((unsigned)((g_rows + kFinRows - 1) / kFinRows)), dim3(kFinRows * kFinGroups), 0, st,
                          part, stride, p.n_vt, tgt, labels + g0, (int)g_rows, (int)p.V, ignore_index,
@@ -565,11 +586,16 @@ mst_status enqueue_forward(const Plan& p, const void* H, const void* W, const in
                            char* ws, float* loss, float* lse, int64_t* n_valid, void* stream) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   float* nll = reinterpret_cast<float*>(ws + p.f_nll);
+  const bool one = finalize_in_one(p);
   const mst_status s = run_forward_chunks(p, static_cast<const __bf16*>(H), static_cast<const __bf16*>(W), labels, ignore_index,
-                                          ws, lse, nll, st, reinterpret_cast<Control*>(ws));
+                                          ws, lse, nll, st, reinterpret_cast<Control*>(ws), !one);
   if (s != MST_OK) return s;
-  {
-    Scope sc(st, MST_K_LOSS_REDUCE);
+  Scope sc(st, MST_K_LOSS_REDUCE);
+  if (one) {
+    hipLaunchKernelGGL(k_finalize_loss, dim3(1), dim3(1024), 0, st, reinterpret_cast<const float2*>(ws + p.f_part),
+                       (size_t)p.fwd_group_rows, p.n_vt, reinterpret_cast<const float*>(ws + p.f_tgt), labels, (int)p.S, (int)p.V,
+                       ignore_index, lse, loss, reinterpret_cast<long long*>(n_valid));
+  } else {
     hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(1024), 0, st, nll, labels, (long long)p.S, (int)p.V, ignore_index, loss,
                        reinterpret_cast<long long*>(n_valid));
   }
@@ -969,6 +995,12 @@ int32_t mst_dh_tile_of_workgroup(int32_t even, int32_t n_split, int32_t n_row_ti
   return ok ? 1 : 0;
 }
 
+int32_t mst_forward_tile_rows(int64_t S, int64_t d, int64_t V, int32_t M) {
+  Plan p;
+  if (make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false) != MST_OK) return -1;
+  return forward_tile_rows(p);
+}
+
 int32_t mst_pair_launches(int64_t S, int64_t d, int64_t V, int32_t M) {
   Plan p;
   if (make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_PAIRS) != MST_OK) return -1;
@@ -980,7 +1012,7 @@ mst_status mst_tile_info(int64_t S, int64_t d, int64_t V, int32_t M, int64_t* in
   Plan p;
   const mst_status s = make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false);
   if (s != MST_OK) return s;
-  info[0] = small_forward(p) ? TileFwdSmall::EB : kTile;
+  info[0] = forward_tile_rows(p) <= 64 ? 64 : kTile;
   info[1] = p.small_dlogits ? Tile64::EA : kTile;
   info[2] = p.small_dh ? Tile64::EA : kTile;
   info[3] = p.small_dw ? Tile64::EA : kTile;

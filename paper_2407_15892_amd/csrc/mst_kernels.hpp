@@ -29,6 +29,8 @@ namespace mst {
 typedef Cfg16<2, 4, 8, 4, 64, 3, 2> Tile16;
 // half of it on the A side, with three stages of both panels: tiles that share a launch with others and would be its end
 typedef Cfg16<2, 4, 4, 4, 64, 3, 3> Tile16Half;
+// half of it on the B side
+typedef Cfg16<2, 4, 8, 2, 64, 3, 3> Tile16Rows128;
 constexpr int kTA16 = Tile16::TA, kTB16 = Tile16::TB;
 constexpr int kTile = 256;             // Tile16::EA == Tile16::EB
 constexpr int kBK = Tile16::BK;
@@ -160,7 +162,7 @@ inline int launch_grid(bool even, int n_slow, int n_fast) { return even ? even_g
 // the third A stage.  The fetch for the tile after this one is issued at the start of a tile and collected behind
 // the first operand loads of its main loop.
 //
-// Only the forward launch works this way.  It runs 250 rounds of tiles at the benchmark shape, so a difference of a
+// Only the forward launch works this way, where it is long (persistent_forward in mst_api.hip).  It runs 250 rounds of tiles at the benchmark shape, so a difference of a
 // few per cent between XCDs adds up to several whole tiles (forward pass -2.3 %, same-box A/B); the backward launches
 // run 2 to 8 rounds, the difference never reaches one tile, and the queue bought nothing there (dlogits -0.2 %,
 // dH + dW 0).
@@ -305,6 +307,18 @@ __device__ __forceinline__ void merge_lse(float& m, float& l, float m2, float l2
   m = mm;
 }
 
+// the same for N pairs at once: one maximum, then the terms in order.  A pair (kMasked, 0) adds nothing, to the bit.
+template <int N>
+__device__ __forceinline__ void fold_lse(float& m, float& l, const float2 (&p)[N]) {
+  float mm = m;
+#pragma unroll
+  for (int i = 0; i < N; ++i) mm = fmaxf(mm, p[i].x);
+  l *= fast_exp2((m - mm) * kLog2e);
+#pragma unroll
+  for (int i = 0; i < N; ++i) l = __builtin_fmaf(p[i].y, fast_exp2((p[i].x - mm) * kLog2e), l);
+  m = mm;
+}
+
 // Running log-sum-exp partials and target logits from the accumulators of a 256-entry vocabulary tile (wave grid 2 x WB,
 // TB row tiles per wave).
 template <int TB>
@@ -421,13 +435,38 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemm_lse(
   }
 }
 
-// per row: combine the vocab-tile partials into lse and nll.  A workgroup owns 64 rows; its 16
-// waves each fold every 16th vocabulary tile in ascending order, then the 16 partial results are
-// folded in wave order: the combination order is fixed, so lse is reproducible bit for bit.  The pairs are loaded eight
-// at a time: folded one by one, every load waited for the exponentials before it.
+// The same with tiles of 128 rows, one workgroup per tile, for problems whose 256-row tiles would leave half of the chip
+// idle or more.
+__global__ __launch_bounds__(kThreads) void k_fwd_gemm_lse_rows128(
+    const __bf16* __restrict__ Hc, const __bf16* __restrict__ W, const int* __restrict__ labels_c,
+    int rows, int d, int V, int n_st, int n_vt, float2* __restrict__ part, size_t part_stride, float* __restrict__ tgt) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  typedef Tile16Rows128 T;
+  static_assert(T::EA == kTile && T::TA == kTA16, "one pair per row and 256 vocabulary entries");
+  int vt, st;
+  if (!even_tile_of_block(blockIdx.x, n_vt, n_st, &vt, &st)) return;
+  const int v0 = vt * kTile, s0 = st * T::EB;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wa = wave / T::WB, wb = wave % T::WB;
+  f32x4 acc[T::TA][T::TB];
+  zero_acc<T::TA, T::TB>(acc);
+  PanelKC16<T, T::EA, T::TA, true> pa;
+  PanelKC16<T, T::EB, T::TB, false> pb;
+  pa.init(W + (size_t)v0 * d, d, V - v0, d, wave, lane, wa);
+  pb.init(Hc + (size_t)s0 * d, d, rows - s0, d, wave, lane, wb);
+  gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, d, wa);
+  lse_epilogue<T::TB>(acc, labels_c, rows, V, vt, s0, part, part_stride, tgt, wa, wb, lane, smem);
+}
+
+// per row: combine the vocab-tile partials into lse and nll.  A workgroup owns 16 rows; its 16 groups of threads each fold
+// every 16th vocabulary tile, sixteen pairs at a time in ascending order, then the 16 results are folded in group order: the
+// combination order is fixed, so lse is reproducible bit for bit.  Bound by latency: of the loads (sixteen in flight, also at
+// the end), of the exponentials (independent of each other within a batch; pair by pair every one waited for the last), and
+// by what one compute unit can load (64 rows per workgroup: 256 KB of pairs at V = 128256).  200 rows, V = 128256: 11 -> 6 us.
 // (Summing the loss in the workgroup that finishes last was slower than a launch of its own: the device-scope release
 // and acquire around its counter took 6 to 16 us.)
-constexpr int kFinRows = 64;
+constexpr int kFinRows = 16;
 constexpr int kFinGroups = 16;
 __global__ __launch_bounds__(kFinRows * kFinGroups) void k_lse_finalize(
     const float2* __restrict__ part, size_t part_stride, int n_vt, const float* __restrict__ tgt,
@@ -437,23 +476,27 @@ __global__ __launch_bounds__(kFinRows * kFinGroups) void k_lse_finalize(
   const int r = threadIdx.x & (kFinRows - 1), g = threadIdx.x / kFinRows;
   const int s = blockIdx.x * kFinRows + r;
   float m = kMasked, l = 0.f;
-  auto fold = [&](float2 p) { merge_lse(m, l, p.x, p.y); };
   if (s < rows) {
-    constexpr int kAhead = 8;
-    int vt = g;
-    for (; vt + (kAhead - 1) * kFinGroups < n_vt; vt += kAhead * kFinGroups) {
-      float2 p[kAhead];
+    constexpr int kBatch = 16;
+    for (int v0 = g; v0 < n_vt; v0 += kBatch * kFinGroups) {
+      float2 p[kBatch];
 #pragma unroll
-      for (int i = 0; i < kAhead; ++i) p[i] = part[(size_t)(vt + i * kFinGroups) * part_stride + s];
-#pragma unroll
-      for (int i = 0; i < kAhead; ++i) fold(p[i]);
+      for (int i = 0; i < kBatch; ++i) {
+        const int vt = v0 + i * kFinGroups;
+        p[i] = vt < n_vt ? part[(size_t)vt * part_stride + s] : make_float2(kMasked, 0.f);
+      }
+      fold_lse(m, l, p);
     }
-    for (; vt < n_vt; vt += kFinGroups) fold(part[(size_t)vt * part_stride + s]);
   }
   sh[g][r] = make_float2(m, l);
   __syncthreads();
   if (g != 0 || s >= rows) return;
-  for (int q = 1; q < kFinGroups; ++q) fold(sh[q][r]);
+  float2 p[kFinGroups];
+#pragma unroll
+  for (int q = 0; q < kFinGroups; ++q) p[q] = sh[q][r];
+  m = kMasked;
+  l = 0.f;
+  fold_lse(m, l, p);
   const float log_l = __builtin_amdgcn_logf(l) * kLn2;     // v_log_f32 is log2
   const float lse = m + log_l;
   const int y = labels_c[s];
@@ -464,15 +507,42 @@ __global__ __launch_bounds__(kFinRows * kFinGroups) void k_lse_finalize(
   if (nll_c) nll_c[s] = valid ? (m - tgt[s]) + log_l : 0.f;
 }
 
+// sum of every thread's `a` (1024 threads) in a fixed order / number of valid labels
+__device__ __forceinline__ void reduce_loss(double a, long long nv, int nb, float* __restrict__ loss, long long* __restrict__ n_valid_out) {
+  __shared__ double sh[1024];
+  __shared__ long long s_valid[16];
+  __shared__ int s_bad[16];
+  sh[threadIdx.x] = a;
+  for (int o = 32; o > 0; o >>= 1) {
+    nv += __shfl_xor(nv, o);
+    nb += __shfl_xor(nb, o);
+  }
+  if ((threadIdx.x & 63) == 0) { s_valid[threadIdx.x >> 6] = nv; s_bad[threadIdx.x >> 6] = nb; }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  // thread t of the first wave: entries t, t + 64, ..., paired as by halving 1024 down to 64, then with its neighbours
+  double v[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = sh[threadIdx.x + 64 * k];
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < o; ++k) v[k] += v[k + o];
+  for (int o = 32; o > 0; o >>= 1) v[0] += __shfl_down(v[0], o);
+  if (threadIdx.x == 0) {
+    long long tv = 0; int tb = 0;
+    for (int k = 0; k < 16; ++k) { tv += s_valid[k]; tb += s_bad[k]; }
+    *loss = tb > 0 ? __builtin_nanf("") : tv > 0 ? (float)(v[0] / (double)tv) : 0.f;
+    if (n_valid_out) *n_valid_out = tb > 0 ? -1 : tv;
+  }
+}
+
 // loss = sum(nll) / n_valid, fixed summation order, fp64 accumulation; counts and range-checks the labels on the way (one
 // launch less than with a scan in front of the GEMM).  One workgroup, bound by the latency of its loads: eight rounds of
 // them at a time.
 __global__ __launch_bounds__(1024) void k_loss_reduce(const float* __restrict__ nll, const int* __restrict__ labels, long long S,
                                                       int V, int ignore_index, float* __restrict__ loss,
                                                       long long* __restrict__ n_valid_out) {
-  __shared__ double sh[1024];
-  __shared__ long long s_valid[16];
-  __shared__ int s_bad[16];
   double a = 0.0;
   long long nv = 0;
   int nb = 0;
@@ -492,23 +562,47 @@ __global__ __launch_bounds__(1024) void k_loss_reduce(const float* __restrict__ 
     for (int k = 0; k < 8; ++k) add(x[k], y[k]);
   }
   for (; i < S; i += 1024) add(nll[i], labels[i]);
-  sh[threadIdx.x] = a;
-  for (int o = 32; o > 0; o >>= 1) {
-    nv += __shfl_xor(nv, o);
-    nb += __shfl_xor(nb, o);
+  reduce_loss(a, nv, nb, loss, n_valid_out);
+}
+
+// lse, nll, loss and label count from one workgroup, for calls of a few rows and vocabulary tiles (see finalize_in_one in
+// mst_api.hip), where a launch takes 3 us whatever it does.  One thread per row, all of a row's pairs in flight at once;
+// folded in the order of k_lse_finalize (group by group, then the groups), the loss summed in that of k_loss_reduce.
+constexpr int kFinOneTiles = 32;       // most vocabulary tiles, so that a row's pairs fit into registers
+__global__ __launch_bounds__(1024) void k_finalize_loss(
+    const float2* __restrict__ part, size_t part_stride, int n_vt, const float* __restrict__ tgt,
+    const int* __restrict__ labels, int rows, int V, int ignore_index, float* __restrict__ lse_out,
+    float* __restrict__ loss, long long* __restrict__ n_valid_out) {
+  const int s = threadIdx.x;
+  float nll = 0.f;
+  long long nv = 0;
+  int nb = 0;
+  if (s < rows) {
+    float2 p[kFinOneTiles];
+#pragma unroll
+    for (int vt = 0; vt < kFinOneTiles; ++vt) p[vt] = vt < n_vt ? part[(size_t)vt * part_stride + s] : make_float2(kMasked, 0.f);
+    const float z_y = tgt[s];
+    const int y = labels[s];
+    float2 groups[kFinGroups];
+#pragma unroll
+    for (int g = 0; g < kFinGroups; ++g) {
+      float2 q[kFinOneTiles / kFinGroups];
+#pragma unroll
+      for (int i = 0; i < kFinOneTiles / kFinGroups; ++i) q[i] = p[g + i * kFinGroups];
+      groups[g] = make_float2(kMasked, 0.f);
+      fold_lse(groups[g].x, groups[g].y, q);
+    }
+    float m = kMasked, l = 0.f;
+    fold_lse(m, l, groups);
+    const float log_l = __builtin_amdgcn_logf(l) * kLn2;
+    const bool valid = (y != ignore_index) && ((unsigned)y < (unsigned)V);
+    if (lse_out) lse_out[s] = m + log_l;
+    nll = valid ? (m - z_y) + log_l : 0.f;
+    if (y != ignore_index) {
+      if ((unsigned)y < (unsigned)V) nv = 1; else nb = 1;
+    }
   }
-  if ((threadIdx.x & 63) == 0) { s_valid[threadIdx.x >> 6] = nv; s_bad[threadIdx.x >> 6] = nb; }
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    long long tv = 0; int tb = 0;
-    for (int k = 0; k < 16; ++k) { tv += s_valid[k]; tb += s_bad[k]; }
-    *loss = tb > 0 ? __builtin_nanf("") : tv > 0 ? (float)(sh[0] / (double)tv) : 0.f;
-    if (n_valid_out) *n_valid_out = tb > 0 ? -1 : tv;
-  }
+  reduce_loss((double)nll, nv, nb, loss, n_valid_out);
 }
 
 // ---------------------------------------------------------------------------

@@ -14,8 +14,9 @@
 
 namespace mst {
 
-// forward: 256 x 64 tiles, pipelined, one workgroup per compute unit (120 KB of LDS)
-typedef CfgSmall<8, 2, 3, 3, true> TileFwdSmall;
+// forward: 256 x 64 and 256 x 32 tiles, pipelined, one workgroup per compute unit (120 and 144 KB of LDS)
+typedef CfgSmall<8, 2, 3, 3, true> TileFwd64;
+typedef CfgSmall<8, 1, 4, 4, true> TileFwd32;
 // 64 x 64: several workgroups on a compute unit, or pipelined for a lone one
 typedef CfgSmall<2, 2, 3, 2, false> Tile64;
 typedef CfgSmall<2, 2, 5, 5, true> Tile64Lone;

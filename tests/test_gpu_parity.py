@@ -188,6 +188,28 @@ def test_forward_tiles_of_either_size_give_the_same_bits():
         assert nv == ref_o[3] and bits[0] == ref[0] and np.array_equal(bits[1], ref[1]), f"M = {M}"
 
 
+@pytest.mark.parametrize("S,d,V,rows_of_m", [
+    (1100, 264, 8005, {1: 256, 100: 128, 150: 64, 1100: 32}),     # ragged in every dimension, last row tiles of 76, 12, 31, 29
+    (300, 72, 8005, {1: 64, 300: 32}),      # M = 1: lse, nll and loss from one workgroup, 32 vocabulary tiles
+    (2, 8, 300, {1: 32, 2: 32}),
+    (1024, 40, 2817, {1: 64, 1024: 32}),    # the most rows and pairs that one workgroup finishes
+])
+def test_forward_tiles_of_every_size_give_the_same_bits(S, d, V, rows_of_m):
+    import paper_2407_15892_amd as mst
+    DeviceRun, _ = _harness()
+    inp = mi.make_inputs(mi.custom_config(S, d, V, 1, index=442, w_std=0.3, ignore_frac=0.07, label_dist="zipf"))
+    loss_ref, lse_ref, _, nv_ref = orc.lmhead_ce_forward(inp.H_f64(), inp.W_f64(), inp.labels, inp.ignore_index)
+    first = None
+    for M, rows in rows_of_m.items():
+        assert mst.mst_forward_tile_rows(S, d, V, M) == rows
+        loss, lse, nv = DeviceRun(inp, M=M).forward()
+        bits = (np.float32(loss).view(np.uint32), lse.astype(np.float32).view(np.uint32))
+        first = bits if first is None else first
+        assert nv == nv_ref and abs(loss - loss_ref) <= LOSS_RTOL * abs(loss_ref)
+        assert np.abs(lse - lse_ref).max() <= 1e-5 * np.abs(lse_ref).max()
+        assert bits[0] == first[0] and np.array_equal(bits[1], first[1]), f"M = {M}"
+
+
 def test_dW_and_dH_bit_identical_across_runs():
     DeviceRun, _ = _harness()
     import torch
