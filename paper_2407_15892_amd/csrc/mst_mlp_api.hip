@@ -9,6 +9,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 namespace {
 
@@ -132,7 +133,8 @@ int rows_of(const Plan& p, int i) {
 //   128 x 256      0.68 per K step + 5, one round: between the 128 x 128 tiles that need two on a compute unit and the large
 //                  ones that leave half of them idle.  Gate/up of 200 tokens, d = 4096, I = 14336: 74 us (448 tiles of
 //                  128 x 128) -> 60 (224), down of 1300 tokens of it 182 -> 137; with two rounds slower than large tiles,
-//                  with K-strided weights as fast as 128 x 128
+//                  with K-strided weights as fast as 128 x 128.  Behind full rounds of large tiles: forward of 1024 tokens,
+//                  I = 11008: 265 us -> 253
 //   64 x 64        0.45 (few workgroups on a compute unit) to 0.85 (four) per K step + 2.5.  1536 tokens, d = 1536,
 //                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256)
 //   64 x 64 lone   0.24 per K step + 2.5.  256 tokens, d = 256, I = 896: down 5.5 against 18; 200 tokens, d = 4096,
@@ -155,7 +157,7 @@ struct TileChoice {
   double us;
 };
 enum Weights { kGateUp, kContiguous, kStrided };                 // gate/up, down, dA and dX
-TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w, bool rest = false) {
+TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
   const bool strided = w == kStrided;
   const double k = (double)ksteps;
   TileChoice best = {kBig, 0, std::ceil(tiles_of(n_a, n_b, 256) / kNumCu) * ((strided ? 1.4 : 1.25) * k + 7.0)};
@@ -167,7 +169,7 @@ TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w, boo
   else consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : 0.3 + 0.7 * x) * (k + 4.0));
   consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.3 + 0.4 * y : 0.45) * k + 2.5);
   if (y <= 0.25 && ksteps >= 64) consider(k64Long, 0.22 * k + 3.5);
-  if (!strided && !rest && std::ceil((double)n_a / 128.0) * std::ceil((double)n_b / 256.0) <= kNumCu) consider(kHalf, 0.68 * k + 5.0);
+  if (!strided && std::ceil((double)n_a / 128.0) * std::ceil((double)n_b / 256.0) <= kNumCu) consider(kHalf, 0.68 * k + 5.0);
   if (w != kGateUp && tiles_of(n_a, n_b, 64) <= (strided ? 64.0 : 128.0)) consider(k32, (strided ? 0.17 : 0.11) * k + 3.0);
   if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
@@ -177,9 +179,10 @@ TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
   const int64_t t_a = (n_a + kTile - 1) / kTile, t_b = (n_b + kTile - 1) / kTile;
   const int64_t full = t_a * t_b / kNumCu * kNumCu, cols = full / t_b;       // full rounds; columns of tiles in them
   if (cols == 0 || cols == t_a) return whole;
-  const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, w, true);
+  const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, w);
   const double t = (double)(full / kNumCu) * ((w == kStrided ? 1.4 : 1.36) * (double)ksteps + 7.0) + rest.us + 2.0;
-  return rest.kind != kBig && t < whole.us ? TileChoice{rest.kind, cols * kTile, t} : whole;
+  const double below = rest.kind == kHalf ? 0.97 : 1.0;       // at 0.98 to 1 of the estimate 128 x 256 ends took 0.99 to 1.04
+  return rest.kind != kBig && t < below * whole.us ? TileChoice{rest.kind, cols * kTile, t} : whole;
 }
 
 // the choices of the four products of a chunk of `rows` rows
@@ -270,19 +273,21 @@ template <bool kBackward>
 void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf16* Wu, int rows, int d, int I,
                    __bf16* A, __bf16* dAG, __bf16* dU) {
   const TileChoice c = gateup_tile(rows, d, I);
-  if (c.kind == kHalf) {
-    const int n_it = (I + Tile16Half::EA / 2 - 1) / (Tile16Half::EA / 2), n_st = (rows + Tile16Half::EB - 1) / Tile16Half::EB;
-    hipLaunchKernelGGL((k_mlp_gateup<Tile16Half, kBackward, false>), dim3(even_grid(n_it, n_st)), dim3(kThreads), kLdsBytes, st,
-                       X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
-    return;
-  }
   const int i0 = (int)(c.head / 2), n_i = I - i0;               // the second launch's indices
+  auto large = [&](auto tile, auto super, int i_first, int n) {
+    typedef decltype(tile) T;
+    const int n_it = (n + T::EA / 2 - 1) / (T::EA / 2), n_st = (rows + T::EB - 1) / T::EB;
+    const size_t w = (size_t)i_first * d;
+    hipLaunchKernelGGL((k_mlp_gateup<T, kBackward, decltype(super)::value>), dim3(decltype(super)::value ? mlp_grid(n_it, n_st) : even_grid(n_it, n_st)),
+                       dim3(kThreads), kLdsBytes, st, X, Wg + w, Wu + w, rows, d, n, I, n_st, n_it,
+                       A + i_first, kBackward ? dAG + i_first : nullptr, kBackward ? dU + i_first : nullptr);
+  };
   if (c.kind == kBig || i0) {
-    const int n_it = ((i0 ? i0 : I) + kGateUpI - 1) / kGateUpI, n_st = (rows + kTile - 1) / kTile;
-    const auto kernel = use_super_tiles(n_it, n_st) ? k_mlp_gateup<Tile16, kBackward, true> : k_mlp_gateup<Tile16, kBackward, false>;
-    hipLaunchKernelGGL(kernel, dim3(mlp_grid(n_it, n_st)), dim3(kThreads), kLdsBytes, st,
-                       X, Wg, Wu, rows, d, I, n_st, n_it, A, dAG, dU);
+    const int n = i0 ? i0 : I;
+    if (use_super_tiles((n + kGateUpI - 1) / kGateUpI, (rows + kTile - 1) / kTile)) large(Tile16{}, std::true_type{}, 0, n);
+    else large(Tile16{}, std::false_type{}, 0, n);
   }
+  if (c.kind == kHalf) return large(Tile16Half{}, std::false_type{}, i0, n_i);
   Wg += (size_t)i0 * d;
   Wu += (size_t)i0 * d;
   A += i0;
@@ -306,12 +311,6 @@ void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows,
 }
 void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
   const TileChoice c = nt_tile(rows, N, K);
-  if (c.kind == kHalf) {
-    const int n_nt = (N + Tile16Half::EA - 1) / Tile16Half::EA, n_st = (rows + Tile16Half::EB - 1) / Tile16Half::EB;
-    hipLaunchKernelGGL((k_mlp_gemm_nt<Tile16Half, false>), dim3(even_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
-                       P, K, Q, K, rows, N, K, n_st, n_nt, out, N);
-    return;
-  }
   const int n0 = (int)c.head;
   if (c.kind == kBig || n0) {
     const int n_nt = ((n0 ? n0 : N) + kTile - 1) / kTile, n_st = (rows + kTile - 1) / kTile;
@@ -321,6 +320,12 @@ void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N
   Q += (size_t)n0 * K;
   out += n0;
   switch (c.kind) {
+    case kHalf: {
+      const int n_nt = (N - n0 + Tile16Half::EA - 1) / Tile16Half::EA, n_st = (rows + Tile16Half::EB - 1) / Tile16Half::EB;
+      hipLaunchKernelGGL((k_mlp_gemm_nt<Tile16Half, false>), dim3(even_grid(n_nt, n_st)), dim3(kThreads), kLdsBytes, st,
+                         P, K, Q, K, rows, N - n0, K, n_st, n_nt, out, N);
+      return;
+    }
     case k128: return launch_nt_small<Tile128>(st, P, Q, rows, N - n0, K, out, N);
     case k128Lone: return launch_nt_small<Tile128Lone>(st, P, Q, rows, N - n0, K, out, N);
     case k64: return launch_nt_small<Tile64>(st, P, Q, rows, N - n0, K, out, N);

@@ -73,7 +73,7 @@ constexpr int kGateUpI = 128;   // intermediate indices per workgroup of large t
 template <class T, bool kBackward, bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
     const __bf16* __restrict__ Xc, const __bf16* __restrict__ Wg, const __bf16* __restrict__ Wu,
-    int rows, int d, int I, int n_st, int n_it,
+    int rows, int d, int I /* indices of this launch */, int ldi, int n_st, int n_it,
     __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int H = T::TA / 2, N = 4 * H;                       // gate tiles of a wave; consecutive indices of a lane
@@ -109,32 +109,33 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
   for (int u = 0; u < T::TB; ++u) {
     const int s_local = s0 + wb * (16 * T::TB) + 16 * u + (lane & 15);
     if (s_local >= rows || ib >= I) continue;                  // I % 8 == 0: a group of 8 is inside or outside
-    const size_t off = (size_t)s_local * I + ib;
-    bf16x8 da[N / 8], a_o[N / 8], g_o[N / 8], u_o[N / 8];
+    const size_t off = (size_t)s_local * ldi + ib;
+    constexpr int kPer = 8;                                    // of a load or store; I % 8 == 0: inside or outside
+    bf16x8 da[N / kPer], a_o[N / kPer], g_o[N / kPer], u_o[N / kPer];
     if (kBackward) {
 #pragma unroll
-      for (int h = 0; h < N / 8; ++h)
-        if (ib + 8 * h < I) da[h] = *reinterpret_cast<const bf16x8*>(dAG + off + 8 * h);
+      for (int h = 0; h < N / kPer; ++h)
+        if (ib + kPer * h < I) da[h] = *reinterpret_cast<const bf16x8*>(dAG + off + kPer * h);
     }
 #pragma unroll
     for (int e = 0; e < N; ++e) {                              // index ib + e: tile e / 4, register e % 4
       const float g = acc[e >> 2][u][e & 3], up = acc[H + (e >> 2)][u][e & 3];
       const float sg = sigmoid_f(g);
       const float act = g * sg;                                // silu(g)
-      a_o[e >> 3][e & 7] = (__bf16)(act * up);
+      a_o[e / kPer][e % kPer] = (__bf16)(act * up);
       if (kBackward) {
-        const float dav = (float)da[e >> 3][e & 7];
-        g_o[e >> 3][e & 7] = (__bf16)(dav * up * (sg * (1.0f + g * (1.0f - sg))));   // dA * U * silu'(G)
-        u_o[e >> 3][e & 7] = (__bf16)(dav * act);                                    // dA * silu(G)
+        const float dav = (float)da[e / kPer][e % kPer];
+        g_o[e / kPer][e % kPer] = (__bf16)(dav * up * (sg * (1.0f + g * (1.0f - sg))));   // dA * U * silu'(G)
+        u_o[e / kPer][e % kPer] = (__bf16)(dav * act);                                    // dA * silu(G)
       }
     }
 #pragma unroll
-    for (int h = 0; h < N / 8; ++h)
-      if (ib + 8 * h < I) {
-        *reinterpret_cast<bf16x8*>(A + off + 8 * h) = a_o[h];
+    for (int h = 0; h < N / kPer; ++h)
+      if (ib + kPer * h < I) {
+        *reinterpret_cast<bf16x8*>(A + off + kPer * h) = a_o[h];
         if (kBackward) {
-          *reinterpret_cast<bf16x8*>(dAG + off + 8 * h) = g_o[h];
-          *reinterpret_cast<bf16x8*>(dU + off + 8 * h) = u_o[h];
+          *reinterpret_cast<bf16x8*>(dAG + off + kPer * h) = g_o[h];
+          *reinterpret_cast<bf16x8*>(dU + off + kPer * h) = u_o[h];
         }
       }
   }

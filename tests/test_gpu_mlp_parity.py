@@ -287,6 +287,8 @@ def test_launches_of_small_problems_match_oracle_and_keep_their_bits(S, d, I, ki
 @pytest.mark.parametrize("S,d,I,products,M", [
     (1281, 4104, 2056, ("gateup", "down"), 3),    # last tiles of one row, of 8 indices and columns
     (700, 1032, 4104, ("gateup",), 2),
+    (1486, 264, 8008, ("gateup",), 2),            # behind a round of large ones
+    (4402, 4744, 1256, ("down",), 7),
 ])
 def test_tiles_of_128_by_256_match_oracle_and_keep_their_bits(S, d, I, products, M):
     import paper_2407_15892_amd as mst
