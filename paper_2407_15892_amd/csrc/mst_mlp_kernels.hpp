@@ -105,18 +105,23 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
   gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, d, wa);
 
   const int ib = i0 + 16 * H * wa + N * (lane >> 4);           // this lane's N consecutive intermediate indices
+  constexpr int kPer = 8;                                      // of a load or store; I % 8 == 0: inside or outside
+  auto row_of = [&](int u) { return s0 + wb * (16 * T::TB) + 16 * u + (lane & 15); };
+  bf16x8 da[T::TB][N / kPer];
+  if (kBackward) {                                             // all of them before the first store, which they could alias
 #pragma unroll
-  for (int u = 0; u < T::TB; ++u) {
-    const int s_local = s0 + wb * (16 * T::TB) + 16 * u + (lane & 15);
-    if (s_local >= rows || ib >= I) continue;                  // I % 8 == 0: a group of 8 is inside or outside
-    const size_t off = (size_t)s_local * ldi + ib;
-    constexpr int kPer = 8;                                    // of a load or store; I % 8 == 0: inside or outside
-    bf16x8 da[N / kPer], a_o[N / kPer], g_o[N / kPer], u_o[N / kPer];
-    if (kBackward) {
+    for (int u = 0; u < T::TB; ++u)
 #pragma unroll
       for (int h = 0; h < N / kPer; ++h)
-        if (ib + kPer * h < I) da[h] = *reinterpret_cast<const bf16x8*>(dAG + off + kPer * h);
-    }
+        if (row_of(u) < rows && ib + kPer * h < I)
+          da[u][h] = *reinterpret_cast<const bf16x8*>(dAG + (size_t)row_of(u) * ldi + ib + kPer * h);
+  }
+#pragma unroll
+  for (int u = 0; u < T::TB; ++u) {
+    const int s_local = row_of(u);
+    if (s_local >= rows || ib >= I) continue;
+    const size_t off = (size_t)s_local * ldi + ib;
+    bf16x8 a_o[N / kPer], g_o[N / kPer], u_o[N / kPer];
 #pragma unroll
     for (int e = 0; e < N; ++e) {                              // index ib + e: tile e / 4, register e % 4
       const float g = acc[e >> 2][u][e & 3], up = acc[H + (e >> 2)][u][e & 3];
@@ -124,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
       const float act = g * sg;                                // silu(g)
       a_o[e / kPer][e % kPer] = (__bf16)(act * up);
       if (kBackward) {
-        const float dav = (float)da[e / kPer][e % kPer];
+        const float dav = (float)da[u][e / kPer][e % kPer];
         g_o[e / kPer][e % kPer] = (__bf16)(dav * up * (sg * (1.0f + g * (1.0f - sg))));   // dA * U * silu'(G)
         u_o[e / kPer][e % kPer] = (__bf16)(dav * act);                                    // dA * silu(G)
       }
@@ -311,14 +316,19 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
     gemm_mainloop_small<C>(acc, pa, pb, smem, 0, d);
   }
   const int ib = i0 + 16 * H * wa + N * (lane >> 4);
+  auto row_of = [&](int u) { return s0 + wb * (16 * C::TB) + 16 * u + (lane & 15); };
+  vec da[C::TB];
+  if (kBackward && !kDa) {                                      // all of them before the first store, which they could alias
+#pragma unroll
+    for (int u = 0; u < C::TB; ++u)
+      if (row_of(u) < rows && ib < I) da[u] = *reinterpret_cast<const vec*>(dAG + (size_t)row_of(u) * ldi + ib);
+  }
 #pragma unroll
   for (int u = 0; u < C::TB; ++u) {
-    const int s_local = s0 + wb * (16 * C::TB) + 16 * u + (lane & 15);
+    const int s_local = row_of(u);
     if (s_local >= rows || ib >= I) continue;                   // I % 8 == 0 and N divides 8
     const size_t off = (size_t)s_local * ldi + ib;
-    vec da, a_o, g_o, u_o;
-    if (kDa) da = da_own[u];
-    else if (kBackward) da = *reinterpret_cast<const vec*>(dAG + off);
+    vec a_o, g_o, u_o;
 #pragma unroll
     for (int e = 0; e < N; ++e) {
       const float g = acc[e >> 2][u][e & 3], up = acc[H + (e >> 2)][u][e & 3];
@@ -326,7 +336,7 @@ __global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
       const float act = g * sg;
       a_o[e] = (__bf16)(act * up);
       if (kBackward) {
-        const float dav = (float)da[e];
+        const float dav = (float)(kDa ? da_own : da)[u][e];
         g_o[e] = (__bf16)(dav * up * (sg * (1.0f + g * (1.0f - sg))));
         u_o[e] = (__bf16)(dav * act);
       }
