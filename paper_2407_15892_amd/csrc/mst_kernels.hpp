@@ -341,6 +341,12 @@ __device__ __forceinline__ void lse_epilogue(f32x4 (&acc)[kTA16][TB], const int*
         }
   }
 
+  int y_u[TB];                                       // on their way while the exponentials are formed
+#pragma unroll
+  for (int u = 0; u < TB; ++u) {
+    const int s_local = s0 + wb * (16 * TB) + 16 * u + c;
+    y_u[u] = labels_c[s_local < rows ? s_local : rows - 1];
+  }
   float2* xch = reinterpret_cast<float2*>(smem);     // [wb][u][16] pairs from the wa == 1 waves
   float m_u[TB], l_u[TB];
 #pragma unroll
@@ -368,7 +374,7 @@ __device__ __forceinline__ void lse_epilogue(f32x4 (&acc)[kTA16][TB], const int*
 
     // target logit straight from the accumulator that holds it
     const int s_local = s0 + wb * (16 * TB) + 16 * u + c;
-    const int y = s_local < rows ? labels_c[s_local] : -1;
+    const int y = s_local < rows ? y_u[u] : -1;
     const int rel = y - (v0 + wa * 128);
     if (rel >= 0 && rel < 128 && y < V && (rel >> 5) == g) {
       const int t_sel = (rel & 31) >> 2, r_sel = rel & 3;
@@ -652,18 +658,28 @@ __global__ __launch_bounds__(kThreads) void k_bwd_gemm_dlogits(
           for (int u = 0; u < kTB16; ++u) acc[t][u][r] = kMasked;
         }
   }
+  // Labels and log-sum-exps of all four rows first: read row by row, behind branches, they were eight loads that each
+  // waited for the one before.
+  int y_u[kTB16];
+  float lse_u[kTB16];
+#pragma unroll
+  for (int u = 0; u < kTB16; ++u) {
+    const int s_local = s0 + wb * 64 + 16 * u + (lane & 15), s_in = s_local < rows ? s_local : rows - 1;
+    y_u[u] = labels_c[s_in];
+    lse_u[u] = lse_c[s_in];
+  }
 #pragma unroll
   for (int u = 0; u < kTB16; ++u) {
     const int row = wb * 64 + 16 * u + (lane & 15);
     const int s_local = s0 + row;
     if (s_local >= rows) continue;
-    const int y_abs = labels_c[s_local];
+    const int y_abs = y_u[u];
     const bool valid = (y_abs != ignore_index) && ((unsigned)y_abs < (unsigned)V_all);
     // z - lse is formed first and scaled afterwards: where a class dominates (z close to lse) the difference is exact,
     // so p - 1 at a confidently predicted label keeps full precision, and a one-class vocabulary gives exactly 0.
     // An ignored row takes lse = +infinity: every p is then exp2(-infinity) = 0 without a select per element, and
     // its label index is moved out of range so that nothing is subtracted.
-    const float lse_s = valid ? lse_c[s_local] : __builtin_inff();
+    const float lse_s = valid ? lse_u[u] : __builtin_inff();
     const int y_lane = valid ? y_abs - v_base - va : -1;   // the label's position among this lane's 32 entries, if it is there
     char* srow = smem + row * kStageRow + (wa * 128 + 32 * (lane >> 4)) * 2;
 #pragma unroll

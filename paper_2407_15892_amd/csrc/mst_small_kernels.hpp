@@ -92,14 +92,22 @@ __global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dlogits_small(
   // now; rows padded by 16 bytes) as whole rows
   constexpr int kPer = 4 * C::TA, kStageRow = C::EA * 2 + 16;
   const int va_tile = wa * (16 * C::TA) + kPer * (lane >> 4), va = v0 + va_tile;
+  int y_u[C::TB];                       // all loads before the first is waited for
+  float lse_u[C::TB];
+#pragma unroll
+  for (int u = 0; u < C::TB; ++u) {
+    const int s_local = s0 + wb * (16 * C::TB) + 16 * u + (lane & 15), s_in = s_local < rows ? s_local : rows - 1;
+    y_u[u] = labels_c[s_in];
+    lse_u[u] = lse_c[s_in];
+  }
 #pragma unroll
   for (int u = 0; u < C::TB; ++u) {
     const int row = wb * (16 * C::TB) + 16 * u + (lane & 15);
     const int s_local = s0 + row;
     if (s_local >= rows) continue;
-    const int y_abs = labels_c[s_local];
+    const int y_abs = y_u[u];
     const bool valid = (y_abs != ignore_index) && ((unsigned)y_abs < (unsigned)V);
-    const float lse_s = valid ? lse_c[s_local] : __builtin_inff();     // an ignored row: every p is exp2(-infinity)
+    const float lse_s = valid ? lse_u[u] : __builtin_inff();           // an ignored row: every p is exp2(-infinity)
     const int y_lane = valid ? y_abs - va : -1;
     char* srow = smem + row * kStageRow + va_tile * 2;
 #pragma unroll
