@@ -16,6 +16,14 @@
 
 namespace mst {
 
+// Second launch bound of every kernel with these tiles (256 threads): at two waves per SIMD a wave has at most 256 registers,
+// and the compiler then keeps accumulators in ordinary ones.  In accumulation registers they were moved about within the main
+// loop: gate/up with 128 x 128 tiles had 64 moves and dependent pairs of MFMAs in a K step of 32 (234 instructions -> 132).
+// Forward of 130 tokens, d = 3072, I = 8192: 62 us -> 58; of 353, d = 2096, I = 5768: 77 -> 73; of 1000, d = 3072: 149 -> 145;
+// step of 512, d = 256, I = 896, M = 2: 41.8 -> 41.2; LM-head forward of 64 rows, d = 4096, V = 128256: 211 -> 206.  The pipelined
+// ones use 90 to 256; only the 256 x 64 forward tile spills, two registers across its loop.
+constexpr int kSmallWavesPerSimd = 2;
+
 // wave tile (16 TA) x (16 TB), NSA and NSB LDS stages of the two panels; kPipelined: see the two main loops
 template <int TA_, int TB_, int NSA_, int NSB_, bool kPipelined_, int BK_ = 64>
 struct CfgSmall {

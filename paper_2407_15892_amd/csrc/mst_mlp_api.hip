@@ -131,7 +131,7 @@ int rows_of(const Plan& p, int i) {
 //   128 x 128 lone 0.55 per K step + 3.2, up to kNumCu tiles.  1024 tokens, d = 4096, I = 14336: down 140 us (256 tiles)
 //                  against 308 (64 tiles of 256), dX 266 against 607
 //   128 x 256      0.68 per K step + 5, one round: between the 128 x 128 tiles that need two on a compute unit and the large
-//                  ones that leave half of them idle.  Gate/up of 200 tokens, d = 4096, I = 14336: 74 us (448 tiles of
+//                  ones that leave half of them idle.  Gate/up of 200 tokens, d = 4096, I = 14336: 65 us (448 tiles of
 //                  128 x 128) -> 60 (224), down of 1300 tokens of it 182 -> 137; with two rounds slower than large tiles,
 //                  with K-strided weights as fast as 128 x 128.  Behind full rounds of large tiles: forward of 1024 tokens,
 //                  I = 11008: 265 us -> 253

@@ -266,7 +266,7 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 // memory.  One launch less, for launches that are one short tile deep (see fuse_da in mst_mlp_api.hip).
 struct DaProblem { const __bf16 *dO, *Wd; };      // [rows][d] of the chunk, [d][ldi]
 template <class C, bool kBackward, bool kDa = false>
-__global__ __launch_bounds__(C::kThreads) void k_mlp_gateup_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gateup_small(
     const __bf16* __restrict__ Xc, const __bf16* __restrict__ Wg, const __bf16* __restrict__ Wu,
     int rows, int d, int I /* indices of this launch */, int ldi, int n_st, int n_it,
     __bf16* __restrict__ A, __bf16* __restrict__ dAG, __bf16* __restrict__ dU, DaProblem da_in) {
@@ -372,7 +372,7 @@ __device__ __forceinline__ void store_small_bf16(const f32x4 (&acc)[C::TA][C::TB
 
 // out[s][n] = sum_k P[s][k] Q[n][k]
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nt_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gemm_nt_small(
     const __bf16* __restrict__ P, int ldp, const __bf16* __restrict__ Q, int ldq, int rows, int N, int K,
     int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -421,7 +421,7 @@ __device__ __forceinline__ void nn_tile_small(
   store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
 }
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_mlp_gemm_nn_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gemm_nn_small(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
     int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
@@ -494,13 +494,13 @@ __device__ __forceinline__ void dw3_tile_small(int b, const DwProblems& ps, int 
   dw_tile_small<C>(q.G, q.ldg, q.ldg, q.H, q.ldh, rows, q.d, q.V, vt, jt, accumulate != 0, 1.0f, q.dW, q.d, smem);
 }
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_mlp_dw3_small(DwProblems ps, int rows, int accumulate) {
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_dw3_small(DwProblems ps, int rows, int accumulate) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   dw3_tile_small<C>(blockIdx.x, ps, rows, accumulate, smem);
 }
 // and with dX beside them (CX: its tile)
 template <class CX, class CW>
-__global__ __launch_bounds__(CW::kThreads) void k_mlp_dx_dw3_small(DxProblem x, DwProblems ps, int rows, int accumulate) {
+__global__ __launch_bounds__(CW::kThreads, kSmallWavesPerSimd) void k_mlp_dx_dw3_small(DxProblem x, DwProblems ps, int rows, int accumulate) {
   static_assert(CX::kThreads == CW::kThreads, "one launch");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   if ((int)blockIdx.x < x.grid) {

@@ -38,7 +38,7 @@ inline double small_launch_us(double tiles, double ksteps) {
 // lse and loss keep their bits.
 // ---------------------------------------------------------------------------
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_fwd_gemm_lse_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_fwd_gemm_lse_small(
     const __bf16* __restrict__ Hc, const __bf16* __restrict__ W, const int* __restrict__ labels_c,
     int rows, int d, int V, int n_st, int n_vt, float2* __restrict__ part, size_t part_stride, float* __restrict__ tgt) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(C::kThreads) void k_fwd_gemm_lse_small(
 // backward 1: recomputed logits -> softmax - onehot, as k_bwd_gemm_dlogits (whole vocabulary)
 // ---------------------------------------------------------------------------
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dlogits_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_bwd_gemm_dlogits_small(
     const __bf16* __restrict__ Hc, const __bf16* __restrict__ W, const int* __restrict__ labels_c,
     const float* __restrict__ lse_c, int rows, int d, int V, int ignore_index, int n_st, int n_vt,
     __bf16* __restrict__ G, int ldg) {
@@ -191,7 +191,7 @@ __device__ __forceinline__ void dh_tile_small(
   }
 }
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dh_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_bwd_gemm_dh_small(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, int rows, int d, int V,
     int n_st, int n_jt, int n_split, int ksteps_per_split, const long long* __restrict__ n_valid, float grad_loss,
     float* __restrict__ partial, int rows_stride, __bf16* __restrict__ dHc) {
@@ -245,7 +245,7 @@ __device__ __forceinline__ void dw_tile_small(const __bf16* __restrict__ G, int 
 }
 
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dw_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_bwd_gemm_dw_small(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ Hc, int rows, int d, int V,
     int n_vt, int n_jt, int accumulate, int last, const long long* __restrict__ n_valid, float grad_loss,
     float* __restrict__ dW) {
@@ -314,7 +314,7 @@ typedef CfgKSplit<4, 2, 2> TileKSplit64x32;
 
 // the first dh_grid workgroups (a multiple of the XCD count): dH, the longer ones
 template <class CH, class CW>
-__global__ __launch_bounds__(CW::kThreads) void k_bwd_gemm_dh_dw_small(
+__global__ __launch_bounds__(CW::kThreads, kSmallWavesPerSimd) void k_bwd_gemm_dh_dw_small(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, const __bf16* __restrict__ Hc, int rows, int d, int V,
     int n_sh, int n_jh, int dh_grid, int n_vt, int n_jt, int accumulate, int last, const long long* __restrict__ n_valid,
     float grad_loss, __bf16* __restrict__ dHc, float* __restrict__ dW) {
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(CW::kThreads) void k_bwd_gemm_dh_dw_small(
 
 // The same for a call of one chunk, where the free dlogits slot holds fp32 partials of dH (for k_bwd_dh_reduce).
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void k_bwd_gemm_dh_split_dw_small(
+__global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_bwd_gemm_dh_split_dw_small(
     const __bf16* __restrict__ G, int ldg, const __bf16* __restrict__ W, const __bf16* __restrict__ Hc, int rows, int d, int V,
     int n_sh, int n_jh, int n_split, int ksteps_per_split, int dh_grid, int n_vt, const long long* __restrict__ n_valid,
     float grad_loss, float* __restrict__ partial, __bf16* __restrict__ dHc, float* __restrict__ dW) {
