@@ -135,6 +135,9 @@ int rows_of(const Plan& p, int i) {
 //                  128 x 128) -> 60 (224), down of 1300 tokens of it 182 -> 137; with two rounds slower than large tiles,
 //                  with K-strided weights as fast as 128 x 128.  Behind full rounds of large tiles: forward of 1024 tokens,
 //                  I = 11008: 265 us -> 253
+//                  The estimates favour 128 x 128 too much: up to 1.12 of theirs (gate/up; down 1.02) 128 x 256 is taken.  24 and
+//                  9 shapes between 1 and that: forward calls 0.84 to 1.02, 0.93 in the mean (231 tokens, d = 3304, I = 8400:
+//                  96 us -> 81) and 0.86 to 1.02, 0.93; beyond it 0.96 to 1.10 (gate/up, 1.0 in the mean), 0.86 to 1.07 (down)
 //   64 x 64        0.45 (few workgroups on a compute unit) to 0.85 (four) per K step + 2.5.  1536 tokens, d = 1536,
 //                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256)
 //   64 x 64 lone   0.24 per K step + 2.5.  256 tokens, d = 256, I = 896: down 5.5 against 18; 200 tokens, d = 4096,
@@ -157,6 +160,7 @@ struct TileChoice {
   double us;
 };
 enum Weights { kGateUp, kContiguous, kStrided };                 // gate/up, down, dA and dX
+double half_us(double k) { return 0.68 * k + 5.0; }                // a round of 128 x 256 tiles
 TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
   const bool strided = w == kStrided;
   const double k = (double)ksteps;
@@ -169,7 +173,11 @@ TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
   else consider(k128, (x >= 1.5 ? x : x > 1.0 ? 1.5 : 0.3 + 0.7 * x) * (k + 4.0));
   consider(k64, (y > 1.0 ? 0.85 * y : y > 0.25 ? 0.3 + 0.4 * y : 0.45) * k + 2.5);
   if (y <= 0.25 && ksteps >= 64) consider(k64Long, 0.22 * k + 3.5);
-  if (!strided && std::ceil((double)n_a / 128.0) * std::ceil((double)n_b / 256.0) <= kNumCu) consider(kHalf, 0.68 * k + 5.0);
+  if (!strided && std::ceil((double)n_a / 128.0) * std::ceil((double)n_b / 256.0) <= kNumCu) {
+    const double t = half_us(k);
+    if (best.kind == k128 && t <= (w == kGateUp ? 1.12 : 1.02) * best.us) best.kind = kHalf;
+    consider(kHalf, t);
+  }
   if (w != kGateUp && tiles_of(n_a, n_b, 64) <= (strided ? 64.0 : 128.0)) consider(k32, (strided ? 0.17 : 0.11) * k + 3.0);
   if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
@@ -181,7 +189,7 @@ TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
   if (cols == 0 || cols == t_a) return whole;
   const TileChoice rest = choose_whole(n_a - cols * kTile, n_b, ksteps, w);
   const double t = (double)(full / kNumCu) * ((w == kStrided ? 1.4 : 1.36) * (double)ksteps + 7.0) + rest.us + 2.0;
-  const double below = rest.kind == kHalf ? 0.97 : 1.0;       // at 0.98 to 1 of the estimate 128 x 256 ends took 0.99 to 1.04
+  const double below = rest.kind == kHalf && rest.us >= half_us((double)ksteps) ? 0.97 : 1.0;   // at 0.98 to 1 they took 0.99 to 1.04
   return rest.kind != kBig && t < below * whole.us ? TileChoice{rest.kind, cols * kTile, t} : whole;
 }
 
