@@ -262,14 +262,15 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
  * Both write the tile of workgroup `workgroup` and return 1, or return 0 for a padding workgroup (it exits at once), or
  * -1 for bad arguments.  Every tile is the image of exactly one workgroup.
  *
- * mst_tile_info (host, pure): info[0] = the forward's tiles, 64 (256 vocabulary entries by 64 or 32 rows) or 256 (by 256 or
- * 128; mst_forward_tile_rows, host, pure, names the rows, -1 for bad arguments),
+ * mst_tile_info (host, pure): info[0] = rows of the forward's tiles (256 vocabulary entries by 32, 64, 128 or 256 rows),
  * info[1..3] = edge of the dlogits, dH and dW tiles in the pair order where each has launches of its own (64 or 256).
  *
  * mst_pair_launches (host, pure): how the pair order launches the three products, -1 for bad arguments.  The joint forms
  * are for problems whose tiles are all 64 x 64: the dlogits of a pair of mini-sequences from one launch, its dH and dW from
  * another, dH in tiles whose contraction is split between the four waves of a workgroup; or, for a single mini-sequence,
  * in the 64 x 64 tiles and the splits that it has in a launch of its own.
+ *
+ * mst_forward_tile_rows (host, pure): info[0] of mst_tile_info as the result, -1 for bad arguments.
  */
 enum {
   MST_PAIR_SEPARATE = 0,

@@ -212,7 +212,7 @@ def mst_bwd_schedule_info(S: int, d: int, V: int, M: int, schedule: Optional[int
 
 
 def mst_tile_info(S: int, d: int, V: int, M: int) -> dict:
-    """Class of the forward's tiles, edges of the pair order's dlogits, dH and dW tiles."""
+    """Rows of the forward's tiles (256 vocabulary entries wide), edges of the pair order's dlogits, dH and dW tiles."""
     info = (ctypes.c_int64 * 4)()
     _check(load_library().mst_tile_info(S, d, V, M, info))
     return dict(zip(("fwd", "dlogits", "dh", "dw"), (int(x) for x in info)))

@@ -1012,7 +1012,7 @@ mst_status mst_tile_info(int64_t S, int64_t d, int64_t V, int32_t M, int64_t* in
   Plan p;
   const mst_status s = make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false);
   if (s != MST_OK) return s;
-  info[0] = forward_tile_rows(p) <= 64 ? 64 : kTile;
+  info[0] = forward_tile_rows(p);
   info[1] = p.small_dlogits ? Tile64::EA : kTile;
   info[2] = p.small_dh ? Tile64::EA : kTile;
   info[3] = p.small_dw ? Tile64::EA : kTile;

@@ -173,8 +173,8 @@ def test_forward_is_bit_identical_for_every_number_of_mini_sequences():
 
 
 def test_forward_tiles_of_either_size_give_the_same_bits():
-    """M decides how many rows a forward launch has, and so whether it takes 256- or 64-row tiles (2048 rows here: 256 for
-    M = 1, 64 for shorter groups; test_library_abi.py asks the library): lse and loss keep their bits."""
+    """M decides how many rows a forward launch has, and so which tiles it takes (here of 128 rows for M = 1, of 64 and 32
+    for shorter groups; test_library_abi.py asks the library): lse and loss keep their bits."""
     DeviceRun, _ = _harness()
     inp = mi.make_inputs(mi.custom_config(2048, 264, 4093, 1, index=441, w_std=0.3, ignore_frac=0.07, label_dist="zipf"))
     ref_o = orc.lmhead_ce_forward(inp.H_f64(), inp.W_f64(), inp.labels, inp.ignore_index)

@@ -364,16 +364,18 @@ def test_tiles_of_the_gpu_tests_are_the_ones_they_name(mst):
         (1300, 520, 7003, 3): (256, 64, 64, 64, 4),
         (650, 1032, 12003, 2): (256, 64, 64, 256, None),
         (200, 1032, 40001, 1): (256, 256, 64, 256, 16),
-        (257, 2056, 3003, 1): (64, 64, 64, 64, None),
-        (65, 264, 4097, 1): (64, 64, 64, 64, None),
+        (257, 2056, 3003, 1): (32, 64, 64, 64, None),
+        (65, 264, 4097, 1): (32, 64, 64, 64, None),
     }
     for shape, (fwd, dlogits, dh, dw, split) in want.items():
         info = mst.mst_tile_info(*shape)
         assert info == {"fwd": fwd, "dlogits": dlogits, "dh": dh, "dw": dw}, (shape, info)
         if split:
             assert mst.mst_bwd_schedule_info(*shape, schedule=mst.BWD_SCHEDULE_PAIRS)["dh_split"] == split
-    # the forward's tile changes with M
-    assert [mst.mst_tile_info(2048, 264, 4093, M)["fwd"] for M in (1, 128, 2048)] == [256, 64, 64]
+    # the forward's tile changes with M; both queries of its rows say the same
+    for shape, rows in (((2048, 264, 4093), {1: 128, 128: 64, 2048: 32}), ((3000, 264, 4093), {1: 256})):
+        for M, want_rows in rows.items():
+            assert mst.mst_tile_info(*shape, M)["fwd"] == mst.mst_forward_tile_rows(*shape, M) == want_rows
     with pytest.raises(mst.MstError):
         mst.mst_tile_info(0, 264, 4093, 1)
     assert mst.load_library().mst_tile_info(2048, 264, 4093, 1, None) == -1
