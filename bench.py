@@ -132,6 +132,19 @@ MLP_KINDS = ("gateup", "down", "da", "gateup_bwd", "dx", "dw")
 # executed flop per step of each MLP kernel kind, in units of S*d*I
 MLP_FLOP_UNITS = {"gateup": 4.0, "down": 2.0, "da": 2.0, "gateup_bwd": 4.0, "dx": 4.0, "dw": 6.0}
 
+
+def mlp_flop_units(issued):
+    """MLP_FLOP_UNITS by the launches that did the work, from the number of launches of every kind: the launch of gate/up's
+    backward computes dA, that of the weight gradients dX, of every chunk for which these have none of their own (chunks
+    of one length; "dw" has one launch per chunk)."""
+    units = dict(MLP_FLOP_UNITS)
+    for kind, host in (("da", "gateup_bwd"), ("dx", "dw")):
+        own = issued[kind] / issued["dw"]
+        units[host] += (1.0 - own) * units[kind]
+        units[kind] *= own
+    return units
+
+
 def mlp_cpu_baseline(inp, sample_rows: int):
     """The fp64 MLP oracle as it stands, timed on the host cores on the first `sample_rows` tokens."""
     import numpy as np
@@ -216,9 +229,7 @@ def main_mlp(args) -> int:
     tflops = f_exec / (ms_per_step * 1e-3) / 1e12
     roofline, kernels = None, {}
     if kern:
-        units = dict(MLP_FLOP_UNITS)
-        if not kern["dx"][2]:          # served by the launch of the weight gradients
-            units["dw"] += units.pop("dx")
+        units = mlp_flop_units({k: issued for k, (_, _, issued) in kern.items()})
         for k, (ms, n, issued) in kern.items():
             if n:
                 fl = units[k] * S * d * I / (issued / args.steps)

@@ -20,6 +20,20 @@ def test_traffic_table_parses_and_covers_the_default_workloads():
     assert bench.pmc_traffic_bytes("lmhead", 3, "pairs", "bwd_gemm_dw") is None
 
 
+def test_flop_of_products_that_share_a_launch_are_counted_where_they_run():
+    import bench
+    apart = {"gateup": 6, "down": 6, "da": 6, "gateup_bwd": 6, "dx": 6, "dw": 6}
+    assert bench.mlp_flop_units(apart) == bench.MLP_FLOP_UNITS
+    # the small forms: dA inside gate/up's backward, dX beside the weight gradients
+    joint = bench.mlp_flop_units(dict(apart, da=0, dx=0))
+    assert joint == dict(bench.MLP_FLOP_UNITS, da=0.0, gateup_bwd=6.0, dx=0.0, dw=10.0)
+    # a step's first of three chunks with a dX launch of its own, the later ones without
+    mixed = bench.mlp_flop_units(dict(apart, dx=2))
+    assert abs(mixed["dx"] - 4 / 3) < 1e-12 and abs(mixed["dw"] - (6 + 8 / 3)) < 1e-12
+    for units in (joint, mixed):
+        assert abs(sum(units.values()) - 22.0) < 1e-12
+
+
 def test_more_than_one_gpu_is_refused_with_a_message():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode == 2 and "ONE GPU" in r.stderr
