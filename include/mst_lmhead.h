@@ -257,7 +257,7 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
  * the latter is the even map of any launch (slow = n_col_tiles, fast = n_row_tiles): every launch with smaller tiles than
  * 256 x 256 has it, and backward launches of 256 x 256 tiles whose slow coordinate would leave more than an eighth of
  * the grid above as padding, or, up to four rounds of workgroups, whose busiest XCD would need a round more with the
- * rectangles.
+ * rectangles, and forward ones without queues (mst_forward_launch) whose busiest XCD would, however many rounds.
  *
  * Both write the tile of workgroup `workgroup` and return 1, or return 0 for a padding workgroup (it exits at once), or
  * -1 for bad arguments.  Every tile is the image of exactly one workgroup.
@@ -271,6 +271,9 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
  * in the 64 x 64 tiles and the splits that it has in a launch of its own.
  *
  * mst_forward_tile_rows (host, pure): info[0] of mst_tile_info as the result, -1 for bad arguments.
+ *
+ * mst_forward_launch (host, pure): how mst_lmhead_ce_fwd's launch for its first group of mini-sequences deals out its tiles
+ * (the same bits), one of MST_FORWARD_*, -1 for bad arguments.
  */
 enum {
   MST_PAIR_SEPARATE = 0,
@@ -279,7 +282,13 @@ enum {
   MST_PAIR_KSPLIT_64X32,
   MST_PAIR_SPLIT              /* one mini-sequence: split partials        */
 };
+enum {
+  MST_FORWARD_RECTANGLES = 0, /* a workgroup per tile, the rectangles of mst_tile_of_workgroup        */
+  MST_FORWARD_EVEN,           /* a workgroup per tile, the even map                                  */
+  MST_FORWARD_QUEUES          /* a workgroup per compute unit; a queue of tiles per XCD, in the order of the rectangles */
+};
 int32_t mst_forward_tile_rows(int64_t S, int64_t d, int64_t V, int32_t M);
+int32_t mst_forward_launch(int64_t S, int64_t d, int64_t V, int32_t M);
 int32_t mst_pair_launches(int64_t S, int64_t d, int64_t V, int32_t M);
 int32_t mst_tile_grid(int32_t n_slow, int32_t n_fast);
 int32_t mst_tile_of_workgroup(int32_t n_slow, int32_t n_fast, int32_t order, int32_t workgroup,

@@ -88,6 +88,8 @@ def load_library() -> ctypes.CDLL:
     lib.mst_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.POINTER(c.c_int64)]
     lib.mst_forward_tile_rows.restype = c.c_int32
     lib.mst_forward_tile_rows.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
+    lib.mst_forward_launch.restype = c.c_int32
+    lib.mst_forward_launch.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_pair_launches.restype = c.c_int32
     lib.mst_pair_launches.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_profile_enable.restype = c.c_int
@@ -221,6 +223,14 @@ def mst_tile_info(S: int, d: int, V: int, M: int) -> dict:
 def mst_forward_tile_rows(S: int, d: int, V: int, M: int) -> int:
     """Rows of the forward's tiles (256 vocabulary entries wide)."""
     return int(load_library().mst_forward_tile_rows(S, d, V, M))
+
+
+FORWARD_LAUNCHES = ("rectangles", "even", "queues")     # MST_FORWARD_*
+
+
+def mst_forward_launch(S: int, d: int, V: int, M: int) -> str:
+    """How the forward's launch deals out its tiles."""
+    return FORWARD_LAUNCHES[load_library().mst_forward_launch(S, d, V, M)]
 
 
 PAIR_LAUNCHES = ("separate", "32x16", "64x16", "64x32", "split")     # MST_PAIR_*

@@ -438,7 +438,8 @@ bool set_kernel_attributes() {   // on the current device
   auto set = [&ok](const void* f) {
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess) ok = false;
   };
-  set((const void*)k_fwd_gemm_lse);
+  set((const void*)k_fwd_gemm_lse<false>);
+  set((const void*)k_fwd_gemm_lse<true>);
   set((const void*)k_fwd_gemm_lse_small<TileFwd64>);
   set((const void*)k_fwd_gemm_lse_small<TileFwd32>);
   set((const void*)k_fwd_gemm_lse_rows128);
@@ -503,8 +504,13 @@ int forward_tile_rows(const Plan& p) {
 // 1984 (4096 rows, d = 4096, V = 128256) 2860 us against 2878, 647: 1096 against 1117, 592: the same, 499: 773 against 755,
 // 128 (200 rows, d = 4096, V = 128256): 252 against 234.
 constexpr int64_t kPersistentSteps = 600;
-bool persistent_forward(const Plan& p, int64_t grid) {
-  return (grid + kNumCu - 1) / kNumCu * ((p.d + kBK - 1) / kBK) >= kPersistentSteps;
+int64_t forward_group_rows(const Plan& p, int64_t g0) { return std::min(p.S - g0, p.fwd_group_rows); }
+int forward_row_tiles(const Plan& p, int64_t g0, int tile_rows) {
+  return (int)((forward_group_rows(p, g0) + tile_rows - 1) / tile_rows);
+}
+bool persistent_forward(const Plan& p) {                           // decided by the first group
+  const int64_t grid = xcd_grid_2d(p.n_vt, forward_row_tiles(p, 0, kTile));
+  return forward_tile_rows(p) == kTile && (grid + kNumCu - 1) / kNumCu * ((p.d + kBK - 1) / kBK) >= kPersistentSteps;
 }
 
 // One workgroup finishes the forward call: a row per thread, its pairs in registers.  At 8192 pairs (512 rows, V = 4096) the
@@ -520,26 +526,25 @@ mst_status run_forward_chunks(const Plan& p, const __bf16* H, const __bf16* W, c
   float* tgt = reinterpret_cast<float*>(ws + p.f_tgt);
   float2* part = reinterpret_cast<float2*>(ws + p.f_part);
   const size_t stride = (size_t)p.fwd_group_rows;
-  auto rows_of_group = [&](int64_t g0) { return (p.S - g0) < p.fwd_group_rows ? (p.S - g0) : p.fwd_group_rows; };
   const int tile_rows = forward_tile_rows(p);
-  const int64_t grid_first = (int64_t)xcd_grid_2d(p.n_vt, (int)((rows_of_group(0) + kTile - 1) / kTile));
-  int* queue = ctl && tile_rows == kTile && persistent_forward(p, grid_first) ? ctl->queue : nullptr;
+  int* queue = ctl && persistent_forward(p) ? ctl->queue : nullptr;
   int queue_base = 0;
   if (queue) {
     Scope sc(st, MST_K_LABEL_SCAN);
     hipLaunchKernelGGL(k_clear_queues, dim3(1), dim3(64), 0, st, ctl);
   }
   for (int64_t g0 = 0; g0 < p.S; g0 += p.fwd_group_rows) {
-    const int64_t g_rows = rows_of_group(g0);
+    const int64_t g_rows = forward_group_rows(p, g0);
     // One launch for the group's mini-sequences.  Rows are independent and no logits are stored, so the row tiles
     // of the launch need not respect the boundaries between the mini-sequences of the group: a mini-sequence
     // shorter than a 256-row tile costs no idle tile rows, and every row's result is bit-identical for every M.
-    const int n_st = (int)((g_rows + tile_rows - 1) / tile_rows);
+    const int n_st = forward_row_tiles(p, g0, tile_rows);
     if (tile_rows == kTile) {
       Scope sc(st, MST_K_FWD_GEMM_LSE);
-      const int tiles = xcd_grid_2d(p.n_vt, n_st);
+      const bool even = !queue && forward_even_map(p.n_vt, n_st);
+      const int tiles = launch_grid(even, p.n_vt, n_st);
       const int grid = queue && tiles > kNumCu ? kNumCu : tiles;
-      hipLaunchKernelGGL(k_fwd_gemm_lse, dim3(grid), dim3(kThreads), kLdsBytes, st,
+      hipLaunchKernelGGL(even ? k_fwd_gemm_lse<true> : k_fwd_gemm_lse<false>, dim3(grid), dim3(kThreads), kLdsBytes, st,
                          H + g0 * p.d, W, labels + g0, (int)g_rows, (int)p.d, (int)p.V, n_st, p.n_vt,
                          part, stride, tgt, queue, queue_base);
       queue_base += tiles / kNumXcd + grid;
@@ -999,6 +1004,14 @@ int32_t mst_forward_tile_rows(int64_t S, int64_t d, int64_t V, int32_t M) {
   Plan p;
   if (make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false) != MST_OK) return -1;
   return forward_tile_rows(p);
+}
+
+int32_t mst_forward_launch(int64_t S, int64_t d, int64_t V, int32_t M) {
+  Plan p;
+  if (make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_AUTO, 0, false) != MST_OK) return -1;
+  if (persistent_forward(p)) return MST_FORWARD_QUEUES;
+  const bool even = forward_tile_rows(p) < kTile || forward_even_map(p.n_vt, forward_row_tiles(p, 0, kTile));
+  return even ? MST_FORWARD_EVEN : MST_FORWARD_RECTANGLES;
 }
 
 int32_t mst_pair_launches(int64_t S, int64_t d, int64_t V, int32_t M) {

@@ -117,8 +117,8 @@ __host__ __device__ inline bool xcd_tile_of_block(int block, int n_slow, int n_f
 constexpr int kXcdRectSlow = 4, kXcdRectFast = 8, kXcdSuper = 32;
 __host__ __device__ inline int xcd_grid_2d(int n_slow, int n_fast) { return kNumXcd * ((n_slow + kNumXcd - 1) / kNumXcd) * n_fast; }
 
-// The map of a backward launch (the forward launch balances itself, see TileFeed): the rectangles above, or an equal share
-// of the tiles for every XCD (gemm_small.hpp).  The latter where the slow coordinate divides so badly over the XCDs that
+// The map of a backward launch: the rectangles above, or an equal share of the tiles for every XCD (gemm_small.hpp).  The
+// latter where the slow coordinate divides so badly over the XCDs that
 // more than an eighth of the grid would be padding (34 vocabulary tiles: 5 per XCD, the last one idle; 12 row tiles: two
 // XCDs idle), and in launches of a few rounds where it saves one (36 x 7 tiles of dlogits: 35 on seven XCDs of 32 compute
 // units, 51 us against 31.6; the step of 4731 tokens, d = 896, V = 62794 that has them 2.83 -> 2.16 ms, its dH and dW
@@ -128,15 +128,24 @@ __host__ __device__ inline int xcd_grid_2d(int n_slow, int n_fast) { return kNum
 inline int xcd_share(int n_slow, int n_fast, bool even) {       // tiles of the XCD that has most
   return even ? (n_slow * n_fast + kNumXcd - 1) / kNumXcd : (n_slow + kNumXcd - 1) / kNumXcd * n_fast;
 }
+constexpr int kXcdCu = 32;                                      // compute units of an XCD
+inline bool fewer_rounds(int share, int even_share) { return (share + kXcdCu - 1) / kXcdCu > (even_share + kXcdCu - 1) / kXcdCu; }
 inline bool saves_a_round(int share, int even_share) {
-  constexpr int kCu = 32, kFewRounds = 4;                       // compute units of an XCD
-  return even_share <= kFewRounds * kCu && (share + kCu - 1) / kCu > (even_share + kCu - 1) / kCu;
+  constexpr int kFewRounds = 4;
+  return even_share <= kFewRounds * kXcdCu && fewer_rounds(share, even_share);
 }
 inline bool uneven_over_xcds(int n_slow) {
   return 8 * (kNumXcd * ((n_slow + kNumXcd - 1) / kNumXcd) - n_slow) > n_slow;
 }
 inline bool use_even_map(int n_slow, int n_fast) {
   return uneven_over_xcds(n_slow) || saves_a_round(xcd_share(n_slow, n_fast, false), xcd_share(n_slow, n_fast, true));
+}
+// The map of a forward launch that does not balance itself (see TileFeed): even wherever that saves a round.  18 x 25 tiles
+// in rectangles are 75 on each of six XCDs, three rounds instead of two: 6328 rows, d = 1704, V = 4480: forward 136 us, 97
+// with equal shares, 115 with queues.  Over 65 shapes in which it saves a round, of 40 to 800 us: 0.56 to 0.97 of the
+// rectangles' time, 0.82 in the mean, and 0.81 of the queues' (1.00 at most).  Where it saves none: 0.92 to 1.04, 1.00.
+inline bool forward_even_map(int n_slow, int n_fast) {
+  return fewer_rounds(xcd_share(n_slow, n_fast, false), xcd_share(n_slow, n_fast, true));
 }
 template <int kRectSlow = kXcdRectSlow, int kRectFast = kXcdRectFast, int kSuper = kXcdSuper>
 __device__ __forceinline__ bool launch_tile(bool even, int block, int n_slow, int n_fast, int* slow, int* fast) {
@@ -410,6 +419,7 @@ __device__ __forceinline__ void lse_epilogue(f32x4 (&acc)[kTA16][TB], const int*
 //   row s and 32 consecutive vocabulary entries, so the row reduction is in-lane
 //   plus exchanges with the other three lane quarters and the other wave row.
 // ---------------------------------------------------------------------------
+template <bool kEven>
 __global__ __launch_bounds__(kThreads) void k_fwd_gemm_lse(
     const __bf16* __restrict__ Hc, const __bf16* __restrict__ W, const int* __restrict__ labels_c,
     int rows, int d, int V, int n_st, int n_vt, float2* __restrict__ part, size_t part_stride,
@@ -417,11 +427,12 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemm_lse(
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wa = wave >> 2, wb = wave & 3;
+  if (kEven) queue = nullptr;                        // one workgroup per tile
   TileFeed feed;
   if (queue) feed.init(queue, queue_base, xcd_grid_2d(n_vt, n_st) / kNumXcd, smem);
   for (int block = queue ? feed.next() : (int)blockIdx.x; block >= 0; block = queue ? feed.next() : -1) {
   int vt, st;                                        // an XCD's resident workgroups: 4 vocabulary x 8 row tiles
-  if (!xcd_tile_of_block<kXcdRectSlow, kXcdRectFast, kXcdSuper>(block, n_vt, n_st, &vt, &st)) {   // padding entry of the map
+  if (!launch_tile(kEven, block, n_vt, n_st, &vt, &st)) {   // padding entry of the map
     if (queue) { feed.issue(); feed.resolve(); }
     continue;
   }

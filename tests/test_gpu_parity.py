@@ -210,6 +210,25 @@ def test_forward_tiles_of_every_size_give_the_same_bits(S, d, V, rows_of_m):
         assert bits[0] == first[0] and np.array_equal(bits[1], first[1]), f"M = {M}"
 
 
+@pytest.mark.parametrize("S,d,V", [
+    (4105, 72, 2104),       # 9 x 17 tiles, one round instead of two; last row tile of 9, last vocabulary tile of 56
+    (2700, 200, 4477),      # 18 x 11
+    (5000, 136, 9001),      # 36 x 20: three rounds instead of four
+])
+def test_forward_tiles_dealt_out_evenly_give_the_same_bits(S, d, V):
+    """256-row tiles whose busiest XCD has fewer rounds for it, against the small tiles of one row per mini-sequence and the
+    oracle; and in the backward call that forms the log-sum-exps itself."""
+    import paper_2407_15892_amd as mst
+    inp = mi.make_inputs(mi.custom_config(S, d, V, 1, index=444, w_std=0.3, ignore_frac=0.07, label_dist="zipf"))
+    assert mst.mst_forward_launch(S, d, V, 1) == "even" and mst.mst_forward_tile_rows(S, d, V, 1) == 256
+    run, ref, _ = _check_full(inp, use_lse=False)
+    loss, lse, nv = run.forward()
+    assert np.abs(lse - ref["lse"]).max() <= 1e-5 * np.abs(ref["lse"]).max()
+    assert mst.mst_forward_tile_rows(S, d, V, S) < 256
+    loss_small, lse_small, nv_small = type(run)(inp, M=S).forward()
+    assert (loss, nv) == (loss_small, nv_small) and np.array_equal(lse, lse_small)
+
+
 def test_dW_and_dH_bit_identical_across_runs():
     DeviceRun, _ = _harness()
     import torch

@@ -379,3 +379,29 @@ def test_tiles_of_the_gpu_tests_are_the_ones_they_name(mst):
     with pytest.raises(mst.MstError):
         mst.mst_tile_info(0, 264, 4093, 1)
     assert mst.load_library().mst_tile_info(2048, 264, 4093, 1, None) == -1
+
+
+def test_forward_takes_no_map_that_costs_a_round(mst):
+    """256-row forward tiles: wherever the rectangles' busiest XCD (32 compute units) needs more rounds than an equal share of
+    the tiles would, the launch deals them out evenly or pulls them from queues."""
+    up = lambda a, b: -(-a // b)
+    seen = {}
+    for d in (64, 640, 1704, 4096):
+        for V in list(range(300, 20000, 611)) + [32000, 50257, 128256]:
+            for S in (300, 1000, 2700, 6328, 9000, 16384, 32768):
+                if S * V >= 2 ** 30:
+                    continue
+                how, rows = mst.mst_forward_launch(S, d, V, 1), mst.mst_forward_tile_rows(S, d, V, 1)
+                n_vt, n_st = up(V, 256), up(S, 256)
+                busiest, equal = up(up(n_vt, 8) * n_st, 32), up(up(n_vt * n_st, 8), 32)
+                seen[how] = seen.get(how, 0) + 1
+                if rows < 256:
+                    assert how == "even"
+                elif busiest > equal:
+                    assert how != "rectangles", (S, d, V)
+                elif how != "queues":
+                    assert how == "rectangles"
+    assert min(seen[k] for k in ("rectangles", "even", "queues")) > 50, seen
+    assert [mst.mst_forward_launch(*shape) for shape in ((32768, 4096, 128256, 32), (200, 4096, 128256, 1), (6328, 1704, 4480, 3))] \
+        == ["queues", "rectangles", "even"]
+    assert mst.load_library().mst_forward_launch(0, 264, 4093, 1) == -1
