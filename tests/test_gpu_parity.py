@@ -229,6 +229,53 @@ def test_forward_tiles_dealt_out_evenly_give_the_same_bits(S, d, V):
     assert (loss, nv) == (loss_small, nv_small) and np.array_equal(lse, lse_small)
 
 
+@pytest.mark.parametrize("S,d,V,Ms", [
+    (4105, 1544, 100003, (1, 64)),     # 17 x 391 tiles, ragged rows, K and vocabulary; then a second group of 10 rows on the same queues
+    (4105, 2568, 60001, (64,)),        # a second group of 235 tiles: fewer workgroups than compute units
+])
+def test_persistent_forward_gives_the_bits_of_one_workgroup_per_tile(S, d, V, Ms):
+    """Launches that pull their tiles from queues against the same rows in launches that do not (M = S: groups too short for
+    queues), eagerly and replayed from a HIP graph with eager calls in between; rows at tile edges against 64 bits."""
+    import torch
+    import paper_2407_15892_amd as mst
+    DeviceRun, _ = _harness()
+    inp = mi.make_inputs(mi.custom_config(S, d, V, 1, index=443, w_std=0.05, ignore_frac=0.07, label_dist="zipf"))
+    plain = DeviceRun(inp, M=S)
+    assert mst.mst_forward_launch(S, d, V, S) != "queues"
+    loss_ref, lse_ref, nv_ref = plain.forward()
+    assert nv_ref == int((inp.labels != inp.ignore_index).sum())
+    rows = [0, 255, 256, 4094, 4095, 4096, 4104]
+    exact = torch.logsumexp(plain.H[rows].double() @ plain.W.double().T, 1).cpu().numpy()
+    # an fp32 sum over d of products of bf16 values, and one over V of its exponentials: 1e-5 as in the other lse tests
+    assert np.abs(lse_ref[rows] - exact).max() <= 1e-5 * np.abs(exact).max()
+
+    for M in Ms:
+        assert mst.mst_forward_launch(S, d, V, M) == "queues"
+        run = DeviceRun(inp, M=M)
+        loss, lse, nv = run.forward()
+        assert nv == nv_ref and loss == loss_ref and np.array_equal(lse, lse_ref), M
+        ws = torch.full((run.fwd_bytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        out = [torch.zeros(1, device="cuda"), torch.zeros(S, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")]
+
+        def call():
+            mst.mst_lmhead_ce_fwd(run.H, run.W, run.labels, inp.ignore_index, M, ws, *out)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call()
+        for _ in range(3):
+            for t in (ws, *out):
+                t.fill_(0x5A)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert int(out[2]) == nv_ref and float(out[0]) == loss_ref
+            assert np.array_equal(out[1].cpu().numpy().astype(np.float64), lse_ref), M
+            call()
+            torch.cuda.synchronize()
+            assert np.array_equal(out[1].cpu().numpy().astype(np.float64), lse_ref), M
+        del graph
+
+
 def test_dW_and_dH_bit_identical_across_runs():
     DeviceRun, _ = _harness()
     import torch
@@ -244,9 +291,25 @@ def test_dW_and_dH_bit_identical_across_runs():
         assert torch.equal(dH0.view(torch.int16), dH1.view(torch.int16))
 
 
-def test_all_rows_ignored():
+# calls that one workgroup finishes and whose gradients come from joint launches; and one finished by two launches, the
+# second with labels in an unrolled round (8192 rows) and behind it, dlogits, dH (8 splits), its reduce and dW in launches
+# of their own
+FEW_LAUNCHES, MANY_LAUNCHES = (256, 64, 500, 2), (8300, 64, 9001, 8)
+
+
+def _assert_launches(shape):
+    import paper_2407_15892_amd as mst
+    assert mst.mst_pair_launches(*shape) == ("separate" if shape == MANY_LAUNCHES else "32x16")
+    if shape == MANY_LAUNCHES:
+        info = mst.mst_bwd_schedule_info(*shape)
+        assert info["schedule"] == mst.BWD_SCHEDULE_PAIRS and info["dh_split"] == 8
+
+
+@pytest.mark.parametrize("S,d,V,M", [(260, 64, 300, 2), MANY_LAUNCHES])
+def test_all_rows_ignored(S, d, V, M):
     DeviceRun, bf2f = _harness()
-    inp = mi.make_inputs(mi.custom_config(260, 64, 300, 2, index=302))
+    _assert_launches((S, d, V, M))
+    inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=302))
     inp.labels[:] = inp.ignore_index
     run = DeviceRun(inp)
     loss, lse, nv = run.forward()
@@ -271,11 +334,17 @@ def test_zero_W_gives_ln_V():
     assert float(dW.double().sum(dim=0).abs().max()) < 2.0 ** -8
 
 
-def test_out_of_range_label_is_reported_not_dereferenced():
+@pytest.mark.parametrize("shape,bad", [
+    (FEW_LAUNCHES, {5: 500, 9: -3}),
+    (MANY_LAUNCHES, {5000: 9001}),
+    (MANY_LAUNCHES, {8250: -3}),
+])
+def test_out_of_range_label_is_reported_not_dereferenced(shape, bad):
     DeviceRun, _ = _harness()
-    inp = mi.make_inputs(mi.custom_config(256, 64, 500, 2, index=304))
-    inp.labels[5] = 500
-    inp.labels[9] = -3
+    _assert_launches(shape)
+    inp = mi.make_inputs(mi.custom_config(*shape, index=304))
+    for row, label in bad.items():
+        inp.labels[row] = label
     run = DeviceRun(inp)
     loss, lse, nv = run.forward()
     assert np.isnan(loss) and nv == -1
