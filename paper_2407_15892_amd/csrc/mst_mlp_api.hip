@@ -147,7 +147,10 @@ int rows_of(const Plan& p, int i) {
 //   32 x 32        0.11 per 64 (0.17 with K-strided weights) + 3 where there are few 64 x 64 tiles (more than 128, or 64
 //                  K-strided, move too much through L2 for this): a quarter of the LDS traffic per K step, and four times
 //                  the compute units.  Forward of 64 tokens, d = 2048, I = 6000: 33 us -> 22, of 500, d = 640, I = 1800:
-//                  18.9 -> 15; backward of 178 tokens, d = 520, I = 1456: 35 -> 30.  Not for gate/up (pairs of row tiles)
+//                  18.9 -> 15; backward of 178 tokens, d = 520, I = 1456: 35 -> 30.  Not for gate/up (pairs of row tiles),
+//                  and not for three rows of them (65 to 96 tokens) that are more than a round and more than 60000 K steps
+//                  in all: 39 forward calls there, d = 3200 to 4096, took 0.96 to 1.10 of their time with 64 x 64 tiles, 1.06
+//                  in the mean; 52 below that line 0.83 to 1.06, 0.98; 97 to 128 tokens 0.88 to 1.07, 0.97
 // Where the large tiles end in a partly filled round, whole columns of them may make up the full rounds and a second
 // launch the rest with smaller tiles: gate/up of 1668 tokens, d = 1544, I = 5384 (301 large tiles) as 252 large and 675 of
 // 64 x 64: step of 5003 tokens 1.31 -> 1.23 ms; dA of 4096 tokens, I = 14336 (896 tiles) as 768 large and 512 of
@@ -178,7 +181,9 @@ TileChoice choose_whole(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
     if (best.kind == k128 && t <= (w == kGateUp ? 1.12 : 1.02) * best.us) best.kind = kHalf;
     consider(kHalf, t);
   }
-  if (w != kGateUp && tiles_of(n_a, n_b, 64) <= (strided ? 64.0 : 128.0)) consider(k32, (strided ? 0.17 : 0.11) * k + 3.0);
+  const double n32 = tiles_of(n_a, n_b, 32);
+  const bool thin = n_b > 64 && n_b <= 96 && n32 > kNumCu && n32 * k >= 60000.0;
+  if (w != kGateUp && !thin && tiles_of(n_a, n_b, 64) <= (strided ? 64.0 : 128.0)) consider(k32, (strided ? 0.17 : 0.11) * k + 3.0);
   if (y <= 0.5) consider(k64Lone, 0.24 * (y > 0.25 ? 4.0 * y : 1.0) * k + 2.5);
   return best;
 }

@@ -116,6 +116,18 @@ def test_tile_shapes_of_the_gpu_test_take_every_tile(mst):
     assert want <= seen, sorted(want - seen)
 
 
+def test_down_of_65_to_96_tokens_takes_32_by_32_tiles_only_for_short_contractions(mst):
+    """Three rows of them, more than one round and a long contraction: 64 x 64 tiles are faster."""
+    down = lambda rows, d, I: mst.mst_mlp_tile_info(rows, d, I)["down"][0]
+    for rows in (33, 64, 97, 128):
+        assert down(rows, 4096, 14336) == "32"
+    for rows in (65, 80, 96):
+        assert down(rows, 4096, 14336) == "64_long"       # 384 tiles, 224 K steps
+        assert down(rows, 3200, 12736) == "32"            # 300 tiles, 199 K steps
+        assert down(rows, 3200, 12800) == "64_long"       # 300 tiles, 200 K steps
+        assert down(rows, 2720, 16384) == "32"            # one round
+
+
 def test_workgroup_to_tile_map_is_a_bijection(mst):
     """Both maps of the 256 x 256 launches, on the host: every tile is the image of exactly one workgroup."""
     import ctypes
