@@ -235,6 +235,11 @@ bool fuse_da(int64_t rows, int64_t d, int64_t I) {
 // Over twenty shapes of 200 to 4096 rows, d = 1024 to 4096, one and two chunks, both ways timed: the backward call took
 // 0.87 to 1.01 of its time with two launches, 0.96 in the mean, and nowhere was the other tile more than 1.5 % faster.
 // kShared: a shared launch must be this much cheaper (what is left alone, 4096 rows, d = 4096: both take the same).
+// A later chunk keeps two launches where one row of large tiles holds it and its 64 x 64 tiles of dX fit a round: the weight
+// gradients are bound by the sums that they read and write again, dX's K steps take 1.0 to 1.25 us beside them and not 0.8,
+// and they are the end of the launch.  212 steps of 2 to 5 chunks of up to 256 rows, d = 1800 to 4096, took 0.98 to 1.20 of
+// their time with two launches, 1.03 in the mean (4 x 244 rows, d = 4096, I = 14336: 2.49 ms, 2.65 with one); 67 with d
+// above 4096 0.93 to 1.13, 0.99.
 constexpr double kShared = 0.98;
 enum DxKind { kDxOwn, kDxWhole, kDxHalf, kDx64, kDx32 };
 DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwChoice& dw) {
@@ -243,6 +248,7 @@ DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwCh
     if (own.kind < k64 || own.head) return kDxOwn;
     return tiles_of(d, rows, 64) <= 72.0 ? kDx32 : kDx64;
   }
+  if (accumulate && rows <= kTile && tiles_of(d, kTile, 64) <= kNumCu) return kDxOwn;
   auto tiles = [&](int64_t a, int64_t b, int64_t e) { return (a + e - 1) / e * ((b + kTile - 1) / kTile); };
   const int64_t n_dw = 2 * tiles(I, d, kTile) + tiles(d, I, kTile);
   const TileCost c = dw_cost(rows, accumulate);

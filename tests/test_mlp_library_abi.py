@@ -128,6 +128,15 @@ def test_down_of_65_to_96_tokens_takes_32_by_32_tiles_only_for_short_contraction
         assert down(rows, 2720, 16384) == "32"            # one round
 
 
+def test_dx_of_later_chunks_of_few_rows_has_a_launch_of_its_own(mst):
+    """Chunks of one row of large tiles whose weight gradients are read back: dX's long tiles would end that launch."""
+    for d, I in ((4096, 14336), (4096, 11008), (3328, 12496)):
+        for rows in (65, 100, 200, 256):
+            assert mst.mst_mlp_dx_tile(rows, d, I, False) == "own", (rows, d, I)
+    assert mst.mst_mlp_dx_tile(300, 4096, 14336, False) == "128"
+    assert mst.mst_mlp_dx_tile(208, 5120, 13824, False) == "128"      # more 64 x 64 tiles than compute units
+
+
 def test_workgroup_to_tile_map_is_a_bijection(mst):
     """Both maps of the 256 x 256 launches, on the host: every tile is the image of exactly one workgroup."""
     import ctypes
