@@ -124,7 +124,7 @@ struct PanelKS16 {
   static constexpr int SPW = NSLOT / C::kWaves;
   static_assert(NSLOT % C::kWaves == 0, "slots must divide over waves");
   static_assert(!kPermute || EXT % (16 * TILES) == 0, "the permutation works on the blocks of 16 TILES indices of a wave");
-  static_assert(EXT == 16 || EXT == 32 || EXT == 64 || EXT == 128 || EXT == 256, "the swizzles below are for these row lengths");
+  static_assert(EXT == 32 || EXT == 64 || EXT == 128 || EXT == 256, "the swizzles below are for these row lengths");
   static_assert(EXT > 32 || !kPermute, "rows of 64 bytes are read in memory order");
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t voff[SPW];
@@ -141,7 +141,6 @@ struct PanelKS16 {
   // EXT = 64: a k row is half the bank window, so the row's bit 0 selects a half already.  Smaller TILES bring the
   // permuted pieces closer together (4 TILES indices apart): the rows then differ in the chunk bits these leave free.
   __device__ __forceinline__ static uint32_t swz(uint32_t krow) {
-    if (EXT == 16) return 0;
     if (EXT == 32) return 2 * ((krow >> 3) & 1);
     if (EXT == 64) return kPermute ? 4 * ((krow >> 1) & 1) : (2 * ((krow >> 1) & 1)) ^ (4 * ((krow >> 3) & 1));
     if (EXT == 128 && kPermute) return (krow & 1) ^ (8 * ((krow >> 1) & 1));

@@ -143,7 +143,7 @@ inline bool use_even_map(int n_slow, int n_fast) {
 // The map of a forward launch that does not balance itself (see TileFeed): even wherever that saves a round.  18 x 25 tiles
 // in rectangles are 75 on each of six XCDs, three rounds instead of two: 6328 rows, d = 1704, V = 4480: forward 136 us, 97
 // with equal shares, 115 with queues.  Over 65 shapes in which it saves a round, of 40 to 800 us: 0.56 to 0.97 of the
-// rectangles' time, 0.82 in the mean, and 0.81 of the queues' (1.00 at most).  Where it saves none: 0.92 to 1.04, 1.00.
+// rectangles' time, 0.82 in the mean, and 0.81 of the queues' (1.00 at most).  Where it saves none: 0.93 to 1.04, 1.00.
 inline bool forward_even_map(int n_slow, int n_fast) {
   return fewer_rounds(xcd_share(n_slow, n_fast, false), xcd_share(n_slow, n_fast, true));
 }

@@ -139,14 +139,15 @@ int rows_of(const Plan& p, int i) {
 //                  9 shapes between 1 and that: forward calls 0.84 to 1.02, 0.93 in the mean (231 tokens, d = 3304, I = 8400:
 //                  96 us -> 81) and 0.86 to 1.02, 0.93; beyond it 0.96 to 1.10 (gate/up, 1.0 in the mean), 0.86 to 1.07 (down)
 //   64 x 64        0.45 (few workgroups on a compute unit) to 0.85 (four) per K step + 2.5.  1536 tokens, d = 1536,
-//                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256)
+//                  I = 4608: down 38 us (576 tiles) against 79 (36 of 256).  Too low behind large tiles: gate/up of 1668
+//                  tokens below is taken at 16.6, a trace has 20.9 (182 lone 128 x 128 tiles would be 17.0 by their line)
 //   64 x 64 lone   0.24 per K step + 2.5.  256 tokens, d = 256, I = 896: down 5.5 against 18; 200 tokens, d = 4096,
 //                  I = 14336: down 63 against 250 (16 tiles of 256), dX 129 against 523
 //   64 x 64 long   the same with K steps of 128, 0.22 per 64 + 3.5, for one workgroup per compute unit: the down of 200
 //                  tokens 53, of 512 tokens (d = 2048, I = 5632) 21.6 against 22.5; slower at fewer than 64 K steps
 //   32 x 32        0.11 per 64 (0.17 with K-strided weights) + 3 where there are few 64 x 64 tiles (more than 128, or 64
-//                  K-strided, move too much through L2 for this): a quarter of the LDS traffic per K step, and four times
-//                  the compute units.  Forward of 64 tokens, d = 2048, I = 6000: 33 us -> 22, of 500, d = 640, I = 1800:
+//                  K-strided, move too much through L2 for this): half of the LDS traffic and a quarter of the MFMAs per K
+//                  step, on four times the compute units.  Forward of 64 tokens, d = 2048, I = 6000: 33 us -> 22, of 500, d = 640, I = 1800:
 //                  18.9 -> 15; backward of 178 tokens, d = 520, I = 1456: 35 -> 30.  Not for gate/up (pairs of row tiles),
 //                  and not for three rows of them (65 to 96 tokens) that are more than a round and more than 60000 K steps
 //                  in all: 39 forward calls there, d = 3200 to 4096, took 0.96 to 1.10 of their time with 64 x 64 tiles, 1.06
@@ -160,7 +161,7 @@ enum TileKind { kBig, k128, k128Lone, k64, k64Lone, k64Long, k32, kHalf };   // 
 struct TileChoice {
   TileKind kind;      // of the whole, or of what follows the first `head` columns
   int64_t head;       // A-side extent, a multiple of 256, that large tiles cover in a launch of its own (0: none)
-  double us;
+  double us;          // of the tile that the ranking is about: of 128 x 128 where 128 x 256 is taken in its place
 };
 enum Weights { kGateUp, kContiguous, kStrided };                 // gate/up, down, dA and dX
 double half_us(double k) { return 0.68 * k + 5.0; }                // a round of 128 x 256 tiles

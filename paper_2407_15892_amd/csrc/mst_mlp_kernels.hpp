@@ -466,6 +466,8 @@ __global__ __launch_bounds__(kThreads) void k_mlp_dw3(DwProblems ps, int rows, i
 // T: 256 x 256, or half of that on the A side (hidden index) where whole tiles would be the end of the launch.
 // Both launches -> one, us: 1024 rows, d = 4096, I = 14336: 638 -> 570 (half tiles); 2048 rows of it 1050 -> 940 (whole);
 // 1668 rows, d = 1544, I = 5384: 206 -> 170 (half).
+// With whole tiles the launch has 36 bytes of scratch per lane, for eight registers that nn_tile spills across its first
+// term's main loop, once per tile (as in k_mlp_gemm_nn); the weight-gradient tiles spill nothing.
 struct DxProblem {
   const __bf16 *dG, *Wg, *dU, *Wu;   // [rows][I], [I][d]
   int d, I, n_st, n_jt, grid;        // grid: workgroups of this problem, a multiple of the XCD count
