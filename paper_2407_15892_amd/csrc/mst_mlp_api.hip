@@ -277,8 +277,14 @@ void launch_dx_dw3_small(hipStream_t st, DxProblem x, const DwProblems& ps, int 
   x.n_jt = (x.d + CX::EA - 1) / CX::EA;
   x.n_st = (rows + CX::EB - 1) / CX::EB;
   x.grid = even_grid(x.n_jt, x.n_st);
-  hipLaunchKernelGGL((k_mlp_dx_dw3_small<CX, CW>), dim3(x.grid + ps.p[0].grid + ps.p[1].grid + ps.p[2].grid), dim3(CW::kThreads),
-                     CX::kLds > CW::kLds ? CX::kLds : CW::kLds, st, x, ps, rows, accumulate);
+  const int dw_grid = ps.p[0].grid + ps.p[1].grid + ps.p[2].grid;
+  // The longer tiles first, where not all workgroups are resident at once (two per compute unit): behind dX the weight
+  // gradients' are dealt out as slots come free, two to one unit while others idle.  dX first, 57 steps with more than 512
+  // tiles of dX and 129 to 256 of the weight gradients took 1.06 of their time with two launches in the mean, up to 1.21 (9764
+  // rows, d = 256, I = 816: 114 us -> 137); with the longer first 38 with more than 512 of dX took 0.89 to 0.99, 0.93.
+  const bool dw_first = 2 * ksteps_of(x.I) < ksteps_of(rows) && x.grid + dw_grid > 2 * kNumCu;
+  hipLaunchKernelGGL((k_mlp_dx_dw3_small<CX, CW>), dim3(x.grid + dw_grid), dim3(CW::kThreads),
+                     CX::kLds > CW::kLds ? CX::kLds : CW::kLds, st, x, ps, rows, accumulate, dw_first ? dw_grid : 0);
 }
 
 // A = silu(X Wg^T) * (X Wu^T) of a chunk, or its backward (dA given)

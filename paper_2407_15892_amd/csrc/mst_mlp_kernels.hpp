@@ -400,9 +400,9 @@ template <class C>
 __device__ __forceinline__ void nn_tile_small(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
-    int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo, char* smem) {
+    int ldp, int ldq, int rows, int N, int K, int block, int n_st, int n_nt, __bf16* __restrict__ out, int ldo, char* smem) {
   int nt, st;
-  if (!even_tile_of_block(blockIdx.x, n_nt, n_st, &nt, &st)) return;
+  if (!even_tile_of_block(block, n_nt, n_st, &nt, &st)) return;
   const int n0 = nt * C::EA, s0 = st * C::EB;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gemm_nn
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
     int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  nn_tile_small<C>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, n_st, n_nt, out, ldo, smem);
+  nn_tile_small<C>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, blockIdx.x, n_st, n_nt, out, ldo, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -500,16 +500,19 @@ __global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_dw3_sma
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   dw3_tile_small<C>(blockIdx.x, ps, rows, accumulate, smem);
 }
-// and with dX beside them (CX: its tile)
+// and with dX beside them (CX: its tile).  dX has the workgroups from dx_from on; the others, before and behind, are those
+// of the weight gradients (dx_from is 0 or all of theirs).
 template <class CX, class CW>
-__global__ __launch_bounds__(CW::kThreads, kSmallWavesPerSimd) void k_mlp_dx_dw3_small(DxProblem x, DwProblems ps, int rows, int accumulate) {
+__global__ __launch_bounds__(CW::kThreads, kSmallWavesPerSimd) void k_mlp_dx_dw3_small(DxProblem x, DwProblems ps, int rows, int accumulate,
+                                                                                      int dx_from) {
   static_assert(CX::kThreads == CW::kThreads, "one launch");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  if ((int)blockIdx.x < x.grid) {
-    nn_tile_small<CX>(x.dG, x.Wg, x.dU, x.Wu, x.I, x.d, rows, x.d, x.I, x.n_st, x.n_jt, x.dX, x.d, smem);
+  const int b = (int)blockIdx.x - dx_from;
+  if (b >= 0 && b < x.grid) {
+    nn_tile_small<CX>(x.dG, x.Wg, x.dU, x.Wu, x.I, x.d, rows, x.d, x.I, b, x.n_st, x.n_jt, x.dX, x.d, smem);
     return;
   }
-  dw3_tile_small<CW>((int)blockIdx.x - x.grid, ps, rows, accumulate, smem);
+  dw3_tile_small<CW>(b < 0 ? (int)blockIdx.x : b - x.grid, ps, rows, accumulate, smem);
 }
 
 }  // namespace mst

@@ -252,6 +252,7 @@ SMALL_SHAPES = [
     (33, 1032, 2056, {1: ("32", False), 2: ("32", False)}),   # dA in 32 x 32 tiles
     (450, 776, 1992, {1: ("64", True), 7: ("32", True)}),
     (2001, 264, 1032, {1: ("64", False), 2: ("64", False)}),
+    (5083, 472, 368, {1: ("64", False), 2: ("64", True)}),    # unsplit: the weight gradients' longer tiles before 640 of dX
     (41, 2056, 4104, {1: ("own", False)}),                    # dX in 32 x 32 tiles, its last K step of 128 ragged
     (300, 520, 16, {1: ("32", True)}),
 ]
