@@ -123,7 +123,10 @@ double pairs_us(const Plan* p) {
 // 64 to 2400 rows, d = 256 to 2112, V = 2012 to 23326: dlogits of the pair as one launch; dH + dW the longer of one dH
 // workgroup by itself (5, and a time per 128 vocabulary entries by its tile) and the dH loads (16 TB/s; 64-byte pieces cost
 // half as much again) on top of the time of dW.  A call of one chunk can keep the split partials of dH instead: its separate
-// launches less 2.
+// launches less 2, unless few tiles of dW have a contraction over so many rows that their pipelined form, which they have in a
+// launch of their own, is worth more (0.45 against 0.25 per K step).  500 calls of one chunk, both ways: 133 in separate
+// launches by this rule took 0.98 to 1.77 of their time in one, 1.26 in the mean (27903 rows, d = 16, V = 55: 102 us, 180
+// in one), the others 0.89 to 1.11, 0.98.
 // kJoint: of 104 shapes timed in every form none takes longer than with separate launches (0.82 of that in the mean), and
 // the form taken is 0.5 % behind the fastest one in the mean, 8 % at most.
 constexpr double kJoint = 0.95;
@@ -143,8 +146,13 @@ void choose_joint(Plan* p) {
   if (!p->small_dlogits || !p->small_dh || !p->small_dw) return;
   p->joint_us = pairs_us(p);
   if (p->n_chunks == 1) {
-    p->joint = MST_PAIR_SPLIT;
-    p->joint_us -= 2.0;
+    const double kw = (double)((p->S + kBK - 1) / kBK), kh = (double)p->small_dh_ksteps;
+    const double apart = 2.0 + small_launch_us(tiles_of(p->S, p->d, 64) * p->small_dh_split, kh) +
+                         small_launch_us(tiles_of(p->V, p->d, 64), kw);
+    if (0.45 * std::max(kw, kh) + 3.5 <= apart) {
+      p->joint = MST_PAIR_SPLIT;
+      p->joint_us -= 2.0;
+    }
   }
   double best = kJoint * p->joint_us;
   for (int k = 0; k < 3; ++k) {

@@ -594,6 +594,7 @@ def test_automatic_block_shapes_with_split_dh_match_oracle(S, d, V, M, row_block
     (257, 2056, 3003, 1, "split"),     # no split: dH straight to bf16
     (1, 8, 2, 1, "split"),
     (1025, 264, 9001, 3, "separate"),  # 64 x 64 tiles throughout, dH in 8 splits
+    (5833, 72, 355, 1, "separate"),    # one chunk, dW's twelve tiles over 92 K steps
 ])
 def test_joint_launches_of_the_pair_order_match_oracle(schedule, S, d, V, M, launches):
     """dH and dW of small problems from one launch, in every form, with and without sums of an earlier pair in dW: against

@@ -381,6 +381,13 @@ def test_tiles_of_the_gpu_tests_are_the_ones_they_name(mst):
     assert mst.load_library().mst_tile_info(2048, 264, 4093, 1, None) == -1
 
 
+def test_few_long_tiles_of_dw_have_a_launch_of_their_own(mst):
+    """One chunk of many rows against a small vocabulary: dW's few tiles keep the pipelined form of a lone launch."""
+    for shape, want in {(27903, 16, 55, 1): "separate", (16354, 40, 22, 1): "separate", (5833, 16, 355, 1): "separate",
+                        (17, 264, 4097, 1): "split", (1500, 104, 700, 1): "split", (257, 2056, 3003, 1): "split"}.items():
+        assert mst.mst_pair_launches(*shape) == want, shape
+
+
 def test_forward_takes_no_map_that_costs_a_round(mst):
     """256-row forward tiles: wherever the rectangles' busiest XCD (32 compute units) needs more rounds than an equal share of
     the tiles would, the launch deals them out evenly or pulls them from queues."""
