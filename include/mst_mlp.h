@@ -64,7 +64,8 @@ const char* mst_mlp_version(void);
 
 /*
  * Bytes of workspace the two calls need (host, pure).
- *   fwd: one chunk of A, C * I bf16.
+ *   fwd: one chunk of A, C * I bf16.  A larger one is used, for the A of more rows at a time; so are the rows of O that are
+ *        not written yet, unless O overlaps an input.
  *   bwd: three chunk-sized bf16 buffers (dA reused for dG, dU, A) = 3 * C * I * 2 bytes.
  * Either output pointer may be NULL.
  */

@@ -300,3 +300,33 @@ def test_tiles_of_128_by_256_match_oracle_and_keep_their_bits(S, d, I, products,
     _, got, _ = _run_all(inp, M=M)
     for k in ("O", "dX"):
         assert np.array_equal(got[k], base[k]), k
+
+
+@pytest.mark.parametrize("S,d,I,M", [
+    (1500, 136, 264, 12),     # chunks of 125 rows; several groups of rows with their A in the output, the last ones in the workspace
+    (1601, 264, 520, 23),     # ragged everywhere, groups of odd numbers of rows
+    (700, 520, 72, 9),        # I < d: the output holds most of A at once
+    (131, 8, 1032, 4),        # I much larger than d: nothing of it
+])
+def test_forward_groups_of_rows_keep_the_bits(S, d, I, M):
+    """Where the forward keeps A -- in the declared workspace, in a larger one, in rows of O that are not written yet -- does
+    not show in O, and it stays inside both.  An O that is X itself (its rows are read before they are written, chunk by
+    chunk) holds no A."""
+    import torch
+    MlpDeviceRun, f64 = _harness()
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=360 + S % 7, w_std=0.05))
+    run = MlpDeviceRun(inp, M=M)
+    ref = _reference(inp)["O"]
+    base = f64(MlpDeviceRun(inp, M=1).forward())
+    assert np.abs(base - ref).max() <= TOL * np.abs(ref).max()
+    for times in (1, 2, 3):
+        ws = torch.full((times * run.fwd_bytes + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        O = torch.full(((S + 2) * d,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        run.mst.mst_mlp_fwd(run.X, run.Wg, run.Wu, run.Wd, M, ws[: times * run.fwd_bytes], O[d:-d].view(S, d))
+        torch.cuda.synchronize()
+        assert np.array_equal(f64(O[d:-d].view(S, d)), base), times
+        assert bool((ws[times * run.fwd_bytes:] == 0xA5).all()) and bool(O[:d].isnan().all()) and bool(O[-d:].isnan().all())
+    X = run.X.clone()
+    run.mst.mst_mlp_fwd(X, run.Wg, run.Wu, run.Wd, M, ws[: run.fwd_bytes], X)
+    torch.cuda.synchronize()
+    assert np.array_equal(f64(X), base)
