@@ -228,6 +228,7 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
  *                            one is clearly below it (blocks by 5 %, pairs by 20 %) and also looks at block shapes that
  *                            the forced orders do not take: a single window, and a window's dH contraction in up to 8
  *                            splits with running sums of their own, added in fixed order at the end.
+ *                            Small hidden sizes may take neither (mst_bwd_streamed).
  * mst_set_bwd_schedule: host; the override belongs to the CALLING THREAD (thread-local, AUTO in every new
  * thread) and takes effect at that thread's next backward call, so one caller's setting never changes the
  * summation order of another thread's call; MST_ERR_BAD_SHAPE for an unknown value.
@@ -241,6 +242,24 @@ enum { MST_BWD_SCHEDULE_AUTO = 0, MST_BWD_SCHEDULE_PAIRS = 1, MST_BWD_SCHEDULE_B
 mst_status mst_set_bwd_schedule(int32_t schedule);
 mst_status mst_bwd_schedule_info(int64_t S, int64_t d, int64_t V, int32_t M, int64_t* info);
 mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M, int32_t schedule, int64_t* info);
+
+/*
+ * mst_bwd_streamed (host, pure): whether the automatic order takes neither of the two for this shape (128 < d <= 512 only):
+ * dlogits are then formed where they are used, once for dH and once for dW, by one launch, and never stored; the workspace
+ * holds fp32 partials of dH.  Returns one of MST_STREAMED_*, 0 where the order of mst_bwd_schedule_info runs, -1 for bad
+ * arguments; *splits (may be NULL): the parts of dH's contraction over the vocabulary, added in a fixed order (0 if not so).
+ */
+enum {
+  MST_STREAMED_NO = 0,
+  MST_STREAMED_256,           /* d <= 256: workgroups that own 128 rows or vocabulary entries             */
+  MST_STREAMED_256_NARROW,    /* 64                                                                       */
+  MST_STREAMED_256_SPLIT,     /* 16 rows or 32 vocabulary entries, whose waves share out the other index  */
+  MST_STREAMED_384,           /* d <= 384: 64                                                             */
+  MST_STREAMED_384_SPLIT,     /* 32, two pairs of waves                                                   */
+  MST_STREAMED_512,           /* d <= 512: 64                                                             */
+  MST_STREAMED_512_SPLIT      /* 32, two pairs of waves                                                   */
+};
+int32_t mst_bwd_streamed(int64_t S, int64_t d, int64_t V, int32_t M, int32_t* splits);
 
 /*
  * Workgroup -> tile maps of the GEMM kernels (host-only test aids; the kernels call the same functions).
@@ -329,7 +348,8 @@ enum {
   MST_K_FWD_GEMM_LSE,    /* logits tile GEMM + running max / sum-exp epilogue   */
   MST_K_LSE_FINALIZE,    /* combine per-vocab-tile partials into lse, nll       */
   MST_K_LOSS_REDUCE,     /* fixed-order sum of nll / N_valid, label range check */
-  MST_K_BWD_GEMM_DLOGITS,/* recomputed logits GEMM + softmax-minus-onehot       */
+  MST_K_BWD_GEMM_DLOGITS,/* recomputed logits GEMM + softmax-minus-onehot; with
+                            both gradients, where mst_bwd_streamed is not 0     */
   MST_K_BWD_GEMM_DH,     /* dH_i = dlogits_i W (split over V)                   */
   MST_K_BWD_DH_REDUCE,   /* fixed-order sum of the dH split partials            */
   MST_K_BWD_GEMM_DW,     /* dW += dlogits_i^T H_i                               */

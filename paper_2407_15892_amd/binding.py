@@ -90,6 +90,8 @@ def load_library() -> ctypes.CDLL:
     lib.mst_forward_tile_rows.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_forward_launch.restype = c.c_int32
     lib.mst_forward_launch.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
+    lib.mst_bwd_streamed.restype = c.c_int32
+    lib.mst_bwd_streamed.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.POINTER(c.c_int32)]
     lib.mst_pair_launches.restype = c.c_int32
     lib.mst_pair_launches.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_profile_enable.restype = c.c_int
@@ -234,6 +236,15 @@ def mst_forward_launch(S: int, d: int, V: int, M: int) -> str:
 
 
 PAIR_LAUNCHES = ("separate", "32x16", "64x16", "64x32", "split")     # MST_PAIR_*
+
+
+STREAMED = ("no", "256", "256_narrow", "256_split", "384", "384_split", "512", "512_split")     # MST_STREAMED_*
+
+
+def mst_bwd_streamed(S: int, d: int, V: int, M: int):
+    """(form, splits of dH) of a backward call under the automatic order that stores no dlogits; ("no", 0) elsewhere."""
+    splits = ctypes.c_int32(0)
+    return STREAMED[load_library().mst_bwd_streamed(S, d, V, M, ctypes.byref(splits))], int(splits.value)
 
 
 def mst_pair_launches(S: int, d: int, V: int, M: int) -> str:

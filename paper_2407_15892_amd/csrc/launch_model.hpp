@@ -33,18 +33,22 @@ inline double launch_us(int64_t tiles, TileCost c, double bytes) {
   const double rounds = (double)((tiles + kNumCu - 1) / kNumCu) * c.alone(), busy = (double)tiles / kNumCu * c.busy();
   return 2.0 + std::max(std::max(rounds, busy), bytes / kHbmBytesPerUs);
 }
-// n1 tiles of c1, then n2 of c2, handed out in this order: n1 % kNumCu units are late for the second kind by one tile of
-// the first, and the others take tiles of it meanwhile.  The end is that of the n2-th tile: a multiple of t2 after the
-// moment `a` when the others are free, or after the late ones are.
-inline double launch_us(int64_t n1, TileCost c1, int64_t n2, TileCost c2, double bytes) {
-  const double t1 = c1.alone(), t2 = c2.alone(), a = (double)(n1 / kNumCu) * t1;
-  const int64_t late = n1 % kNumCu, others = kNumCu - late;
-  const int64_t f = late ? (int64_t)(t1 / t2) : 0, c = late ? f + 1 : 0;    // whole tiles before the late ones' first, + 1
+// The time until n1 pieces of work of t1, then n2 of t2, handed out in this order to `units`, are done: n1 % units of them are
+// late for the second kind by one piece of the first, and the others take pieces of it meanwhile.  The end is that of the
+// n2-th piece: a multiple of t2 after the moment `a` when the others are free, or after the late ones are.
+inline double span_us(int64_t n1, double t1, int64_t n2, double t2, int64_t units) {
+  const double a = (double)(n1 / units) * t1;
+  const int64_t late = n1 % units, others = units - late;
+  const int64_t f = late ? (int64_t)(t1 / t2) : 0, c = late ? f + 1 : 0;    // whole pieces before the late ones' first, + 1
   auto up = [](int64_t n, int64_t by) { return n > 0 ? (n + by - 1) / by : 0; };
   const int64_t j = up(n2, others);
-  const double with_others = (double)(j <= c ? j : up(n2 + late * c, kNumCu)) * t2;
-  const double with_late = t1 + (double)up(n2 - others * f, kNumCu) * t2;
-  const double span = a + (late ? std::max(t1, std::min(with_others, with_late)) : with_others);
+  const double with_others = (double)(j <= c ? j : up(n2 + late * c, units)) * t2;
+  const double with_late = t1 + (double)up(n2 - others * f, units) * t2;
+  return a + (late ? std::max(t1, std::min(with_others, with_late)) : with_others);
+}
+// n1 tiles of c1, then n2 of c2
+inline double launch_us(int64_t n1, TileCost c1, int64_t n2, TileCost c2, double bytes) {
+  const double span = span_us(n1, c1.alone(), n2, c2.alone(), kNumCu);
   const double busy = ((double)n1 * c1.busy() + (double)n2 * c2.busy()) / kNumCu;
   return 2.0 + std::max(std::max(span, busy), 1.3 * bytes / kHbmBytesPerUs);
 }

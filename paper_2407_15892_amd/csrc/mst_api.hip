@@ -8,6 +8,7 @@
 #include "host_util.hpp"
 #include "launch_model.hpp"
 #include "mst_small_kernels.hpp"
+#include "mst_stream_kernels.hpp"
 
 #include <algorithm>
 #include <atomic>
@@ -63,6 +64,9 @@ struct Plan {
   int blk_split;      // splits of a window's dH contraction, each with running sums of its own
   size_t blk_acc;     // byte offset of the dH sums
   double est_pairs_us, est_blocks_us;   // the cost model's figures (for the record; see choose_schedule)
+  // Neither order: dlogits formed where they are used (MST_STREAMED_* of the header, 0: not so)
+  int streamed;
+  int stream_split, stream_per_split;   // shares of dH's contraction, vocabulary entries of each
 };
 
 // ------------------------------------------------------------------ backward schedule
@@ -263,6 +267,80 @@ int best_dh_split(const Plan* p, int ksteps, int most) {
   return (ksteps + per - 1) / per;
 }
 
+// ---- backward without dlogits in memory (mst_stream_kernels.hpp), for 128 < d <= 512 and the automatic order only
+typedef CfgStream<256, 2, 1, 4> Stream256;          // 128 owners, two workgroups on a compute unit
+typedef CfgStream<256, 1, 1, 4> Stream256Narrow;    // 64 owners
+typedef CfgStream<256, 1, 4, 2> Stream256SplitH;    // 16 and 32 owners, whose waves share out the stream: for few owners
+typedef CfgStream<256, 2, 4, 2> Stream256SplitW;
+typedef CfgStream<384, 1, 1, 3> Stream384;          // 64 owners
+typedef CfgStream<384, 1, 2, 2> Stream384Split;     // 32 owners
+typedef CfgStream<512, 1, 1, 2> Stream512;
+typedef CfgStream<512, 1, 2, 2> Stream512Split;
+
+typedef void (*StreamLaunch)(hipStream_t, const StreamProblem&, int split, int per_split, float*, __bf16*, float*);
+template <class CH, class CW>
+void launch_streamed(hipStream_t st, const StreamProblem& q, int split, int per_split, float* partial, __bf16* dH, float* dW) {
+  const int dh_grid = even_grid(split, (q.S + CH::kOwners - 1) / CH::kOwners), dw_grid = even_grid((q.V + CW::kOwners - 1) / CW::kOwners, 1);
+  const bool dw_first = q.S > per_split;               // steps of a workgroup
+  hipLaunchKernelGGL((k_bwd_stream<CH, CW>), dim3(dh_grid + dw_grid), dim3(CH::kThreads), CH::kLds > CW::kLds ? CH::kLds : CW::kLds, st,
+                     q, dw_first ? dw_grid : 0, dh_grid, split, per_split, partial, dH, dW);
+}
+// Microseconds: a step of a workgroup by itself, a step's share of a compute unit with all of them busy, the ends of a
+// workgroup (in steps), the launch.  Fitted to 260 shapes of 64 to 32768 rows, d = 136 to 512, V = 1000 to 128000, every
+// form with 1 to 64 splits (within 4 to 8 % rms; the form and split taken are 2.5 % behind the fastest in the mean).  A step
+// of dW takes up to 1.7 times that where its 16 OT entries are likely to be labels; operands, dW and partials at 2.5 TB/s.
+struct StreamForm { int dk, owners_h, owners_w, ot_w, rings, per_cu; double step, busy, ends, fixed; StreamLaunch launch; };
+template <class CH, class CW>
+constexpr StreamForm stream_form(double step, double busy, double ends, double fixed) {
+  static_assert(CH::NWS == CW::NWS && CH::DK == CW::DK, "one launch");
+  return {CH::DK, CH::kOwners, CW::kOwners, CW::OT, CH::NWS, CH::kLds > 81920 ? 1 : 2, step, busy, ends, fixed, launch_streamed<CH, CW>};
+}
+constexpr StreamForm kStreamForms[] = {                // MST_STREAMED_*, from 1 on, in this order
+    stream_form<Stream256, Stream256>(0.89, 0.80, 0.0, 8.5),
+    stream_form<Stream256Narrow, Stream256Narrow>(0.63, 0.52, 0.0, 6.0),
+    stream_form<Stream256SplitH, Stream256SplitW>(0.62, 0.66, 7.1, 1.1),
+    stream_form<Stream384, Stream384>(0.84, 0.77, 0.0, 5.9),
+    stream_form<Stream384Split, Stream384Split>(1.00, 0.90, 4.0, 2.8),
+    stream_form<Stream512, Stream512>(1.09, 1.00, 2.0, 3.2),
+    stream_form<Stream512Split, Stream512Split>(1.32, 1.20, 3.1, 2.8)};
+double stream_us(const Plan* p, const StreamForm& f, int split, int per_split) {
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t n_h = up(p->S, f.owners_h) * split, n_w = up(p->V, f.owners_w);
+  const double by_label = 1.0 + 0.7 * std::min(1.0, 512.0 * f.ot_w / (double)p->V);
+  const double t_h = (double)up(per_split, 32 * f.rings) + f.ends, t_w = ((double)up(p->S, 32 * f.rings) + f.ends) * by_label;
+  const double partials = split > 1 ? 4.0 * (double)split * (double)(p->S * p->d) : 0.0;
+  const int64_t units = (int64_t)kNumCu * f.per_cu;
+  const double chain = f.step * (t_w > t_h ? span_us(n_w, t_w, n_h, t_h, units) : span_us(n_h, t_h, n_w, t_w, units));
+  const double busy = f.busy * ((double)n_h * t_h + (double)n_w * t_w) / kNumCu, bytes = (8.0 * (double)(p->V * p->d) + partials) / 2.5e6;
+  const double t = f.fixed + std::cbrt(chain * chain * chain + busy * busy * busy + bytes * bytes * bytes);     // the longest, smoothed
+  return split > 1 ? t + 3.5 + partials / kHbmBytesPerUs : t;
+}
+// Taken where it is estimated this much below the order that would run (the estimates of blocks are 8 % too high in the mean).
+// Of the 260 shapes 139 are; they took 0.60 of that order's time in the mean, three of them 1.06 to 1.09 (V = 1673 to 4116), and
+// of the others 37 would have been faster by more than 3 %.
+constexpr double kStreamedPairs = 0.9, kStreamedBlocks = 0.78;
+void choose_streamed(Plan* p) {
+  const int64_t S = p->S, d = p->d, V = p->V;
+  if (d <= 128 || d > 512 || S * d >= (int64_t(1) << 30) || V * d >= (int64_t(1) << 30)) return;   // 32-bit byte offsets of whole operands
+  const int64_t room = (int64_t)(p->b_total / ((size_t)(S * d) * 4));
+  double best = p->blk_use ? kStreamedBlocks * p->est_blocks_us : kStreamedPairs * p->est_pairs_us;
+  for (int k = 0; k < (int)(sizeof(kStreamForms) / sizeof(kStreamForms[0])); ++k) {
+    const StreamForm& f = kStreamForms[k];
+    if (f.dk < d || f.dk - d >= (f.dk == 256 ? 256 : 128)) continue;
+    for (const int n : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64}) {
+      if (n > 1 && n > room) break;
+      const int per_split = (int)(((V + n - 1) / n + 31) / 32 * 32), split = (int)((V + per_split - 1) / per_split);   // all begin inside V
+      if (split != n) continue;
+      const double t = stream_us(p, f, split, per_split);
+      if (t >= best) continue;
+      best = t;
+      p->streamed = k + 1;
+      p->stream_split = split;
+      p->stream_per_split = per_split;
+    }
+  }
+}
+
 void choose_schedule(Plan* p, int forced) {
   choose_joint(p);
   const int64_t S = p->S, d = p->d, V = p->V, C = p->C;
@@ -339,6 +417,7 @@ void choose_schedule(Plan* p, int forced) {
   else if (forced == MST_BWD_SCHEDULE_AUTO) {
     if (!(best < pairs)) p->blk_use = false;
     choose_split_blocks(p);
+    choose_streamed(p);
   }
   // MST_BWD_SCHEDULE_BLOCKS and _BLOCKS_FUSED keep the best block shape whenever one fits
 }
@@ -423,6 +502,7 @@ mst_status make_plan(int64_t S, int64_t d, int64_t V, int32_t M, Plan* p, int fo
   p->b_lse = p->b_ctl + sizeof(Control);
   p->b_fwd = p->b_lse + align_up((size_t)S * 4, 256);
   p->b_total_max = p->b_fwd + p->f_total;
+  p->streamed = 0;
   if (schedule) choose_schedule(p, forced);
   return MST_OK;
 }
@@ -461,6 +541,13 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_bwd_gemm_dh_dw_small<TileKSplit64x16, Tile64>);
   set((const void*)k_bwd_gemm_dh_dw_small<TileKSplit64x32, Tile64>);
   set((const void*)k_bwd_gemm_dh_split_dw_small<Tile64>);
+  set((const void*)k_bwd_stream<Stream256, Stream256>);
+  set((const void*)k_bwd_stream<Stream256Narrow, Stream256Narrow>);
+  set((const void*)k_bwd_stream<Stream256SplitH, Stream256SplitW>);
+  set((const void*)k_bwd_stream<Stream384, Stream384>);
+  set((const void*)k_bwd_stream<Stream384Split, Stream384Split>);
+  set((const void*)k_bwd_stream<Stream512, Stream512>);
+  set((const void*)k_bwd_stream<Stream512Split, Stream512Split>);
   set((const void*)k_bwd_gemm_dlogits<false>);
   set((const void*)k_bwd_gemm_dlogits<true>);
   set((const void*)k_bwd_gemm_dh<false>);
@@ -761,6 +848,21 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
   }
   __bf16* slot[2] = {reinterpret_cast<__bf16*>(ws), reinterpret_cast<__bf16*>(ws + p.b_slot)};
   __bf16* dHb = static_cast<__bf16*>(dH);
+  if (p.streamed) {
+    float* const partial = reinterpret_cast<float*>(ws);
+    {
+      Scope sc(st, MST_K_BWD_GEMM_DLOGITS);
+      const StreamProblem q = {Hb, Wb, labels, lse, (int)S, (int)d, (int)V, ignore_index, nv, grad_loss};
+      kStreamForms[p.streamed - 1].launch(st, q, p.stream_split, p.stream_per_split, partial, dHb, dW);
+    }
+    if (p.stream_split > 1) {
+      Scope sc(st, MST_K_BWD_DH_REDUCE);
+      const size_t n = (size_t)S * d;
+      hipLaunchKernelGGL(k_bwd_dh_reduce, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st, partial, p.stream_split, n, n, nv,
+                         grad_loss, dHb);
+    }
+    return check_launch();
+  }
 
   auto rows_of = [&](int i) { const int64_t r0 = (int64_t)i * p.C; return (int)((p.S - r0) < p.C ? (p.S - r0) : p.C); };
   auto dlogits = [&](int i, int rows, __bf16* G) {        // of `rows` rows from chunk i on
@@ -1026,6 +1128,13 @@ int32_t mst_pair_launches(int64_t S, int64_t d, int64_t V, int32_t M) {
   Plan p;
   if (make_plan(S, d, V, M, &p, MST_BWD_SCHEDULE_PAIRS) != MST_OK) return -1;
   return p.joint;
+}
+
+int32_t mst_bwd_streamed(int64_t S, int64_t d, int64_t V, int32_t M, int32_t* splits) {
+  Plan p;
+  if (make_plan(S, d, V, M, &p) != MST_OK) return -1;
+  if (splits) *splits = p.streamed ? p.stream_split : 0;
+  return p.streamed;
 }
 
 mst_status mst_tile_info(int64_t S, int64_t d, int64_t V, int32_t M, int64_t* info) {

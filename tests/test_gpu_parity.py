@@ -869,3 +869,73 @@ def test_kernel_timing_covers_every_nth_launch_of_each_kind():
     assert {k: v[2] for k, v in counts[1].items()} == {k: v[2] for k, v in counts[3].items()}
     assert counts[1]["fwd_gemm_lse"][2] == 2 and counts[1]["bwd_gemm_dlogits"][2] >= 2
     assert all(v == (0.0, 0, 0) for v in mst.mst_profile_collect().values()), "collect clears the record"
+
+
+@pytest.mark.parametrize("S,d,V,M,form,splits", [
+    (354, 136, 22785, 2, "256", 48),           # most splits, a last share of 33 entries; three row owners, 17 of 32 K chunks used
+    (1398, 200, 7156, 3, "256_narrow", 5),
+    (8, 136, 41, 5, "256_narrow", 1),          # fewer rows, and in the last step fewer entries, than a tile
+    (1327, 248, 6079, 3, "256_split", 1),      # dH straight to bf16; waves with different numbers of whole steps
+    (1103, 216, 8395, 7, "256_split", 3),
+    (11, 136, 165, 3, "256_split", 1),
+    (512, 256, 4096, 4, "256_split", 4),
+    (749, 360, 7413, 2, "384", 10),
+    (10, 280, 33, 4, "384", 1),
+    (1446, 360, 3961, 7, "384_split", 1),
+    (9, 296, 1775, 4, "384_split", 2),
+    (823, 392, 5894, 3, "512", 5),
+    (139, 408, 184, 5, "512", 1),
+    (209, 504, 262, 3, "512_split", 1),
+    (1414, 456, 3111, 7, "512_split", 1),
+    (742, 512, 9357, 7, "512_split", 2),
+    (742, 424, 6357, 5, "512_split", 3),
+])
+def test_backward_without_stored_dlogits_matches_oracle(S, d, V, M, form, splits):
+    """Every form of the streamed backward, at ragged ends of rows, vocabulary, hidden size and shares: against the oracle,
+    with and without the saved log-sum-exps, the same bits call after call, within the declared workspace; ignored rows
+    whose ignore value is a class of the vocabulary; a label outside it; all rows ignored."""
+    import torch
+    import paper_2407_15892_amd as mst
+    assert mst.mst_bwd_streamed(S, d, V, M) == (form, splits)
+    inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=480 + S % 97, w_std=0.3, ignore_frac=0.1, label_dist="zipf"))
+    _check_full(inp, grad_loss=0.8, use_lse=False)
+    run, _, _ = _check_full(inp, grad_loss=0.8)
+    first = (run.dH_t.clone(), run.dW_t.clone())
+    run.pad = 4096
+    run.backward(grad_loss=0.8)
+    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
+    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
+    assert bool((run.last_ws[-4096:] == 0xA5).all()), "wrote past the declared workspace"
+    inside = mi.make_inputs(mi.custom_config(S, d, V, M, index=480 + S % 97, w_std=0.3, ignore_frac=0.0, label_dist="zipf"))
+    inside.ignore_index = int(inside.labels[0])
+    _check_full(inside)
+    inp.labels[S // 2] = V
+    run.labels = torch.from_numpy(inp.labels).cuda()
+    run.forward()
+    for t in run.backward(poison="zero"):
+        assert torch.isnan(t.float()).all()
+    inp.labels[:] = inp.ignore_index
+    run.labels = torch.from_numpy(inp.labels).cuda()
+    run.forward()
+    for t in run.backward():
+        assert float(t.float().abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("S,d,V,split", [
+    (490, 608, 13770, 8),
+    (644, 600, 20683, 8),      # 81 x 3 dlogits tiles, dealt out evenly to save a round
+    (730, 728, 7883, 4),
+    (1257, 952, 5943, 2),
+])
+def test_splits_of_one_window_match_oracle_at_larger_hidden_sizes(S, d, V, split):
+    """The same block shapes as above, for hidden sizes that keep their dlogits in memory."""
+    import torch
+    import paper_2407_15892_amd as mst
+    info = mst.mst_bwd_schedule_info(S, d, V, 1)
+    assert (info["schedule"], info["row_blocks"], info["windows"], info["dh_split"]) == (mst.BWD_SCHEDULE_BLOCKS_FUSED, 1, 1, split), info
+    assert mst.mst_bwd_streamed(S, d, V, 1) == ("no", 0)
+    run, _, _ = _check_full(mi.make_inputs(mi.custom_config(S, d, V, 1, index=490, w_std=0.3, ignore_frac=0.1, label_dist="zipf")), grad_loss=0.8)
+    first = (run.dH_t.clone(), run.dW_t.clone())
+    run.backward(grad_loss=0.8)
+    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
+    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))

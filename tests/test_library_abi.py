@@ -412,3 +412,28 @@ def test_forward_takes_no_map_that_costs_a_round(mst):
     assert [mst.mst_forward_launch(*shape) for shape in ((32768, 4096, 128256, 32), (200, 4096, 128256, 1), (6328, 1704, 4480, 3))] \
         == ["queues", "rectangles", "even"]
     assert mst.load_library().mst_forward_launch(0, 264, 4093, 1) == -1
+
+
+def test_streamed_backward_keeps_its_shares_inside_the_vocabulary_and_the_workspace(mst):
+    """Host-only, over random shapes: every share of dH's contraction begins inside the vocabulary, the partials fit the
+    declared workspace, and only hidden sizes of the kernels are taken."""
+    import random
+    rng = random.Random(20240717)
+    seen = {}
+    for _ in range(20000):
+        S, d, V = round(2 ** rng.uniform(0, 14)), 8 * rng.randint(1, 80), round(2 ** rng.uniform(0, 17))
+        M = rng.randint(1, min(S, 40))
+        if mst.binding.mst_workspace_bytes_status(S, d, V, M) != 0:
+            continue
+        form, n = mst.mst_bwd_streamed(S, d, V, M)
+        seen[form] = seen.get(form, 0) + 1
+        if form == "no":
+            assert n == 0
+            continue
+        assert {"256": 128 < d <= 256, "384": 256 < d <= 384, "512": 384 < d <= 512}[form[:3]], (form, d)
+        per = -(-(-(-V // n)) // 32) * 32
+        assert n >= 1 and (n - 1) * per < V <= n * per, (S, d, V, M, n)
+        assert n == 1 or n * S * d * 4 <= mst.mst_workspace_bytes(S, d, V, M)[1]
+        assert S * d < 2 ** 30 and V * d < 2 ** 30
+    assert set(seen) == set(mst.binding.STREAMED) and min(seen.values()) > 20, seen
+    assert mst.load_library().mst_bwd_streamed(0, 256, 4096, 1, None) == -1
