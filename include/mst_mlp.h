@@ -134,11 +134,13 @@ mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info);
 enum {
   MST_MLP_DX_OWN = 0,     /* in a launch of its own, with the tiles that mst_mlp_tile_info names   */
   MST_MLP_DX_SHARED_256,  /* by the launch of the weight gradients, 256 x 256 tiles                */
-  MST_MLP_DX_SHARED_128,  /* the same, 128 (hidden index) x 256 (rows)                             */
+  MST_MLP_DX_SHARED_128,  /* the same, 128 (hidden index) x 256 or 128 (rows, see below)           */
   MST_MLP_DX_SHARED_64,   /* the same, 64 x 64 tiles, as those of the weight gradients             */
   MST_MLP_DX_SHARED_32    /* the same, 32 x 32                                                     */
 };
 int32_t mst_mlp_dx_tile(int64_t rows, int64_t d, int64_t I, int32_t first);
+/* Rows of that tile: 256 or 128 of MST_MLP_DX_SHARED_128, 256, 64 or 32 of the others, 0 of _OWN; -1 on bad shapes. */
+int32_t mst_mlp_dx_tile_rows(int64_t rows, int64_t d, int64_t I, int32_t first);
 
 /*
  * 1 where dA of a chunk of `rows` rows is computed by the launch of gate/up's backward, 0 where it has a launch of its own

@@ -31,6 +31,9 @@ typedef Cfg16<2, 4, 8, 4, 64, 3, 2> Tile16;
 typedef Cfg16<2, 4, 4, 4, 64, 3, 3> Tile16Half;
 // half of it on the B side
 typedef Cfg16<2, 4, 8, 2, 64, 3, 3> Tile16Rows128;
+// half of it on both sides, with five stages of both panels and the software-pipelined main loop: the shortest long tiles of a
+// shared launch (see nn_tile)
+typedef Cfg16<2, 4, 4, 2, 64, 5, 5> Tile16Quarter;
 constexpr int kTA16 = Tile16::TA, kTB16 = Tile16::TB;
 constexpr int kTile = 256;             // Tile16::EA == Tile16::EB
 constexpr int kBK = Tile16::BK;

@@ -101,6 +101,7 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_mlp_dw3<true, true>);
   set_dx_dw3_attributes<Tile16>(set);
   set_dx_dw3_attributes<Tile16Half>(set);
+  set_dx_dw3_attributes<Tile16Quarter>(set);
   return ok;
 }
 
@@ -265,8 +266,14 @@ bool fuse_da(int64_t rows, int64_t d, int64_t I) {
 // and they are the end of the launch.  212 steps of 2 to 5 chunks of up to 256 rows, d = 1800 to 4096, took 0.98 to 1.20 of
 // their time with two launches, 1.03 in the mean (4 x 244 rows, d = 4096, I = 14336: 2.49 ms, 2.65 with one); 67 with d
 // above 4096 0.93 to 1.13, 0.99.
-constexpr double kShared = 0.98;
-enum DxKind { kDxOwn, kDxWhole, kDxHalf, kDx64, kDx32 };
+// 128 x 128 tiles of dX (Tile16Quarter): a K step takes 0.58 beside the weight gradients, so its contraction over 2 I, which no
+// other workgroup can help with, ends sooner than in a half tile, for 1.4 times its compute unit time.  Backward of 3 chunks of
+// 888 rows, d = 1776, I = 6936: 869 us -> 708; of 707 rows, d = 1504, I = 5208: 182 -> 142.  70 backward calls of 1 to 3 chunks
+// of 100 to 7000 rows, d = 792 to 4016, each timed with every kind: 0.953 of their time without this one in the mean, 0.77 to
+// 1.02, and 0.6 % behind the fastest kind.  kQuarter: its estimate is a tenth too high.  Those had I = 2.5 to 4 d; not taken
+// below 2 d, where the contraction is no longer than the weight gradients' tiles.
+constexpr double kShared = 0.98, kQuarter = 0.9;
+enum DxKind { kDxOwn, kDxWhole, kDxHalf, kDx64, kDx32, kDxQuarter };
 DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwChoice& dw) {
   if (dw.small) {
     const TileChoice own = nn_tile(rows, d, I, 2);
@@ -274,15 +281,17 @@ DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwCh
     return tiles_of(d, rows, 64) <= 72.0 ? kDx32 : kDx64;
   }
   if (accumulate && rows <= kTile && tiles_of(d, kTile, 64) <= kNumCu) return kDxOwn;
-  auto tiles = [&](int64_t a, int64_t b, int64_t e) { return (a + e - 1) / e * ((b + kTile - 1) / kTile); };
+  auto tiles = [&](int64_t a, int64_t b, int64_t e, int64_t f = kTile) { return (a + e - 1) / e * ((b + f - 1) / f); };
   const int64_t n_dw = 2 * tiles(I, d, kTile) + tiles(d, I, kTile);
   const TileCost c = dw_cost(rows, accumulate);
   const double bytes = (accumulate ? 24.0 : 12.0) * (double)(I * d), ksteps = 2.0 * (double)ksteps_of(I);
   const double own = kShared * (nn_tile(rows, d, I, 2).us + 2.0 + launch_us(n_dw, c, bytes));
   const double whole = launch_us(tiles(d, rows, kTile), TileCost{ksteps, 7.0, 1.4, 1.5}, n_dw, c, bytes);
   const double half = launch_us(tiles(d, rows, Tile16Half::EA), TileCost{ksteps, 7.0, 0.8, 0.9}, n_dw, c, bytes);
-  if (whole > own && half > own) return kDxOwn;
-  return half < whole ? kDxHalf : kDxWhole;
+  const double quarter = launch_us(tiles(d, rows, Tile16Quarter::EA, Tile16Quarter::EB), TileCost{ksteps, 7.0, 0.58, 0.65}, n_dw, c, bytes);
+  const double best = std::min(whole, I >= 2 * d ? std::min(half, kQuarter * quarter) : half);
+  if (best > own) return kDxOwn;
+  return best == whole ? kDxWhole : best == half ? kDxHalf : kDxQuarter;
 }
 template <class T>
 void launch_dx_dw3(hipStream_t st, DxProblem x, const DwProblems& ps, int rows, bool even, bool accumulate, int more) {
@@ -556,7 +565,7 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
       if (dx == kDx64 || dx == kDx32) {
         (dx == kDx32 ? launch_dx_dw3_small<Tile32> : launch_dx_dw3_small<Tile64Lone>)(st, x, ps, rows, acc);
       } else if (dx != kDxOwn) {
-        (dx == kDxHalf ? launch_dx_dw3<Tile16Half> : launch_dx_dw3<Tile16>)(st, x, ps, rows, dw.even, acc != 0, i + 1 < p.n_chunks ? 1 : 0);
+        (dx == kDxHalf ? launch_dx_dw3<Tile16Half> : dx == kDxQuarter ? launch_dx_dw3<Tile16Quarter> : launch_dx_dw3<Tile16>)(st, x, ps, rows, dw.even, acc != 0, i + 1 < p.n_chunks ? 1 : 0);
       } else if (dw.small) {
         if (dw.lone)
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64Lone>, grid, dim3(Tile64Lone::kThreads), Tile64Lone::kLds, st, ps, rows, acc);
@@ -596,7 +605,20 @@ mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info) 
 int32_t mst_mlp_dx_tile(int64_t rows, int64_t d, int64_t I, int32_t first) {
   Plan p;
   if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
-  return choose_dx(rows, d, I, !first, dw_choice(rows, d, I));
+  const DxKind dx = choose_dx(rows, d, I, !first, dw_choice(rows, d, I));
+  return dx == kDxQuarter ? kDxHalf : dx;
+}
+
+int32_t mst_mlp_dx_tile_rows(int64_t rows, int64_t d, int64_t I, int32_t first) {
+  Plan p;
+  if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
+  switch (choose_dx(rows, d, I, !first, dw_choice(rows, d, I))) {
+    case kDxWhole: case kDxHalf: return kTile;
+    case kDxQuarter: return Tile16Quarter::EB;
+    case kDx64: return Tile64Lone::EB;
+    case kDx32: return Tile32::EB;
+    default: return 0;
+  }
 }
 
 int32_t mst_mlp_da_in_gateup(int64_t rows, int64_t d, int64_t I) {

@@ -213,7 +213,14 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nt(
 //   used for dA = dO Wd (one term, K = d) and dX = dG Wg + dU Wu (two terms, K = I each)
 //   A side = n (columns of Q, read transposed with the row permutation, so a lane holds 32 consecutive n
 //   and stores 64 bytes), B side = s (rows of P).
+//   Tile16Quarter: 128 x 128 with eight waves of 64 x 32, software-pipelined.  What bounds it is LDS (64 reads of 1 KB more a
+//   K step than the 64 x 64 of four waves, but a wave to issue while the other of its SIMD waits): 0.48 to 0.55 us a K step.
 // ---------------------------------------------------------------------------
+template <class T, class PA, class PB>
+__device__ __forceinline__ void nn_mainloop(f32x4 (&acc)[T::TA][T::TB], const PA& pa, const PB& pb, char* smem, int K, int wa) {
+  if constexpr (T::NSA == 5) gemm_mainloop_pipelined<T>(acc, pa, pb, smem, 0, K);
+  else gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, K, wa);
+}
 template <class T>
 __device__ __forceinline__ void nn_tile(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
@@ -231,14 +238,14 @@ __device__ __forceinline__ void nn_tile(
     PanelKC16<T, T::EB, T::TB, false> pb;
     pa.init(Q1 + n0, ldq, K, N - n0, wave, lane, wa);
     pb.init(P1 + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
-    gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, K, wa);
+    nn_mainloop<T>(acc, pa, pb, smem, K, wa);
   }
   if (P2 != nullptr) {
     PanelKS16<T, T::EA, T::TA, true> pa;
     PanelKC16<T, T::EB, T::TB, false> pb;
     pa.init(Q2 + n0, ldq, K, N - n0, wave, lane, wa);
     pb.init(P2 + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
-    gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, K, wa);
+    nn_mainloop<T>(acc, pa, pb, smem, K, wa);
   }
   store_rows_bf16<T>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
 }

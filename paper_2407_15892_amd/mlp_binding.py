@@ -50,6 +50,8 @@ def load_mlp_library() -> ctypes.CDLL:
     lib.mst_mlp_tile_info.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.POINTER(c.c_int64)]
     lib.mst_mlp_dx_tile.restype = c.c_int32
     lib.mst_mlp_dx_tile.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
+    lib.mst_mlp_dx_tile_rows.restype = c.c_int32
+    lib.mst_mlp_dx_tile_rows.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_mlp_da_in_gateup.restype = c.c_int32
     lib.mst_mlp_da_in_gateup.argtypes = [c.c_int64, c.c_int64, c.c_int64]
     lib.mst_mlp_tile_grid.restype = c.c_int32
@@ -131,6 +133,11 @@ MLP_DX_TILES = ("own", "256", "128", "64", "32")     # MST_MLP_DX_*
 def mst_mlp_dx_tile(rows: int, d: int, I: int, first: bool) -> str:
     """How dX of a chunk is computed: in a launch of its own, or by that of the weight gradients with this tile."""
     return MLP_DX_TILES[load_mlp_library().mst_mlp_dx_tile(rows, d, I, int(first))]
+
+
+def mst_mlp_dx_tile_rows(rows: int, d: int, I: int, first: bool) -> int:
+    """Rows of that tile, 0 where dX has a launch of its own."""
+    return load_mlp_library().mst_mlp_dx_tile_rows(rows, d, I, int(first))
 
 
 def mst_mlp_da_in_gateup(rows: int, d: int, I: int) -> bool:

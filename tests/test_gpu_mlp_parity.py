@@ -242,6 +242,25 @@ def test_dx_beside_the_weight_gradients_matches_oracle_and_keeps_its_bits(S, d, 
         assert np.array_equal(got["dX"], base), M      # a token's dX does not depend on who computed it
 
 
+@pytest.mark.parametrize("S,d,I,kinds", [
+    (833, 1544, 4616, {1: [128], 2: [0, 128]}),          # ragged everywhere: a last row tile of 65 and of 32 rows
+    (1929, 1032, 2584, {1: [256], 2: [128, 128]}),       # first chunk in tiles of 256 rows, of 965 in 128 x 128; one row, 8 columns
+    (385, 2184, 5464, {1: [128]}),                       # one row past three row tiles, last K steps ragged
+])
+def test_dx_in_128_by_128_tiles_beside_the_weight_gradients(S, d, I, kinds):
+    import paper_2407_15892_amd as mst
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=370 + S % 7, w_std=0.05))
+    base = None
+    for M, want in list(kinds.items()) + [(max(2, S // 60), None)]:      # the last in chunks of up to 64 rows, launches of their own
+        C = -(-S // M)
+        rows = [min(C, S - i * C) for i in range(-(-S // C))]
+        got_rows = [mst.mst_mlp_dx_tile_rows(r, d, I, i == 0) for i, r in enumerate(rows)]
+        assert got_rows == want if want else 128 not in got_rows, (M, got_rows)
+        _, got, _, _ = _check(inp, M=M)
+        base = got["dX"] if base is None else base
+        assert np.array_equal(got["dX"], base), M
+
+
 # (S, d, I, {M: (how dX of every chunk is computed, dA in the launch of gate/up's backward)}): the launches of small problems,
 # and 32 x 32 tiles in every product that takes them
 SMALL_SHAPES = [
