@@ -287,7 +287,7 @@ int32_t mst_bwd_streamed(int64_t S, int64_t d, int64_t V, int32_t M, int32_t* sp
  * mst_pair_launches (host, pure): how the pair order launches the three products, -1 for bad arguments.  The joint forms
  * are for problems whose tiles are all 64 x 64: the dlogits of a pair of mini-sequences from one launch, its dH and dW from
  * another, dH in tiles whose contraction is split between the four waves of a workgroup; or, for a single mini-sequence,
- * in the 64 x 64 tiles and the splits that it has in a launch of its own.
+ * in the 64 x 64 tiles and the splits that it has in a launch of its own.  The last form is the same with large tiles.
  *
  * mst_forward_tile_rows (host, pure): info[0] of mst_tile_info as the result, -1 for bad arguments.
  *
@@ -299,7 +299,8 @@ enum {
   MST_PAIR_KSPLIT_32X16,      /* dH tiles of 32 hidden indices by 16 rows */
   MST_PAIR_KSPLIT_64X16,
   MST_PAIR_KSPLIT_64X32,
-  MST_PAIR_SPLIT              /* one mini-sequence: split partials        */
+  MST_PAIR_SPLIT,             /* one mini-sequence: split partials        */
+  MST_PAIR_DH128              /* large tiles of dW; dH in 128 x 128 tiles over the whole vocabulary */
 };
 enum {
   MST_FORWARD_RECTANGLES = 0, /* a workgroup per tile, the rectangles of mst_tile_of_workgroup        */

@@ -235,7 +235,7 @@ def mst_forward_launch(S: int, d: int, V: int, M: int) -> str:
     return FORWARD_LAUNCHES[load_library().mst_forward_launch(S, d, V, M)]
 
 
-PAIR_LAUNCHES = ("separate", "32x16", "64x16", "64x32", "split")     # MST_PAIR_*
+PAIR_LAUNCHES = ("separate", "32x16", "64x16", "64x32", "split", "128x128")     # MST_PAIR_*
 
 
 STREAMED = ("no", "256", "256_narrow", "256_split", "384", "384_split", "512", "512_split")     # MST_STREAMED_*

@@ -247,6 +247,39 @@ void choose_split_blocks(Plan* p) {
   p->est_blocks_us = found ? best : p->blk_use ? so_far : cheapest;
 }
 
+// The pair order with one launch for the pair's dlogits and one for its dH and dW, dH in 128 x 128 tiles over the whole
+// vocabulary (k_bwd_gemm_dh128_dw): two launches instead of seven, for pairs that are less than a few rounds of tiles, as long
+// as a dH tile's chain of V / 64 K steps is not much longer than dW's work.  Backward, us: 3094 rows, d = 2696, V = 12307, M = 6:
+// 1357 -> 760; 1232, 2096, 14469, 4: 588 -> 351; 2980, 824, 7045, 4: 297 -> 183; but 1700, 1472, 9339, 6: 288 -> 300.
+// Microseconds: a K step of a dH tile 0.55, 0.65 with all compute units busy, 8 for its ends; dlogits and dW as above.  Of 70
+// shapes of 219 to 19863 rows, d = 408 to 3112, V = 4117 to 69139, timed both ways, this estimate takes it for 12, at 0.56 to
+// 0.90 of their time, and the choice is 0.4 % behind the faster way in the mean.  kDh128Blocks: blocks are a little faster than
+// estimated; four shapes of 0.7 to 0.95 of their estimate took 0.94 to 1.06 of their time.
+constexpr double kDh128Pairs = 0.95, kDh128Blocks = 0.7;
+bool small_pair_dlogits(const Plan& p, int64_t rows) {
+  const double k = (double)((p.d + kBK - 1) / kBK);
+  return small_launch_us(tiles_of(rows, p.V, 64), k) < big_launch_us(tiles_of(rows, p.V, kTile), k);
+}
+double dh128_us(const Plan* p, int64_t rows, bool add) {
+  const double w_all = 2.0 * (double)p->V * (double)p->d, g = 2.0 * (double)rows * (double)p->V;
+  const double dlogits = small_pair_dlogits(*p, rows) ? small_launch_us(tiles_of(rows, p->V, 64), (double)((p->d + kBK - 1) / kBK))
+                                                      : launch_us((rows + kTile - 1) / kTile * p->n_vt, dlogits_cost(p->d), w_all + g);
+  return dlogits + launch_us((int64_t)tiles_of(rows, p->d, Tile16Quarter::EA),
+                             TileCost{(double)((p->V + kBK - 1) / kBK), 8.0, 0.55, 0.65},
+                             (int64_t)p->n_vt * p->n_jt, dw_cost(rows, add), w_all + g + (add ? 4.0 : 2.0) * w_all);
+}
+void choose_dh128(Plan* p) {
+  if (p->small_dlogits && p->small_dh && p->small_dw) return;                        // has joint launches of its own
+  if (2 * (int64_t)p->C * p->ldg >= (int64_t(1) << 30)) return;                      // 32-bit offsets inside a pair
+  if (p->blk_use && (int64_t)(p->blk_rows / kTile) * p->n_jt >= 2 * kNumCu) return;
+  double t = 0.0;
+  for (int64_t r0 = 0; r0 < p->S; r0 += 2 * (int64_t)p->C) t += dh128_us(p, std::min(2 * (int64_t)p->C, p->S - r0), r0 > 0);
+  if (t >= (p->blk_use ? kDh128Blocks * p->est_blocks_us : kDh128Pairs * pairs_us(p))) return;
+  p->joint = MST_PAIR_DH128;
+  p->blk_use = false;
+  p->est_pairs_us = t;
+}
+
 int64_t dh_split_room(const Plan* p) { return ((int64_t)p->C * p->ldg * 2) / ((int64_t)p->C * p->d * 4); }
 
 // Splits of the pair order's dH: among the counts that fit (at most `most`, at most one per K step, partials must fit into
@@ -413,10 +446,14 @@ void choose_schedule(Plan* p, int forced) {
     }
   }
   p->est_blocks_us = best;
-  if (forced == MST_BWD_SCHEDULE_PAIRS) p->blk_use = false;
+  if (forced == MST_BWD_SCHEDULE_PAIRS) {
+    p->blk_use = false;
+    choose_dh128(p);
+  }
   else if (forced == MST_BWD_SCHEDULE_AUTO) {
     if (!(best < pairs)) p->blk_use = false;
     choose_split_blocks(p);
+    choose_dh128(p);
     choose_streamed(p);
   }
   // MST_BWD_SCHEDULE_BLOCKS and _BLOCKS_FUSED keep the best block shape whenever one fits
@@ -560,6 +597,10 @@ bool set_kernel_attributes() {   // on the current device
   set((const void*)k_bwd_gemm_dh_dw<true, false>);
   set((const void*)k_bwd_gemm_dh_dw<false, true>);
   set((const void*)k_bwd_gemm_dh_dw<true, true>);
+  set((const void*)k_bwd_gemm_dh128_dw<false, false>);
+  set((const void*)k_bwd_gemm_dh128_dw<true, false>);
+  set((const void*)k_bwd_gemm_dh128_dw<false, true>);
+  set((const void*)k_bwd_gemm_dh128_dw<true, true>);
   return ok;
 }
 
@@ -869,7 +910,7 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     const int64_t r0 = (int64_t)i * p.C;
     const int n_st = (rows + kTile - 1) / kTile;
     Scope sc(st, MST_K_BWD_GEMM_DLOGITS);
-    if (p.small_dlogits) {
+    if (p.joint == MST_PAIR_DH128 ? small_pair_dlogits(p, rows) : p.small_dlogits) {
       const int n_vh = (int)((p.V + Tile64::EA - 1) / Tile64::EA), n_sh = (rows + Tile64::EB - 1) / Tile64::EB;
       const bool lone = lone_small((double)n_vh * n_sh);
       hipLaunchKernelGGL(lone ? k_bwd_gemm_dlogits_small<Tile64Lone> : k_bwd_gemm_dlogits_small<Tile64>,
@@ -1019,6 +1060,23 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
     if (split > 1) dh_reduce(0, rows, slot[1], split);
     return check_launch();
   }
+  if (p.joint == MST_PAIR_DH128) {
+    const bool even = use_even_map(p.n_vt, p.n_jt);
+    for (int ia = 0; ia < p.n_chunks; ia += 2) {          // the two slots are contiguous: the pair's dlogits are one matrix
+      const int64_t r0 = (int64_t)ia * p.C;
+      const int rows = (int)std::min(2 * (int64_t)p.C, p.S - r0);
+      const int n_sq = (rows + Tile16Quarter::EB - 1) / Tile16Quarter::EB, n_jq = (int)((p.d + Tile16Quarter::EA - 1) / Tile16Quarter::EA);
+      dlogits(ia, rows, slot[0]);
+      Scope sc(st, MST_K_BWD_GEMM_DH_DW);
+      const auto kernel = even ? (ia > 0 ? k_bwd_gemm_dh128_dw<false, true> : k_bwd_gemm_dh128_dw<true, true>)
+                               : (ia > 0 ? k_bwd_gemm_dh128_dw<false, false> : k_bwd_gemm_dh128_dw<true, false>);
+      const int dh_grid = even_grid(n_jq, n_sq);
+      hipLaunchKernelGGL(kernel, dim3(dh_grid + launch_grid(even, p.n_vt, p.n_jt)), dim3(kThreads), kLdsBytes, st, slot[0], p.ldg, Wb,
+                         Hb + r0 * p.d, rows, (int)p.d, (int)p.V, n_sq, n_jq, dh_grid, p.n_vt, p.n_jt, ia + 2 >= p.n_chunks ? 1 : 0,
+                         nv, grad_loss, dHb + r0 * p.d, dW);
+    }
+    return check_launch();
+  }
   if (p.joint) {
     // the two slots are contiguous: the pair's dlogits are one matrix
     for (int ia = 0; ia < p.n_chunks; ia += 2) {
@@ -1068,7 +1126,7 @@ mst_status mst_bwd_schedule_info_for(int64_t S, int64_t d, int64_t V, int32_t M,
   info[2] = p.blk_use ? p.blk_n_rb : (p.n_chunks + 1) / 2;
   info[3] = p.blk_use ? (int64_t)p.blk_win_tiles * kTile : p.V;
   info[4] = p.blk_use ? p.blk_n_win : 1;
-  info[5] = p.blk_use ? p.blk_split : p.joint && p.joint != MST_PAIR_SPLIT ? TileKSplit64x16::kSplit : p.small_dh ? p.small_dh_split : p.dh_split;
+  info[5] = p.blk_use ? p.blk_split : p.joint == MST_PAIR_DH128 ? 1 : p.joint && p.joint != MST_PAIR_SPLIT ? TileKSplit64x16::kSplit : p.small_dh ? p.small_dh_split : p.dh_split;
   info[6] = (int64_t)p.est_pairs_us;
   info[7] = (int64_t)p.est_blocks_us;
   return MST_OK;

@@ -146,42 +146,6 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gateup(
   }
 }
 
-// epilogue of the two plain GEMMs: a lane holds, for each of its rows s, 32 consecutive n (A side, permuted),
-// i.e. 64 contiguous bytes of bf16, and the lanes of a wave instruction hold 16 different rows.  Stored directly,
-// every instruction would be 64 separate 16-byte writes; instead the bf16 tile is staged in LDS (free after the main
-// loop; rows padded by 16 bytes, which spreads the 16 rows of a quarter wave over all banks) and every wave
-// instruction then writes two whole rows of the tile.
-template <class T>
-__device__ __forceinline__ void store_rows_bf16(const f32x4 (&acc)[T::TA][T::TB], __bf16* __restrict__ out, int ldo,
-                                                int rows, int N, int s0, int n0, int wa, int wb, int wave, int lane,
-                                                char* smem) {
-  constexpr int kStageRow = T::EA * 2 + 16;
-#pragma unroll
-  for (int u = 0; u < T::TB; ++u) {
-    const int row = wb * (16 * T::TB) + 16 * u + (lane & 15);
-    char* srow = smem + row * kStageRow + (wa * (16 * T::TA) + 4 * T::TA * (lane >> 4)) * 2;
-#pragma unroll
-    for (int p = 0; p < T::TA / 2; ++p) {            // tiles 2p and 2p + 1: n = nb + 8p .. + 7
-      bf16x8 o;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = (__bf16)acc[2 * p + (e >> 2)][u][e & 3];
-      *reinterpret_cast<bf16x8*>(srow + 16 * p) = o;
-    }
-  }
-  __syncthreads();
-  constexpr int kLanesPerRow = T::EA / 8, kRowsPerStore = 64 / kLanesPerRow;
-  const int col = (lane % kLanesPerRow) * 8;         // 8 entries = 16 bytes per lane
-  const bool col_ok = n0 + col < N;                  // N % 8 == 0
-  constexpr int kRowsPerWave = T::EB / T::kWaves;
-#pragma unroll
-  for (int i = 0; i < kRowsPerWave / kRowsPerStore; ++i) {
-    const int row = kRowsPerWave * wave + kRowsPerStore * i + lane / kLanesPerRow;
-    if (s0 + row < rows && col_ok)
-      *reinterpret_cast<bf16x8*>(out + (size_t)(s0 + row) * ldo + n0 + col) =
-          *reinterpret_cast<const bf16x8*>(smem + row * kStageRow + col * 2);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // out[s][n] = sum_k P[s][k] Q[n][k]      (both operands K-contiguous; used for O_chunk = A Wd^T)
 //   A side = n (rows of Q, permuted so a lane holds 32 consecutive n), B side = s (rows of P)
@@ -208,47 +172,6 @@ __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nt(
   store_rows_bf16<T>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
 }
 
-// ---------------------------------------------------------------------------
-// out[s][n] = sum_k P1[s][k] Q1[k][n] (+ sum_k P2[s][k] Q2[k][n])   (Q K-strided)
-//   used for dA = dO Wd (one term, K = d) and dX = dG Wg + dU Wu (two terms, K = I each)
-//   A side = n (columns of Q, read transposed with the row permutation, so a lane holds 32 consecutive n
-//   and stores 64 bytes), B side = s (rows of P).
-//   Tile16Quarter: 128 x 128 with eight waves of 64 x 32, software-pipelined.  What bounds it is LDS (64 reads of 1 KB more a
-//   K step than the 64 x 64 of four waves, but a wave to issue while the other of its SIMD waits): 0.48 to 0.55 us a K step.
-// ---------------------------------------------------------------------------
-template <class T, class PA, class PB>
-__device__ __forceinline__ void nn_mainloop(f32x4 (&acc)[T::TA][T::TB], const PA& pa, const PB& pb, char* smem, int K, int wa) {
-  if constexpr (T::NSA == 5) gemm_mainloop_pipelined<T>(acc, pa, pb, smem, 0, K);
-  else gemm_mainloop_pp<T>(acc, pa, pb, smem, 0, K, wa);
-}
-template <class T>
-__device__ __forceinline__ void nn_tile(
-    const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
-    const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
-    int ldp, int ldq, int rows, int N, int K, int nt, int st, __bf16* __restrict__ out, int ldo, char* smem) {
-  const int n0 = nt * T::EA, s0 = st * T::EB;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wa = wave / T::WB, wb = wave % T::WB;
-
-  f32x4 acc[T::TA][T::TB];
-  zero_acc<T::TA, T::TB>(acc);
-  {
-    PanelKS16<T, T::EA, T::TA, true> pa;
-    PanelKC16<T, T::EB, T::TB, false> pb;
-    pa.init(Q1 + n0, ldq, K, N - n0, wave, lane, wa);
-    pb.init(P1 + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
-    nn_mainloop<T>(acc, pa, pb, smem, K, wa);
-  }
-  if (P2 != nullptr) {
-    PanelKS16<T, T::EA, T::TA, true> pa;
-    PanelKC16<T, T::EB, T::TB, false> pb;
-    pa.init(Q2 + n0, ldq, K, N - n0, wave, lane, wa);
-    pb.init(P2 + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
-    nn_mainloop<T>(acc, pa, pb, smem, K, wa);
-  }
-  store_rows_bf16<T>(acc, out, ldo, rows, N, s0, n0, wa, wb, wave, lane, smem);
-}
 template <class T, bool kSuper>
 __global__ __launch_bounds__(kThreads) void k_mlp_gemm_nn(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,

@@ -615,6 +615,31 @@ def test_joint_launches_of_the_pair_order_match_oracle(schedule, S, d, V, M, lau
 
 
 @pytest.mark.parametrize("S,d,V,M", [
+    (705, 1544, 4099, 3),      # a pair, then one chunk whose dW adds; last tiles of few rows, 8 columns, 3 entries
+    (1411, 1160, 6001, 5),     # three passes over dW
+    (641, 2312, 3001, 1),      # one chunk, one row past five dH tiles
+    (1537, 1288, 4099, 1),     # large tiles of dlogits
+])
+def test_pair_order_with_dh_in_128_by_128_tiles_matches_oracle(schedule, S, d, V, M):
+    """dlogits of a pair from one launch, dH over the whole vocabulary beside large tiles of dW: against the oracle, the same
+    bits call after call and from the automatic order, within the declared workspace."""
+    import torch
+    import paper_2407_15892_amd as mst
+    schedule(mst.BWD_SCHEDULE_PAIRS)
+    assert mst.mst_pair_launches(S, d, V, M) == "128x128"
+    inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=480 + S % 97, w_std=0.3, ignore_frac=0.1, label_dist="zipf"))
+    run, _, _ = _check_full(inp, grad_loss=0.8)
+    first = (run.dH_t.clone(), run.dW_t.clone())
+    schedule(mst.BWD_SCHEDULE_AUTO)
+    assert mst.mst_bwd_schedule_info(S, d, V, M)["schedule"] == mst.BWD_SCHEDULE_PAIRS
+    run.pad = 4096
+    run.backward(grad_loss=0.8)
+    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
+    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
+    assert bool((run.last_ws[-4096:] == 0xA5).all()), "wrote past the declared workspace"
+
+
+@pytest.mark.parametrize("S,d,V,M", [
     (975, 1176, 4099, 3),      # 64 x 64 tiles in dlogits, dH and dW, whose second pass (one chunk) adds
     (712, 1920, 6637, 2),      # in dlogits and dH only
 ])
