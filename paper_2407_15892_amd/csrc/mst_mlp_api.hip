@@ -20,7 +20,6 @@ struct Plan {
   int64_t S, d, I;
   int M;
   int C;            // rows per chunk = ceil(S / M)
-  int n_chunks;     // non-empty chunks
   size_t slot;      // bytes of one chunk-sized bf16 [C, I] buffer
 };
 
@@ -33,7 +32,6 @@ mst_status make_plan(int64_t S, int64_t d, int64_t I, int32_t M, Plan* p) {
   if (C * I >= (int64_t(1) << 30) || C * d >= (int64_t(1) << 30)) return MST_ERR_BAD_SHAPE;
   p->S = S; p->d = d; p->I = I; p->M = M;
   p->C = (int)C;
-  p->n_chunks = (int)((S + C - 1) / C);
   p->slot = mst_host::align_up((size_t)C * I * 2, 256);
   return MST_OK;
 }
@@ -117,11 +115,6 @@ mst_status prepare_device() {
   return MST_OK;
 }
 
-int rows_of(const Plan& p, int i) {
-  const int64_t r0 = (int64_t)i * p.C;
-  return (int)((p.S - r0) < p.C ? (p.S - r0) : p.C);
-}
-
 bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
   return x < y + nb && y < x + na;
@@ -146,6 +139,56 @@ ForwardGroup forward_group(const Plan& p, int64_t left, size_t workspace_bytes, 
   return {(left + groups(left) - 1) / groups(left), false};                                        // what is left in equal groups
 }
 
+// The backward's groups of rows, likewise: of dG, dU and A of a group, up to three are kept in the rows of dX behind it, and
+// the workspace then holds those of one and a half times or three times the rows of a chunk.  The largest group is kept as
+// small as the number of groups allows; without fewer groups than chunks all are equal and in the workspace.  Backward, us, chunk
+// by chunk -> this: 22592 rows, d = 616, I = 1560, M = 37: 1488 -> 1139; 32128, 640, 2264, 50: 2381 -> 1744; 20288, 1760, 5776, 12:
+// 3938 -> 3484.  Groups as large as fit, where that makes no fewer of them: 8128, 1376, 3760, 4: 788 -> 820.
+struct BackwardGroups {
+  const Plan& p;
+  int64_t room[4];                // rows whose dG, dU and A fit with k of them in dX: of the workspace
+  int64_t cap;                    // most rows of a group
+  bool in_dx;
+  BackwardGroups(const Plan& plan, size_t workspace_bytes, bool dx_is_free) : p(plan), in_dx(false) {
+    const int64_t most = std::min(((int64_t(1) << 30) - 1) / p.I, ((int64_t(1) << 30) - 1) / p.d);                 // 32-bit offsets
+    for (int k = 0; k < 3; ++k) room[k] = std::min((int64_t)(slot(workspace_bytes, k) / (2 * (size_t)p.I)), most);  // room[0] >= C
+    room[3] = most;
+    const int64_t n = (p.S + room[0] - 1) / room[0];
+    cap = (p.S + n - 1) / n;
+    if (n < 4 || !dx_is_free) return;
+    in_dx = true;
+    const int64_t equal = cap;
+    cap = most;
+    const int64_t fewest = count();
+    if (fewest >= n) {
+      in_dx = false;
+      cap = equal;
+      return;
+    }
+    int64_t low = (p.S + fewest - 1) / fewest - 1, high = 0;
+    for (int k = 0; k <= 3; ++k) high = std::max(high, fits(p.S, k));      // the largest group there can be
+    while (high - low > 32) {     // the smallest cap with which there are no more of them
+      cap = (low + high) / 2;
+      (count() > fewest ? low : high) = cap;
+    }
+    cap = high;
+  }
+  static size_t slot(size_t workspace_bytes, int k) { return workspace_bytes / (size_t)(3 - k) / 256 * 256; }   // a buffer's share of it
+  int64_t fits(int64_t left, int k) const { return k ? std::min(room[k], left * p.d / (k * p.I + p.d)) : room[0]; }   // k rows I <= (left - rows) d
+  int64_t next(int64_t left, int* k) const {            // rows of the next group; how many of its buffers are in dX
+    const int64_t most = std::min(left, cap);
+    *k = 0;
+    for (int j = 1; j <= 3 && in_dx && fits(left, *k) < most; ++j)
+      if (fits(left, j) > fits(left, *k)) *k = j;
+    return std::min(most, fits(left, *k));
+  }
+  int64_t count() const {
+    int64_t n = 0;
+    int k;
+    for (int64_t left = p.S; left > 0; ++n) left -= next(left, &k);
+    return n;
+  }
+};
 
 // Which block tile a GEMM of n_a x n_b outputs (A side: weights, B side: tokens) and `ksteps` K steps of 64 runs with.
 // The figures are microseconds fitted to launches of the three kinds (gate/up, down, dA/dX) at 64 to 3000 tokens,
@@ -521,19 +564,26 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
   const __bf16* dOb = static_cast<const __bf16*>(dO);
   __bf16* dXb = static_cast<__bf16*>(dX);
   char* ws = static_cast<char*>(workspace);
-  __bf16* bufG = reinterpret_cast<__bf16*>(ws);               // dA, then dG in place
-  __bf16* bufU = reinterpret_cast<__bf16*>(ws + p.slot);      // dU
-  __bf16* bufA = reinterpret_cast<__bf16*>(ws + 2 * p.slot);  // A
   const int dI = (int)p.I, dd = (int)p.d;
-  const DwChoice dw = dw_choice(p.C, p.d, p.I);
+  const size_t x_bytes = (size_t)S * d * 2, w_bytes = (size_t)I * d * 2;
+  const bool dx_is_free = !overlap(dX, x_bytes, X, x_bytes) && !overlap(dX, x_bytes, dO, x_bytes) && !overlap(dX, x_bytes, Wg, w_bytes) &&
+                          !overlap(dX, x_bytes, Wu, w_bytes) && !overlap(dX, x_bytes, Wd, w_bytes);
+  const BackwardGroups groups(p, workspace_bytes, dx_is_free);
+  const DwChoice dw = dw_choice(std::min(groups.cap, p.S), p.d, p.I);
 
-  // Algorithm 3: loop over the mini-sequences; dX_i lands in its row range, the weight gradients accumulate
-  for (int i = 0; i < p.n_chunks; ++i) {
-    const int64_t r0 = (int64_t)i * p.C;
-    const int rows = rows_of(p, i);
+  // Algorithm 3: loop over groups of mini-sequences; dX_i lands in its row range, the weight gradients accumulate
+  for (int64_t r0 = 0; r0 < p.S;) {
+    int in_dx = 0;
+    const int rows = (int)groups.next(p.S - r0, &in_dx);
+    __bf16* buf[3];                                             // dA, then dG in place; dU; A
+    for (int k = 0; k < 3; ++k)
+      buf[k] = k < in_dx ? dXb + p.S * p.d - (k + 1) * (int64_t)rows * p.I
+                         : reinterpret_cast<__bf16*>(ws + (k - in_dx) * BackwardGroups::slot(workspace_bytes, in_dx));
+    __bf16 *const bufG = buf[0], *const bufU = buf[1], *const bufA = buf[2];
+    const bool more = r0 + rows < p.S;
     const __bf16* Xc = Xb + r0 * p.d;
     const __bf16* dOc = dOb + r0 * p.d;
-    const int acc = i > 0 ? 1 : 0;
+    const int acc = r0 > 0 ? 1 : 0;
     const bool da_in_gateup = fuse_da(rows, p.d, p.I);
     if (!da_in_gateup) {
       Scope sc(st, MST_MLP_K_DA);
@@ -565,7 +615,7 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
       if (dx == kDx64 || dx == kDx32) {
         (dx == kDx32 ? launch_dx_dw3_small<Tile32> : launch_dx_dw3_small<Tile64Lone>)(st, x, ps, rows, acc);
       } else if (dx != kDxOwn) {
-        (dx == kDxHalf ? launch_dx_dw3<Tile16Half> : dx == kDxQuarter ? launch_dx_dw3<Tile16Quarter> : launch_dx_dw3<Tile16>)(st, x, ps, rows, dw.even, acc != 0, i + 1 < p.n_chunks ? 1 : 0);
+        (dx == kDxHalf ? launch_dx_dw3<Tile16Half> : dx == kDxQuarter ? launch_dx_dw3<Tile16Quarter> : launch_dx_dw3<Tile16>)(st, x, ps, rows, dw.even, acc != 0, more ? 1 : 0);
       } else if (dw.small) {
         if (dw.lone)
           hipLaunchKernelGGL(k_mlp_dw3_small<Tile64Lone>, grid, dim3(Tile64Lone::kThreads), Tile64Lone::kLds, st, ps, rows, acc);
@@ -574,9 +624,10 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
       } else {
         const auto kernel = dw.even ? (acc ? k_mlp_dw3<false, true> : k_mlp_dw3<true, true>)
                                  : (acc ? k_mlp_dw3<false, false> : k_mlp_dw3<true, false>);
-        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), kLdsBytes, st, ps, rows, i + 1 < p.n_chunks ? 1 : 0);
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), kLdsBytes, st, ps, rows, more ? 1 : 0);
       }
     }
+    r0 += rows;
   }
   return check_launch();
 }

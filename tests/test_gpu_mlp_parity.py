@@ -349,3 +349,32 @@ def test_forward_groups_of_rows_keep_the_bits(S, d, I, M):
     run.mst.mst_mlp_fwd(X, run.Wg, run.Wu, run.Wd, M, ws[: run.fwd_bytes], X)
     torch.cuda.synchronize()
     assert np.array_equal(f64(X), base)
+
+
+@pytest.mark.parametrize("S,d,I,M", [
+    (1500, 136, 264, 12),     # one or two of dG, dU and A in dX behind the group, the last groups' all in the workspace
+    (1601, 264, 520, 23),     # ragged everywhere
+    (2401, 72, 168, 80),      # all three of them first
+    (5207, 520, 1304, 11),    # larger tiles
+    (700, 520, 72, 9),        # I < d
+    (131, 8, 1032, 4),        # I much larger than d: nothing in dX
+])
+def test_backward_groups_of_rows_match_oracle_and_keep_the_bits_of_dx(S, d, I, M):
+    """Where the backward keeps dG, dU and A does not show in dX, and it stays inside the declared workspace and dX."""
+    import torch
+    MlpDeviceRun, f64 = _harness()
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=380 + S % 7, w_std=0.05))
+    ref = _reference(inp)
+    base = f64(MlpDeviceRun(inp, M=1).backward()[0])
+    assert np.abs(base - ref["dX"]).max() <= TOL * np.abs(ref["dX"]).max()
+    run = MlpDeviceRun(inp, M=M)
+    for times in (1, 2):
+        ws = torch.full((times * run.bwd_bytes + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        dX = torch.full(((S + 2) * d,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dW = [torch.full(shape, float("nan"), device="cuda") for shape in ((I, d), (I, d), (d, I))]
+        run.mst.mst_mlp_bwd(run.X, run.Wg, run.Wu, run.Wd, run.dO, M, ws[: times * run.bwd_bytes], dX[d:-d].view(S, d), *dW)
+        torch.cuda.synchronize()
+        assert np.array_equal(f64(dX[d:-d].view(S, d)), base), times
+        for k, got in zip(("dWg", "dWu", "dWd"), dW):
+            assert np.abs(got.double().cpu().numpy() - ref[k]).max() <= TOL * np.abs(ref[k]).max(), (k, times)
+        assert bool((ws[times * run.bwd_bytes:] == 0xA5).all()) and bool(dX[:d].isnan().all()) and bool(dX[-d:].isnan().all())
