@@ -119,8 +119,8 @@ __device__ __forceinline__ void gemm_mainloop_shared(f32x4 (&acc)[C::TA][C::TB],
 template <class C, class PA, class PB>
 __device__ __forceinline__ void gemm_mainloop_pipelined(f32x4 (&acc)[C::TA][C::TB], const PA& pa, const PB& pb, char* smem,
                                                         int k_begin, int k_end) {
-  static_assert(C::NSA == C::NSB && C::NSA >= 3, "as many stages of both panels");
-  constexpr int NS = C::NSA;
+  constexpr int NS = C::NSA, kBehind = PA::kLines || PB::kLines ? 1 : 0;       // stages that a step reads behind its own
+  static_assert(C::NSA == C::NSB && C::NSA >= 3 + 2 * kBehind, "as many stages of both panels");
   constexpr int kLoads = PB::SPW + PA::SPW, kFrags = C::kKK * (C::TA + C::TB), kMma = C::kKK * C::TA * C::TB;
   const uint32_t ldsA = lds_addr_of(smem), ldsB = ldsA + NS * C::kPanelA;
   const char* smemB = smem + NS * C::kPanelA;
@@ -130,7 +130,7 @@ __device__ __forceinline__ void gemm_mainloop_pipelined(f32x4 (&acc)[C::TA][C::T
     pb.issue(ldsB + j * C::kPanelB, k_begin + j * C::BK);
     pa.issue(ldsA + j * C::kPanelA, k_begin + j * C::BK);
   }
-  wait_vmcnt<(NS - 2) * kLoads>();
+  wait_vmcnt<(NS - 2 - kBehind) * kLoads>();
   __builtin_amdgcn_s_barrier();
   typedef bf16x8 FragsA[C::kKK][C::TA];
   typedef bf16x8 FragsB[C::kKK][C::TB];
@@ -139,18 +139,19 @@ __device__ __forceinline__ void gemm_mainloop_pipelined(f32x4 (&acc)[C::TA][C::T
 #pragma unroll
   for (int kk = 0; kk < C::kKK; ++kk) {
 #pragma unroll
-    for (int t = 0; t < C::TA; ++t) a0[kk][t] = pa.frag(smem, t, kk);
+    for (int t = 0; t < C::TA; ++t) a0[kk][t] = pa.frag(smem, smem + C::kPanelA, t, kk);
 #pragma unroll
-    for (int u = 0; u < C::TB; ++u) b0[kk][u] = pb.frag(smemB, u, kk);
+    for (int u = 0; u < C::TB; ++u) b0[kk][u] = pb.frag(smemB, smemB + C::kPanelB, u, kk);
   }
   int rd = 1, ld = NS - 1, kl = k_begin + (NS - 1) * C::BK;      // stage to read, stage to load, its k
   auto step = [&](FragsA& a, FragsB& b, FragsA& an, FragsB& bn) {
-    wait_vmcnt<(NS - 3) * kLoads>();
+    wait_vmcnt<(NS - 3 - kBehind) * kLoads>();
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    const char* a_panel = smem + rd * C::kPanelA;
-    const char* b_panel = smemB + rd * C::kPanelB;
+    const int next = rd + 1 == NS ? 0 : rd + 1;
+    const char *a_panel = smem + rd * C::kPanelA, *a_next = smem + next * C::kPanelA;
+    const char *b_panel = smemB + rd * C::kPanelB, *b_next = smemB + next * C::kPanelB;
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
       if (j < PB::SPW) pb.issue_one(j, ldsB + ld * C::kPanelB, kl);
@@ -158,8 +159,8 @@ __device__ __forceinline__ void gemm_mainloop_pipelined(f32x4 (&acc)[C::TA][C::T
 #pragma unroll
       for (int f = j * kFrags / kLoads; f < (j + 1) * kFrags / kLoads; ++f) {
         const int kk = f / (C::TA + C::TB), r = f % (C::TA + C::TB);
-        if (r < C::TA) an[kk][r] = pa.frag(a_panel, r, kk);
-        else bn[kk][r - C::TA] = pb.frag(b_panel, r - C::TA, kk);
+        if (r < C::TA) an[kk][r] = pa.frag(a_panel, a_next, r, kk);
+        else bn[kk][r - C::TA] = pb.frag(b_panel, b_next, r - C::TA, kk);
       }
 #pragma unroll
       for (int m = j * kMma / kLoads; m < (j + 1) * kMma / kLoads; ++m) {
@@ -169,7 +170,7 @@ __device__ __forceinline__ void gemm_mainloop_pipelined(f32x4 (&acc)[C::TA][C::T
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    rd = rd + 1 == NS ? 0 : rd + 1;
+    rd = next;
     ld = ld + 1 == NS ? 0 : ld + 1;
     kl += C::BK;
   };

@@ -107,6 +107,66 @@ struct PanelKC16 {
   __device__ __forceinline__ bf16x8 frag(const char* panel, int t, int kk) const {
     return *reinterpret_cast<const bf16x8*>(panel + rd[kk] + t * (16 * RB));
   }
+  static constexpr bool kLines = false;
+  __device__ __forceinline__ bf16x8 frag(const char* panel, const char*, int t, int kk) const { return frag(panel, t, kk); }
+};
+
+// The same panel for rows that are not whole cache lines: every row is loaded at its own line offset, so that a K step takes
+// whole 128-byte lines of it, each once; loaded at the same k for all rows, every line is fetched by two K steps.  LDS row r of
+// stage s holds the 16-byte chunks CPR s - m(r) .. CPR s - m(r) + CPR - 1 of its source row, m(r) the chunks by which that
+// begins behind a line, and a K step's fragments come from two stages, which of them a constant of the lane.  Down of 800
+// rows, d = 2048, I = 7176, 64 x 64 tiles: 66 us -> 45 (16 KB a K step instead of 32 from L2, which is what bounds them).  With the permutation m differs between even and odd t.
+template <class C, int EXT, int TILES, bool kPermute>
+struct PanelKC16Lines {
+  typedef PanelKC16<C, EXT, TILES, kPermute> Panel;
+  static constexpr int RB = Panel::RB, CPR = Panel::CPR, RPS = Panel::RPS, SPW = Panel::SPW, kKinds = kPermute ? 2 : 1;
+  static constexpr bool kLines = true;
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t voff[SPW], kelem[SPW];              // of a row's first chunks below 0: out of range, as every k past the end
+  uint32_t k_limit, slot0;
+  uint32_t rd[C::kKK][kKinds];
+  bool second[C::kKK][kKinds];                 // the chunk is in the following stage
+
+  __device__ __forceinline__ void init(const void* base, uint32_t ld_elems, uint32_t rows_valid, uint32_t k_elems,
+                                       int wave, int lane, int wave_side_index) {
+    const uint32_t ld_bytes = ld_elems * 2, rows = rows_valid < (uint32_t)EXT ? rows_valid : (uint32_t)EXT;
+    const uint32_t first = (uint32_t)(reinterpret_cast<uint64_t>(base) >> 4), pitch = ld_elems / 8;
+    auto behind = [&](int row) { return (int)((first + (uint32_t)row * pitch) & 7); };
+    rsrc = make_rsrc(base, rows * ld_bytes);
+    k_limit = k_elems;
+    slot0 = wave * SPW;
+    const int rin = lane / CPR, p = lane % CPR;
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      constexpr int kBlock = 16 * TILES;
+      const int lrow = RPS * (slot0 + i) + rin;
+      const int row = (lrow & ~(kBlock - 1)) + a_row_of_block_row16<kPermute, TILES>(lrow & (kBlock - 1));
+      const int chunk = (p ^ Panel::swz(lrow)) - behind(row);
+      kelem[i] = (uint32_t)(chunk * 8);
+      voff[i] = (uint32_t)row * ld_bytes + (uint32_t)(chunk * 16);
+    }
+    const int row0 = wave_side_index * (16 * TILES) + (lane & 15);
+#pragma unroll
+    for (int kk = 0; kk < C::kKK; ++kk)
+#pragma unroll
+      for (int t = 0; t < kKinds; ++t) {
+        const int row = wave_side_index * (16 * TILES) + a_row_of_block_row16<kPermute, TILES>(16 * t + (lane & 15));
+        const int chunk = 4 * kk + (lane >> 4) + behind(row);
+        second[kk][t] = chunk >= CPR;
+        rd[kk][t] = row0 * RB + (((chunk & (CPR - 1)) ^ Panel::swz(row0)) * 16);
+      }
+  }
+  __device__ __forceinline__ void issue_one(int i, uint32_t panel_lds, uint32_t k0) const {
+    dma16(rsrc, (k0 + kelem[i]) < k_limit ? voff[i] + k0 * 2 : kOutOfRange, panel_lds + (slot0 + i) * 1024);
+  }
+  __device__ __forceinline__ void issue(uint32_t panel_lds, uint32_t k0) const {
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) issue_one(i, panel_lds, k0);
+  }
+  __device__ __forceinline__ bf16x8 frag(const char* panel, const char* following, int t, int kk) const {
+    const int kind = t & (kKinds - 1);
+    return *reinterpret_cast<const bf16x8*>((second[kk][kind] ? following : panel) + rd[kk][kind] + t * (16 * RB));
+  }
 };
 
 // K-strided panel [BK k][EXT index], read with the transposing LDS read.  A quarter wave (16 lanes) feeds
@@ -176,6 +236,8 @@ struct PanelKS16 {
 #pragma unroll
     for (int i = 0; i < SPW; ++i) issue_one(i, panel_lds, k0);
   }
+  static constexpr bool kLines = false;
+  __device__ __forceinline__ bf16x8 frag(const char* panel, const char*, int t, int kk) const { return frag(panel, t, kk); }
   __device__ __forceinline__ bf16x8 frag(const char* panel, int t, int kk) const {
     typedef __attribute__((address_space(3))) i16x4* lds_i16x4_ptr;
     const char* p = panel + rd[t] + kk * (32 * RB);

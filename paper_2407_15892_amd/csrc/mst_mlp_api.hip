@@ -52,7 +52,7 @@ template <class C, class Set>
 void set_small_attributes(Set set) {
   set((const void*)k_mlp_gateup_small<C, false>);
   set((const void*)k_mlp_gateup_small<C, true>);
-  set((const void*)k_mlp_gemm_nt_small<C>);
+  set((const void*)k_mlp_gemm_nt_small<C, false>);
   set((const void*)k_mlp_gemm_nn_small<C>);
 }
 
@@ -84,7 +84,8 @@ bool set_kernel_attributes() {   // on the current device
   set_small_attributes<Tile64>(set);
   set_small_attributes<Tile64Lone>(set);
   set_small_attributes<Tile64Long>(set);
-  set((const void*)k_mlp_gemm_nt_small<Tile32>);
+  set((const void*)k_mlp_gemm_nt_small<Tile32, false>);
+  set((const void*)k_mlp_gemm_nt_small<Tile64Lone, true>);
   set((const void*)k_mlp_gemm_nn_small<Tile32>);
   set((const void*)k_mlp_gateup_small<Tile64Lone, true, true>);
   set((const void*)k_mlp_dx_dw3_small<Tile64Lone, Tile64Lone>);
@@ -270,7 +271,19 @@ TileChoice choose_tile(int64_t n_a, int64_t n_b, int64_t ksteps, Weights w) {
 // the choices of the four products of a chunk of `rows` rows
 int64_t ksteps_of(int64_t k) { return (k + kBK - 1) / kBK; }
 TileChoice gateup_tile(int64_t rows, int64_t d, int64_t I) { return choose_tile(2 * I, rows, ksteps_of(d), kGateUp); }
-TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) { return choose_tile(N, rows, ksteps_of(K), kContiguous); }
+// Lone 64 x 64 tiles load rows that are not whole cache lines line by line (PanelKC16Lines), the other tiles fetch their lines
+// twice.  Down of 800 rows, d = 2048: 45 us at I = 7168, at 7176 66 -> 45; 507 rows, d = 2688, I = 7120: 64 -> 45.  With that they
+// are faster than 128 x 128 tiles in a long contraction, too: forward of 1421 rows, d = 2752, I = 6952: 220 us -> 176; 3341, 1192,
+// 3920: 128 -> 113; 3410, 1264, 4440: 144 -> 137.  With K steps of 128, which straddle half as many lines, the panels gained
+// nothing (64 x 64: 62 us either way) or lost (32 x 32: 10.1 us -> 13.1, one stage less ahead), in larger tiles there is no
+// stage of LDS left for them.  Forward of 38 shapes, d = 320 to 3072: 0.77 to 0.95 with more tiles than compute units; with
+// fewer, where a stage less ahead costs as much as the lines, 0.96 to 1.06, so not there.
+bool whole_lines(int64_t K) { return K % 64 == 0; }
+TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) {
+  TileChoice c = choose_tile(N, rows, ksteps_of(K), kContiguous);
+  if (c.kind == k128 && c.head == 0 && !whole_lines(K) && ksteps_of(K) >= 60) c.kind = k64Lone;
+  return c;
+}
 TileChoice nn_tile(int64_t rows, int64_t N, int64_t K, int terms) { return choose_tile(N, rows, terms * ksteps_of(K), kStrided); }
 
 // The weight gradients have one tile kind for all chunks: what the large tiles keep between them is not row-major.
@@ -408,8 +421,10 @@ void launch_gateup(hipStream_t st, const __bf16* X, const __bf16* Wg, const __bf
 template <class C>
 void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out, int ldo) {
   const int n_nt = (N + C::EA - 1) / C::EA, n_st = (rows + C::EB - 1) / C::EB;
-  hipLaunchKernelGGL(k_mlp_gemm_nt_small<C>, dim3(even_grid(n_nt, n_st)), dim3(C::kThreads), C::kLds, st,
-                     P, K, Q, K, rows, N, K, n_st, n_nt, out, ldo);
+  constexpr bool kCan = std::is_same_v<C, Tile64Lone>;
+  const bool lines = kCan && n_nt * n_st > kNumCu && (!whole_lines(K) || misaligned(P, 128) || misaligned(Q, 128));
+  hipLaunchKernelGGL((lines ? k_mlp_gemm_nt_small<C, kCan> : k_mlp_gemm_nt_small<C, false>), dim3(even_grid(n_nt, n_st)), dim3(C::kThreads),
+                     C::kLds, st, P, K, Q, K, rows, N, K, n_st, n_nt, out, ldo);
 }
 void launch_nt(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out) {
   const TileChoice c = nt_tile(rows, N, K);

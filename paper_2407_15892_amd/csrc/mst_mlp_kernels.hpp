@@ -18,6 +18,8 @@
 #pragma once
 #include "mst_small_kernels.hpp"
 
+#include <type_traits>
+
 namespace mst {
 
 // Workgroup -> tile mapping of the 256 x 256 kernels: cut into 8 x 4 (slow x fast) super-tiles, XCD x owning
@@ -300,8 +302,8 @@ __device__ __forceinline__ void store_small_bf16(const f32x4 (&acc)[C::TA][C::TB
   }
 }
 
-// out[s][n] = sum_k P[s][k] Q[n][k]
-template <class C>
+// out[s][n] = sum_k P[s][k] Q[n][k].   kLines: rows are not whole cache lines (PanelKC16Lines).
+template <class C, bool kLines>
 __global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gemm_nt_small(
     const __bf16* __restrict__ P, int ldp, const __bf16* __restrict__ Q, int ldq, int rows, int N, int K,
     int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
@@ -316,8 +318,8 @@ __global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gemm_nt
   f32x4 acc[C::TA][C::TB];
   zero_acc<C::TA, C::TB>(acc);
   {
-    PanelKC16<C, C::EA, C::TA, true> pa;
-    PanelKC16<C, C::EB, C::TB, false> pb;
+    std::conditional_t<kLines, PanelKC16Lines<C, C::EA, C::TA, true>, PanelKC16<C, C::EA, C::TA, true>> pa;
+    std::conditional_t<kLines, PanelKC16Lines<C, C::EB, C::TB, false>, PanelKC16<C, C::EB, C::TB, false>> pb;
     pa.init(Q + (size_t)n0 * ldq, ldq, N - n0, K, wave, lane, wa);
     pb.init(P + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
     gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K);

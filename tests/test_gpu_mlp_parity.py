@@ -378,3 +378,31 @@ def test_backward_groups_of_rows_match_oracle_and_keep_the_bits_of_dx(S, d, I, M
         for k, got in zip(("dWg", "dWu", "dWd"), dW):
             assert np.abs(got.double().cpu().numpy() - ref[k]).max() <= TOL * np.abs(ref[k]).max(), (k, times)
         assert bool((ws[times * run.bwd_bytes:] == 0xA5).all()) and bool(dX[:d].isnan().all()) and bool(dX[-d:].isnan().all())
+
+
+@pytest.mark.parametrize("S,d,I,M", [
+    (1537, 712, 2312, 4),      # rows of 4624 bytes, 16 behind a line one after the other; a last K step of 8, last tiles of one row
+    (2049, 520, 2072, 3),      # odd multiples of 8
+    (1990, 584, 2136, 5),      # rows of 4272 bytes: 48 behind
+    (1100, 1160, 4104, 6),     # the last K step's chunks reach into one more stage for some rows only
+])
+def test_down_of_rows_that_are_not_whole_lines_keeps_its_bits(S, d, I, M):
+    """Down in lone 64 x 64 tiles, more of them than compute units: the same bits as chunk by chunk, where fewer tiles load the
+    same k of all rows, wherever A begins (in the workspace, or anywhere in rows of O)."""
+    import torch
+    import paper_2407_15892_amd as mst
+    MlpDeviceRun, f64 = _harness()
+    assert mst.mst_mlp_tile_info(S, d, I)["down"][:2] == ("64_lone", 0) and -(-S // 64) * -(-d // 64) > 256
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=390 + S % 7, w_std=0.05))
+    run = MlpDeviceRun(inp, M=1)
+    whole = f64(run.forward())
+    assert np.abs(whole - _reference(inp)["O"]).max() <= TOL * np.abs(_reference(inp)["O"]).max()
+    assert np.array_equal(f64(MlpDeviceRun(inp, M=M).forward()), whole)
+    C = -(-S // M)
+    O = torch.empty((C, d), dtype=torch.bfloat16, device="cuda")          # every chunk as a call of its own
+    ws = torch.empty(run.fwd_bytes, dtype=torch.uint8, device="cuda")
+    for r0 in range(0, S, C):
+        n = min(C, S - r0)
+        mst.mst_mlp_fwd(run.X[r0:r0 + n], run.Wg, run.Wu, run.Wd, 1, ws, O[:n])
+        torch.cuda.synchronize()
+        assert np.array_equal(f64(O[:n]), whole[r0:r0 + n]), r0
