@@ -113,7 +113,8 @@ __device__ __forceinline__ void gemm_mainloop_shared(f32x4 (&acc)[C::TA][C::TB],
 //
 // Stages, of NS per panel: step kt reads stage kt + 1, loads stage kt + NS - 1 into the place of stage kt - 1 (whose
 // fragments every wave has in registers, as its MFMAs of step kt - 1 needed them before the barrier), and stages
-// kt + 2 .. kt + NS - 2 are in flight at its wait.  64 x 64 tiles, NS = 5, 512 tokens, d = 2048, I = 5632: dX 41 us
+// kt + 2 .. kt + NS - 2 are in flight at its wait.  Panels whose fragments come from two stages (PanelKC16Lines) have one
+// stage less in flight.  64 x 64 tiles, NS = 5, 512 tokens, d = 2048, I = 5632: dX 41 us
 // against 57 with the loop above, down 22 against 27; 128 x 128, NS = 4, 1668 tokens, d = 1544, I = 5384: dX 91
 // against 120, down 52 against 58.
 template <class C, class PA, class PB>
