@@ -53,7 +53,7 @@ void set_small_attributes(Set set) {
   set((const void*)k_mlp_gateup_small<C, false>);
   set((const void*)k_mlp_gateup_small<C, true>);
   set((const void*)k_mlp_gemm_nt_small<C, false>);
-  set((const void*)k_mlp_gemm_nn_small<C>);
+  set((const void*)k_mlp_gemm_nn_small<C, false>);
 }
 
 template <class T, class Set>
@@ -86,10 +86,12 @@ bool set_kernel_attributes() {   // on the current device
   set_small_attributes<Tile64Long>(set);
   set((const void*)k_mlp_gemm_nt_small<Tile32, false>);
   set((const void*)k_mlp_gemm_nt_small<Tile64Lone, true>);
-  set((const void*)k_mlp_gemm_nn_small<Tile32>);
+  set((const void*)k_mlp_gemm_nn_small<Tile32, false>);
+  set((const void*)k_mlp_gemm_nn_small<Tile64Lone, true>);
   set((const void*)k_mlp_gateup_small<Tile64Lone, true, true>);
-  set((const void*)k_mlp_dx_dw3_small<Tile64Lone, Tile64Lone>);
-  set((const void*)k_mlp_dx_dw3_small<Tile32, Tile64Lone>);
+  set((const void*)k_mlp_dx_dw3_small<Tile64Lone, Tile64Lone, false>);
+  set((const void*)k_mlp_dx_dw3_small<Tile64Lone, Tile64Lone, true>);
+  set((const void*)k_mlp_dx_dw3_small<Tile32, Tile64Lone, false>);
   set((const void*)k_mlp_gemm_nn<Tile16, false>);
   set((const void*)k_mlp_gemm_nn<Tile16, true>);
   set((const void*)k_mlp_dw3_small<Tile64>);
@@ -278,7 +280,12 @@ TileChoice gateup_tile(int64_t rows, int64_t d, int64_t I) { return choose_tile(
 // nothing (64 x 64: 62 us either way) or lost (32 x 32: 10.1 us -> 13.1, one stage less ahead), in larger tiles there is no
 // stage of LDS left for them.  Forward of 38 shapes, d = 320 to 3072: 0.77 to 0.95 with more tiles than compute units; with
 // fewer, where a stage less ahead costs as much as the lines, 0.96 to 1.06, so not there.
+// The same for the rows of dG, dU and dO in dX's and dA's lone 64 x 64 tiles: 33 backward calls with dX beside small tiles of the
+// weight gradients 0.94 to 1.06 of their time, 0.97 in the mean; 793 rows, d = 1336, I = 3368, dX alone: 151 us -> 142.
 bool whole_lines(int64_t K) { return K % 64 == 0; }
+bool by_lines(int64_t tiles, int64_t K, const void* p, const void* q) {
+  return tiles > kNumCu && (!whole_lines(K) || misaligned(p, 128) || misaligned(q, 128));
+}
 TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) {
   TileChoice c = choose_tile(N, rows, ksteps_of(K), kContiguous);
   if (c.kind == k128 && c.head == 0 && !whole_lines(K) && ksteps_of(K) >= 60) c.kind = k64Lone;
@@ -372,7 +379,9 @@ void launch_dx_dw3_small(hipStream_t st, DxProblem x, const DwProblems& ps, int 
   // tiles of dX and 129 to 256 of the weight gradients took 1.06 of their time with two launches in the mean, up to 1.21 (9764
   // rows, d = 256, I = 816: 114 us -> 137); with the longer first 38 with more than 512 of dX took 0.89 to 0.99, 0.93.
   const bool dw_first = 2 * ksteps_of(x.I) < ksteps_of(rows) && x.grid + dw_grid > 2 * kNumCu;
-  hipLaunchKernelGGL((k_mlp_dx_dw3_small<CX, CW>), dim3(x.grid + dw_grid), dim3(CW::kThreads),
+  constexpr bool kCan = std::is_same_v<CX, Tile64Lone>;
+  const bool lines = kCan && by_lines(x.grid + dw_grid, x.I, x.dG, x.dU);
+  hipLaunchKernelGGL((lines ? k_mlp_dx_dw3_small<CX, CW, kCan> : k_mlp_dx_dw3_small<CX, CW, false>), dim3(x.grid + dw_grid), dim3(CW::kThreads),
                      CX::kLds > CW::kLds ? CX::kLds : CW::kLds, st, x, ps, rows, accumulate, dw_first ? dw_grid : 0);
 }
 
@@ -422,7 +431,7 @@ template <class C>
 void launch_nt_small(hipStream_t st, const __bf16* P, const __bf16* Q, int rows, int N, int K, __bf16* out, int ldo) {
   const int n_nt = (N + C::EA - 1) / C::EA, n_st = (rows + C::EB - 1) / C::EB;
   constexpr bool kCan = std::is_same_v<C, Tile64Lone>;
-  const bool lines = kCan && n_nt * n_st > kNumCu && (!whole_lines(K) || misaligned(P, 128) || misaligned(Q, 128));
+  const bool lines = kCan && by_lines(n_nt * n_st, K, P, Q);
   hipLaunchKernelGGL((lines ? k_mlp_gemm_nt_small<C, kCan> : k_mlp_gemm_nt_small<C, false>), dim3(even_grid(n_nt, n_st)), dim3(C::kThreads),
                      C::kLds, st, P, K, Q, K, rows, N, K, n_st, n_nt, out, ldo);
 }
@@ -458,8 +467,10 @@ template <class C>
 void launch_nn_small(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16* P2, const __bf16* Q2,
                      int rows, int N, int K, int ldq, __bf16* out) {
   const int n_nt = (N + C::EA - 1) / C::EA, n_st = (rows + C::EB - 1) / C::EB;
-  hipLaunchKernelGGL(k_mlp_gemm_nn_small<C>, dim3(even_grid(n_nt, n_st)), dim3(C::kThreads), C::kLds, st,
-                     P1, Q1, P2, Q2, K, ldq, rows, N, K, n_st, n_nt, out, ldq);
+  constexpr bool kCan = std::is_same_v<C, Tile64Lone>;
+  const bool lines = kCan && by_lines(n_nt * n_st, K, P1, P2 ? P2 : P1);
+  hipLaunchKernelGGL((lines ? k_mlp_gemm_nn_small<C, kCan> : k_mlp_gemm_nn_small<C, false>), dim3(even_grid(n_nt, n_st)), dim3(C::kThreads),
+                     C::kLds, st, P1, Q1, P2, Q2, K, ldq, rows, N, K, n_st, n_nt, out, ldq);
 }
 void launch_nn(hipStream_t st, const __bf16* P1, const __bf16* Q1, const __bf16* P2, const __bf16* Q2,
                int rows, int N, int K, __bf16* out) {

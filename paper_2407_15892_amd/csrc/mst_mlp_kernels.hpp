@@ -327,8 +327,8 @@ __global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gemm_nt
   store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
 }
 
-// out[s][n] = sum_k P1[s][k] Q1[k][n] (+ sum_k P2[s][k] Q2[k][n])
-template <class C>
+// out[s][n] = sum_k P1[s][k] Q1[k][n] (+ sum_k P2[s][k] Q2[k][n]).   kLines: rows of P are not whole cache lines.
+template <class C, bool kLines = false>
 __device__ __forceinline__ void nn_tile_small(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
@@ -345,20 +345,20 @@ __device__ __forceinline__ void nn_tile_small(
   const int terms = P2 != nullptr ? 2 : 1;
   for (int term = 0; term < terms; ++term) {
     PanelKS16<C, C::EA, C::TA, (C::TA > 1)> pa;                   // one 16-row tile: the permutation is the identity
-    PanelKC16<C, C::EB, C::TB, false> pb;
+    std::conditional_t<kLines, PanelKC16Lines<C, C::EB, C::TB, false>, PanelKC16<C, C::EB, C::TB, false>> pb;
     pa.init((term ? Q2 : Q1) + n0, ldq, K, N - n0, wave, lane, wa);
     pb.init((term ? P2 : P1) + (size_t)s0 * ldp, ldp, rows - s0, K, wave, lane, wb);
     gemm_mainloop_small<C>(acc, pa, pb, smem, 0, K);
   }
   store_small_bf16<C>(acc, out, ldo, rows, N, s0, n0, wa, wb, lane);
 }
-template <class C>
+template <class C, bool kLines>
 __global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_gemm_nn_small(
     const __bf16* __restrict__ P1, const __bf16* __restrict__ Q1,
     const __bf16* __restrict__ P2, const __bf16* __restrict__ Q2,
     int ldp, int ldq, int rows, int N, int K, int n_st, int n_nt, __bf16* __restrict__ out, int ldo) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  nn_tile_small<C>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, blockIdx.x, n_st, n_nt, out, ldo, smem);
+  nn_tile_small<C, kLines>(P1, Q1, P2, Q2, ldp, ldq, rows, N, K, blockIdx.x, n_st, n_nt, out, ldo, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -434,14 +434,14 @@ __global__ __launch_bounds__(C::kThreads, kSmallWavesPerSimd) void k_mlp_dw3_sma
 }
 // and with dX beside them (CX: its tile).  dX has the workgroups from dx_from on; the others, before and behind, are those
 // of the weight gradients (dx_from is 0 or all of theirs).
-template <class CX, class CW>
+template <class CX, class CW, bool kLines>
 __global__ __launch_bounds__(CW::kThreads, kSmallWavesPerSimd) void k_mlp_dx_dw3_small(DxProblem x, DwProblems ps, int rows, int accumulate,
                                                                                       int dx_from) {
   static_assert(CX::kThreads == CW::kThreads, "one launch");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int b = (int)blockIdx.x - dx_from;
   if (b >= 0 && b < x.grid) {
-    nn_tile_small<CX>(x.dG, x.Wg, x.dU, x.Wu, x.I, x.d, rows, x.d, x.I, b, x.n_st, x.n_jt, x.dX, x.d, smem);
+    nn_tile_small<CX, kLines>(x.dG, x.Wg, x.dU, x.Wu, x.I, x.d, rows, x.d, x.I, b, x.n_st, x.n_jt, x.dX, x.d, smem);
     return;
   }
   dw3_tile_small<CW>(b < 0 ? (int)blockIdx.x : b - x.grid, ps, rows, accumulate, smem);
