@@ -47,8 +47,9 @@
  *   - Arithmetic: bf16 operands, fp32 MFMA accumulation; silu, its derivative
  *     and the products in fp32 on the accumulators; A, dA, dG, dU rounded to
  *     bf16 (nearest even) before the GEMMs that consume them; O and dX
- *     rounded to bf16; the three weight gradients fp32, accumulated chunk by
- *     chunk in a fixed order without atomics (bit-identical across calls).
+ *     rounded to bf16; the three weight gradients fp32, accumulated in a fixed
+ *     order without atomics (bit-identical across calls with as large a
+ *     workspace).
  */
 #ifndef MST_MLP_H
 #define MST_MLP_H
@@ -94,10 +95,11 @@ mst_status mst_mlp_fwd(const void* X, const void* Wg, const void* Wu, const void
 
 /*
  * Backward (Algorithm 3).  Nothing is kept from the forward call: the gate and
- * up projections of every chunk are recomputed.
+ * up projections of every chunk are recomputed.  One to three of dG, dU and A
+ * of a group of chunks may be kept in rows of dX that are not final yet.
  *   dO  [S, d] bf16      upstream gradient of O
  *   dX  [S, d] bf16      out, fully overwritten
- *   dWg [I, d] fp32      out, fully overwritten (first chunk stores, later chunks accumulate)
+ *   dWg [I, d] fp32      out, fully overwritten (first group stores, later ones accumulate)
  *   dWu [I, d] fp32      out
  *   dWd [d, I] fp32      out
  */
