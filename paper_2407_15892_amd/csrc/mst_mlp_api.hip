@@ -275,8 +275,12 @@ int64_t ksteps_of(int64_t k) { return (k + kBK - 1) / kBK; }
 TileChoice gateup_tile(int64_t rows, int64_t d, int64_t I) { return choose_tile(2 * I, rows, ksteps_of(d), kGateUp); }
 // Lone 64 x 64 tiles load rows that are not whole cache lines line by line (PanelKC16Lines), the other tiles fetch their lines
 // twice.  Down of 800 rows, d = 2048: 45 us at I = 7168, at 7176 66 -> 45; 507 rows, d = 2688, I = 7120: 64 -> 45.  With that they
-// are faster than 128 x 128 tiles in a long contraction, too: forward of 1421 rows, d = 2752, I = 6952: 220 us -> 176; 3341, 1192,
-// 3920: 128 -> 113; 3410, 1264, 4440: 144 -> 137.  With K steps of 128, which straddle half as many lines, the panels gained
+// are faster than 128 x 128 tiles in a long contraction that has a few more of those than compute units.  Forwards timed with
+// both: 80 of up to 1144 tiles of 64 x 64 took 0.77 to 1.02 of their time, 0.90 in the mean (1421 rows, d = 2752, I = 6952: 220 us
+// -> 176), 26 of 1887 to 2040 1.04 to 1.24 (2400, 3216, 9248: 396 -> 450), and there is nothing between: up to five rounds.  Where
+// rows begin on a line or half way into one (K % 64 == 32) half as much is to gain: 8 of up to four rounds 0.88 to 0.99, 11 of more
+// 0.99 to 1.07, 1.03 in the mean.
+// With K steps of 128, which straddle half as many lines, the panels gained
 // nothing (64 x 64: 62 us either way) or lost (32 x 32: 10.1 us -> 13.1, one stage less ahead), in larger tiles there is no
 // stage of LDS left for them.  Forward of 38 shapes, d = 320 to 3072: 0.77 to 0.95 with more tiles than compute units; with
 // fewer, where a stage less ahead costs as much as the lines, 0.96 to 1.06, so not there.
@@ -288,7 +292,9 @@ bool by_lines(int64_t tiles, int64_t K, const void* p, const void* q) {
 }
 TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) {
   TileChoice c = choose_tile(N, rows, ksteps_of(K), kContiguous);
-  if (c.kind == k128 && c.head == 0 && !whole_lines(K) && ksteps_of(K) >= 60) c.kind = k64Lone;
+  if (c.kind == k128 && c.head == 0 && !whole_lines(K) && ksteps_of(K) >= 60 &&
+      tiles_of(N, rows, 64) <= (K % 64 == 32 ? 4.0 : 5.0) * kNumCu)
+    c.kind = k64Lone;
   return c;
 }
 TileChoice nn_tile(int64_t rows, int64_t N, int64_t K, int terms) { return choose_tile(N, rows, terms * ksteps_of(K), kStrided); }

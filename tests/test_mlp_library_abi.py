@@ -128,6 +128,18 @@ def test_down_of_65_to_96_tokens_takes_32_by_32_tiles_only_for_short_contraction
         assert down(rows, 2720, 16384) == "32"            # one round
 
 
+def test_down_takes_line_panels_in_place_of_128_by_128_tiles_only_where_they_are_faster(mst):
+    """A few more 128 x 128 tiles than compute units, and rows that begin anywhere in a line."""
+    down = lambda rows, d, I: mst.mst_mlp_tile_info(rows, d, I)["down"][:2]
+    assert down(1169, 3296, 11048) == ("64_lone", 0) and down(3612, 1200, 4296) == ("64_lone", 0)    # 260 and 290 tiles
+    for rows, d, I in ((2400, 3216, 9248), (2068, 3776, 12760), (4895, 1584, 5296)):                  # 494 to 510
+        assert down(rows, d, I) == ("128", 0), (rows, d, I)
+    assert down(1264, 3224, 8544) == ("64_lone", 0) and down(2508, 1568, 3936) == ("64_lone", 0)      # every second row on a line
+    for rows, d, I in ((2038, 2088, 6240), (2356, 1800, 5664)):                                       # and more than four rounds
+        assert down(rows, d, I) == ("128", 0), (rows, d, I)
+    assert down(1169, 3296, 11072) == ("128", 0)                                                      # all of them
+
+
 def test_dx_of_later_chunks_of_few_rows_has_a_launch_of_its_own(mst):
     """Chunks of one row of large tiles whose weight gradients are read back: dX's long tiles would end that launch."""
     for d, I in ((4096, 14336), (4096, 11008), (3328, 12496)):
