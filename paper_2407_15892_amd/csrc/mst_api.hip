@@ -320,8 +320,11 @@ void launch_streamed(hipStream_t st, const StreamProblem& q, int split, int per_
 }
 // Microseconds: a step of a workgroup by itself, a step's share of a compute unit with all of them busy, the ends of a
 // workgroup (in steps), the launch.  Fitted to 260 shapes of 64 to 32768 rows, d = 136 to 512, V = 1000 to 128000, every
-// form with 1 to 64 splits (within 4 to 8 % rms; the form and split taken are 2.5 % behind the fastest in the mean).  A step
-// of dW takes up to 1.7 times that where its 16 OT entries are likely to be labels; operands, dW and partials at 2.5 TB/s.
+// form with 1 to 64 splits (within 4 to 8 % rms; the form and split taken are 2.5 % behind the fastest in the mean).  The chain is
+// that of the XCD that has most workgroups: 154 of dW and 100 of dH are 254 in all, but 20 + 13 on one XCD, a second round (308
+// rows, d = 256, V = 4928: 23.1 us in five splits, 16.1 in four; 120 shapes whose form or split this changes: 0.90 in the mean, 0.69
+// to 1.21).  A step of dW takes up to 1.7 times that where its 16 OT entries are likely to be labels; operands, dW and partials at
+// 2.5 TB/s.
 struct StreamForm { int dk, owners_h, owners_w, ot_w, rings, per_cu; double step, busy, ends, fixed; StreamLaunch launch; };
 template <class CH, class CW>
 constexpr StreamForm stream_form(double step, double busy, double ends, double fixed) {
@@ -342,21 +345,34 @@ double stream_us(const Plan* p, const StreamForm& f, int split, int per_split) {
   const double by_label = 1.0 + 0.7 * std::min(1.0, 512.0 * f.ot_w / (double)p->V);
   const double t_h = (double)up(per_split, 32 * f.rings) + f.ends, t_w = ((double)up(p->S, 32 * f.rings) + f.ends) * by_label;
   const double partials = split > 1 ? 4.0 * (double)split * (double)(p->S * p->d) : 0.0;
-  const int64_t units = (int64_t)kNumCu * f.per_cu;
-  const double chain = f.step * (t_w > t_h ? span_us(n_w, t_w, n_h, t_h, units) : span_us(n_h, t_h, n_w, t_w, units));
+  const int64_t units = (int64_t)kXcdCu * f.per_cu, x_h = up(n_h, kNumXcd), x_w = up(n_w, kNumXcd);   // of the XCD that has most
+  const double chain = f.step * (t_w > t_h ? span_us(x_w, t_w, x_h, t_h, units) : span_us(x_h, t_h, x_w, t_w, units));
   const double busy = f.busy * ((double)n_h * t_h + (double)n_w * t_w) / kNumCu, bytes = (8.0 * (double)(p->V * p->d) + partials) / 2.5e6;
   const double t = f.fixed + std::cbrt(chain * chain * chain + busy * busy * busy + bytes * bytes * bytes);     // the longest, smoothed
   return split > 1 ? t + 3.5 + partials / kHbmBytesPerUs : t;
 }
-// Taken where it is estimated this much below the order that would run (the estimates of blocks are 8 % too high in the mean).
-// Of the 260 shapes 139 are; they took 0.60 of that order's time in the mean, three of them 1.06 to 1.09 (V = 1673 to 4116), and
-// of the others 37 would have been faster by more than 3 %.
-constexpr double kStreamedPairs = 0.9, kStreamedBlocks = 0.78;
+// Taken where it is estimated this much below the order that would run.  The estimates of blocks are 8 % too high in the mean;
+// those of joint launches 3 us a pair where pairs are short, their last launch being less than a round of short tiles; and of
+// one chunk with split partials beside dW the sum over many splits of few rows costs more than estimated.  750 shapes that this
+// takes, of 32 to 32768 rows, V = 300 to 128256, took 0.67 of that order's time in the mean, ten of them 1.04 to 1.11; without the
+// 3 us and the limit of splits 35 of 300 calls of up to 3000 rows took 1.02 to 1.28 (99 rows, d = 192, V = 5908, M = 1: 15.5 us, 19.3
+// streamed).  Blocks from 0.78 to 0.82 of theirs: 60 shapes 0.74 to 1.07.
+constexpr double kStreamedPairs = 0.9, kStreamedJoint = 0.9, kStreamedBlocks = 0.82, kShortPair = 20.5, kShortPairLess = 3.0;
+constexpr int kStreamedSplits = 10;
 void choose_streamed(Plan* p) {
   const int64_t S = p->S, d = p->d, V = p->V;
   if (d <= 128 || d > 512 || S * d >= (int64_t(1) << 30) || V * d >= (int64_t(1) << 30)) return;   // 32-bit byte offsets of whole operands
-  const int64_t room = (int64_t)(p->b_total / ((size_t)(S * d) * 4));
-  double best = p->blk_use ? kStreamedBlocks * p->est_blocks_us : kStreamedPairs * p->est_pairs_us;
+  int64_t room = (int64_t)(p->b_total / ((size_t)(S * d) * 4));
+  double best = kStreamedPairs * p->est_pairs_us;
+  if (p->blk_use) {
+    best = kStreamedBlocks * p->est_blocks_us;
+  } else if (p->joint == MST_PAIR_SPLIT) {
+    best = kStreamedJoint * p->est_pairs_us;
+    room = std::min(room, (int64_t)kStreamedSplits);
+  } else if (p->joint && p->joint != MST_PAIR_DH128) {
+    const double pairs = (double)((p->n_chunks + 1) / 2);
+    best = kStreamedJoint * (p->est_pairs_us - (p->est_pairs_us < kShortPair * pairs ? kShortPairLess * pairs : 0.0));
+  }
   for (int k = 0; k < (int)(sizeof(kStreamForms) / sizeof(kStreamForms[0])); ++k) {
     const StreamForm& f = kStreamForms[k];
     if (f.dk < d || f.dk - d >= (f.dk == 256 ? 256 : 128)) continue;

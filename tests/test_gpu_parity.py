@@ -907,10 +907,10 @@ def test_kernel_timing_covers_every_nth_launch_of_each_kind():
     (749, 360, 7413, 2, "384", 10),
     (10, 280, 33, 4, "384", 1),
     (1446, 360, 3961, 7, "384_split", 1),
-    (9, 296, 1775, 4, "384_split", 2),
+    (5, 264, 2722, 5, "384_split", 2),
     (823, 392, 5894, 3, "512", 5),
     (139, 408, 184, 5, "512", 1),
-    (209, 504, 262, 3, "512_split", 1),
+    (171, 456, 101, 5, "512_split", 1),
     (1414, 456, 3111, 7, "512_split", 1),
     (742, 512, 9357, 7, "512_split", 2),
     (742, 424, 6357, 5, "512_split", 3),

@@ -437,3 +437,16 @@ def test_streamed_backward_keeps_its_shares_inside_the_vocabulary_and_the_worksp
         assert S * d < 2 ** 30 and V * d < 2 ** 30
     assert set(seen) == set(mst.binding.STREAMED) and min(seen.values()) > 20, seen
     assert mst.load_library().mst_bwd_streamed(0, 256, 4096, 1, None) == -1
+
+
+def test_streamed_backward_is_taken_only_where_it_is_faster(mst):
+    """Short calls, for which the launches of the pair order are cheaper than estimated (each timed both ways, slower
+    streamed), and splits whose workgroups are no second round on any XCD."""
+    for shape in ((99, 208, 1100, 2), (42, 320, 864, 3), (144, 200, 1080, 2), (2510, 176, 509, 3), (838, 176, 1447, 1), (36, 368, 3996, 3)):
+        assert mst.mst_bwd_streamed(*shape) == ("no", 0), shape
+    assert mst.mst_bwd_streamed(308, 256, 4928, 1) == ("256_split", 4)       # 20 + 10 workgroups on an XCD, with five splits 20 + 13
+    assert mst.mst_bwd_streamed(512, 256, 4096, 4) == ("256_split", 4)
+    for shape in ((308, 256, 4928, 1), (347, 256, 4672, 1), (229, 256, 5696, 1), (283, 200, 4668, 1)):
+        form, n = mst.mst_bwd_streamed(*shape)
+        S, _, V, _ = shape
+        assert form == "no" or -(--(-V // 32) // 8) + -(-n * -(-S // 16) // 8) <= 32, (shape, n)
