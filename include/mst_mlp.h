@@ -48,8 +48,9 @@
  *     and the products in fp32 on the accumulators; A, dA, dG, dU rounded to
  *     bf16 (nearest even) before the GEMMs that consume them; O and dX
  *     rounded to bf16; the three weight gradients fp32, accumulated in a fixed
- *     order without atomics (bit-identical across calls with as large a
- *     workspace).
+ *     order without atomics, which depends on S, d, I and M alone and on
+ *     whether dX overlaps an input (bit-identical across calls, whatever
+ *     workspace they are handed).
  */
 #ifndef MST_MLP_H
 #define MST_MLP_H
@@ -95,8 +96,11 @@ mst_status mst_mlp_fwd(const void* X, const void* Wg, const void* Wu, const void
 
 /*
  * Backward (Algorithm 3).  Nothing is kept from the forward call: the gate and
- * up projections of every chunk are recomputed.  One to three of dG, dU and A
- * of a group of chunks may be kept in rows of dX that are not final yet.
+ * up projections of every chunk are recomputed.  The rows are taken in groups,
+ * not necessarily of whole chunks: one to three of dG, dU and A of a group may
+ * be kept in rows of dX that are not final yet.  A dX that overlaps X or dO has
+ * to begin at least C rows before it (the groups are then the chunks, one after
+ * the other); it must not overlap a weight.
  *   dO  [S, d] bf16      upstream gradient of O
  *   dX  [S, d] bf16      out, fully overwritten
  *   dWg [I, d] fp32      out, fully overwritten (first group stores, later ones accumulate)

@@ -143,29 +143,29 @@ ForwardGroup forward_group(const Plan& p, int64_t left, size_t workspace_bytes, 
 }
 
 // The backward's groups of rows, likewise: of dG, dU and A of a group, up to three are kept in the rows of dX behind it, and
-// the workspace then holds those of one and a half times or three times the rows of a chunk.  The largest group is kept as
-// small as the number of groups allows; without fewer groups than chunks all are equal and in the workspace.  Backward, us, chunk
+// the workspace then holds those of one and a half times or three times the rows of a chunk.  The groups are the order in which
+// the weight gradients are summed, so they depend on the shape alone: of a larger workspace only what the call needs is used.
+// The largest group is kept as small as the number of groups allows; without fewer groups than chunks they are the chunks.  Backward, us, chunk
 // by chunk -> this: 22592 rows, d = 616, I = 1560, M = 37: 1488 -> 1139; 32128, 640, 2264, 50: 2381 -> 1744; 20288, 1760, 5776, 12:
 // 3938 -> 3484.  Groups as large as fit, where that makes no fewer of them: 8128, 1376, 3760, 4: 788 -> 820.
 struct BackwardGroups {
   const Plan& p;
-  int64_t room[4];                // rows whose dG, dU and A fit with k of them in dX: of the workspace
+  int64_t room[4];                // rows whose dG, dU and A fit with k of them in dX: of the workspace (a chunk with none)
   int64_t cap;                    // most rows of a group
   bool in_dx;
-  BackwardGroups(const Plan& plan, size_t workspace_bytes, bool dx_is_free) : p(plan), in_dx(false) {
-    const int64_t most = std::min(((int64_t(1) << 30) - 1) / p.I, ((int64_t(1) << 30) - 1) / p.d);                 // 32-bit offsets
-    for (int k = 0; k < 3; ++k) room[k] = std::min((int64_t)(slot(workspace_bytes, k) / (2 * (size_t)p.I)), most);  // room[0] >= C
+  BackwardGroups(const Plan& plan, bool dx_is_free) : p(plan), in_dx(false) {
+    const int64_t most = std::min(((int64_t(1) << 30) - 1) / p.I, ((int64_t(1) << 30) - 1) / p.d);        // 32-bit offsets
+    room[0] = cap = p.C;
+    for (int k = 1; k < 3; ++k) room[k] = std::min((int64_t)(slot(k) / (2 * (size_t)p.I)), most);
     room[3] = most;
-    const int64_t n = (p.S + room[0] - 1) / room[0];
-    cap = (p.S + n - 1) / n;
+    const int64_t n = (p.S + p.C - 1) / p.C;
     if (n < 4 || !dx_is_free) return;
     in_dx = true;
-    const int64_t equal = cap;
     cap = most;
     const int64_t fewest = count();
     if (fewest >= n) {
       in_dx = false;
-      cap = equal;
+      cap = p.C;
       return;
     }
     int64_t low = (p.S + fewest - 1) / fewest - 1, high = 0;
@@ -176,7 +176,7 @@ struct BackwardGroups {
     }
     cap = high;
   }
-  static size_t slot(size_t workspace_bytes, int k) { return workspace_bytes / (size_t)(3 - k) / 256 * 256; }   // a buffer's share of it
+  size_t slot(int k) const { return 3 * p.slot / (size_t)(3 - k) / 256 * 256; }   // a buffer's share of the workspace
   int64_t fits(int64_t left, int k) const { return k ? std::min(room[k], left * p.d / (k * p.I + p.d)) : room[0]; }   // k rows I <= (left - rows) d
   int64_t next(int64_t left, int* k) const {            // rows of the next group; how many of its buffers are in dX
     const int64_t most = std::min(left, cap);
@@ -600,7 +600,7 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
   const size_t x_bytes = (size_t)S * d * 2, w_bytes = (size_t)I * d * 2;
   const bool dx_is_free = !overlap(dX, x_bytes, X, x_bytes) && !overlap(dX, x_bytes, dO, x_bytes) && !overlap(dX, x_bytes, Wg, w_bytes) &&
                           !overlap(dX, x_bytes, Wu, w_bytes) && !overlap(dX, x_bytes, Wd, w_bytes);
-  const BackwardGroups groups(p, workspace_bytes, dx_is_free);
+  const BackwardGroups groups(p, dx_is_free);
   const DwChoice dw = dw_choice(std::min(groups.cap, p.S), p.d, p.I);
 
   // Algorithm 3: loop over groups of mini-sequences; dX_i lands in its row range, the weight gradients accumulate
@@ -610,7 +610,7 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
     __bf16* buf[3];                                             // dA, then dG in place; dU; A
     for (int k = 0; k < 3; ++k)
       buf[k] = k < in_dx ? dXb + p.S * p.d - (k + 1) * (int64_t)rows * p.I
-                         : reinterpret_cast<__bf16*>(ws + (k - in_dx) * BackwardGroups::slot(workspace_bytes, in_dx));
+                         : reinterpret_cast<__bf16*>(ws + (k - in_dx) * groups.slot(in_dx));
     __bf16 *const bufG = buf[0], *const bufU = buf[1], *const bufA = buf[2];
     const bool more = r0 + rows < p.S;
     const __bf16* Xc = Xb + r0 * p.d;

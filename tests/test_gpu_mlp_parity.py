@@ -381,6 +381,54 @@ def test_backward_groups_of_rows_match_oracle_and_keep_the_bits_of_dx(S, d, I, M
 
 
 @pytest.mark.parametrize("S,d,I,M", [
+    (1500, 136, 264, 12),
+    (1601, 264, 520, 23),
+    (2612, 776, 264, 3),      # chunk by chunk
+    (300, 72, 8, 37),         # chunks of nine rows, whose 144 bytes a buffer are rounded up to 256
+])
+def test_weight_gradients_keep_their_bits_in_a_larger_workspace(S, d, I, M):
+    """The order of their sums depends on the shape alone, and of a larger workspace nothing but the declared size is written."""
+    import torch
+    MlpDeviceRun, _ = _harness()
+    run = MlpDeviceRun(mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=385, w_std=0.05)))
+    base = run.backward()
+    for more in (256, run.bwd_bytes, 7 * run.bwd_bytes):
+        run.pad = more
+        ws = run._ws(run.bwd_bytes)
+        got = [torch.full_like(t, float("nan")) for t in base]
+        run.mst.mst_mlp_bwd(run.X, run.Wg, run.Wu, run.Wd, run.dO, M, ws, *got)
+        torch.cuda.synchronize()
+        for a, b in zip(got, base):
+            assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
+                               b.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32)), more
+        assert bool((ws[run.bwd_bytes:] == 0xA5).all()), more
+
+
+@pytest.mark.parametrize("of", ["X", "dO"])
+def test_dx_that_overlaps_rows_already_read_is_formed_chunk_by_chunk(of):
+    """dX a chunk of rows before X or dO in the same buffer: a chunk's rows are overwritten after they have been read.  Without
+    the overlap this shape takes fewer, larger groups of rows."""
+    import torch
+    MlpDeviceRun, f64 = _harness()
+    S, d, I, M = 1500, 136, 264, 12
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=386, w_std=0.05))
+    ref = _reference(inp)
+    run = MlpDeviceRun(inp)
+    base = run.backward()
+    C = S // M
+    both = torch.empty((S + C, d), dtype=torch.bfloat16, device="cuda")
+    both[C:] = getattr(run, of)
+    ins = {"X": run.X, "dO": run.dO, of: both[C:]}
+    got = [both[:S]] + [torch.full_like(t, float("nan")) for t in base[1:]]
+    ws = run._ws(run.bwd_bytes)
+    run.mst.mst_mlp_bwd(ins["X"], run.Wg, run.Wu, run.Wd, ins["dO"], M, ws, *got)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0].view(torch.int16), base[0].view(torch.int16))
+    for k, t in zip(NAMES[2:], got[1:]):
+        assert np.abs(f64(t) - ref[k]).max() <= TOL * np.abs(ref[k]).max(), k
+
+
+@pytest.mark.parametrize("S,d,I,M", [
     (1537, 712, 2312, 4),      # rows of 4624 bytes, 16 behind a line one after the other; a last K step of 8, last tiles of one row
     (2049, 520, 2072, 3),      # odd multiples of 8
     (1990, 584, 2136, 5),      # rows of 4272 bytes: 48 behind
