@@ -113,12 +113,12 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
                        void* dX, float* dWg, float* dWu, float* dWd, void* stream);
 
 /*
- * Which block tiles the launches of a chunk of `rows` rows take (host, pure; a test aid).  All give the same O and dX
+ * Which block tiles the launches of a group of `rows` rows take (host, pure; a test aid).  All give the same O and dX
  * bit for bit.  info[0..2] = gate/up (forward and backward), info[3..5] = down, info[6..8] = dA and info[9..11] = dX
  * where they have launches of their own (mst_mlp_da_in_gateup, mst_mlp_dx_tile), each as
  * {MST_MLP_TILE_* of the launch, or of its end; leading columns (of I, d, I, d) that a launch of 256 x 256 tiles of its
  * own takes before it, 0 for none; 1 where 256 x 256 tiles are laid out in super-tiles}; info[12..13] = the weight
- * gradients of a call whose chunks have `rows` rows: {MST_MLP_TILE_256, _64 or _64_LONE; 1 where the tiles are dealt out
+ * gradients of a call whose largest group has `rows` rows: {MST_MLP_TILE_256, _64 or _64_LONE; 1 where the tiles are dealt out
  * evenly over the XCDs}.
  */
 enum {
@@ -134,8 +134,7 @@ enum {
 mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info);
 
 /*
- * How dX of a chunk of `rows` rows is computed, in a call whose chunks have that many rows; first: it is the call's first
- * chunk.  One of MST_MLP_DX_*, -1 on bad shapes (host, pure; a test aid).  dX has the same bits either way.
+ * How dX of a group of `rows` rows is computed, in a call whose largest group has that many; first: it is the call's first.  One of MST_MLP_DX_*, -1 on bad shapes (host, pure; a test aid).  dX has the same bits either way.
  */
 enum {
   MST_MLP_DX_OWN = 0,     /* in a launch of its own, with the tiles that mst_mlp_tile_info names   */
@@ -149,7 +148,31 @@ int32_t mst_mlp_dx_tile(int64_t rows, int64_t d, int64_t I, int32_t first);
 int32_t mst_mlp_dx_tile_rows(int64_t rows, int64_t d, int64_t I, int32_t first);
 
 /*
- * 1 where dA of a chunk of `rows` rows is computed by the launch of gate/up's backward, 0 where it has a launch of its own
+ * The groups of rows that a call takes, each with the launches that the queries around this one name for its rows (host, pure;
+ * test aids): their number, -1 for bad arguments; info of the first `room` of them.
+ * mst_mlp_fwd_groups: per group {rows, 1 where its A is kept in the rows of O behind it, 0 in the workspace}; output_overlaps:
+ * whether O overlaps an input.
+ * mst_mlp_bwd_groups: per group {rows; how many of dG, dU and A are in the rows of dX behind it; MST_MLP_DX_* and the rows of
+ * that tile; 1 where dA is computed by the launch of gate/up's backward; MST_MLP_TILE_* of the weight gradients, which have
+ * those of the largest group}; dx_overlaps: whether dX overlaps an input.
+ */
+int64_t mst_mlp_fwd_groups(int64_t S, int64_t d, int64_t I, int32_t M, size_t workspace_bytes, int32_t output_overlaps,
+                           int64_t room, int64_t* info);
+int64_t mst_mlp_bwd_groups(int64_t S, int64_t d, int64_t I, int32_t M, int32_t dx_overlaps, int64_t room, int64_t* info);
+
+/*
+ * Which products of `rows` rows, the first of their call, load rows that are not whole cache lines line by line, their operands
+ * beginning on one (host, pure; a test aid): a sum of MST_MLP_LINES_*, -1 on bad shapes.  The same bits either way.
+ */
+enum {
+  MST_MLP_LINES_DOWN = 1,
+  MST_MLP_LINES_DA = 2,
+  MST_MLP_LINES_DX = 4    /* in a launch of its own or beside the weight gradients (mst_mlp_dx_tile) */
+};
+int32_t mst_mlp_line_panels(int64_t rows, int64_t d, int64_t I);
+
+/*
+ * 1 where dA of a group of `rows` rows is computed by the launch of gate/up's backward, 0 where it has a launch of its own
  * (with the tiles that mst_mlp_tile_info names), -1 on bad shapes (host, pure; a test aid).
  */
 int32_t mst_mlp_da_in_gateup(int64_t rows, int64_t d, int64_t I);

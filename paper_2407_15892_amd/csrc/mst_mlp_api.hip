@@ -312,6 +312,8 @@ DwChoice dw_choice(int64_t C, int64_t d, int64_t I) {
   return c;
 }
 
+TileKind dw_tile(const DwChoice& c) { return c.small ? (c.lone ? k64Lone : k64) : kBig; }
+
 // dA computed by gate/up's backward launch: where both are one short tile deep, a launch less is worth more than the
 // second contraction in it.  Up to 16 K steps: backward of 256 tokens, d = 256, I = 896: 22.4 -> 19.6 us; of 256, d = 1024,
 // I = 2816: 46.7 -> 45.2; from 24 on nothing (100 tokens, d = 1536) to 3 % slower (64, d = 4096).
@@ -361,6 +363,16 @@ DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwCh
   const double best = std::min(whole, I >= 2 * d ? std::min(half, kQuarter * quarter) : half);
   if (best > own) return kDxOwn;
   return best == whole ? kDxWhole : best == half ? kDxHalf : kDxQuarter;
+}
+int dx_tile(DxKind dx) { return dx == kDxQuarter ? kDxHalf : dx; }       // MST_MLP_DX_* of the header
+int dx_tile_rows(DxKind dx) {
+  switch (dx) {
+    case kDxWhole: case kDxHalf: return kTile;
+    case kDxQuarter: return Tile16Quarter::EB;
+    case kDx64: return Tile64Lone::EB;
+    case kDx32: return Tile32::EB;
+    default: return 0;
+  }
 }
 template <class T>
 void launch_dx_dw3(hipStream_t st, DxProblem x, const DwProblems& ps, int rows, bool even, bool accumulate, int more) {
@@ -680,7 +692,7 @@ mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info) 
   put(6, nn_tile(rows, I, d, 1), I, kTile);
   put(9, nn_tile(rows, d, I, 2), d, kTile);
   const DwChoice dw = dw_choice(rows, d, I);
-  info[12] = dw.small ? (dw.lone ? k64Lone : k64) : kBig;
+  info[12] = dw_tile(dw);
   info[13] = dw.even;
   return MST_OK;
 }
@@ -688,20 +700,59 @@ mst_status mst_mlp_tile_info(int64_t rows, int64_t d, int64_t I, int64_t* info) 
 int32_t mst_mlp_dx_tile(int64_t rows, int64_t d, int64_t I, int32_t first) {
   Plan p;
   if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
-  const DxKind dx = choose_dx(rows, d, I, !first, dw_choice(rows, d, I));
-  return dx == kDxQuarter ? kDxHalf : dx;
+  return dx_tile(choose_dx(rows, d, I, !first, dw_choice(rows, d, I)));
 }
 
 int32_t mst_mlp_dx_tile_rows(int64_t rows, int64_t d, int64_t I, int32_t first) {
   Plan p;
   if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
-  switch (choose_dx(rows, d, I, !first, dw_choice(rows, d, I))) {
-    case kDxWhole: case kDxHalf: return kTile;
-    case kDxQuarter: return Tile16Quarter::EB;
-    case kDx64: return Tile64Lone::EB;
-    case kDx32: return Tile32::EB;
-    default: return 0;
+  return dx_tile_rows(choose_dx(rows, d, I, !first, dw_choice(rows, d, I)));
+}
+
+int64_t mst_mlp_fwd_groups(int64_t S, int64_t d, int64_t I, int32_t M, size_t workspace_bytes, int32_t output_overlaps,
+                           int64_t room, int64_t* info) {
+  Plan p;
+  if (make_plan(S, d, I, M, &p) != MST_OK || workspace_bytes < p.slot || room < 0 || (room && !info)) return -1;
+  int64_t n = 0;
+  for (int64_t left = S; left > 0; ++n) {
+    const ForwardGroup g = forward_group(p, left, workspace_bytes, !output_overlaps);
+    left -= g.rows;
+    if (n >= room) continue;
+    info[2 * n] = g.rows;
+    info[2 * n + 1] = g.in_output;
   }
+  return n;
+}
+
+int64_t mst_mlp_bwd_groups(int64_t S, int64_t d, int64_t I, int32_t M, int32_t dx_overlaps, int64_t room, int64_t* info) {
+  Plan p;
+  if (make_plan(S, d, I, M, &p) != MST_OK || room < 0 || (room && !info)) return -1;
+  const BackwardGroups groups(p, !dx_overlaps);
+  const DwChoice dw = dw_choice(std::min(groups.cap, S), d, I);
+  int64_t n = 0;
+  for (int64_t left = S; left > 0; ++n) {
+    int in_dx = 0;
+    const int64_t rows = groups.next(left, &in_dx);
+    const DxKind dx = choose_dx(rows, d, I, left < S, dw);
+    left -= rows;
+    if (n >= room) continue;
+    const int64_t values[6] = {rows, in_dx, dx_tile(dx), dx_tile_rows(dx), fuse_da(rows, d, I), dw_tile(dw)};
+    std::copy(values, values + 6, info + 6 * n);
+  }
+  return n;
+}
+
+int32_t mst_mlp_line_panels(int64_t rows, int64_t d, int64_t I) {
+  Plan p;
+  if (make_plan(rows, d, I, 1, &p) != MST_OK) return -1;
+  auto lone = [&](TileChoice c, int64_t N, int64_t K) { return c.kind == k64Lone && by_lines((int64_t)tiles_of(N - c.head, rows, 64), K, nullptr, nullptr); };
+  const DwChoice dw = dw_choice(rows, d, I);
+  const DxKind dx = choose_dx(rows, d, I, false, dw);
+  const int n_d = (int)((d + 63) / 64), n_i = (int)((I + 63) / 64), n_s = (int)((rows + 63) / 64);
+  const int64_t shared = even_grid(n_d, n_s) + 2 * even_grid(n_i, n_d) + even_grid(n_d, n_i);
+  return (lone(nt_tile(rows, d, I), d, I) ? MST_MLP_LINES_DOWN : 0) |
+         (!fuse_da(rows, d, I) && lone(nn_tile(rows, I, d, 1), I, d) ? MST_MLP_LINES_DA : 0) |
+         ((dx == kDxOwn ? lone(nn_tile(rows, d, I, 2), d, I) : dx == kDx64 && by_lines(shared, I, nullptr, nullptr)) ? MST_MLP_LINES_DX : 0);
 }
 
 int32_t mst_mlp_da_in_gateup(int64_t rows, int64_t d, int64_t I) {

@@ -52,6 +52,12 @@ def load_mlp_library() -> ctypes.CDLL:
     lib.mst_mlp_dx_tile.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
     lib.mst_mlp_dx_tile_rows.restype = c.c_int32
     lib.mst_mlp_dx_tile_rows.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32]
+    lib.mst_mlp_fwd_groups.restype = c.c_int64
+    lib.mst_mlp_fwd_groups.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.c_size_t, c.c_int32, c.c_int64, c.POINTER(c.c_int64)]
+    lib.mst_mlp_bwd_groups.restype = c.c_int64
+    lib.mst_mlp_bwd_groups.argtypes = [c.c_int64, c.c_int64, c.c_int64, c.c_int32, c.c_int32, c.c_int64, c.POINTER(c.c_int64)]
+    lib.mst_mlp_line_panels.restype = c.c_int32
+    lib.mst_mlp_line_panels.argtypes = [c.c_int64, c.c_int64, c.c_int64]
     lib.mst_mlp_da_in_gateup.restype = c.c_int32
     lib.mst_mlp_da_in_gateup.argtypes = [c.c_int64, c.c_int64, c.c_int64]
     lib.mst_mlp_tile_grid.restype = c.c_int32
@@ -117,7 +123,7 @@ MLP_TILES = ("256", "128", "128_lone", "64", "64_lone", "64_long", "32", "128x25
 
 
 def mst_mlp_tile_info(rows: int, d: int, I: int) -> dict:
-    """What a chunk of `rows` rows runs with: per product (tile, leading columns that large tiles take in a launch of their
+    """What a group of `rows` rows runs with: per product (tile, leading columns that large tiles take in a launch of their
     own, large tiles in super-tiles), and for the weight gradients (tile, dealt out evenly)."""
     a = (ctypes.c_int64 * 14)()
     _check(load_mlp_library().mst_mlp_tile_info(rows, d, I, a))
@@ -131,7 +137,7 @@ MLP_DX_TILES = ("own", "256", "128", "64", "32")     # MST_MLP_DX_*
 
 
 def mst_mlp_dx_tile(rows: int, d: int, I: int, first: bool) -> str:
-    """How dX of a chunk is computed: in a launch of its own, or by that of the weight gradients with this tile."""
+    """How dX of a group of rows is computed: in a launch of its own, or by that of the weight gradients with this tile."""
     return MLP_DX_TILES[load_mlp_library().mst_mlp_dx_tile(rows, d, I, int(first))]
 
 
@@ -141,8 +147,40 @@ def mst_mlp_dx_tile_rows(rows: int, d: int, I: int, first: bool) -> int:
 
 
 def mst_mlp_da_in_gateup(rows: int, d: int, I: int) -> bool:
-    """Whether dA of a chunk is computed by the launch of gate/up's backward."""
+    """Whether dA of a group of rows is computed by the launch of gate/up's backward."""
     return load_mlp_library().mst_mlp_da_in_gateup(rows, d, I) == 1
+
+
+def mst_mlp_fwd_groups(S: int, d: int, I: int, M: int, workspace_bytes=None, output_overlaps: bool = False) -> list:
+    """The groups of rows a forward call takes, as (rows, A in the rows of O behind the group).  workspace_bytes: of the
+    workspace handed in (default: as many as the call needs)."""
+    if workspace_bytes is None:
+        workspace_bytes = mst_mlp_workspace_bytes(S, d, I, M)[0]
+    lib = load_mlp_library()
+    n = lib.mst_mlp_fwd_groups(S, d, I, M, workspace_bytes, int(output_overlaps), 0, None)
+    a = (ctypes.c_int64 * (2 * max(n, 0)))()
+    lib.mst_mlp_fwd_groups(S, d, I, M, workspace_bytes, int(output_overlaps), max(n, 0), a)
+    return [(int(a[2 * i]), bool(a[2 * i + 1])) for i in range(n)]
+
+
+def mst_mlp_bwd_groups(S: int, d: int, I: int, M: int, dx_overlaps: bool = False) -> list:
+    """The groups of rows a backward call takes, each as a dict: its rows, how many of dG, dU and A are in dX, how dX is computed
+    and the rows of its tile, whether dA is by the launch of gate/up's backward, the tile of the weight gradients."""
+    lib = load_mlp_library()
+    n = lib.mst_mlp_bwd_groups(S, d, I, M, int(dx_overlaps), 0, None)
+    a = (ctypes.c_int64 * (6 * max(n, 0)))()
+    lib.mst_mlp_bwd_groups(S, d, I, M, int(dx_overlaps), max(n, 0), a)
+    return [{"rows": int(r[0]), "in_dx": int(r[1]), "dx": MLP_DX_TILES[r[2]], "dx_tile_rows": int(r[3]), "da_in_gateup": bool(r[4]),
+             "dw": MLP_TILES[r[5]]} for r in (a[6 * i:6 * i + 6] for i in range(n))]
+
+
+MLP_LINES = ("down", "da", "dx")     # MST_MLP_LINES_*
+
+
+def mst_mlp_line_panels(rows: int, d: int, I: int) -> set:
+    """The products that load rows which are not whole cache lines line by line."""
+    mask = load_mlp_library().mst_mlp_line_panels(rows, d, I)
+    return {name for i, name in enumerate(MLP_LINES) if mask >> i & 1}
 
 
 def mst_mlp_profile_enable(every) -> None:

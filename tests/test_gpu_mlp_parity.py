@@ -174,9 +174,9 @@ TILE_SHAPES = [
     (1700, 1032, 9800, (1, 2)),
     # the same for down and dX
     (1700, 9480, 1032, (1, 2)),
-    # long contractions on few tiles (K steps of 128 in down and dX, the last one ragged), one chunk of 65 rows
+    # long contractions on few tiles (K steps of 128 in down and dX, the last one ragged), chunks of 65 rows
     (195, 520, 4360, (1, 3)),
-    # chunks of 129 and 65 rows: one row past a tile of the smaller ones
+    # chunks of 129 rows, forward groups of 257 and 65: one row past a tile of the smaller ones
     (387, 2056, 1032, (3, 6)),
     # down and dX: lone 128 x 128 unsplit; weight gradients of lone 64 x 64 tiles over three chunks
     (7709, 488, 328, (1, 3)),
@@ -202,8 +202,8 @@ TILE_SHAPES = [
 
 @pytest.mark.parametrize("S,d,I,Ms", TILE_SHAPES)
 def test_every_block_tile_matches_oracle_and_gives_the_same_bits(S, d, I, Ms):
-    """Which block tile a launch takes depends on the rows of a chunk; a token's O and dX must not.  The weight gradients
-    of every chunking (their sums are formed chunk by chunk) against the oracle."""
+    """Which block tile a launch takes depends on the rows of a group; a token's O and dX must not.  The weight gradients
+    of every chunking (their sums are formed group by group) against the oracle."""
     inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, Ms[0], index=320 + S % 7, w_std=0.05))
     _, base, ref, _ = _check(inp, M=Ms[0])
     for M in Ms[1:]:
@@ -214,7 +214,7 @@ def test_every_block_tile_matches_oracle_and_gives_the_same_bits(S, d, I, Ms):
             assert np.abs(got[k] - ref[k]).max() <= TOL * np.abs(ref[k]).max(), (k, M)
 
 
-# (S, d, I, {M: how dX of each chunk is computed}): in a launch of its own, or by that of the weight gradients with 256 x 256
+# (S, d, I, {M: how dX of each group of rows is computed}): in a launch of its own, or by that of the weight gradients with 256 x 256
 # or 128 x 256 tiles (its own dealt out evenly or in rectangles)
 DX_SHAPES = [
     (797, 2080, 1008, {1: ["128"], 2: ["128", "128"], 3: ["64"] * 3}),
@@ -234,9 +234,7 @@ def test_dx_beside_the_weight_gradients_matches_oracle_and_keeps_its_bits(S, d, 
     inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=330 + S % 7, w_std=0.05))
     base = None
     for M, want in kinds.items():
-        C = -(-S // M)
-        rows = [min(C, S - i * C) for i in range(M)]
-        assert [mst.mst_mlp_dx_tile(r, d, I, i == 0) for i, r in enumerate(rows)] == want
+        assert [g["dx"] for g in mst.mst_mlp_bwd_groups(S, d, I, M)] == want
         _, got, _, _ = _check(inp, M=M)
         base = got["dX"] if base is None else base
         assert np.array_equal(got["dX"], base), M      # a token's dX does not depend on who computed it
@@ -251,17 +249,15 @@ def test_dx_in_128_by_128_tiles_beside_the_weight_gradients(S, d, I, kinds):
     import paper_2407_15892_amd as mst
     inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=370 + S % 7, w_std=0.05))
     base = None
-    for M, want in list(kinds.items()) + [(max(2, S // 60), None)]:      # the last in chunks of up to 64 rows, launches of their own
-        C = -(-S // M)
-        rows = [min(C, S - i * C) for i in range(-(-S // C))]
-        got_rows = [mst.mst_mlp_dx_tile_rows(r, d, I, i == 0) for i, r in enumerate(rows)]
+    for M, want in list(kinds.items()) + [(max(2, S // 60), None)]:      # the last in groups of up to 140 rows, launches of their own
+        got_rows = [g["dx_tile_rows"] for g in mst.mst_mlp_bwd_groups(S, d, I, M)]
         assert got_rows == want if want else 128 not in got_rows, (M, got_rows)
         _, got, _, _ = _check(inp, M=M)
         base = got["dX"] if base is None else base
         assert np.array_equal(got["dX"], base), M
 
 
-# (S, d, I, {M: (how dX of every chunk is computed, dA in the launch of gate/up's backward)}): the launches of small problems,
+# (S, d, I, {M: (how dX of every group of rows is computed, dA in the launch of gate/up's backward)}): the launches of small problems,
 # and 32 x 32 tiles in every product that takes them
 SMALL_SHAPES = [
     (65, 264, 904, {1: ("32", True), 2: ("32", True)}),       # last tiles of one row, of 8 columns
@@ -284,10 +280,8 @@ def test_launches_of_small_problems_match_oracle_and_keep_their_bits(S, d, I, ki
     inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=340 + S % 7, w_std=0.05))
     base = None
     for M, (dx, da) in kinds.items():
-        C = -(-S // M)
-        rows = [min(C, S - i * C) for i in range(M)]
-        assert {mst.mst_mlp_dx_tile(r, d, I, i == 0) for i, r in enumerate(rows)} == {dx}
-        assert {mst.mst_mlp_da_in_gateup(r, d, I) for r in rows} == {da}
+        groups = mst.mst_mlp_bwd_groups(S, d, I, M)
+        assert {g["dx"] for g in groups} == {dx} and {g["da_in_gateup"] for g in groups} == {da}
         _, got, _, _ = _check(inp, M=M)
         base = got if base is None else base
         for k in ("O", "dX"):
@@ -312,8 +306,9 @@ def test_launches_of_small_problems_match_oracle_and_keep_their_bits(S, d, I, ki
 ])
 def test_tiles_of_128_by_256_match_oracle_and_keep_their_bits(S, d, I, products, M):
     import paper_2407_15892_amd as mst
-    whole, split = mst.mst_mlp_tile_info(S, d, I), mst.mst_mlp_tile_info(-(-S // M), d, I)
-    assert all(whole[p][0] == "128x256" != split[p][0] for p in products)
+    whole = mst.mst_mlp_tile_info(S, d, I)
+    for rows, _ in mst.mst_mlp_fwd_groups(S, d, I, M):
+        assert all(whole[p][0] == "128x256" != mst.mst_mlp_tile_info(rows, d, I)[p][0] for p in products)
     inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=350 + S % 7, w_std=0.05))
     _, base, _, _ = _check(inp, M=1)
     _, got, _ = _run_all(inp, M=M)
@@ -436,11 +431,12 @@ def test_dx_that_overlaps_rows_already_read_is_formed_chunk_by_chunk(of):
 ])
 def test_down_of_rows_that_are_not_whole_lines_keeps_its_bits(S, d, I, M):
     """Down in lone 64 x 64 tiles, more of them than compute units: the same bits as chunk by chunk, where fewer tiles load the
-    same k of all rows, wherever A begins (in the workspace, or anywhere in rows of O)."""
+    same k of all rows."""
     import torch
     import paper_2407_15892_amd as mst
     MlpDeviceRun, f64 = _harness()
-    assert mst.mst_mlp_tile_info(S, d, I)["down"][:2] == ("64_lone", 0) and -(-S // 64) * -(-d // 64) > 256
+    assert "down" in mst.mst_mlp_line_panels(S, d, I)
+    assert all("down" not in mst.mst_mlp_line_panels(rows, d, I) for rows, _ in mst.mst_mlp_fwd_groups(S, d, I, M))
     inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=390 + S % 7, w_std=0.05))
     run = MlpDeviceRun(inp, M=1)
     whole = f64(run.forward())
@@ -454,3 +450,109 @@ def test_down_of_rows_that_are_not_whole_lines_keeps_its_bits(S, d, I, M):
         mst.mst_mlp_fwd(run.X[r0:r0 + n], run.Wg, run.Wu, run.Wd, 1, ws, O[:n])
         torch.cuda.synchronize()
         assert np.array_equal(f64(O[:n]), whole[r0:r0 + n]), r0
+
+
+def _offset(t, elements):
+    """A copy of t that begins `elements` elements behind a line."""
+    import torch
+    buf = torch.empty(t.numel() + 64 + elements, dtype=t.dtype, device="cuda")
+    first = -buf.data_ptr() // t.element_size() % (128 // t.element_size()) + elements
+    out = buf[first:first + t.numel()].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+@pytest.mark.parametrize("S,d,I,M,elements", [
+    (3023, 584, 496, 19, 0),       # the first groups' A in rows of O, 48 bytes behind a line
+    (1537, 712, 2312, 1, 8),       # weights 16 bytes behind a line, A on one
+    (1152, 1024, 1088, 1, 56),     # rows that are whole lines, all beginning 112 bytes behind one
+])
+def test_down_by_lines_wherever_its_operands_begin(S, d, I, M, elements):
+    """Line panels of operands that do not begin on a line: the same bits as where they do, or as where fewer tiles load the
+    same k of all rows."""
+    import torch
+    import paper_2407_15892_amd as mst
+    MlpDeviceRun, f64 = _harness()
+    if M > 1:
+        rows, in_output = mst.mst_mlp_fwd_groups(S, d, I, M)[0]
+        assert in_output and 2 * (S * d - rows * I) % 128 == 48 and "down" in mst.mst_mlp_line_panels(rows, d, I)
+    else:
+        assert mst.mst_mlp_tile_info(S, d, I)["down"][:2] == ("64_lone", 0) and -(-S // 64) * -(-d // 64) > 256
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=400 + S % 7, w_std=0.05))
+    run = MlpDeviceRun(inp)
+    ref = _reference(inp)["O"]
+    O = _offset(torch.full((S, d), float("nan"), dtype=torch.bfloat16, device="cuda"), 0)
+    ws = run._ws(run.fwd_bytes)
+    run.mst.mst_mlp_fwd(run.X, run.Wg, run.Wu, _offset(run.Wd, elements), M, ws, O)
+    torch.cuda.synchronize()
+    got = f64(O)
+    assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
+    part = torch.empty((500, d), dtype=torch.bfloat16, device="cuda")
+    assert "down" not in mst.mst_mlp_line_panels(500, d, I)
+    ws = torch.empty(mst.mst_mlp_workspace_bytes(500, d, I, 1)[0], dtype=torch.uint8, device="cuda")
+    for r0 in range(0, S, 500):
+        n = min(500, S - r0)
+        mst.mst_mlp_fwd(run.X[r0:r0 + n], run.Wg, run.Wu, run.Wd, 1, ws, part[:n])
+        torch.cuda.synchronize()
+        assert np.array_equal(f64(part[:n]), got[r0:r0 + n]), r0
+
+
+@pytest.mark.parametrize("S,d,I,product,dx", [
+    (515, 264, 1808, "da", "32"),          # rows of dO of 528 bytes; a last row tile of three
+    (648, 1512, 1384, "dx", "own"),        # both terms, each with a stage behind its last; rows of 2768 bytes
+    (793, 1336, 3368, "dx", "own"),
+    (668, 400, 520, "dx", "64"),           # beside the weight gradients
+])
+def test_gradients_by_lines_keep_their_bits(S, d, I, product, dx):
+    """dA and dX in lone 64 x 64 tiles whose token rows are loaded line by line: dX has the bits of the same rows in calls that
+    are too short for that."""
+    import torch
+    import paper_2407_15892_amd as mst
+    MlpDeviceRun, f64 = _harness()
+    assert product in mst.mst_mlp_line_panels(S, d, I) and mst.mst_mlp_dx_tile(S, d, I, True) == dx
+    inp = mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, 1, index=410 + S % 7, w_std=0.05))
+    run, got, _, _ = _check(inp)
+    ws = torch.empty(mst.mst_mlp_workspace_bytes(100, d, I, 1)[1], dtype=torch.uint8, device="cuda")
+    dX = torch.empty((100, d), dtype=torch.bfloat16, device="cuda")
+    dW = [torch.empty(shape, device="cuda") for shape in ((I, d), (I, d), (d, I))]
+    assert product not in mst.mst_mlp_line_panels(100, d, I)
+    for r0 in range(0, S, 100):
+        n = min(100, S - r0)
+        mst.mst_mlp_bwd(run.X[r0:r0 + n], run.Wg, run.Wu, run.Wd, run.dO[r0:r0 + n], 1, ws, dX[:n], *dW)
+        torch.cuda.synchronize()
+        assert np.array_equal(f64(dX[:n]), got["dX"][r0:r0 + n]), r0
+
+
+@pytest.mark.parametrize("S,d,I,M", [
+    (1500, 136, 264, 12),      # A in O, one or two of dG, dU and A in dX, small tiles
+    (1929, 1032, 2584, 2),     # dX in 128 x 128 tiles
+    (3023, 584, 496, 19),      # rows of A line by line
+])
+def test_forward_and_backward_replay_from_a_hip_graph(S, d, I, M):
+    """Nothing but kernels is enqueued: every replay, with eager work and synchronisation in between, gives the eager bits,
+    also where intermediates are kept in rows of O and dX."""
+    import torch
+    MlpDeviceRun, _ = _harness()
+    run = MlpDeviceRun(mi.make_mlp_inputs(mi.custom_mlp_config(S, d, I, M, index=420 + S % 7, w_std=0.05)))
+    eager = [run.forward().clone()] + [t.clone() for t in run.backward()]
+    out = [torch.empty_like(t) for t in eager]
+    ws = run._ws(run.bwd_bytes)
+
+    def step():
+        run.mst.mst_mlp_fwd(run.X, run.Wg, run.Wu, run.Wd, M, ws, out[0])
+        run.mst.mst_mlp_bwd(run.X, run.Wg, run.Wu, run.Wd, run.dO, M, ws, *out[1:])
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for _ in range(3):
+        for t in out:
+            t.fill_(float("nan"))
+        ws.fill_(0xA5)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, eager):
+            bits = torch.int16 if a.dtype == torch.bfloat16 else torch.int32
+            assert torch.equal(a.view(bits), b.view(bits))
+    del graph

@@ -557,17 +557,20 @@ def test_pair_order_with_every_tile_size_matches_oracle(schedule, S, d, V, M):
 
 @pytest.mark.parametrize("S,d,V,M,row_blocks,windows,split", [
     (495, 112, 63400, 7, 1, 5, 8),      # the most splits, five windows; ragged rows, columns and last window
-    (835, 368, 18219, 1, 1, 1, 8),      # splits of one window: stored, then added by the reduce
+    (490, 608, 13770, 1, 1, 1, 8),      # splits of one window: stored, then added by the reduce
     (2295, 528, 22619, 7, 3, 2, 4),     # three row blocks: dW read back, last column tile of 16
     (5772, 712, 3700, 3, 2, 1, 1),      # one window, no split: dH straight to bf16
     (1165, 296, 12987, 1, 1, 1, 8),     # 51 x 5 dlogits tiles, dealt out evenly to save a round
-    (764, 384, 16575, 1, 1, 1, 8),      # 8 x 3 x 2 dH and 65 x 2 dW tiles, dealt out evenly for their sum
+    (644, 600, 20683, 1, 1, 1, 8),      # 81 x 3 of them; 8 x 3 x 3 dH and 81 x 3 dW tiles, dealt out evenly for their sum
+    (730, 728, 7883, 1, 1, 1, 4),
+    (1257, 952, 5943, 1, 1, 1, 2),
 ])
 def test_automatic_block_shapes_with_split_dh_match_oracle(S, d, V, M, row_blocks, windows, split):
     """The block shapes that only the automatic choice takes (dH's contraction split, every split with running sums of
     its own; one window), against the oracle, bit-identical across calls and within the declared workspace."""
     import torch
     import paper_2407_15892_amd as mst
+    assert mst.mst_bwd_streamed(S, d, V, M) == ("no", 0)
     info = mst.mst_bwd_schedule_info(S, d, V, M)
     assert (info["schedule"], info["row_blocks"], info["windows"], info["dh_split"]) == \
         (mst.BWD_SCHEDULE_BLOCKS_FUSED, row_blocks, windows, split), info
@@ -622,7 +625,8 @@ def test_joint_launches_of_the_pair_order_match_oracle(schedule, S, d, V, M, lau
 ])
 def test_pair_order_with_dh_in_128_by_128_tiles_matches_oracle(schedule, S, d, V, M):
     """dlogits of a pair from one launch, dH over the whole vocabulary beside large tiles of dW: against the oracle, the same
-    bits call after call and from the automatic order, within the declared workspace."""
+    bits call after call and from the automatic order, within the declared workspace; a label outside the vocabulary; all
+    rows ignored."""
     import torch
     import paper_2407_15892_amd as mst
     schedule(mst.BWD_SCHEDULE_PAIRS)
@@ -637,18 +641,31 @@ def test_pair_order_with_dh_in_128_by_128_tiles_matches_oracle(schedule, S, d, V
     assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
     assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))
     assert bool((run.last_ws[-4096:] == 0xA5).all()), "wrote past the declared workspace"
+    inp.labels[S // 2] = V
+    run.labels = torch.from_numpy(inp.labels).cuda()
+    run.forward()
+    for t in run.backward(poison="zero"):
+        assert torch.isnan(t.float()).all()
+    inp.labels[:] = inp.ignore_index
+    run.labels = torch.from_numpy(inp.labels).cuda()
+    run.forward()
+    for t in run.backward():
+        assert float(t.float().abs().max()) == 0.0
 
 
 @pytest.mark.parametrize("S,d,V,M", [
     (975, 1176, 4099, 3),      # 64 x 64 tiles in dlogits, dH and dW, whose second pass (one chunk) adds
-    (712, 1920, 6637, 2),      # in dlogits and dH only
+    (205, 1096, 6065, 2),      # in dlogits and dH only, launches of their own
+    (712, 1920, 6637, 2),      # in dlogits; dH in 128 x 128 tiles beside dW
 ])
 def test_automatic_order_that_goes_back_to_pairs_matches_oracle(S, d, V, M):
     """Shapes for which the automatic choice drops a block shape for the pair order: its gradients against the oracle, and
     the same bits as the pair order asked for."""
     import torch
     import paper_2407_15892_amd as mst
-    assert mst.mst_bwd_schedule_info(S, d, V, M)["schedule"] == mst.BWD_SCHEDULE_PAIRS
+    info = mst.mst_bwd_schedule_info(S, d, V, M)
+    assert info["schedule"] == mst.BWD_SCHEDULE_PAIRS and info["est_blocks_us"] > 0 and mst.mst_bwd_streamed(S, d, V, M) == ("no", 0)
+    assert mst.mst_pair_launches(S, d, V, M) == {975: "64x32", 205: "separate", 712: "128x128"}[S]
     inp = mi.make_inputs(mi.custom_config(S, d, V, M, index=460 + S % 97, w_std=0.3, ignore_frac=0.1, label_dist="zipf"))
     run, _, _ = _check_full(inp, grad_loss=0.8)
     first = (run.dH_t.clone(), run.dW_t.clone())
@@ -814,6 +831,37 @@ def test_forward_and_backward_replay_from_a_hip_graph(schedule):
         del graph
 
 
+@pytest.mark.parametrize("S,d,V,M,path", [
+    (1024, 256, 6000, 4, "256_split"),       # streamed
+    (1398, 200, 7156, 3, "256_narrow"),      # with splits and their sum
+    (705, 1544, 4099, 3, "128x128"),         # dH and dW of a pair
+])
+def test_the_automatic_order_replays_from_a_hip_graph(S, d, V, M, path):
+    """The same for launches that only the automatic order has, or has by itself."""
+    import torch
+    import paper_2407_15892_amd as mst
+    DeviceRun, _ = _harness()
+    assert path in (mst.mst_bwd_streamed(S, d, V, M)[0], mst.mst_pair_launches(S, d, V, M))
+    run = DeviceRun(mi.make_inputs(mi.custom_config(S, d, V, M, index=432, w_std=0.3, ignore_frac=0.05)))
+    run.forward()
+    eager = [t.clone() for t in run.backward()]
+    out = [torch.empty_like(t) for t in eager]
+    ws = run._ws(run.bwd_bytes)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mst.mst_lmhead_ce_bwd(run.H, run.W, run.labels, run.inp.ignore_index, M, 1.0, run.lse, run.nv, ws, *out)
+    for _ in range(3):
+        for t in out:
+            t.fill_(float("nan"))
+        ws.fill_(0xA5)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0].view(torch.int16), eager[0].view(torch.int16))
+        assert torch.equal(out[1].view(torch.int32), eager[1].view(torch.int32))
+    del graph
+
+
 def test_two_callers_on_two_streams_do_not_disturb_each_other():
     """Two unrelated problems, each with its own buffers and workspace, enqueued alternately on two side streams of the
     default priority with no synchronisation between them: every output of both equals, bit for bit, what the same
@@ -905,6 +953,8 @@ def test_kernel_timing_covers_every_nth_launch_of_each_kind():
     (11, 136, 165, 3, "256_split", 1),
     (512, 256, 4096, 4, "256_split", 4),
     (749, 360, 7413, 2, "384", 10),
+    (835, 368, 18219, 1, "384", 16),
+    (764, 384, 16575, 1, "384", 20),
     (10, 280, 33, 4, "384", 1),
     (1446, 360, 3961, 7, "384_split", 1),
     (5, 264, 2722, 5, "384_split", 2),
@@ -944,23 +994,3 @@ def test_backward_without_stored_dlogits_matches_oracle(S, d, V, M, form, splits
     run.forward()
     for t in run.backward():
         assert float(t.float().abs().max()) == 0.0
-
-
-@pytest.mark.parametrize("S,d,V,split", [
-    (490, 608, 13770, 8),
-    (644, 600, 20683, 8),      # 81 x 3 dlogits tiles, dealt out evenly to save a round
-    (730, 728, 7883, 4),
-    (1257, 952, 5943, 2),
-])
-def test_splits_of_one_window_match_oracle_at_larger_hidden_sizes(S, d, V, split):
-    """The same block shapes as above, for hidden sizes that keep their dlogits in memory."""
-    import torch
-    import paper_2407_15892_amd as mst
-    info = mst.mst_bwd_schedule_info(S, d, V, 1)
-    assert (info["schedule"], info["row_blocks"], info["windows"], info["dh_split"]) == (mst.BWD_SCHEDULE_BLOCKS_FUSED, 1, 1, split), info
-    assert mst.mst_bwd_streamed(S, d, V, 1) == ("no", 0)
-    run, _, _ = _check_full(mi.make_inputs(mi.custom_config(S, d, V, 1, index=490, w_std=0.3, ignore_frac=0.1, label_dist="zipf")), grad_loss=0.8)
-    first = (run.dH_t.clone(), run.dW_t.clone())
-    run.backward(grad_loss=0.8)
-    assert torch.equal(run.dH_t.view(torch.int16), first[0].view(torch.int16))
-    assert torch.equal(run.dW_t.view(torch.int32), first[1].view(torch.int32))

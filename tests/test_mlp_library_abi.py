@@ -92,28 +92,69 @@ def test_null_workspace_and_alignment_errors_come_before_any_launch(mst):
 
 
 def test_tile_shapes_of_the_gpu_test_take_every_tile(mst):
-    """The library's own answer to which block tiles the shapes of the GPU test run with: every tile of every product alone,
-    large tiles in both maps, every smaller tile (the rare one with K steps of 128 aside) behind full rounds of large
-    ones, and every tile of the weight gradients in a first and in a later chunk."""
-    from tests.test_gpu_mlp_parity import TILE_SHAPES
+    """The library's own answer to which block tiles the shapes of the GPU tests run with, group of rows by group of rows:
+    every tile of every product alone, large tiles in both maps, every smaller tile (the rare one with K steps of 128 aside)
+    behind full rounds of large ones, and every tile of the weight gradients in a first and in a later group."""
+    from tests.test_gpu_mlp_parity import DX_SHAPES, TILE_SHAPES
     seen = set()
-    for S, d, I, Ms in TILE_SHAPES:
+    for S, d, I, Ms in TILE_SHAPES + [(S, d, I, tuple(kinds)) for S, d, I, kinds in DX_SHAPES]:
         for M in Ms:
-            C = -(-S // M)
-            n = -(-S // C)
-            for rows in {C, S - (n - 1) * C}:
-                info = mst.mst_mlp_tile_info(rows, d, I)
-                for product in ("gateup", "down", "da", "dx"):
-                    tile, head, super_tiles = info[product]
-                    assert 0 <= head < (I if product in ("gateup", "da") else d) and (head == 0 or tile != "256")
-                    seen.add((product, tile, super_tiles if tile == "256" else head > 0))
-            tile, even = mst.mst_mlp_tile_info(C, d, I)["dw"]
-            seen |= {("dw", tile, even, 0), ("dw", tile, even, min(n - 1, 1))}
+            forward, backward = mst.mst_mlp_fwd_groups(S, d, I, M), mst.mst_mlp_bwd_groups(S, d, I, M)
+            launches = [(product, rows) for rows, _ in forward for product in ("gateup", "down")]
+            for g in backward:
+                launches += [("gateup", g["rows"])] + [("da", g["rows"])] * (not g["da_in_gateup"]) + [("dx", g["rows"])] * (g["dx"] == "own")
+            for product, rows in launches:
+                tile, head, super_tiles = mst.mst_mlp_tile_info(rows, d, I)[product]
+                assert 0 <= head < (I if product in ("gateup", "da") else d) and (head == 0 or tile != "256")
+                seen.add((product, tile, super_tiles if tile == "256" else head > 0))
+            tile, even = mst.mst_mlp_tile_info(max(g["rows"] for g in backward), d, I)["dw"]
+            assert {g["dw"] for g in backward} == {tile}
+            seen |= {("dw", tile, even, min(i, 1)) for i in range(len(backward))}
     want = {("dw", t, e, c) for t, e in (("256", False), ("256", True), ("64", True), ("64_lone", True)) for c in (0, 1)}
     for product in ("gateup", "down", "da", "dx"):
         want |= {(product, "256", False), (product, "256", True), (product, "64_long", False)}
         want |= {(product, t, tail) for t in ("128", "128_lone", "64", "64_lone") for tail in (False, True)}
     assert want <= seen, sorted(want - seen)
+
+
+def test_groups_of_rows_fit_the_memory_they_are_kept_in(mst):
+    """Over random shapes: the groups make up the rows, what they keep fits into the workspace and into the rows behind them,
+    there are no more of them than chunks, and those of the backward are the chunks where dX is not free."""
+    import random
+    rng = random.Random(20240718)
+    seen = set()
+    for _ in range(4000):
+        S, d, I = round(2 ** rng.uniform(0, 14)), 8 * round(2 ** rng.uniform(0, 9)), 8 * round(2 ** rng.uniform(0, 10))
+        M = rng.randint(1, min(S, 80))
+        C = -(-S // M)
+        chunks = [min(C, S - r) for r in range(0, S, C)]
+        need, need_bwd = mst.mst_mlp_workspace_bytes(S, d, I, M)
+        for workspace, overlaps in ((need, False), (need, True), (need_bwd, False), (need + 256 * rng.randint(0, 2000), False)):
+            left = S
+            groups = mst.mst_mlp_fwd_groups(S, d, I, M, workspace, overlaps)
+            for rows, in_output in groups:
+                left -= rows
+                assert rows > 0 and rows * I < 2 ** 30 and rows * d < 2 ** 30
+                assert rows * I <= left * d if in_output else rows * I * 2 <= workspace
+                assert not (in_output and overlaps)
+                seen.add(("A", in_output))
+            assert left == 0 and len(groups) <= len(chunks)
+        left = S
+        groups = mst.mst_mlp_bwd_groups(S, d, I, M)
+        for g in groups:
+            rows, k = g["rows"], g["in_dx"]
+            left -= rows
+            assert rows > 0 and rows * I < 2 ** 30 and rows * d < 2 ** 30 and k * rows * I <= left * d
+            assert k == 3 or rows * I * 2 <= need_bwd // (3 - k) // 256 * 256
+            seen.add(("dX", k))
+        assert left == 0 and len(groups) <= len(chunks)
+        assert [g["rows"] for g in mst.mst_mlp_bwd_groups(S, d, I, M, dx_overlaps=True)] == chunks
+    assert seen == {("A", False), ("A", True)} | {("dX", k) for k in range(4)}
+    lib = mst.load_mlp_library()
+    assert lib.mst_mlp_fwd_groups(64, 16, 40, 2, 256, 0, 0, None) == -1      # less than one chunk of A
+    assert lib.mst_mlp_fwd_groups(64, 16, 40, 2, 1 << 20, 0, 1, None) == -1
+    assert lib.mst_mlp_bwd_groups(64, 16, 40, 65, 0, 0, None) == -1
+    assert lib.mst_mlp_line_panels(64, 12, 40) == -1
 
 
 def test_down_of_65_to_96_tokens_takes_32_by_32_tiles_only_for_short_contractions(mst):
