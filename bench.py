@@ -37,6 +37,25 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E, published
 # executed flop per step of each GEMM kernel kind, in units of S*d*V (a kind with no launches in a run is skipped)
 GEMM_KINDS = {"fwd_gemm_lse": 2.0, "bwd_gemm_dlogits": 2.0, "bwd_gemm_dh": 2.0, "bwd_gemm_dw": 2.0, "bwd_gemm_dh_dw": 4.0}
 
+
+def gemm_kinds(schedule: str) -> dict:
+    """GEMM_KINDS of a backward order.  The streamed backward has one launch, of the kind bwd_gemm_dlogits: the logits twice,
+    for dH and for dW, and both gradients."""
+    return dict(GEMM_KINDS, bwd_gemm_dlogits=8.0) if schedule == "streamed" else GEMM_KINDS
+
+
+def backward_schedule(mst, S: int, d: int, V: int, M: int, order: str = "auto") -> dict:
+    """What a backward call under this order (a choice of --bwd-schedule) runs: its name, its blocks and splits."""
+    names = {mst.BWD_SCHEDULE_PAIRS: "pairs", mst.BWD_SCHEDULE_BLOCKS: "blocks", mst.BWD_SCHEDULE_BLOCKS_FUSED: "blocks_fused"}
+    if order == "auto":
+        form, splits = mst.mst_bwd_streamed(S, d, V, M)
+        if form != "no":
+            return {"schedule": "streamed", "form": form, "dh_split": splits}
+    forced = {"auto": mst.BWD_SCHEDULE_AUTO, **{name: value for value, name in names.items()}}[order]
+    sched = mst.mst_bwd_schedule_info(S, d, V, M, schedule=forced)
+    return dict(sched, schedule=names[sched["schedule"]])
+
+
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pmc_traffic_per_launch.txt")
 
 
@@ -133,13 +152,16 @@ MLP_KINDS = ("gateup", "down", "da", "gateup_bwd", "dx", "dw")
 MLP_FLOP_UNITS = {"gateup": 4.0, "down": 2.0, "da": 2.0, "gateup_bwd": 4.0, "dx": 4.0, "dw": 6.0}
 
 
-def mlp_flop_units(issued):
-    """MLP_FLOP_UNITS by the launches that did the work, from the number of launches of every kind: the launch of gate/up's
-    backward computes dA, that of the weight gradients dX, of every chunk for which these have none of their own (chunks
-    of one length; "dw" has one launch per chunk)."""
+def mlp_flop_units(issued, groups=None):
+    """MLP_FLOP_UNITS by the launches that did the work: the launch of gate/up's backward computes dA, that of the weight
+    gradients dX, of every group of rows for which these have no launch of their own.  groups: the call's, as the library
+    names them; without them, from the number of launches of every kind, as of groups of one length ("dw" has one launch
+    per group)."""
     units = dict(MLP_FLOP_UNITS)
+    rows = sum(g["rows"] for g in groups) if groups else 0
+    apart = {"da": lambda g: not g["da_in_gateup"], "dx": lambda g: g["dx"] == "own"}
     for kind, host in (("da", "gateup_bwd"), ("dx", "dw")):
-        own = issued[kind] / issued["dw"]
+        own = sum(g["rows"] for g in groups if apart[kind](g)) / rows if groups else issued[kind] / issued["dw"]
         units[host] += (1.0 - own) * units[kind]
         units[kind] *= own
     return units
@@ -229,7 +251,7 @@ def main_mlp(args) -> int:
     tflops = f_exec / (ms_per_step * 1e-3) / 1e12
     roofline, kernels = None, {}
     if kern:
-        units = mlp_flop_units({k: issued for k, (_, _, issued) in kern.items()})
+        units = mlp_flop_units({k: issued for k, (_, _, issued) in kern.items()}, mst.mst_mlp_bwd_groups(S, d, I, M))
         for k, (ms, n, issued) in kern.items():
             if n:
                 fl = units[k] * S * d * I / (issued / args.steps)
@@ -325,9 +347,8 @@ def main() -> int:
         cfg = dataclasses.replace(cfg, S=args.rows or cfg.S, M=args.m or cfg.M,
                                   name=cfg.name + "-variant" + (f"-S{args.rows}" if args.rows else "") +
                                   (f"-M{args.m}" if args.m else ""))
-    sched = mst.mst_bwd_schedule_info(cfg.S, cfg.d, cfg.V, cfg.M)
-    sched["schedule"] = {mst.BWD_SCHEDULE_PAIRS: "pairs", mst.BWD_SCHEDULE_BLOCKS: "blocks",
-                         mst.BWD_SCHEDULE_BLOCKS_FUSED: "blocks_fused"}[sched["schedule"]]
+    sched = backward_schedule(mst, cfg.S, cfg.d, cfg.V, cfg.M, args.bwd_schedule)
+    units = gemm_kinds(sched["schedule"])
     t0 = time.perf_counter()
     inp = mi.make_inputs(cfg)
     gen_s = time.perf_counter() - t0
@@ -391,7 +412,7 @@ def main() -> int:
     per_step = sorted(marks[i].elapsed_time(marks[i + 1]) for i in range(args.steps))
 
     ms_per_step = dt * 1e3 / args.steps
-    f_exec = 8.0 * S * d * V                      # fwd GEMM + recompute + dH + dW
+    f_exec = 8.0 * S * d * V                      # fwd GEMM + recompute + dH + dW; what streaming computes twice is not counted
     tflops = f_exec / (ms_per_step * 1e-3) / 1e12
 
     # roofline of the dominant kernel (largest share of the timed region)
@@ -402,10 +423,10 @@ def main() -> int:
             if n:
                 kernels[k] = {"launches": issued, "timed_launches": n, "avg_ms": ms / n,
                               "total_ms_per_step": ms / n * issued / args.steps}
-        # a GEMM kind executes GEMM_KINDS[kind] * S*d*V flop per step in total, split over its launches of that step
+        # a GEMM kind executes units[kind] * S*d*V flop per step in total, split over its launches of that step
         def flop_per_launch(kind):
-            return GEMM_KINDS[kind] * S * d * V / (kern[kind][2] / args.steps)
-        dom = max(GEMM_KINDS, key=lambda k: kernels.get(k, {}).get("total_ms_per_step", 0.0))
+            return units[kind] * S * d * V / (kern[kind][2] / args.steps)
+        dom = max(units, key=lambda k: kernels.get(k, {}).get("total_ms_per_step", 0.0))
         ms, n, issued = kern[dom]
         achieved = flop_per_launch(dom) / (ms / n * 1e-3) / 1e12
         traffic = None if (args.m or args.rows) else pmc_traffic_bytes("lmhead", args.config, sched["schedule"], dom)
@@ -422,7 +443,7 @@ def main() -> int:
             roofline["hbm_side"] = {"algorithmic_bytes_per_launch": alg_bytes,
                                     "achieved_GBs": alg_bytes / (ms / n * 1e-3) / 1e9, "peak_GBs": PEAK_HBM_GBS,
                                     "frac": alg_bytes / (ms / n * 1e-3) / 1e9 / PEAK_HBM_GBS}
-        for k in GEMM_KINDS:
+        for k in units:
             ms_k, n_k, _ = kern.get(k, (0.0, 0, 0))
             if n_k:
                 kernels[k]["tflops"] = flop_per_launch(k) / (ms_k / n_k * 1e-3) / 1e12
@@ -449,6 +470,7 @@ def main() -> int:
         "fwd_ms": fwd_ms, "bwd_ms": bwd_ms,
         "peak_workspace_bytes": {"fwd": fwd_bytes, "bwd": bwd_bytes, "cap_one_fp32_logits_chunk": cfg.C * V * 4},
         "loss": float(loss.item()), "n_valid": int(nv.item()), "bwd_schedule": sched,
+        "computed_flop_units_of_SdV": 10.0 if sched["schedule"] == "streamed" else 8.0,
         "roofline": roofline, "kernels": kernels, "input_generation_s": gen_s,
     }
     out["empirical_mfma_peak"] = mfma_probe(mst, torch)

@@ -210,9 +210,9 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
                              void* stream);
 
 /*
- * Order of the backward pass (Algorithm 4).  Both orders recompute every logit once, keep at most the
- * bytes mst_workspace_bytes reports (one mini-sequence of fp32 logits, (S/M) * V * 4) and give the same
- * dH and dW up to fp32 summation order; each is deterministic.
+ * Order of the backward pass (Algorithm 4).  Both orders recompute every logit once (streaming, see
+ * mst_bwd_streamed, twice), keep at most the bytes mst_workspace_bytes reports (one mini-sequence of fp32
+ * logits, (S/M) * V * 4) and give the same dH and dW up to fp32 summation order; each is deterministic.
  *   MST_BWD_SCHEDULE_PAIRS   the loop over mini-sequences as printed, two per dW pass: the block of dlogits
  *                            alive at a time is 2 * ceil(S/M) rows by all of V; dW is read and rewritten
  *                            once per pair.
@@ -222,13 +222,12 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
  *   MST_BWD_SCHEDULE_BLOCKS_FUSED  the block order with the dH and the dW GEMM of each (row block, window)
  *                            in one launch: their tile spaces then share one partly filled last round of
  *                            workgroups instead of leaving one each (same arithmetic as BLOCKS, bit for bit).
- *   MST_BWD_SCHEDULE_AUTO    (default) PAIRS or BLOCKS_FUSED, whichever a host-side cost model (rounds of
+ *   MST_BWD_SCHEDULE_AUTO    (default) PAIRS or BLOCKS_FUSED or, for small hidden sizes, neither (mst_bwd_streamed), whichever a host-side cost model (rounds of
  *                            workgroups plus fp32 gradient traffic) ranks faster for the shape.  Shapes with few
  *                            dH tiles are then ranked again with a finer model, which changes the order where another
  *                            one is clearly below it (blocks by 5 %, pairs by 20 %) and also looks at block shapes that
  *                            the forced orders do not take: a single window, and a window's dH contraction in up to 8
  *                            splits with running sums of their own, added in fixed order at the end.
- *                            Small hidden sizes may take neither (mst_bwd_streamed).
  * mst_set_bwd_schedule: host; the override belongs to the CALLING THREAD (thread-local, AUTO in every new
  * thread) and takes effect at that thread's next backward call, so one caller's setting never changes the
  * summation order of another thread's call; MST_ERR_BAD_SHAPE for an unknown value.
@@ -236,7 +235,8 @@ mst_status mst_lmhead_ce_bwd(const void* H, const void* W, const int32_t* labels
  * under the override `schedule`, rows per block, row blocks, vocabulary entries per window, windows, dH
  * split count, cost estimate of PAIRS in us, of the block order that would be chosen in us (0 if no block
  * shape fits), both from the model that decided}.  mst_bwd_schedule_info: the same with the calling thread's
- * current override.
+ * current override.  Under AUTO, where mst_bwd_streamed is not 0, info[0..5] describe the order that would run
+ * instead, not one that does.
  */
 enum { MST_BWD_SCHEDULE_AUTO = 0, MST_BWD_SCHEDULE_PAIRS = 1, MST_BWD_SCHEDULE_BLOCKS = 2, MST_BWD_SCHEDULE_BLOCKS_FUSED = 3 };
 mst_status mst_set_bwd_schedule(int32_t schedule);
