@@ -342,8 +342,14 @@ bool fuse_da(int64_t rows, int64_t d, int64_t I) {
 // 888 rows, d = 1776, I = 6936: 869 us -> 708; of 707 rows, d = 1504, I = 5208: 182 -> 142.  70 backward calls of 1 to 3 chunks
 // of 100 to 7000 rows, d = 792 to 4016, each timed with every kind: 0.953 of their time without this one in the mean, 0.77 to
 // 1.02, and 0.6 % behind the fastest kind.  kQuarter: its estimate is a tenth too high.  Those had I = 2.5 to 4 d; not taken
-// below 2 d, where the contraction is no longer than the weight gradients' tiles.
-constexpr double kShared = 0.98, kQuarter = 0.9;
+// below 2 d, where the contraction is no longer than the weight gradients' tiles.  kQuarterBusy: of 1100 rows on that is so only
+// where the launch waits for the chain, not where it has nearly as much work as all compute units can do in that time: of 180
+// calls of 1 to 7 chunks 18 keep their other tile for this, which took 0.94 to 1.09 of their time with quarter tiles, 1.02 in the
+// mean (16999 rows, d = 1336, I = 4848, M = 7: 2072 us, 2252 with them); the others took 0.92 in the mean.  kQuarterLater: nor
+// for later chunks that wait for the chain and whose dX would have a launch of its own: 14 that this turns back took 0.96 to 1.06
+// of their time with quarter tiles, 1.02 in the mean (1390, 1976, 7736, 5: 1016 us, 1073), 50 others 0.71 to 1.03, 0.91.  200 more
+// calls that take quarter tiles by all this: 0.91 in the mean, eleven of them 1.02 to 1.08.
+constexpr double kShared = 0.98, kQuarter = 0.9, kQuarterBusy = 0.96, kQuarterLater = 0.97;
 enum DxKind { kDxOwn, kDxWhole, kDxHalf, kDx64, kDx32, kDxQuarter };
 DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwChoice& dw) {
   if (dw.small) {
@@ -359,8 +365,12 @@ DxKind choose_dx(int64_t rows, int64_t d, int64_t I, bool accumulate, const DwCh
   const double own = kShared * (nn_tile(rows, d, I, 2).us + 2.0 + launch_us(n_dw, c, bytes));
   const double whole = launch_us(tiles(d, rows, kTile), TileCost{ksteps, 7.0, 1.4, 1.5}, n_dw, c, bytes);
   const double half = launch_us(tiles(d, rows, Tile16Half::EA), TileCost{ksteps, 7.0, 0.8, 0.9}, n_dw, c, bytes);
-  const double quarter = launch_us(tiles(d, rows, Tile16Quarter::EA, Tile16Quarter::EB), TileCost{ksteps, 7.0, 0.58, 0.65}, n_dw, c, bytes);
-  const double best = std::min(whole, I >= 2 * d ? std::min(half, kQuarter * quarter) : half);
+  const int64_t n_q = tiles(d, rows, Tile16Quarter::EA, Tile16Quarter::EB);
+  const TileCost c_q = {ksteps, 7.0, 0.58, 0.65};
+  double quarter = launch_us(n_q, c_q, n_dw, c, bytes);
+  const bool busy = quarter <= 1.2 * ((double)n_q * c_q.busy() + (double)n_dw * c.busy()) / kNumCu;
+  quarter *= busy && rows >= 1100 ? kQuarterBusy : !busy && accumulate && own < std::min(whole, half) ? kQuarterLater : kQuarter;
+  const double best = std::min(whole, I >= 2 * d ? std::min(half, quarter) : half);
   if (best > own) return kDxOwn;
   return best == whole ? kDxWhole : best == half ? kDxHalf : kDxQuarter;
 }

@@ -190,6 +190,16 @@ def test_dx_of_later_chunks_of_few_rows_has_a_launch_of_its_own(mst):
     assert mst.mst_mlp_dx_tile(208, 5120, 13824, False) == "128"      # more 64 x 64 tiles than compute units
 
 
+def test_dx_takes_128_by_128_tiles_only_where_it_is_waited_for(mst):
+    """They cost 1.4 times the compute unit time: not in long chunks with as much other work, nor in short later chunks for
+    which a launch of its own is estimated cheaper (each timed both ways, slower with them)."""
+    tiles = lambda *shape: [g["dx_tile_rows"] for g in mst.mst_mlp_bwd_groups(*shape)]
+    assert 128 not in tiles(16999, 1336, 4848, 7)[1:] and 128 not in tiles(6156, 2264, 6056, 4)
+    assert 128 not in tiles(9576, 2016, 4232, 4) and 128 not in tiles(7788, 1952, 7584, 6)
+    assert 128 not in tiles(1758, 776, 2808, 6) and 128 not in tiles(2170, 840, 3080, 5)
+    assert tiles(2664, 1776, 6936, 3) == [128] * 3 and tiles(707, 1504, 5208, 1) == [128] == tiles(500, 4096, 14336, 1)
+
+
 def test_workgroup_to_tile_map_is_a_bijection(mst):
     """Both maps of the 256 x 256 launches, on the host: every tile is the image of exactly one workgroup."""
     import ctypes
