@@ -13,8 +13,11 @@
  * mini-sequences of C = ceil(S / M) rows (Algorithm 1, line 1).  For chunk i
  * the forward pass forms the C x I intermediate A_i = silu(X_i Wg^T) * (X_i Wu^T)
  * in the workspace, writes O_i = A_i Wd^T into rows i*C.. of O (Algorithm 1,
- * lines 3 and 5) and reuses the workspace for the next chunk, so only one
- * C x I intermediate is alive instead of S x I.  The backward pass recomputes
+ * lines 3 and 5) and reuses the workspace for the next chunk, so that the
+ * workspace holds one C x I intermediate instead of S x I.  Rows are
+ * independent, so a call takes them in groups that need not be the chunks: as
+ * many as there is memory for, in the workspace and in rows of the output that
+ * are not written yet.  The backward pass recomputes
  * the chunk's gate and up projections and forms (Algorithm 3, lines 4-5)
  *
  *     dA_i  = dO_i Wd

@@ -250,10 +250,12 @@ void choose_split_blocks(Plan* p) {
 // The pair order with one launch for the pair's dlogits and one for its dH and dW, dH in 128 x 128 tiles over the whole
 // vocabulary (k_bwd_gemm_dh128_dw): two launches instead of seven, for pairs that are less than a few rounds of tiles, as long
 // as a dH tile's chain of V / 64 K steps is not much longer than dW's work.  Backward, us: 3094 rows, d = 2696, V = 12307, M = 6:
-// 1357 -> 760; 1232, 2096, 14469, 4: 588 -> 351; 2980, 824, 7045, 4: 297 -> 183; but 1700, 1472, 9339, 6: 288 -> 300.
+// 1374 -> 762; 1232, 2096, 14469, 4: 590 -> 351; 2980, 824, 7045, 4: 298 -> 184; but, where it is not taken, 1700, 1472, 9339, 6:
+// 288 -> 300.
 // Microseconds: a K step of a dH tile 0.55, 0.65 with all compute units busy, 8 for its ends; dlogits and dW as above.  Of 70
 // shapes of 219 to 19863 rows, d = 408 to 3112, V = 4117 to 69139, timed both ways, this estimate takes it for 12, at 0.56 to
-// 0.90 of their time, and the choice is 0.4 % behind the faster way in the mean.  kDh128Blocks: blocks are a little faster than
+// 0.90 of their time, and the choice is 0.4 % behind the faster way in the mean; 30 others that it takes 0.54 to 1.00, 0.79.
+// kDh128Blocks: blocks are a little faster than
 // estimated; four shapes of 0.7 to 0.95 of their estimate took 0.94 to 1.06 of their time.
 constexpr double kDh128Pairs = 0.95, kDh128Blocks = 0.7;
 bool small_pair_dlogits(const Plan& p, int64_t rows) {

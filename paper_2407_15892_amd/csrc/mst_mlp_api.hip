@@ -129,7 +129,7 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 // chunks), or in the rows of O behind the group, which nobody has written yet, where that makes fewer groups.  One chunk of a
 // small block is far from a round of tiles, and a launch takes 4 us whatever it does.  Chunk by chunk -> this: step of 512
 // rows, d = 256, I = 896, M = 2: 41.4 us -> 33.9; of 5003, d = 1544, I = 5384, M = 3: 1214 -> 1135; forward alone of 31999,
-// d = 416, I = 1160, M = 77: 818 -> 285.  Of 120 calls with two or more chunks, d = 256 to 3840: 0.35 to 1.0, the steps 0.89
+// d = 416, I = 1160, M = 77: 819 -> 286.  Of 120 calls with two or more chunks, d = 256 to 3840: 0.35 to 1.0, the steps 0.89
 // in the mean, the forwards alone 0.83.
 struct ForwardGroup { int64_t rows; bool in_output; };
 ForwardGroup forward_group(const Plan& p, int64_t left, size_t workspace_bytes, bool output_is_free) {
@@ -146,8 +146,8 @@ ForwardGroup forward_group(const Plan& p, int64_t left, size_t workspace_bytes, 
 // the workspace then holds those of one and a half times or three times the rows of a chunk.  The groups are the order in which
 // the weight gradients are summed, so they depend on the shape alone: of a larger workspace only what the call needs is used.
 // The largest group is kept as small as the number of groups allows; without fewer groups than chunks they are the chunks.  Backward, us, chunk
-// by chunk -> this: 22592 rows, d = 616, I = 1560, M = 37: 1488 -> 1139; 32128, 640, 2264, 50: 2381 -> 1744; 20288, 1760, 5776, 12:
-// 3938 -> 3484.  Groups as large as fit, where that makes no fewer of them: 8128, 1376, 3760, 4: 788 -> 820.
+// by chunk -> this: 22592 rows, d = 616, I = 1560, M = 37: 1436 -> 1044; 32128, 640, 2264, 50: 2381 -> 1678; 20288, 1760, 5776, 12:
+// 3750 -> 3496.  Groups as large as fit, where that makes no fewer of them: 8128, 1376, 3760, 4: 788 -> 820.
 struct BackwardGroups {
   const Plan& p;
   int64_t room[4];                // rows whose dG, dU and A fit with k of them in dX: of the workspace (a chunk with none)
@@ -299,7 +299,7 @@ TileChoice nt_tile(int64_t rows, int64_t N, int64_t K) {
 }
 TileChoice nn_tile(int64_t rows, int64_t N, int64_t K, int terms) { return choose_tile(N, rows, terms * ksteps_of(K), kStrided); }
 
-// The weight gradients have one tile kind for all chunks: what the large tiles keep between them is not row-major.
+// The weight gradients have one tile kind for all groups of rows: what the large tiles keep between them is not row-major.
 struct DwChoice { bool small, lone, even; };
 DwChoice dw_choice(int64_t C, int64_t d, int64_t I) {
   const double tiles64 = 3.0 * tiles_of(I, d, 64), ksteps = (double)ksteps_of(C);
@@ -579,7 +579,8 @@ mst_status mst_mlp_fwd(const void* X, const void* Wg, const void* Wu, const void
   const size_t x_bytes = (size_t)S * d * 2, w_bytes = (size_t)I * d * 2;
   const bool output_is_free = !overlap(O, x_bytes, X, x_bytes) && !overlap(O, x_bytes, Wg, w_bytes) &&
                               !overlap(O, x_bytes, Wu, w_bytes) && !overlap(O, x_bytes, Wd, w_bytes);
-  // Algorithm 1: loop over groups of mini-sequences; O_i lands in its row range of O (the concatenation of line 5)
+  // Algorithm 1: loop over groups of rows (whole or parts of mini-sequences); each lands in its row range of O (the concatenation
+  // of line 5)
   for (int64_t r0 = 0; r0 < p.S;) {
     const ForwardGroup g = forward_group(p, p.S - r0, workspace_bytes, output_is_free);
     const int rows = (int)g.rows;
@@ -625,7 +626,7 @@ mst_status mst_mlp_bwd(const void* X, const void* Wg, const void* Wu, const void
   const BackwardGroups groups(p, dx_is_free);
   const DwChoice dw = dw_choice(std::min(groups.cap, p.S), p.d, p.I);
 
-  // Algorithm 3: loop over groups of mini-sequences; dX_i lands in its row range, the weight gradients accumulate
+  // Algorithm 3: loop over groups of rows, likewise; their dX lands in its row range, the weight gradients accumulate
   for (int64_t r0 = 0; r0 < p.S;) {
     int in_dx = 0;
     const int rows = (int)groups.next(p.S - r0, &in_dx);

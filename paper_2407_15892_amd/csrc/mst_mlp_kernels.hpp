@@ -1,6 +1,6 @@
 // Device kernels of the mini-sequence MLP path (gfx950).
 //
-// Per mini-sequence (chunk) of C rows, following Algorithm 1 (forward) and
+// Per mini-sequence (chunk) of C rows, or group of rows (see forward_group and BackwardGroups in mst_mlp_api.hip), following Algorithm 1 (forward) and
 // Algorithm 3 (backward with recomputation) of the paper, for the block
 // O = (silu(X Wg^T) * (X Wu^T)) Wd^T of Theorem 1 / Appendix C:
 //
@@ -374,7 +374,7 @@ struct DwProblem {
   float* dW;                     // [V][d]
 };
 struct DwProblems { DwProblem p[3]; };
-// kStoreOnly: the first chunk only stores; later chunks add to the stored sums; `more`: another chunk follows
+// kStoreOnly: the first group of rows only stores; later ones add to the stored sums; `more`: another one follows
 template <bool kStoreOnly, bool kEven>
 __device__ __forceinline__ void dw3_tile(int b, const DwProblems& ps, int rows, int more, char* smem) {
   int which = 0;

@@ -15,14 +15,17 @@
 // Every logit is formed once more than with dlogits in memory (8 S d V flop instead of 6).  In return there is one launch (and
 // dH's reduce) instead of two or three per pair of mini-sequences or block, whose size the workspace limits, and a logit's K
 // loop of four to eight steps of 64 has no epilogue through memory: with d = 256 a 256 x 256 tile of dlogits takes 5 us of
-// main loop and 7 at its ends.  Backward, us, before -> this: 512 rows, d = 256, V = 4096, M = 4: 31.1 -> 16.5; 1706, 256,
-// 38336, 6: 283 -> 168; 4096, 384, 32000, 16: 830 -> 445; 5470, 512, 15850, 21: 895 -> 595; 8192, 256, 65536, 64: 2346 -> 860
-// (1280 TFLOP/s).
+// main loop and 7 at its ends.  Backward calls, us, before -> this: 512 rows, d = 256, V = 4096, M = 4: 31.0 -> 16.2; 1706,
+// 256, 38336, 6: 283 -> 139; 4096, 384, 32000, 16: 826 -> 439; 5470, 512, 15850, 21: 899 -> 630; 8192, 256, 65536, 64: 2375 -> 895
+// (1230 TFLOP/s).
 //
 // What bounds it: with two workgroups on a compute unit the 64 MFMAs of a wave and step (1024 clocks), the exponentials (450
-// to 600 clocks, overlapped with the other wave's MFMAs) and the LDS reads (each fragment feeds OT MFMAs).  Fragments are read
-// a few MFMAs ahead by hand: left to the compiler every read was waited for at once (1706 rows: 211 us).  d > 512 would need
-// more accumulators than two waves per SIMD have; there dlogits in memory are the better way.
+// to 600 clocks, overlapped with the other wave's MFMAs) and the LDS reads (each fragment feeds OT MFMAs).  Of the clocks of the
+// last of these calls the matrix cores are busy 54 %, LDS 42 % (a third of that bank conflicts), of the third call 40 and 62 %; waves
+// wait to issue for 40 % of their time and at waits and barriers for 24 %.  In the first one, whose launch takes 15 us (and dH's
+// sum 4), the ends of the workgroups are all (8 and 12 %).  Fragments are read a few MFMAs ahead by hand: left to the compiler
+// every read was waited for at once (1706 rows: 211 us).  d > 512 would need more accumulators than two waves per SIMD have;
+// there dlogits in memory are the better way.
 #pragma once
 #include "mst_small_kernels.hpp"
 
@@ -60,7 +63,8 @@ struct StreamPanel {
   uint32_t rd, rt;
 
   // XOR swizzle of the 16-byte chunk index by the row, for both kinds of reads: sixteen lanes read sixteen rows at one
-  // chunk (all sixteen values differ), and 32 lanes read eight rows at a pair of chunks (the upper three bits differ).
+  // chunk (all sixteen values differ), and 32 lanes read eight rows at a pair of chunks (the upper three bits differ).  A third
+  // of the clocks that LDS works are conflicts all the same.
   __device__ __forceinline__ static uint32_t swz(uint32_t row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
 
   __device__ __forceinline__ void init(const void* base, int d, int rows, int wave_of_ring, int lane) {
