@@ -1,6 +1,7 @@
 // Device kernels of the mini-sequence MLP path (gfx950).
 //
-// Per mini-sequence (chunk) of C rows, or group of rows (see forward_group and BackwardGroups in mst_mlp_api.hip), following Algorithm 1 (forward) and
+// Per mini-sequence (chunk) of C rows, or group of rows (see forward_group and
+// BackwardGroups in mst_mlp_api.hip), following Algorithm 1 (forward) and
 // Algorithm 3 (backward with recomputation) of the paper, for the block
 // O = (silu(X Wg^T) * (X Wu^T)) Wd^T of Theorem 1 / Appendix C:
 //
